@@ -335,8 +335,9 @@ def tree_walk(pb: Problem, outcome, token, accept_depth=None, emitted=None):
     return ad, em
 
 
-# Up to this many tree nodes per batch, StepPlan.run() lets the verify kernel walk the trees
-# itself (two launches per step).  The arrival count keeps a finished workgroup about a
+# Up to this many tree nodes per batch, StepPlan.run() hands the verify call its workspace, with which
+# the kernel walks the trees itself (two launches per step); beyond it the call launches the walk
+# behind the kernel (rows short enough for whole trees in a workgroup are walked inside either way).  The arrival count keeps a finished workgroup about a
 # microsecond longer on its compute unit, which costs more than the walk's own launch
 # (2-3 us) once a batch is several times what the chip holds at once: measured on one MI355X,
 # 31-node trees at V = 32000, the two placements timed in turns in one process: B = 16 26.4 against
@@ -349,8 +350,8 @@ class StepPlan:
     """Marshalled arguments of one draft + verify + walk step, so that a serving loop pays
     two or three foreign calls per step and nothing else.  The tensors handed in must stay
     alive and in place for the life of the plan.  walk_in_verify: True = the verify kernel
-    walks the trees (one launch), False = mdsd_tree_walk as a launch of its own, None = by
-    batch size (WALK_IN_VERIFY_MAX_NODES)."""
+    walks the trees (one launch), False = the verify call places the walk (a launch of its own but for
+    short rows), None = by batch size (WALK_IN_VERIFY_MAX_NODES)."""
 
     def __init__(self, method: str, pb: Problem, u_draft, u_verify, *, flags=True, hand_stats=True,
                  walk_in_verify=None):
@@ -399,6 +400,7 @@ class StepPlan:
         self._fres = fres
         fresp = C.byref(fres)
         self._verify_walk = lambda st: vfn(pbp, tk, uv, fresp, wsp, wsn, st)
+        self._verify_then_walk = lambda st: vfn(pbp, tk, uv, fresp, None, 0, st)
         # path-only: its result structure carries the walk outputs, the walk is in the kernel
         pres = _Result()
         for name in ("outcome", "token", "flags", "accept_depth", "emitted"):
@@ -440,11 +442,9 @@ class StepPlan:
     def run(self, stream=None):
         st = _stream() if stream is None else stream
         self.draft(st)
-        if self.walk_in_verify:
-            self.verify_and_walk(st)
-        else:
-            self.verify(st)
-            self.walk(st)
+        rc = self._verify_walk(st) if self.walk_in_verify else self._verify_then_walk(st)
+        if rc != 0:
+            raise MdsdError(rc, self.method + "_verify")
         return self.out
 
 

@@ -8,21 +8,19 @@ namespace MDSD_NS {
 
 // ---------------------------------------------------------------- draft kernel
 template <int DT, bool LOGITS, int METHOD, int NIT, bool MASKED = true>
-__global__ __launch_bounds__(kWG * kNodesPerWG) void draft_kernel(const Params P)
+__global__ __launch_bounds__(kWG) void draft_kernel(const Params P)
 {
     constexpr int E = Elem<DT>::kPerChunk;
     using CV = ToWeight<LOGITS>;
-    __shared__ Shared shs[kNodesPerWG];
-    Shared& sh = shs[node_slot()];
+    __shared__ Shared sh;
     int phase = 0;
     // one group of kWG threads per node; a leaf only records that it has no hub
     const NodeId id = node_of_block(P);
-    if (id.b < 0) return;
     const int b = id.b, n = id.n, c0 = id.c0;
     const int64_t row = id.row;
-    if (n == 0 && node_thread() == 0) P.tokens_out[(int64_t)b * P.N] = -1;
+    if (n == 0 && (int)threadIdx.x == 0) P.tokens_out[(int64_t)b * P.N] = -1;
     if (c0 < 0) {
-        if (node_thread() == 0) {
+        if ((int)threadIdx.x == 0) {
             if (P.hub_out) P.hub_out[row] = -1;
             if (P.flags) P.flags[row] = 0;
             if (P.stats_out) P.stats_out[row] = mdsd_row_stats{0.f, 0.f, -1, 0};
@@ -162,7 +160,7 @@ __global__ __launch_bounds__(kWG * kNodesPerWG) void draft_kernel(const Params P
             else
                 remove_token(a_virt);
             W2 = slab_total(rq.nslab, sv);
-            if (P.stats_out && node_thread() == 0)
+            if (P.stats_out && (int)threadIdx.x == 0)
                 P.stats_out[row] = mdsd_row_stats{mm[0], W2, a_virt - rq.head, 0};
         }
         if (v != a_virt) {
@@ -183,7 +181,7 @@ __global__ __launch_bounds__(kWG * kNodesPerWG) void draft_kernel(const Params P
         // LDS behind one barrier instead of one barrier per draw (a node with a single wavefront has
         // no barriers to save and takes the plain loop below)
         const float W = slab_total(rq.nslab, sv);
-        if (P.stats_out && node_thread() == 0) P.stats_out[row] = mdsd_row_stats{mm[0], W, -1, 0};
+        if (P.stats_out && (int)threadIdx.x == 0) P.stats_out[row] = mdsd_row_stats{mm[0], W, -1, 0};
         for (int i = 0; i < k; ++i) {
             SlabHit h{-1, 0.f, 0.f};
             const bool found = icdf_find_slab(rq.nslab, ur[i], W, sv, h);  // the same in every wave
@@ -193,7 +191,7 @@ __global__ __launch_bounds__(kWG * kNodesPerWG) void draft_kernel(const Params P
                 const int v = icdf_in_slab<E>(w, h);
                 if ((threadIdx.x & 63) == 0) sh.node_x[i] = v;
             }
-            if (!found && node_thread() == 0) sh.node_x[i] = -1;
+            if (!found && (int)threadIdx.x == 0) sh.node_x[i] = -1;
         }
         node_barrier();
         int prev = rq.head;
@@ -211,7 +209,7 @@ __global__ __launch_bounds__(kWG * kNodesPerWG) void draft_kernel(const Params P
         // found first (slab sums, no memory), their chunks asked for together, and the draws finished as
         // the chunks arrive -- one trip to memory per four draws instead of one per draw
         const float W = slab_total(rq.nslab, sv);
-        if (P.stats_out && node_thread() == 0) P.stats_out[row] = mdsd_row_stats{mm[0], W, -1, 0};
+        if (P.stats_out && (int)threadIdx.x == 0) P.stats_out[row] = mdsd_row_stats{mm[0], W, -1, 0};
         int prev = rq.head;
         constexpr int kBatch = 4;
         for (int i0 = 0; i0 < k; i0 += kBatch) {
@@ -248,7 +246,7 @@ __global__ __launch_bounds__(kWG * kNodesPerWG) void draft_kernel(const Params P
         int prev = rq.head;
         for (int i = 0; i < k; ++i) {
             const float W = slab_total(rq.nslab, sv);
-            if (i == 0 && P.stats_out && node_thread() == 0)  // with replacement: maximum and total mass
+            if (i == 0 && P.stats_out && (int)threadIdx.x == 0)  // with replacement: maximum and total mass
                 P.stats_out[row] = mdsd_row_stats{mm[0], W, -1, 0};
             int v;
             if constexpr (NIT == 0 && METHOD == kRRSw) {
@@ -283,7 +281,7 @@ __global__ __launch_bounds__(kWG * kNodesPerWG) void draft_kernel(const Params P
             out_tok[i] = v - rq.head;
         }
     }
-    if (node_thread() == 0) {
+    if ((int)threadIdx.x == 0) {
         for (int i = 0; i < k; ++i) xt[i] = out_tok[i];
         if (P.hub_out) P.hub_out[row] = (METHOD == kSpecHub) ? a_virt - rq.head : -1;
         if (P.flags) P.flags[row] = flags;

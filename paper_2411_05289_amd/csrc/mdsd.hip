@@ -3,6 +3,7 @@
 // draft_*.hip; the device code they share is in node_common.h), the tree walk and Philox
 // kernels, and the C entry points.
 #include "launch.h"
+#include "launch_group.h"
 #include "launch_half.h"
 #include "launch_small.h"
 
@@ -126,6 +127,10 @@ static int validate(const mdsd_problem* pb, int method, bool need_target, Params
     P->depth = pb->depth;
     P->n_internal = (int)n_internal;
     P->first_child = pb->first_child;
+    P->masked = (ad & 15) || ((pb->ld_d * es) & 15) || (pb->V % per_chunk) ||
+                (need_target && ((at & 15) || ((pb->ld_t * es) & 15)));
+    // rows that start anywhere: up to per_chunk - 1 masked elements in front
+    P->row_chunks = (int)(((int64_t)pb->V + (P->masked ? 2 * per_chunk - 2 : 0)) / per_chunk);
     return MDSD_OK;
 }
 
@@ -141,9 +146,10 @@ static int resident_chunks(const mdsd_problem* pb)
     if (per_lane <= 16) return 16;
     return 0;
 }
-// Short rows go to a build of the generic kernels with fewer threads per node (1, 2 or 4 wavefronts:
-// four chunks per lane) instead of one 512-thread workgroup most of whose wavefronts would hold no
-// part of the row; 0 = the main build
+// Rows too long for a group of lanes (and SpecHub nodes in large batches, see verify_lanes()) but short
+// go to a build of the generic kernels with fewer threads per node (1, 2 or 4 wavefronts: four chunks per
+// lane) instead of one 512-thread workgroup most of whose wavefronts would hold no part of the row; 0 =
+// the main build
 static int small_build(const mdsd_problem* pb)
 {
     const int per_chunk = pb->dtype == MDSD_FP32 ? 4 : 8;
@@ -178,14 +184,34 @@ static dim3 node_grid(const Params& P, int nit)
 // tree nodes per batch from which the 256-thread verify kernels take over from the 512-thread ones
 constexpr int64_t kHalfWidthMinNodes = 2300;
 
+// SpecHub nodes of more than 64 chunks per row, from this many on: one wavefront per node with the rows
+// in registers and more wavefronts on a SIMD (60000 nodes of 1000 bf16 elements 68 -> 55 us, of 2000 90 ->
+// 77; 8000 nodes 11.3 against 11.8 us).  The RRS methods gain from their groups at every size (119 -> 80,
+// 146 -> 100 us).
+// Path-only from 2048 trees on (4000 trees, 1000 elements 25.4 -> 22.6 us, 2000 elements 33.5 -> 29.7).
+constexpr int64_t kWaveSpecHubMinNodes = 16384, kWaveSpecHubMinPathTrees = 2048;
+
+// lanes per node of the verify kernels for short rows; 0: another build takes the call
+static int verify_lanes(int method, const Params& P, bool path)
+{
+    const int64_t nodes = (int64_t)P.B * (path ? 1 : P.N);
+    if (method == kSpecHub && P.row_chunks > 64 && nodes >= (path ? kWaveSpecHubMinPathTrees : kWaveSpecHubMinNodes)) return 0;
+    return group_lanes(P.row_chunks, nodes, !path && P.accept_depth ? P.N : 1, path);
+}
+
 // path == false: one workgroup per node.  path == true: one workgroup per tree.
 static void launch_verify(int method, const mdsd_problem* pb, const Params& P, bool path, hipStream_t st)
 {
     const bool lg = pb->kind == MDSD_LOGITS;
+    if (const int lanes = verify_lanes(method, P, path)) {
+        (method == kSpecHub ? launch_group_spechub : method == kRRS ? launch_group_rrs : launch_group_rrsw)(
+            lanes, pb->dtype, lg, path, st, P);
+        return;
+    }
     int nit = resident_chunks(pb);
     const dim3 grid = path ? dim3((unsigned)P.B) : node_grid(P, nit), block(kWG);
     switch (small_build(pb)) {
-    case 1: mdsd_wave::launch_verify(method, pb->dtype, lg, path, grid, st, P); return;
+    case 1: mdsd_wave::launch_spechub(pb->dtype, lg, path, grid, st, P); return;  // verify_lanes() left it SpecHub nodes
     case 2: mdsd_pair::launch_verify(method, pb->dtype, lg, path, grid, st, P); return;
     case 4: mdsd_quad::launch_verify(method, pb->dtype, lg, path, grid, st, P); return;
     default: break;
@@ -229,6 +255,10 @@ static void launch_verify(int method, const mdsd_problem* pb, const Params& P, b
 static void launch_draft(int method, const mdsd_problem* pb, const Params& P, hipStream_t st)
 {
     const bool lg = pb->kind == MDSD_LOGITS;
+    if (const int lanes = group_lanes(P.row_chunks, (int64_t)P.B * (P.first_child ? P.N : P.n_internal), 1, false)) {
+        launch_group_draft(method, lanes, pb->dtype, lg, st, P);
+        return;
+    }
     int nit = resident_chunks(pb);
     // Rows of sixteen chunks per lane are streamed: the draft kernel with such a row in registers
     // fits two workgroups on a CU, the streaming one four, and its one-sweep statistics are the
@@ -237,7 +267,6 @@ static void launch_draft(int method, const mdsd_problem* pb, const Params& P, hi
     if (nit == 16 && lg) nit = 0;  // (rows of probabilities have no one-sweep form and stay in registers)
     const dim3 grid = node_grid(P, nit), block(kWG);
     switch (small_build(pb)) {
-    case 1: mdsd_wave::launch_draft(method, pb->dtype, lg, st, P); return;
     case 2: mdsd_pair::launch_draft(method, pb->dtype, lg, st, P); return;
     case 4: mdsd_quad::launch_draft(method, pb->dtype, lg, st, P); return;
     default: break;
@@ -284,10 +313,13 @@ static int verify_entry(int method, const mdsd_problem* pb, const int32_t* token
     if ((out->accept_depth == nullptr) != (out->emitted == nullptr)) return MDSD_E_NULL;
     if (path && !out->accept_depth) return MDSD_E_NULL;
     if (path && out->resid_prob) return MDSD_E_UNSUPPORTED;
-    const bool walk_inside = !path && out->accept_depth && tree_count;
     P.accept_depth = out->accept_depth;
     P.emitted = out->emitted;
-    P.tree_count = walk_inside ? tree_count : nullptr;
+    // short rows: where a workgroup holds whole trees it walks them without counting arrivals
+    const int lanes = path ? 0 : verify_lanes(method, P, false);
+    const bool trees_whole = lanes && out->accept_depth && group_walks_inside(lanes, P.N, (int64_t)P.B * P.N);
+    const bool walk_inside = !path && out->accept_depth && (tree_count || trees_whole);
+    P.tree_count = walk_inside && !trees_whole ? tree_count : nullptr;
     P.tokens = tokens;
     P.u = u;
     P.outcome = out->outcome;

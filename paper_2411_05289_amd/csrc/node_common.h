@@ -91,13 +91,6 @@ __device__ __forceinline__ NodeId node_of_item(const Params& P, int w)
 // dimension (gridDim.y == 1) and take the division.
 __device__ __forceinline__ NodeId node_of_block(const Params& P)
 {
-    if constexpr (kNodesPerWG > 1) {
-        // several nodes per workgroup, numbered in one dimension; a slot past the last node has
-        // none (b = -1) and its wavefront leaves at once
-        const int64_t w = (int64_t)blockIdx.x * kNodesPerWG + node_slot();
-        if (w >= (int64_t)P.B * P.N) return NodeId{-1, -1, -1, -1};
-        return node_of_item(P, (int)w);
-    }
     if (gridDim.y == 1) return node_of_item(P, blockIdx.x);
     NodeId id;
     // Workgroup i of a launch runs on XCD i mod 8, and with the tree as the fast index that would
@@ -215,8 +208,8 @@ __device__ __forceinline__ void wave_walk(const int32_t* outcome, const int32_t*
 __device__ __forceinline__ void write_node_outputs(const Params& P, const NodeId& id, int outcome, int token,
                                                    float rmass, int flags)
 {
-    if (node_thread() >= kWave) return;
-    const bool first = node_thread() == 0;
+    if ((int)threadIdx.x >= kWave) return;
+    const bool first = (int)threadIdx.x == 0;
     if (first) {
         if (P.resid_mass) P.resid_mass[id.row] = rmass;
         if (P.flags) P.flags[id.row] = flags;
@@ -619,9 +612,8 @@ __device__ __forceinline__ float uniform(float v) { return as_f(__builtin_amdgcn
 template <class VerifyNode>
 __device__ __forceinline__ void walk_and_verify(const Params& P, VerifyNode verify_node)
 {
-    const int b = (int)blockIdx.x * kNodesPerWG + node_slot();
-    if (b >= P.B) return;
-    for (int i = node_thread(); i < P.N; i += kWG) {
+    const int b = (int)blockIdx.x;
+    for (int i = (int)threadIdx.x; i < P.N; i += kWG) {
         const int64_t r = (int64_t)b * P.N + i;
         P.outcome[r] = MDSD_UNVISITED;
         P.token[r] = -1;
@@ -629,7 +621,7 @@ __device__ __forceinline__ void walk_and_verify(const Params& P, VerifyNode veri
         if (P.resid_mass) P.resid_mass[r] = 0.f;
     }
     int32_t* em = P.emitted + (int64_t)b * P.depth;
-    for (int i = node_thread(); i < P.depth; i += kWG) em[i] = -1;
+    for (int i = (int)threadIdx.x; i < P.depth; i += kWG) em[i] = -1;
     // the visited nodes' entries are rewritten below by another thread of this workgroup
     __threadfence_block();
     node_barrier();
@@ -648,13 +640,13 @@ __device__ __forceinline__ void walk_and_verify(const Params& P, VerifyNode veri
         id.row = (int64_t)b * P.N + n;
         const NodeOut o = verify_node(id);
         const int outcome = uniform(o.outcome), token = uniform(o.token);
-        if (node_thread() == 0 && d < P.depth) em[d] = token;
+        if ((int)threadIdx.x == 0 && d < P.depth) em[d] = token;
         if (id.c0 < 0 || outcome < 0 || outcome >= P.k || d + 1 >= P.depth) break;
         n = id.c0 + outcome;
         ++d;
         node_barrier();  // the next node reuses the LDS areas of this one
     }
-    if (node_thread() == 0) P.accept_depth[b] = d;
+    if ((int)threadIdx.x == 0) P.accept_depth[b] = d;
 }
 
 // One sweep over a logit row that is streamed from memory (too long for registers), instead of

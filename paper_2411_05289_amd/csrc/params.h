@@ -16,6 +16,8 @@ struct Params {
     // kernels would otherwise each compute again with a dozen instructions per wave
     float scale_t, scale_d;
     int B, N, V, k, depth, n_internal;
+    int masked;      // some row may start or end inside a 16-byte chunk
+    int row_chunks;  // 16-byte chunks that a row touches at most
     const int32_t* first_child;
     const int32_t* tokens;
     const float* u;

@@ -2,5 +2,4 @@
 #define MDSD_WG 256
 #define MDSD_NS mdsd_quad
 #define MDSD_MAX_SLABS 16
-#define MDSD_NODES_PER_WG 1
 #include "small_draft_launch.h"

@@ -507,21 +507,18 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
 }
 
 template <int DT, bool LOGITS, int METHOD, int NIT>
-__global__ __launch_bounds__(kWG * kNodesPerWG) void verify_kernel(const Params P)
+__global__ __launch_bounds__(kWG) void verify_kernel(const Params P)
 {
-    __shared__ Shared shs[kNodesPerWG];
-    Shared& sh = shs[node_slot()];
+    __shared__ Shared sh;
     int phase = 0;
     const NodeId id = node_of_block(P);
-    if (id.b < 0) return;
     verify_node<DT, LOGITS, METHOD, NIT>(P, id, sh, phase);
 }
 
 template <int DT, bool LOGITS, int METHOD, int NIT>
-__global__ __launch_bounds__(kWG * kNodesPerWG) void verify_path_kernel(const Params P)
+__global__ __launch_bounds__(kWG) void verify_path_kernel(const Params P)
 {
-    __shared__ Shared shs[kNodesPerWG];
-    Shared& sh = shs[node_slot()];
+    __shared__ Shared sh;
     int phase = 0;
     walk_and_verify(P, [&](const NodeId& id) { return verify_node<DT, LOGITS, METHOD, NIT>(P, id, sh, phase); });
 }

@@ -11,13 +11,9 @@
 namespace MDSD_NS {
 
 constexpr int kWave = 64;
-// A node is handled by kWG threads = kWaves wavefronts.  A workgroup holds kNodesPerWG such groups:
-// more than one only where a group is a single wavefront, so that the groups of a workgroup share
-// nothing and never have to meet at a barrier.
+// A node is handled by a workgroup of kWG threads = kWaves wavefronts.
 constexpr int kWG = MDSD_WG;
 constexpr int kWaves = kWG / kWave;
-constexpr int kNodesPerWG = MDSD_NODES_PER_WG;
-static_assert(kNodesPerWG == 1 || kWaves == 1, "several nodes per workgroup: one wavefront each");
 
 // index of this wavefront among those of its node, as a scalar: the compiler cannot see that
 // threadIdx.x / 64 is the same in all 64 lanes, and would otherwise guard every per-wave
@@ -34,21 +30,6 @@ __device__ __forceinline__ int wave_id()
     } else {
         return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64u));
     }
-}
-// which of the workgroup's nodes this thread works on, and its number among that node's threads
-__device__ __forceinline__ int node_slot()
-{
-    if constexpr (kNodesPerWG == 1)
-        return 0;
-    else
-        return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64u));
-}
-__device__ __forceinline__ int node_thread()
-{
-    if constexpr (kNodesPerWG == 1)
-        return (int)threadIdx.x;
-    else
-        return (int)(threadIdx.x & 63u);
 }
 // every thread of the node has arrived and sees the others' writes to LDS.  A single wavefront
 // runs its LDS instructions in order, so there only the compiler has to be kept from moving them.

@@ -320,6 +320,46 @@ def test_batches_of_more_than_2300_nodes(method, dtype, V, off, request):
     note(request, check_case(method, wl, seed=V % 1000, seqs=[0, 1, Bn // 2, Bn - 1], full_outputs=False))
 
 
+# ----------------------------------------------------------------- short rows: lanes per node
+# (dtype, kind, V, row offset, nodes per tree's depth, trees): 4, 8, 16, 32 and 64 lanes per node at the
+# last row they hold and the first they do not (16-byte chunks 4 G and 4 G + 1), in batches small enough
+# for more lanes and large enough for the fewest, in trees that share a workgroup and trees that do not
+_SHORT = [
+    ("bf16", "logits", 128, 0, 3, 3000),    # 16 chunks, many nodes: 4 lanes
+    ("fp32", "logits", 62, 1, 3, 3000),     # 17 with the head: 8 lanes
+    ("bf16", "probs", 256, 0, 2, 8000),     # 32 chunks: 8 lanes, the walk a launch of its own
+    ("fp32", "logits", 129, 0, 4, 1200),    # 33 chunks, rows on every phase: 16 lanes
+    ("bf16", "logits", 505, 0, 2, 6000),    # 64 chunks with the head: 16 lanes
+    ("fp32", "logits", 260, 0, 2, 6000),    # 65: 32 lanes (SpecHub: one wavefront per node)
+    ("bf16", "logits", 1024, 0, 3, 300),    # 128 chunks: 64 lanes in a small batch
+    ("fp32", "probs", 1017, 0, 2, 900),     # 255 chunks with the head: 64 lanes
+    ("bf16", "logits", 2, 0, 2, 40000),     # one chunk
+    ("bf16", "logits", 24, 0, 6, 40),       # 63-node trees
+]
+
+
+@pytest.mark.parametrize("method", ALL)
+@pytest.mark.parametrize("dtype,kind,V,off,depth,Bn", _SHORT, ids=["%s_%s_V%d_off%d_d%d_B%d" % v for v in _SHORT])
+def test_short_rows_lanes_per_node(method, dtype, kind, V, off, depth, Bn, request):
+    k = 2
+    if method == "rrsw" and V < 3:
+        pytest.skip("cannot draw two distinct tokens plus a residual from V = 2")
+    N = W.tree_nodes(k, depth)
+    td = torch.float32 if dtype == "fp32" else torch.bfloat16
+    t, d = W.llm_like_logits(Bn, N, V, logit_std=2.0, draft_noise_std=1.0, dtype=torch.float32, seed=V, device=DEV,
+                             chunk_rows=1 << 16)
+    if kind == "probs":
+        t, d = torch.softmax(t.double(), -1), torch.softmax(d.double(), -1)
+    big_t = torch.zeros((Bn * N * V + off,), dtype=td, device=DEV)
+    big_d = torch.zeros((Bn * N * V + off,), dtype=td, device=DEV)
+    tv, dv = big_t[off:].view(Bn, N, V), big_d[off:].view(Bn, N, V)
+    tv.copy_(t)
+    dv.copy_(d)
+    temps = (0.9, 1.2) if kind == "logits" else (1.0, 1.0)
+    wl = W.Workload("short_%s_V%d" % (dtype, V), Bn, N, V, k, depth, dtype, kind, temps[0], temps[1], tv, dv)
+    note(request, check_case(method, wl, seed=V, seqs=[0, 1, 2, 3, Bn // 2, Bn - 2, Bn - 1], full_outputs=V <= 300))
+
+
 # ----------------------------------------------------------------- general topology
 @pytest.mark.parametrize("V", [2500, 12000])
 @pytest.mark.parametrize("method", ALL)
