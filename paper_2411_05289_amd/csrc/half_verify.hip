@@ -27,29 +27,21 @@ void launch_spechub(int dtype, bool masked, dim3 grid, hipStream_t st, const Par
     }
 }
 
-// fp32 rows masked or not, bf16 rows that need no masking (as in the main build)
-bool rrs_covers(int dtype, bool masked) { return dtype == MDSD_FP32 || !masked; }
-
-template <bool WO>
-static void launch_rrs_of(int dtype, bool masked, dim3 grid, hipStream_t st, const Params& P)
+template <int DT, bool WO>
+static void launch_rrs_of(bool masked, dim3 grid, hipStream_t st, const Params& P)
 {
-    const dim3 block(kWG);
-    if (dtype == MDSD_FP32) {
-        if (masked)
-            hipLaunchKernelGGL((rrs_verify_resident<0, 16, true, WO>), grid, block, 0, st, P);
-        else
-            hipLaunchKernelGGL((rrs_verify_resident<0, 16, false, WO>), grid, block, 0, st, P);
-    } else {
-        hipLaunchKernelGGL((rrs_verify_resident<1, 16, false, WO>), grid, block, 0, st, P);
-    }
+    if (masked)
+        hipLaunchKernelGGL((rrs_verify_resident<DT, 16, true, WO, true>), grid, dim3(kWG), 0, st, P);
+    else
+        hipLaunchKernelGGL((rrs_verify_resident<DT, 16, false, WO, true>), grid, dim3(kWG), 0, st, P);
 }
 
 void launch_rrs(bool without_replacement, int dtype, bool masked, dim3 grid, hipStream_t st, const Params& P)
 {
-    if (without_replacement)
-        launch_rrs_of<true>(dtype, masked, grid, st, P);
+    if (dtype == MDSD_FP32)
+        without_replacement ? launch_rrs_of<0, true>(masked, grid, st, P) : launch_rrs_of<0, false>(masked, grid, st, P);
     else
-        launch_rrs_of<false>(dtype, masked, grid, st, P);
+        without_replacement ? launch_rrs_of<1, true>(masked, grid, st, P) : launch_rrs_of<1, false>(masked, grid, st, P);
 }
 
 }  // namespace mdsd_half

@@ -10,10 +10,9 @@ namespace MDSD_NS {
 void launch_spechub_resident(int dtype, int nit, bool masked, bool path, dim3 grid, dim3 block, hipStream_t st,
                              const Params& P);
 
-// rrs_resident.hip: RRS / RRSw on logit rows in registers with the draft call's records
-bool rrs_resident_covers(int dtype, int nit, bool masked);
-void launch_rrs_resident(bool without_replacement, int dtype, int nit, bool masked, dim3 grid, dim3 block,
-                         hipStream_t st, const Params& P);
+// rrs_resident.hip, rrsw_resident.hip: RRS / RRSw on logit rows in registers
+void launch_rrs_resident(int dtype, int nit, bool masked, dim3 grid, dim3 block, hipStream_t st, const Params& P);
+void launch_rrsw_resident(int dtype, int nit, bool masked, dim3 grid, dim3 block, hipStream_t st, const Params& P);
 
 // verify_generic_*.hip: every other case (nit = 0: rows streamed in every pass)
 void launch_verify_generic_spechub(int dtype, bool logits, int nit, bool path, dim3 grid, dim3 block,

@@ -14,8 +14,7 @@ constexpr int kMaxChunks = 16 * 256;
 
 // SpecHub with P.stats_in set
 void launch_spechub(int dtype, bool masked, dim3 grid, hipStream_t st, const mdsd::Params& P);
-// RRS / RRSw with P.stats_in set; covers(): the shapes built (the others take the 512-thread path)
-bool rrs_covers(int dtype, bool masked);
+// RRS / RRSw with P.stats_in set
 void launch_rrs(bool without_replacement, int dtype, bool masked, dim3 grid, hipStream_t st, const mdsd::Params& P);
 
 }  // namespace mdsd_half

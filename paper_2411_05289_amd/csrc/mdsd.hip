@@ -226,7 +226,7 @@ static void launch_verify(int method, const mdsd_problem* pb, const Params& P, b
         mdsd_half::launch_spechub(pb->dtype, rows_need_mask(pb), grid, st, P);
         return;
     }
-    if (half_width && method != kSpecHub && mdsd_half::rrs_covers(pb->dtype, rows_need_mask(pb))) {
+    if (half_width) {
         mdsd_half::launch_rrs(method == kRRSw, pb->dtype, rows_need_mask(pb), grid, st, P);
         return;
     }
@@ -234,10 +234,8 @@ static void launch_verify(int method, const mdsd_problem* pb, const Params& P, b
         launch_spechub_resident(pb->dtype, nit, rows_need_mask(pb), path, grid, block, st, P);
         return;
     }
-    if (method != kSpecHub && lg && P.stats_in != nullptr && !path &&
-        rrs_resident_covers(pb->dtype, nit, rows_need_mask(pb))) {
-        // logit rows in registers, the draft call's records at hand
-        launch_rrs_resident(method == kRRSw, pb->dtype, nit, rows_need_mask(pb), grid, block, st, P);
+    if (method != kSpecHub && lg && nit > 0 && !path) {
+        (method == kRRSw ? launch_rrsw_resident : launch_rrs_resident)(pb->dtype, nit, rows_need_mask(pb), grid, block, st, P);
         return;
     }
     // The generic RRS rounds hold many registers beside two resident rows (8 chunks per lane and

@@ -25,12 +25,13 @@ __device__ __forceinline__ uint4 select_chunk(const uint4 (&d)[NIT], int it)
     return make_uint4(x, y, z, w);
 }
 
-// this lane's register chunk `it` (run-time value) as floats, boundary elements masked
+// this lane's register chunk `it` (run-time value) as floats
 template <int DT, int NIT, bool MASKED>
 __device__ __forceinline__ void get_dyn(const RowSrc<DT, NIT, MASKED>& src, int it, float (&a)[Elem<DT>::kPerChunk])
 {
-    unpack<DT>(select_chunk<NIT>(src.d, it), a);
-    src.mask((it * kWaves + wave_id()) * 64 + (int)(threadIdx.x & 63), a);
+    uint4 c = select_chunk<NIT>(src.d, it);
+    if constexpr (MASKED) fill_ends<DT>(c, src.r, it * kWaves + wave_id(), (int)(threadIdx.x & 63), src.fill_words());
+    unpack<DT>(c, a);
 }
 
 // the element of this lane's registers at virtual index v (the lane must own v)

@@ -7,21 +7,28 @@
 namespace MDSD_NS {
 
 // ---------------------------------------------------------------- RRS / RRSw, rows in registers
-// Alg. 1 for one internal node when the draft call left its record of the draft row (largest
-// stored element, total mass): the target row sits in registers, the draft row is streamed once
+// Alg. 1 for one internal node, with the draft call's record of the draft row (largest stored element,
+// total mass) where there is one: the target row sits in registers, the draft row is streamed once
 // per rejected round, and a node whose first draft is accepted never reads it.  The state after
 // i rejections is the residual U = max(p - c q, 0) with mass W (c_1 = 0, W_0 = 1,
 // c_{i+1} = c_i + W_i rho_{i+1}): round i + 1 accepts x with probability U(x) / (W q_{i+1}(x)).
 // WO (without replacement): q_{i+1} is q without the tokens rejected so far, rescaled by
 // rho_{i+1} = (mass of q) / (mass left); the mass outside all k drafted tokens is summed (positive
 // terms only) in the first pass over the draft row, the masses left are that plus the later drafts'.
+// STATS = false: no record; the draft row's largest element and mass come from one more pass over it,
+// while the target row is on its way.
 // The first pass over the draft row leaves its first kDraftChunksKept chunks per lane in LDS, so
 // that the passes of later rounds read only the rest of it from memory.
+// Bound by instruction issue and the reads of the draft row in about equal parts (see the residual pass).
+// Marked tokens as bits and row ends filled in the packed chunks: bf16 rows of 32001 elements, 31-node
+// trees, B = 64: rrs_verify 49.7 -> 39.8 us, rrsw_verify 52.0 -> 47.9, B = 128 rrsw_verify 94 -> 71; of 50257
+// elements, B = 16: 29.1 -> 25.0 and 32.5 -> 27.5 (those rows were streamed before).  Without records, B = 64
+// trees of 15: 45.7 -> 33.4 us.
 // (40 KB per node at 512 threads, three nodes per CU; 28 KB at 256 threads, four nodes per CU)
 template <int NIT>
 constexpr int kDraftChunksKept = kWG == 256 ? (NIT < 7 ? NIT : 7) : (NIT < 5 ? NIT : 5);
 
-template <int DT, int NIT, bool MASKED, bool WO>
+template <int DT, int NIT, bool MASKED, bool WO, bool STATS>
 __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, const RowView& rp,
                                              const RowView& rq, const RowSrc<DT, NIT, MASKED>& sp,
                                              bool need_full, float* rprob, Shared& sh,
@@ -33,7 +40,8 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
     const int k = P.k;
     const float* ur = P.u + id.row * (k + 1);
     const int32_t* xt = P.tokens + (int64_t)id.b * P.N + id.c0;
-    const mdsd_row_stats st = P.stats_in[id.row];
+    mdsd_row_stats st;
+    if constexpr (STATS) st = P.stats_in[id.row];
     // tokens, the stored logits at them and the uniforms go through LDS (lane i of the first wave
     // fetches draft i), so that no lane holds arrays of them; visible after the first barrier.
     // The tokens and uniforms come over the scalar path (their addresses are the same in every
@@ -63,10 +71,29 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
     }
     if (threadIdx.x == 0) sh.node_u[k] = u_k;
 
-    // ---- target row: shift (cheap estimate first, where there is one) and Zp
     ExpW cp, cq;
     cp.s = P.scale_t;
     cq.s = P.scale_d;
+    if constexpr (!STATS) {
+        RowSrc<DT, 0> row;
+        row.init(rq, ExpW::fill());
+        if (!sweep_streamed_row<DT, false, 2>(row, cq.s, sh, phase, st.max_stored, st.rest_mass)) {
+            float m1[1] = {lane_max(row)};
+            block_max<kWaves, 1>(m1, sh.red, phase);
+            st.max_stored = m1[0];
+            cq.ms = m1[0] * cq.s;
+            float z1[1] = {0.f};
+            row.for_each([&](int, int, const float(&a)[E]) {
+                float w[E];
+#pragma unroll
+                for (int e = 0; e < E; ++e) w[e] = cq(a[e]);
+                z1[0] += chunk_sum<E>(w);
+            });
+            block_sum<kWaves, 1>(z1, sh.red, phase);
+            st.rest_mass = z1[0];
+        }
+    }
+    // ---- target row: shift (cheap estimate first, where there is one) and Zp
     cq.ms = uniform(st.max_stored * cq.s);
     float z1[1];
     auto normaliser = [&](float lane_m) {
@@ -93,14 +120,25 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
     bool decided = false, slabs_current = false;
     int n_rej = 0;
     float rem_k = 0.f;  // WO: unnormalised draft mass outside all k drafted tokens (after the first pass)
-    // one pass over both rows: slab sums (and total) of max(p - c_new q, 0), rejected tokens masked;
-    // with want_rem also the draft mass outside the drafted tokens
-    auto residual_pass = [&](float c_new, bool want_rem, auto KEPT) {
+    // The marked tokens that this lane's chunks hold, one bit per element: a chunk whose byte is 0 in
+    // every lane -- nearly all are -- costs a pass one test.  (The tokens' places compared chunk by chunk
+    // instead filled the passes with scalars: 390 to 2800 spills of them.)
+    constexpr int kWords = (NIT * E + 31) / 32;
+    uint32_t marks[kWords] = {};
+    auto mark = [&](int token) {
+        const int v = token + rp.head, chunk = v / E, s = chunk / 64;
+        const int bit = (s / kWaves) * E + v % E;
+        const bool here = s % kWaves == wave_id() && (chunk & 63) == (int)(threadIdx.x & 63);
+#pragma unroll
+        for (int i = 0; i < kWords; ++i) marks[i] |= here && bit / 32 == i ? 1u << (bit & 31) : 0u;
+    };
+    // One pass over both rows: slab sums (and total) of max(p - c_new q, 0), rejected tokens counting 0.
+    // KEPT: part of the draft row comes from LDS.  REM (without replacement, the first rejected round):
+    // the draft mass outside the drafted tokens is summed as well; the marks are then those of all drafted
+    // tokens, of which the first is the rejected one.  Otherwise they are those of the rejected tokens.
+    auto residual_pass = [&](float c_new, auto KEPT, auto REM_) {
+        constexpr bool REM = decltype(REM_)::value;
         const float c_iZq = c_new * iZq;
-        // slabs of the first two tokens to mask (with more than two, every slab takes the slow check)
-        const int n_mask = want_rem ? k : n_rej;
-        const int s_lo = (sh.node_x[0] + rp.head) / (64 * E);
-        const int s_hi = n_mask > 1 ? (sh.node_x[1] + rp.head) / (64 * E) : s_lo;
         float lane_rem = 0.f;
         SlabSums<NIT> sums;
         // Opaque copies: the weights of the target row do not change from round to round, and
@@ -109,43 +147,32 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
         int lane_o = threadIdx.x & 63, wave_o = wave_id();
         ExpW cpo = cp;
         asm volatile("" : "+v"(lane_o), "+s"(wave_o), "+s"(cpo.ms));
-        for_each_streamed_cached<1, kDraftChunksKept<NIT>, decltype(KEPT)::value>(lane_o, wave_o, sp, rq, ExpW::fill(), q_kept, [&](int it, int s, int chunk, const uint4& dp, const uint4& dq) {
+        for_each_streamed_cached<1, kDraftChunksKept<NIT>, decltype(KEPT)::value>(lane_o, wave_o, sp, rq, ExpW::fill(), q_kept, [&](int it, int, int chunk, const uint4& dp, const uint4& dq) {
+            const uint32_t bits = marks[it * E / 32] >> (it * E % 32);
+            const bool some = __ballot((bits & ((1u << E) - 1u)) != 0) != 0;
             float part[2];
             auto half = [&](auto H) {
                 constexpr int hv = decltype(H)::value;
                 float ep[HE], eq[HE], w[HE];
-                unpack_half<DT, MASKED, hv>(dp, rp, ExpW::fill(), chunk, ep);
-                unpack_half<DT, MASKED, hv>(dq, rq, ExpW::fill(), chunk, eq);
+                unpack_half<DT, hv>(dp, ep);
+                unpack_half<DT, hv>(dq, eq);
 #pragma unroll
                 for (int e = 0; e < HE; ++e) {
                     eq[e] = cq(eq[e]);
                     w[e] = rrs_term(cpo(ep[e]), eq[e], iZp, c_iZq);
                 }
-                if (__builtin_expect(s == s_lo || s == s_hi || n_mask > 2, 0)) {
+                if (__builtin_expect(some, 0)) {
                     asm volatile("" ::: "memory");
-                    for (int j = 0; j < n_mask; ++j) {
-                        const int off = sh.node_x[j] + rp.head - (chunk * E + hv * HE);
+                    const int v_first = REM ? uniform(sh.node_x[0]) + rp.head : 0;
 #pragma unroll
-                        for (int e = 0; e < HE; ++e) {
-                            if (off == e) {
-                                if (j < n_rej) w[e] = 0.f;
-                                eq[e] = 0.f;  // only summed with want_rem, where every drafted token is left out
-                            }
-                        }
+                    for (int e = 0; e < HE; ++e) {
+                        const bool marked = (bits >> (hv * HE + e)) & 1u;
+                        w[e] = (REM ? chunk * E + hv * HE + e == v_first : marked) ? 0.f : w[e];
+                        if constexpr (REM) eq[e] = marked ? 0.f : eq[e];
                     }
                 }
-                if constexpr (HE == 4)
-                    part[hv] = (w[0] + w[1]) + (w[2] + w[3]);
-                else
-                    part[hv] = w[0] + w[1];
-                if constexpr (WO) {
-                    if (want_rem) {
-                        if constexpr (HE == 4)
-                            lane_rem += (eq[0] + eq[1]) + (eq[2] + eq[3]);
-                        else
-                            lane_rem += eq[0] + eq[1];
-                    }
-                }
+                part[hv] = HE == 4 ? (w[0] + w[1]) + (w[HE - 2] + w[HE - 1]) : w[0] + w[1];
+                if constexpr (REM) lane_rem += HE == 4 ? (eq[0] + eq[1]) + (eq[HE - 2] + eq[HE - 1]) : eq[0] + eq[1];
             };
             half(std::integral_constant<int, 0>{});
             __builtin_amdgcn_sched_barrier(0);
@@ -153,12 +180,10 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
             sums.put(it, part[0] + part[1]);
         });
         sums.store(sh.slab_w, rp.nslab);
-        if constexpr (WO) {
-            if (want_rem) {
-                float rr[1] = {lane_rem};
-                block_sum<kWaves, 1>(rr, sh.red, phase);
-                rem_k = rr[0];
-            }
+        if constexpr (REM) {
+            float rr[1] = {lane_rem};
+            block_sum<kWaves, 1>(rr, sh.red, phase);
+            rem_k = rr[0];
         }
         __syncthreads();
         return slab_total(rp.nslab, [&](int j) { return sh.slab_w[j]; });
@@ -198,8 +223,21 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
         const float c_new = fmaf(Wc, rho, c);
         n_rej = i + 1;
         if (i > 0) __syncthreads();  // earlier readers of the slab sums are done
-        const float W_new = i == 0 ? residual_pass(c_new, WO, std::false_type{})
-                                   : residual_pass(c_new, false, std::true_type{});
+        float W_new;
+        if (i == 0) {
+            if constexpr (WO)
+                for (int j = 1; j < k; ++j) mark(sh.node_x[j]);
+            mark(xi);
+            W_new = residual_pass(c_new, std::false_type{}, std::bool_constant<WO>{});
+            if constexpr (WO) {
+#pragma unroll
+                for (int j = 0; j < kWords; ++j) marks[j] = 0;
+                mark(xi);
+            }
+        } else {
+            mark(xi);
+            W_new = residual_pass(c_new, std::true_type{}, std::false_type{});
+        }
         if (W_new > 0.f) {
             c = c_new;
             Wc = W_new;
@@ -218,7 +256,7 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
     if (decided && !need_full) return;
     if (!slabs_current) {
         __syncthreads();
-        residual_pass(c, false, std::false_type{});  // rare: all of the draft row from memory again
+        residual_pass(c, std::false_type{}, std::false_type{});  // rare: all of the draft row from memory again
     }
     const float c_iZq = c * iZq;
     auto cw = [&](int s, float(&w)[E]) {
@@ -243,7 +281,7 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
     if (rprob) write_resid_prob<DT>(rprob, rp, W, cw);
 }
 
-template <int DT, int NIT, bool MASKED, bool WO>
+template <int DT, int NIT, bool MASKED, bool WO, bool STATS>
 __device__ __forceinline__ NodeOut rrs_node_resident(const Params& P, const NodeId& id, Shared& sh,
                                                      uint4 (*q_kept)[kWG], int& phase)
 {
@@ -254,22 +292,22 @@ __device__ __forceinline__ NodeOut rrs_node_resident(const Params& P, const Node
     sp.issue(rp, ExpW::fill());
     NodeOut o{MDSD_NONE, -1, 0, 0.f};
     if (id.c0 < 0) {
-        leaf_resident<DT, NIT, MASKED, false>(P, rp, sp, P.u[id.row * (P.k + 1) + P.k], rprob, sh, phase, o);
+            leaf_resident<DT, NIT, MASKED, false>(P, rp, sp, P.u[id.row * (P.k + 1) + P.k], rprob, sh, phase, o);
     } else {
         const RowView rq = make_row<DT>(P.draft, P.ld_d, id.row, P.V);
-        rrs_resident<DT, NIT, MASKED, WO>(P, id, rp, rq, sp, need_full, rprob, sh, q_kept, phase, o);
+        rrs_resident<DT, NIT, MASKED, WO, STATS>(P, id, rp, rq, sp, need_full, rprob, sh, q_kept, phase, o);
     }
     write_node_outputs(P, id, o.outcome, o.token, o.rmass, o.flags);
     return o;
 }
 
-template <int DT, int NIT, bool MASKED, bool WO>
+template <int DT, int NIT, bool MASKED, bool WO, bool STATS>
 __global__ __launch_bounds__(kWG, (kWG == 256 || NIT > 8 ? 4 : kStatsWavesPerSimd)) void rrs_verify_resident(const Params P)
 {
     __shared__ Shared sh;
     __shared__ uint4 q_kept[kDraftChunksKept<NIT>][kWG];
     int phase = 0;
-    rrs_node_resident<DT, NIT, MASKED, WO>(P, node_of_block(P), sh, q_kept, phase);
+    rrs_node_resident<DT, NIT, MASKED, WO, STATS>(P, node_of_block(P), sh, q_kept, phase);
 }
 
 }  // namespace MDSD_NS

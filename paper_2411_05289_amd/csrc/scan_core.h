@@ -47,11 +47,55 @@ __device__ __forceinline__ float chunk_sum(const float (&w)[E])
         return (w[0] + w[1]) + (w[2] + w[3]);
 }
 
+// The words of a packed chunk with the elements outside [lo, hi) replaced by the fill (both halves of fw
+// for bf16), as masks: ones where the fill goes.  lo and hi are the same in every lane.
+template <int DT>
+__device__ __forceinline__ uint32_t fill_mask(int j, int lo, int hi)
+{
+    if constexpr (DT == 0)
+        return j < lo || j >= hi ? 0xffffffffu : 0u;
+    else
+        return (2 * j < lo || 2 * j >= hi ? 0x0000ffffu : 0u) | (2 * j + 1 < lo || 2 * j + 1 >= hi ? 0xffff0000u : 0u);
+}
+template <int DT>
+__device__ __forceinline__ void fill_outside(uint4& d, bool here, int lo, int hi, uint32_t fw)
+{
+    uint32_t w[4] = {d.x, d.y, d.z, d.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t m = here ? fill_mask<DT>(j, lo, hi) : 0u;
+        w[j] = (w[j] & ~m) | (fw & m);
+    }
+    d = make_uint4(w[0], w[1], w[2], w[3]);
+}
+// real elements in the last chunk of a row
+template <int DT>
+__device__ __forceinline__ int tail_elements(const RowView& r)
+{
+    return r.nvirt - (r.nchunk - 1) * Elem<DT>::kPerChunk;
+}
+// d, the wave's slab s of row r, with the fill in place of what is not the row's in its first and its
+// last chunk.  Two slabs of a row: real branches, so that their work costs the others a scalar test.
+template <int DT>
+__device__ __forceinline__ void fill_ends(uint4& d, const RowView& r, int s, int lane, uint32_t fw)
+{
+    if (__builtin_expect(s == 0 && r.head > 0, 0)) {
+        asm volatile("" ::: "memory");
+        fill_outside<DT>(d, lane == 0, r.head, Elem<DT>::kPerChunk, fw);
+    }
+    if (__builtin_expect(s == r.nslab - 1, 0)) {
+        asm volatile("" ::: "memory");
+        fill_outside<DT>(d, lane == ((r.nchunk - 1) & 63), 0, tail_elements<DT>(r), fw);
+    }
+}
+
 // A row as the passes see it.  NIT == 0: every pass streams the row from memory
 // (any V).  NIT > 0: the row is loaded once, NIT chunks per lane, and stays in
 // registers for all passes (V up to NIT * kWaves * 64 chunks); chunk `it` of a
 // lane belongs to slab it * kWaves + wave, so each load instruction of a wave
-// still covers 1 KiB of consecutive memory.  Masked elements hold `fill`.
+// still covers 1 KiB of consecutive memory.  Masked elements read as `fill`: with MASKED
+// every pass fills the ends of its packed chunks in branches that the wave with such a chunk takes, one
+// scalar test for all others.
 // MASKED = false: the caller has checked that every row starts on a 16-byte boundary and
 // that V is a whole number of chunks, so no element ever needs masking.
 template <int DT, int NIT, bool MASKED = true>
@@ -68,8 +112,7 @@ struct RowSrc {
         r = rv;
         fill = f;
         const int lane = threadIdx.x & 63, wave = wave_id();
-        const uint32_t fb = __builtin_bit_cast(uint32_t, f);
-        const uint32_t fw = DT == 0 ? fb : ((fb >> 16) | (fb & 0xffff0000u));
+        const uint32_t fw = fill_words();
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
             const int chunk = (it * kWaves + wave) * 64 + lane;
@@ -78,24 +121,24 @@ struct RowSrc {
     }
     __device__ __forceinline__ void init(const RowView& rv, float f) { issue(rv, f); }
 
-    // the first and the last chunk of the row may hold elements that are not the row's:
-    // those read as `fill`.  The registers themselves are left alone.
-    __device__ __forceinline__ void mask(int chunk, float (&a)[E]) const
+    // this lane's register chunk `it` with the fill in place of the elements that are not the row's.  (The
+    // registers themselves are left alone: changed in place they cost the RRS kernels a hundred spills.)
+    __device__ __forceinline__ uint4 chunk_of(int it, int lane, int wave) const
     {
-        if constexpr (!MASKED) return;
-        const int v0 = chunk * E;
-        if (v0 < r.head || v0 + E > r.nvirt) {
-#pragma unroll
-            for (int e = 0; e < E; ++e)
-                if (v0 + e < r.head || v0 + e >= r.nvirt) a[e] = fill;
-        }
+        uint4 c = d[it];
+        if constexpr (MASKED) fill_ends<DT>(c, r, it * kWaves + wave, lane, fill_words());
+        return c;
+    }
+    __device__ __forceinline__ uint32_t fill_words() const
+    {
+        const uint32_t fb = __builtin_bit_cast(uint32_t, fill);
+        return DT == 0 ? fb : ((fb >> 16) | (fb & 0xffff0000u));
     }
 
     // this lane's register chunk `it` as floats (it: compile-time constant after unrolling)
     __device__ __forceinline__ void get(int it, float (&a)[E]) const
     {
-        unpack<DT>(d[it], a);
-        mask((it * kWaves + wave_id()) * 64 + (int)(threadIdx.x & 63), a);
+        unpack<DT>(chunk_of(it, (int)(threadIdx.x & 63), wave_id()), a);
     }
 
     // body(slab, chunk, a[E])
@@ -130,13 +173,12 @@ struct RowSrc {
         }
     }
 
-    // A softmax shift for a quarter of the work of an exact maximum.  bf16 rows that need no
-    // masking only: the largest 32-bit word of this lane's chunks read as a float, which is the
+    // A softmax shift for a quarter of the work of an exact maximum.  bf16 rows only: the largest 32-bit word of this lane's chunks read as a float, which is the
     // odd-indexed element with its neighbour's bits as extra mantissa (less than one bf16 ulp
     // away from it).  The even-indexed elements may lie above it: whoever shifts by this
     // value checks that the sum of the weights stayed finite and positive, and takes the
     // exact maximum if not.
-    static constexpr bool kHasShiftEstimate = DT == 1 && !MASKED;
+    static constexpr bool kHasShiftEstimate = DT == 1;
     __device__ __forceinline__ float lane_shift_estimate() const
     {
         const int lane = threadIdx.x & 63, wave = wave_id();
@@ -144,8 +186,9 @@ struct RowSrc {
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
             if ((it * kWaves + wave) * 64 + lane < r.nchunk) {
-                m = fmaxf(fmaxf(m, __builtin_bit_cast(float, d[it].x)), __builtin_bit_cast(float, d[it].y));
-                m = fmaxf(fmaxf(m, __builtin_bit_cast(float, d[it].z)), __builtin_bit_cast(float, d[it].w));
+                const uint4 c = chunk_of(it, lane, wave);
+                m = fmaxf(fmaxf(m, __builtin_bit_cast(float, c.x)), __builtin_bit_cast(float, c.y));
+                m = fmaxf(fmaxf(m, __builtin_bit_cast(float, c.z)), __builtin_bit_cast(float, c.w));
             }
         }
         return m;
@@ -235,13 +278,10 @@ __device__ __forceinline__ void for_each2(const RowSrc<DT, NIT, MASKED>& sa, con
     }
 }
 
-// half H (0 or 1) of a 16-byte chunk as floats; `chunk` is its number in row r, whose masked
-// elements read as `fill`
-template <int DT, bool MASKED, int H>
-__device__ __forceinline__ void unpack_half(const uint4& d, const RowView& r, float fill, int chunk,
-                                            float (&v)[Elem<DT>::kPerChunk / 2])
+// half H (0 or 1) of a 16-byte chunk as floats
+template <int DT, int H>
+__device__ __forceinline__ void unpack_half(const uint4& d, float (&v)[Elem<DT>::kPerChunk / 2])
 {
-    constexpr int E = Elem<DT>::kPerChunk, HE = E / 2;
     const uint32_t w0 = H == 0 ? d.x : d.z, w1 = H == 0 ? d.y : d.w;
     if constexpr (DT == 0) {
         v[0] = __builtin_bit_cast(float, w0);
@@ -251,14 +291,6 @@ __device__ __forceinline__ void unpack_half(const uint4& d, const RowView& r, fl
         v[1] = __builtin_bit_cast(float, w0 & 0xffff0000u);
         v[2] = __builtin_bit_cast(float, w1 << 16);
         v[3] = __builtin_bit_cast(float, w1 & 0xffff0000u);
-    }
-    if constexpr (MASKED) {
-        const int v0 = chunk * E + H * HE;
-        if (v0 < r.head || v0 + HE > r.nvirt) {
-#pragma unroll
-            for (int e = 0; e < HE; ++e)
-                if (v0 + e < r.head || v0 + e >= r.nvirt) v[e] = fill;
-        }
     }
 }
 
@@ -305,7 +337,8 @@ __device__ __forceinline__ void for_each_streamed_at(int lane, int wave, const R
             if ((s + 1) * 64 > rb.nchunk) {  // the row's last slab, not full
                 if (s * 64 + lane >= rb.nchunk) cur = make_uint4(fw, fw, fw, fw);
             }
-            body(it, s, s * 64 + lane, sa.d[it], cur);
+            if constexpr (MASKED) fill_ends<DT>(cur, rb, s, lane, fw);
+            body(it, s, s * 64 + lane, sa.chunk_of(it, lane, wave), cur);
         }
         __builtin_amdgcn_sched_barrier(0);  // one chunk pair at a time
     }
@@ -353,8 +386,9 @@ __device__ __forceinline__ void for_each_streamed_cached(int lane, int wave, con
             if ((s + 1) * 64 > rb.nchunk) {  // the row's last slab, not full
                 if (s * 64 + lane >= rb.nchunk) cur = make_uint4(fw, fw, fw, fw);
             }
+            if constexpr (MASKED && !(CACHED && it < QC)) fill_ends<DT>(cur, rb, s, lane, fw);
             if constexpr (!CACHED && it < QC) cache[it][tid] = cur;
-            body(it, s, s * 64 + lane, sa.d[it], cur);
+            body(it, s, s * 64 + lane, sa.chunk_of(it, lane, wave), cur);
         }
         __builtin_amdgcn_sched_barrier(0);  // one chunk pair at a time
     });

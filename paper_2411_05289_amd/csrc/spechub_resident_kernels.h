@@ -280,8 +280,8 @@ __device__ __forceinline__ void spechub_resident(const Params& P, const NodeIn& 
             auto half = [&](auto H) {
                 constexpr int hv = decltype(H)::value;
                 float ep[HE], eq[HE];
-                unpack_half<DT, MASKED, hv>(dp, rp, ExpW::fill(), chunk, ep);
-                unpack_half<DT, MASKED, hv>(dq, rq, ExpW::fill(), chunk, eq);
+                unpack_half<DT, hv>(dp, ep);
+                unpack_half<DT, hv>(dq, eq);
 #pragma unroll
                 for (int e = 0; e < HE; ++e) {
                     ep[e] = cp(ep[e]);

@@ -535,12 +535,25 @@ static void launch_verify_n(int nit, bool path, dim3 grid, dim3 block, hipStream
             hipLaunchKernelGGL((verify_path_kernel<DT, LG, METHOD, 0>), grid, block, 0, st, P);
         return;
     }
-    switch (nit) {
-    case 4: hipLaunchKernelGGL((verify_kernel<DT, LG, METHOD, 4>), grid, block, 0, st, P); break;
-    case 8: hipLaunchKernelGGL((verify_kernel<DT, LG, METHOD, 8>), grid, block, 0, st, P); break;
-    case 16: hipLaunchKernelGGL((verify_kernel<DT, LG, METHOD, 16>), grid, block, 0, st, P); break;
-    default: hipLaunchKernelGGL((verify_kernel<DT, LG, METHOD, 0>), grid, block, 0, st, P); break;
+    // logit rows that fit in registers have kernels of their own; rows of probabilities in registers: any
+    // size for SpecHub, the smallest for the RRS methods (whose rounds need the registers)
+    if constexpr (!LG) {
+        if (nit == 4) {
+            hipLaunchKernelGGL((verify_kernel<DT, LG, METHOD, 4>), grid, block, 0, st, P);
+            return;
+        }
+        if constexpr (METHOD == kSpecHub) {
+            if (nit == 8) {
+                hipLaunchKernelGGL((verify_kernel<DT, LG, METHOD, 8>), grid, block, 0, st, P);
+                return;
+            }
+            if (nit == 16) {
+                hipLaunchKernelGGL((verify_kernel<DT, LG, METHOD, 16>), grid, block, 0, st, P);
+                return;
+            }
+        }
     }
+    hipLaunchKernelGGL((verify_kernel<DT, LG, METHOD, 0>), grid, block, 0, st, P);
 }
 
 template <int METHOD>

@@ -255,6 +255,9 @@ _VARIANTS = [
     ("bf16", "logits", 50304, 0),    # bf16, 16 chunks per lane, no masking
     ("bf16", "logits", 50257, 0),    # ... masked
     ("bf16", "logits", 65520, 0),    # the longest row that stays in registers
+    ("bf16", "logits", 16385, 5),    # ... masked, one element into a slab
+    ("bf16", "logits", 32767, 7),    # ... one element short of one, rows starting at a chunk's last element
+    ("fp32", "logits", 8193, 3),     # ... fp32
     ("bf16", "probs", 1000, 0),      # bf16 probabilities: one wavefront per node
     ("bf16", "probs", 4099, 3),      # ... masked
     ("bf16", "probs", 40000, 0),     # ... 16 chunks per lane / streamed
