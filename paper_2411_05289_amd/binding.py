@@ -3,6 +3,8 @@
 Argument marshalling only: torch supplies device memory and the HIP stream;
 every step of the method runs inside ``libmdsd.so``.  There is no fallback: if
 the library has not been built, or a tensor is not on the GPU, the call raises.
+Calls that allocate their outputs are marshalled in native code (``_host.so``,
+csrc/host.cpp); it hands anything out of the ordinary back to the functions here.
 """
 from __future__ import annotations
 
@@ -93,6 +95,22 @@ def lib():
     return _lib
 
 
+_host = None
+
+
+def _native():
+    """The native marshalling of the calls that allocate their outputs."""
+    global _host
+    if _host is None:
+        lib()
+        try:
+            from . import _host as module
+        except ImportError as e:
+            raise RuntimeError("_host.so is not built (run `python -m paper_2411_05289_amd.build`)") from e
+        _host = module
+    return _host
+
+
 def strerror(code: int) -> str:
     return lib().mdsd_strerror(code).decode()
 
@@ -180,7 +198,14 @@ def _c_problem(pb: Problem) -> _Problem:
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current HIP stream of the current device as an integer.  (torch.cuda.current_stream() makes a
+    Stream object on the way: 2.9 us a call against 0.2.)"""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+_METHODS = ("spechub", "rrs", "rrsw")
+_DRAFT_CALLS = {m + "_draft": i for i, m in enumerate(_METHODS)}
+_VERIFY_CALLS = {m + "_verify" + p: i + 3 * j for j, p in enumerate(("", "_path")) for i, m in enumerate(_METHODS)}
 
 
 def workspace_bytes(pb: Problem) -> int:
@@ -189,6 +214,13 @@ def workspace_bytes(pb: Problem) -> int:
 
 
 def _draft(fn_name, pb: Problem, u: torch.Tensor, out, with_hub: bool):
+    if out is None and pb.draft.is_cuda:
+        got = _native().draft(_DRAFT_CALLS[fn_name], _stream(), pb.target, pb.draft, pb.kind, pb.k, pb.depth,
+                              pb.temp_target, pb.temp_draft, pb.first_child, pb.draft_stats, u)
+        if type(got) is dict:
+            return got
+        if got is not None:
+            raise MdsdError(got, fn_name)
     cp = _c_problem(pb)
     B, N, _ = pb.draft.shape
     dev = pb.draft.device
@@ -251,6 +283,24 @@ def alloc_workspace(pb: Problem) -> torch.Tensor:
 
 
 def _verify(fn_name, pb: Problem, tokens: torch.Tensor, u: torch.Tensor, out, workspace=None, **want):
+    if out is None and workspace is None and pb.draft.is_cuda:
+        return _verify_new(fn_name, pb, tokens, u, **want)
+    return _verify_into(fn_name, pb, tokens, u, out, workspace, **want)
+
+
+def _verify_new(fn_name, pb: Problem, tokens, u, *, resid_mass=False, flags=True, resid_prob=False, walk=True):
+    got = _native().verify(_VERIFY_CALLS[fn_name], _stream(), pb.target, pb.draft, pb.kind, pb.k, pb.depth,
+                           pb.temp_target, pb.temp_draft, pb.first_child, pb.draft_stats, tokens, u,
+                           resid_mass, flags, resid_prob, walk)
+    if type(got) is dict:
+        return got
+    if got is not None:
+        raise MdsdError(got, fn_name)
+    return _verify_into(fn_name, pb, tokens, u, None, None, resid_mass=resid_mass, flags=flags,
+                        resid_prob=resid_prob, walk=walk)
+
+
+def _verify_into(fn_name, pb: Problem, tokens: torch.Tensor, u: torch.Tensor, out, workspace, **want):
     cp = _c_problem(pb)
     if pb.target is None:
         raise ValueError("verify needs target rows")

@@ -15,6 +15,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmdsd.so")
+HOST = os.path.join(HERE, "_host.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -36,6 +37,26 @@ def jobs() -> int:
     except ValueError:
         n = 0
     return max(1, min(n or (os.cpu_count() or 1), 16))
+
+
+def build_host(verbose: bool = True) -> str:
+    """The native marshalling of the Python binding (host code only), linked to libmdsd.so."""
+    import sysconfig
+    import torch
+    where = os.path.dirname(torch.__file__)
+    tmp = HOST + ".tmp%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           "-I", os.path.join(ROOT, "include"), "-I", os.path.join(where, "include"),
+           "-I", os.path.join(where, "include", "torch", "csrc", "api", "include"),
+           "-I", sysconfig.get_paths()["include"], "-o", tmp, os.path.join(CSRC, "host.cpp"),
+           "-L", HERE, "-l:libmdsd.so", "-L", os.path.join(where, "lib"),
+           "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, HOST)
+    return HOST
 
 
 def build(verbose: bool = True, extra=()) -> str:
@@ -60,6 +81,7 @@ def build(verbose: bool = True, extra=()) -> str:
     subprocess.check_call(cmd)
     os.replace(tmp, LIB)
     shutil.rmtree(OBJ, ignore_errors=True)
+    build_host(verbose)
     return LIB
 
 

@@ -435,6 +435,38 @@ def test_workspace_is_checked():
     assert torch.equal(a["outcome"], b["outcome"]) and not ws.any()
 
 
+# ----------------------------------------------------------------- calls that allocate their outputs
+def test_calls_outside_the_native_marshalling():
+    """Arguments that the native marshalling hands back (integer temperatures, tensor subclasses) give the
+    same results as those it takes, and what was refused stays refused, with the same errors."""
+    import dataclasses
+    wl = W.config(3, device=DEV, B=3, V=300, depth=3, seed=81)
+    pb = B.Problem.from_workload(wl)
+    u_d, u_v = uniforms(wl, 81)
+    tok = B.spechub_draft(pb, u_d)["tokens"]
+    want = B.spechub_verify(pb, tok, u_v, resid_mass=True, resid_prob=True)
+    class Sub(torch.Tensor):
+        pass
+    for other in (dataclasses.replace(pb, temp_target=1, temp_draft=1),
+                  dataclasses.replace(pb, target=pb.target.as_subclass(Sub), draft=pb.draft.as_subclass(Sub))):
+        d = B.spechub_draft(other, u_d)
+        assert list(d) == ["tokens", "flags", "hub"] and torch.equal(d["tokens"], tok)
+        got = B.spechub_verify(other, tok, u_v, resid_mass=True, resid_prob=True)
+        assert list(got) == list(want) and all(torch.equal(got[k], want[k]) for k in want)
+    for bad in (lambda: B.spechub_draft(pb, u_d.double()), lambda: B.spechub_verify(pb, tok.long(), u_v),
+                lambda: B.spechub_verify(pb, tok, u_v[:, :, :2]), lambda: B.rrs_draft(pb, u_d.cpu()),
+                lambda: B.spechub_draft(dataclasses.replace(pb, draft=pb.draft.transpose(0, 1)), u_d),
+                lambda: B.spechub_verify(dataclasses.replace(pb, target=None), tok, u_v),
+                lambda: B.spechub_verify(dataclasses.replace(pb, target=pb.target.float()), tok, u_v)):
+        with pytest.raises(ValueError):
+            bad()
+    with pytest.raises(TypeError):
+        B.spechub_verify(pb, tok, u_v, no_such_output=True)
+    with pytest.raises(B.MdsdError) as err:
+        B.rrs_verify(dataclasses.replace(pb, depth=2), tok, u_v)
+    assert err.value.code == -2
+
+
 # ----------------------------------------------------------------- degenerate and invalid inputs
 def _tiny_probs(p_rows, q_rows, k=2, depth=2):
     p = torch.tensor(p_rows, dtype=torch.float32, device=DEV).view(1, -1, len(p_rows[0]))
