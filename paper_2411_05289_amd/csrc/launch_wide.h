@@ -1,0 +1,24 @@
+// Launchers of the kernels for logit rows in registers built for 1024 threads per node: batches that leave
+// CUs without a node, where a node's own chain of passes is what a call waits for.  Twice the wavefronts
+// ask for the row at once and share every pass; and long rows of the RRS methods, of which a CU's registers
+// and LDS (nine chunks per lane of the draft row) hold what 512-thread workgroups would stream again in
+// every rejected round.  The caller chooses by size (mdsd.hip, where the two sides are measured).
+// nit = 4, 8, 16 or, RRS methods, 20 chunks per lane (20: some of the row spilled, and still ahead: bf16 rows
+// of 152064, k = 4, 672 nodes 145 -> 93 us); SpecHub verify without the draft call's records, which keeps
+// both rows, up to 8; draft 4, fp32 8.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include "params.h"
+
+namespace mdsd_wide {
+
+constexpr int kThreads = 1024;
+constexpr int kMaxNitTwoRows = 8;
+
+void launch_spechub(int dtype, int nit, bool path, dim3 grid, hipStream_t st, const mdsd::Params& P);
+void launch_rrs(int dtype, int nit, dim3 grid, hipStream_t st, const mdsd::Params& P);
+void launch_rrsw(int dtype, int nit, dim3 grid, hipStream_t st, const mdsd::Params& P);
+void launch_draft(int method, int dtype, int nit, dim3 grid, hipStream_t st, const mdsd::Params& P);
+
+}  // namespace mdsd_wide

@@ -6,6 +6,7 @@
 #include "launch_group.h"
 #include "launch_half.h"
 #include "launch_small.h"
+#include "launch_wide.h"
 
 #include <atomic>
 
@@ -184,6 +185,48 @@ static dim3 node_grid(const Params& P, int nit)
 // tree nodes per batch from which the 256-thread verify kernels take over from the 512-thread ones
 constexpr int64_t kHalfWidthMinNodes = 2300;
 
+// ---- 1024 threads per node, logit rows in registers
+// chunks per lane of such a workgroup; 0: the row is too long
+static int wide_chunks(const Params& P)
+{
+    const int per_lane = (P.row_chunks + mdsd_wide::kThreads - 1) / mdsd_wide::kThreads;
+    return per_lane <= 4 ? 4 : per_lane <= 8 ? 8 : per_lane <= 16 ? 16 : per_lane <= 20 ? 20 : 0;
+}
+// a batch that leaves CUs without a node
+constexpr int64_t kWideMaxNodes = 256;
+// RRS methods on rows that the 512-thread kernels would stream again in every rejected round: up to this many
+// nodes.  One node per CU gains on the nodes that reject and loses on leaves, which are loaded and worked
+// on in turns (bf16 rows of 100 thousand, k = 4: 672 nodes 99 -> 57 us, 1344 142 -> 105, 2688 181 -> 176;
+// k = 2, where leaves are the larger part: 480 nodes 60 -> 41 us, 960 88 -> 82, 1920 124 -> 140).  Nodes
+// with children here and leaves streamed, in two launches, was slower than either (k = 4, 2688 nodes
+// of 152064: 216 + 133 us against 268).
+constexpr int64_t kWideLongRowNodes = 1024, kWideLongRowNodesManyDrafts = 1536;
+// Verify.  SpecHub, which reads its rows once or twice: rows of more than eight chunks per lane of a
+// 512-thread workgroup, few nodes (60 nodes of 100 thousand: 28 -> 22 us; rows of 32 thousand 10.3 -> 10.9).
+static int wide_verify_chunks(int method, const mdsd_problem* pb, const Params& P, bool path)
+{
+    if (pb->kind != MDSD_LOGITS || (path && method != kSpecHub)) return 0;
+    const int nit = wide_chunks(P);
+    const int64_t nodes = (int64_t)P.B * (path ? 1 : P.N);
+    if (method != kSpecHub) {
+        const int64_t most = P.row_chunks <= 16 * kWG ? kWideMaxNodes
+                             : P.k > 2                ? kWideLongRowNodesManyDrafts
+                                                      : kWideLongRowNodes;
+        return P.row_chunks > 4 * kWG && nodes <= most ? nit : 0;
+    }
+    const int most_nit = P.stats_in ? 16 : mdsd_wide::kMaxNitTwoRows;
+    return P.row_chunks > 8 * kWG && nodes <= kWideMaxNodes && nit <= most_nit ? nit : 0;
+}
+// Draft: few nodes, rows whose passes outweigh the draws behind them, which cost more threads' time (7 nodes,
+// fp32 rows of 32000 9.4 -> 8.4 us, bf16 8.3 -> 7.5; bf16 rows of 50257 9.5 -> 10.1).
+static int wide_draft_chunks(const mdsd_problem* pb, const Params& P)
+{
+    const int64_t nodes = (int64_t)P.B * (P.first_child ? P.N : P.n_internal);
+    if (pb->kind != MDSD_LOGITS || nodes > kWideMaxNodes / 2 || P.row_chunks <= 4 * kWG) return 0;
+    const int nit = wide_chunks(P);
+    return nit <= (pb->dtype == MDSD_FP32 ? 8 : 4) ? nit : 0;
+}
+
 // SpecHub nodes of more than 64 chunks per row, from this many on: one wavefront per node with the rows
 // in registers and more wavefronts on a SIMD (60000 nodes of 1000 bf16 elements 68 -> 55 us, of 2000 90 ->
 // 77; 8000 nodes 11.3 against 11.8 us).  The RRS methods gain from their groups at every size (119 -> 80,
@@ -215,6 +258,13 @@ static void launch_verify(int method, const mdsd_problem* pb, const Params& P, b
     case 2: mdsd_pair::launch_verify(method, pb->dtype, lg, path, grid, st, P); return;
     case 4: mdsd_quad::launch_verify(method, pb->dtype, lg, path, grid, st, P); return;
     default: break;
+    }
+    if (const int wide = wide_verify_chunks(method, pb, P, path)) {
+        if (method == kSpecHub)
+            mdsd_wide::launch_spechub(pb->dtype, wide, path, path ? grid : node_grid(P, wide), st, P);
+        else
+            (method == kRRS ? mdsd_wide::launch_rrs : mdsd_wide::launch_rrsw)(pb->dtype, wide, node_grid(P, wide), st, P);
+        return;
     }
     // Rows of eight chunks per lane, the draft call's records at hand, and a batch that fills the chip
     // several times over: 256 threads per node with sixteen chunks per lane, four nodes per CU
@@ -268,6 +318,10 @@ static void launch_draft(int method, const mdsd_problem* pb, const Params& P, hi
     case 2: mdsd_pair::launch_draft(method, pb->dtype, lg, st, P); return;
     case 4: mdsd_quad::launch_draft(method, pb->dtype, lg, st, P); return;
     default: break;
+    }
+    if (const int wide = wide_draft_chunks(pb, P)) {
+        mdsd_wide::launch_draft(method, pb->dtype, wide, node_grid(P, wide), st, P);
+        return;
     }
     const int es = pb->dtype == MDSD_FP32 ? 4 : 2;
     const bool masked = ((uintptr_t)pb->draft & 15) || ((pb->ld_d * es) & 15) || (pb->V % (16 / es));

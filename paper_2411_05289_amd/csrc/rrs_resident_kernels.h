@@ -24,9 +24,12 @@ namespace MDSD_NS {
 // trees, B = 64: rrs_verify 49.7 -> 39.8 us, rrsw_verify 52.0 -> 47.9, B = 128 rrsw_verify 94 -> 71; of 50257
 // elements, B = 16: 29.1 -> 25.0 and 32.5 -> 27.5 (those rows were streamed before).  Without records, B = 64
 // trees of 15: 45.7 -> 33.4 us.
-// (40 KB per node at 512 threads, three nodes per CU; 28 KB at 256 threads, four nodes per CU)
+// (40 KB per node at 512 threads, three nodes per CU; 28 KB at 256 threads, four nodes per CU; 144 KB at
+// 1024 threads, one node per CU)
 template <int NIT>
-constexpr int kDraftChunksKept = kWG == 256 ? (NIT < 7 ? NIT : 7) : (NIT < 5 ? NIT : 5);
+constexpr int kDraftChunksKept = kWG == 1024  ? (NIT < 9 ? NIT : 9)
+                                 : kWG == 256 ? (NIT < 7 ? NIT : 7)
+                                              : (NIT < 5 ? NIT : 5);
 
 template <int DT, int NIT, bool MASKED, bool WO, bool STATS>
 __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, const RowView& rp,
@@ -302,7 +305,7 @@ __device__ __forceinline__ NodeOut rrs_node_resident(const Params& P, const Node
 }
 
 template <int DT, int NIT, bool MASKED, bool WO, bool STATS>
-__global__ __launch_bounds__(kWG, (kWG == 256 || NIT > 8 ? 4 : kStatsWavesPerSimd)) void rrs_verify_resident(const Params P)
+__global__ __launch_bounds__(kWG, (kWG != 512 || NIT > 8 ? 4 : kStatsWavesPerSimd)) void rrs_verify_resident(const Params P)
 {
     __shared__ Shared sh;
     __shared__ uint4 q_kept[kDraftChunksKept<NIT>][kWG];

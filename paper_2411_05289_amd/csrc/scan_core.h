@@ -83,7 +83,7 @@ __device__ __forceinline__ void fill_ends(uint4& d, const RowView& r, int s, int
         asm volatile("" ::: "memory");
         fill_outside<DT>(d, lane == 0, r.head, Elem<DT>::kPerChunk, fw);
     }
-    if (__builtin_expect(s == r.nslab - 1, 0)) {
+    if (__builtin_expect(s == r.nslab - 1 && tail_elements<DT>(r) < Elem<DT>::kPerChunk, 0)) {
         asm volatile("" ::: "memory");
         fill_outside<DT>(d, lane == ((r.nchunk - 1) & 63), 0, tail_elements<DT>(r), fw);
     }

@@ -8,9 +8,14 @@ namespace MDSD_NS {
 
 // Waves per SIMD the kernels are held to.  512 threads per node: with the draft call's records 6
 // (80 registers, three workgroups per CU), without them 4, with 16 chunks per lane 2.  256 threads
-// per node (16 chunks per lane, records at hand): 4 = 128 registers = four nodes per CU.
+// per node (16 chunks per lane, records at hand): 4 = 128 registers = four nodes per CU.  1024 threads:
+// 4, one node per CU.
 template <int NIT, bool STATS>
-constexpr int kVerifyWavesPerSimd = kWG == 256 ? (STATS ? 4 : 2) : (NIT <= 8 ? (STATS ? kStatsWavesPerSimd : 4) : (STATS ? 4 : 2));
+constexpr int kVerifyWavesPerSimd = kWG == 1024  ? 4
+                                    : kWG == 256 ? (STATS ? 4 : 2)
+                                                 : (NIT <= 8 ? (STATS ? kStatsWavesPerSimd : 4) : (STATS ? 4 : 2));
+template <int NIT>
+constexpr int kPathWavesPerSimd = kWG == 1024 || NIT <= 8 ? 4 : 2;
 
 // the scalars of one node that come from memory: the pair, the stored logits at its tokens,
 // the uniforms.  Asked for together with the rows, used after the first passes.
@@ -424,7 +429,7 @@ __global__ __launch_bounds__(kWG, (kVerifyWavesPerSimd<NIT, STATS>)) void spechu
 }
 
 template <int DT, int NIT, bool MASKED, bool STATS>
-__global__ __launch_bounds__(kWG, (NIT <= 8 ? 4 : 2)) void spechub_path_resident(const Params P)
+__global__ __launch_bounds__(kWG, (kPathWavesPerSimd<NIT>)) void spechub_path_resident(const Params P)
 {
     __shared__ Shared sh;
     int phase = 0;

@@ -323,6 +323,32 @@ def test_batches_of_more_than_2300_nodes(method, dtype, V, off, request):
     note(request, check_case(method, wl, seed=V % 1000, seqs=[0, 1, Bn // 2, Bn - 1], full_outputs=False))
 
 
+# ----------------------------------------------------------------- few nodes, long rows: 1024 threads per node
+# (dtype, V, row offset, trees): 4, 8, 16 and 20 chunks per lane of 1024 threads at the last row they hold
+# (chunks 1024 x 4, 8, 16, 20) and the first they do not; more than 20: streamed
+_WIDE = [
+    ("bf16", 32768, 0, 2), ("bf16", 32761, 3, 2), ("fp32", 16388, 0, 2), ("bf16", 65536, 0, 2),
+    ("bf16", 65538, 1, 2), ("fp32", 65533, 3, 1), ("bf16", 131072, 0, 1), ("bf16", 131075, 7, 1),
+    ("bf16", 163840, 0, 1), ("bf16", 163842, 0, 1),
+]
+
+
+@pytest.mark.parametrize("method", ALL)
+@pytest.mark.parametrize("dtype,V,off,Bn", _WIDE, ids=["%s_V%d_off%d_B%d" % v for v in _WIDE])
+def test_few_nodes_with_long_rows(method, dtype, V, off, Bn, request):
+    k, depth = (2, 3) if method == "spechub" else (4, 2)
+    N = W.tree_nodes(k, depth)
+    td = torch.float32 if dtype == "fp32" else torch.bfloat16
+    t, d = W.llm_like_logits(Bn, N, V, logit_std=3.0, draft_noise_std=2.0, dtype=td, seed=V + 5, device=DEV)
+    big_t = torch.zeros((Bn * N * V + off,), dtype=td, device=DEV)
+    big_d = torch.zeros((Bn * N * V + off,), dtype=td, device=DEV)
+    tv, dv = big_t[off:].view(Bn, N, V), big_d[off:].view(Bn, N, V)
+    tv.copy_(t)
+    dv.copy_(d)
+    wl = W.Workload("wide_%s_V%d" % (dtype, V), Bn, N, V, k, depth, dtype, "logits", 0.9, 1.1, tv, dv)
+    note(request, check_case(method, wl, seed=V % 1000))
+
+
 # ----------------------------------------------------------------- short rows: lanes per node
 # (dtype, kind, V, row offset, nodes per tree's depth, trees): 4, 8, 16, 32 and 64 lanes per node at the
 # last row they hold and the first they do not (16-byte chunks 4 G and 4 G + 1), in batches small enough
