@@ -659,7 +659,10 @@ __device__ __forceinline__ void walk_and_verify(const Params& P, VerifyNode veri
 // nothing finite, which refers to 0: its weights may then have lost their low bits).
 // On success: M = maximum of the stored row, Z = sum of 2^((l - M) s); with SLABS the slab
 // sums in LDS are in the same units and visible to every wave.
-template <int DT, bool SLABS, int AHEAD = 1, class Src>
+// BY4: the slab sums reduced four slabs at a time (the draft kernels that are bound by issue: SpecHub, 960
+// rows of 128256 bf16 elements 31.4 -> 27.9 us, RRSw, 896 rows of 100 thousand 52.8 -> 48.8; the RRS draft
+// 47.9 -> 49.2 and the verify kernels, config 4's 456 -> 475, lose by it).
+template <int DT, bool SLABS, int AHEAD = 1, bool BY4 = false, class Src>
 __device__ __forceinline__ bool sweep_streamed_row(const Src& src, float s, Shared& sh, int& phase, float& M,
                                                    float& Z, float* lane_max_out = nullptr,
                                                    int* lane_max_chunk_out = nullptr)
@@ -679,7 +682,7 @@ __device__ __forceinline__ bool sweep_streamed_row(const Src& src, float s, Shar
     cw.ms = uniform(r * s);
     float lane_m = ninf, lane_z = 0.f;
     int lane_m_chunk = 0;  // the first of this lane's chunks that holds lane_m
-    src.template for_each<AHEAD>([&](int sl, int chunk, const float(&a)[E]) {
+    auto sweep = [&](int, int chunk, const float(&a)[E]) {
         float w[E];
         float cm = a[0];
 #pragma unroll
@@ -690,8 +693,15 @@ __device__ __forceinline__ bool sweep_streamed_row(const Src& src, float s, Shar
         for (int e = 0; e < E; ++e) w[e] = cw(a[e]);
         const float cs = chunk_sum<E>(w);
         lane_z += cs;
-        if constexpr (SLABS) store_slab_sum(sh.slab_w, sl, cs);
-    });
+        return cs;
+    };
+    if constexpr (SLABS && BY4)
+        src.template for_each_sums<AHEAD>(sh.slab_w, sweep);
+    else
+        src.template for_each<AHEAD>([&](int sl, int chunk, const float(&a)[E]) {
+            const float cs = sweep(sl, chunk, a);
+            if constexpr (SLABS) store_slab_sum(sh.slab_w, sl, cs);
+        });
     if (lane_max_out) *lane_max_out = lane_m;
     if (lane_max_chunk_out) *lane_max_chunk_out = lane_m_chunk;
     float mm[1] = {lane_m};

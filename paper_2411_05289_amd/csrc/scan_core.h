@@ -229,7 +229,59 @@ struct RowSrc<DT, 0, MASKED> {
             c[AHEAD - 1] = nxt;
         }
     }
+
+    // the wave's packed slab s with the fill in place of what is not the row's
+    __device__ __forceinline__ void end_of_row(uint4& d, int s, int lane) const
+    {
+        const uint32_t fb = __builtin_bit_cast(uint32_t, fill);
+        const uint32_t fw = DT == 0 ? fb : ((fb >> 16) | (fb & 0xffff0000u));
+        if (__builtin_expect((s + 1) * 64 > r.nchunk, 0)) {  // the row's last slab, not full
+            asm volatile("" ::: "memory");
+            if (s * 64 + lane >= r.nchunk) d = make_uint4(fw, fw, fw, fw);
+        }
+        fill_ends<DT>(d, r, s, lane, fw);
+    }
+
+    // The same for passes that leave slab sums in LDS: float body(slab, chunk, a[E]) gives this lane's part
+    // of the slab's sum, and the wave's sums are reduced and stored four slabs at a time (a third of the
+    // instructions of one reduction per slab).
+    template <int AHEAD = 1, class Body>
+    __device__ __forceinline__ void for_each_sums(float* slab_w, Body body) const
+    {
+        static_assert(AHEAD == 1 || AHEAD == 2, "one or two steps ahead");
+        const int lane = threadIdx.x & 63, wave = wave_id();
+        uint4 c[AHEAD];
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) c[i] = fetch_chunk(r, (wave + i * kWaves) * 64 + lane);
+        for (int s0 = wave; s0 < r.nslab; s0 += 4 * kWaves) {
+            float sums[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int s = s0 + j * kWaves;
+                if (j > 0 && s >= r.nslab) break;
+                const uint4 nxt = fetch_chunk(r, (s + AHEAD * kWaves) * 64 + lane);
+                uint4 cur = c[0];
+                end_of_row(cur, s, lane);
+                float a[E];
+                unpack<DT>(cur, a);
+                sums[j] = body(s, s * 64 + lane, a);
+#pragma unroll
+                for (int i = 0; i + 1 < AHEAD; ++i) c[i] = c[i + 1];
+                c[AHEAD - 1] = nxt;
+            }
+            const float t = wave_sums4(sums);
+            const int s = s0 + lane * kWaves;
+            if (lane < 4 && s < r.nslab) slab_w[s] = t;
+        }
+    }
 };
+
+// store one slab's sum: every lane passes its chunk sum, lane 63 writes
+__device__ __forceinline__ void store_slab_sum(float* slab_w, int s, float lane_sum)
+{
+    const float t = wave_scan_add(lane_sum);
+    if ((threadIdx.x & 63) == 63) slab_w[s] = t;
+}
 
 // body(slab, chunk, a[E], b[E]) over two rows with the same head and length.  Streamed rows are
 // asked for AHEAD (1 or 2) steps before their use; the steps past the end read the rows' last
@@ -392,13 +444,6 @@ __device__ __forceinline__ void for_each_streamed_cached(int lane, int wave, con
         }
         __builtin_amdgcn_sched_barrier(0);  // one chunk pair at a time
     });
-}
-
-// store one slab's sum: every lane passes its chunk sum, lane 63 writes
-__device__ __forceinline__ void store_slab_sum(float* slab_w, int s, float lane_sum)
-{
-    const float t = wave_scan_add(lane_sum);
-    if ((threadIdx.x & 63) == 63) slab_w[s] = t;
 }
 
 // The slab sums of a row held in registers, reduced eight at a time: put() takes this lane's sum

@@ -55,8 +55,8 @@ __device__ __forceinline__ float dpp(float old, float v)
 
 constexpr int kRowShr1 = 0x111, kRowShr2 = 0x112, kRowShr4 = 0x114, kRowShr8 = 0x118;
 constexpr int kRowBcast15 = 0x142, kRowBcast31 = 0x143, kWaveShr1 = 0x138;
-// lane i reads lane 7 - i of its group of 8; lane i ^ 1; lane i ^ 2; lane i ^ 8
-constexpr int kRowHalfMirror = 0x141, kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowRor8 = 0x128;
+// lane i reads lane 7 - i of its group of 8; lane i ^ 1; lane i ^ 2; lane i - 4, i - 8 (mod 16) of its row
+constexpr int kRowHalfMirror = 0x141, kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowRor4 = 0x124, kRowRor8 = 0x128;
 
 // Inclusive prefix sum over the 64 lanes; lane 63 ends with the wave total.
 __device__ __forceinline__ float wave_scan_add(float v)
@@ -122,6 +122,30 @@ __device__ __forceinline__ float wave_sums8(const float (&v)[8])
     r += __shfl_xor(r, 16, 64);
     r += __shfl_xor(r, 32, 64);
     return r;
+}
+
+// Four wave-wide sums for the price of about one and a half: on return lane l holds the sum over all 64
+// lanes of value number (l & 3).  Two halving steps inside each group of 4 lanes, then the 16 groups are
+// added up.  Fixed order of additions.
+__device__ __forceinline__ float wave_sums4(const float (&v)[4])
+{
+    const int lane = threadIdx.x & 63;
+    const bool b0 = lane & 1, b1 = lane & 2;
+    float k[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const float keep = b0 ? v[2 * j + 1] : v[2 * j], send = b0 ? v[2 * j] : v[2 * j + 1];
+        k[j] = keep + dpp<kQuadXor1>(0.f, send);
+    }
+    const float keep = b1 ? k[1] : k[0], send = b1 ? k[0] : k[1];
+    float r = keep + dpp<kQuadXor2>(0.f, send);
+    r += dpp<kRowRor4>(0.f, r);
+    r += dpp<kRowRor8>(0.f, r);
+    // the two results of a swap hold the values of the even and of the odd rows (halves) in every lane
+    const auto p = __builtin_amdgcn_permlane16_swap((uint32_t)as_i(r), (uint32_t)as_i(r), false, false);
+    r = as_f((int)p[0]) + as_f((int)p[1]);
+    const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)as_i(r), (uint32_t)as_i(r), false, false);
+    return as_f((int)h[0]) + as_f((int)h[1]);
 }
 
 // value of the lane below (lane 0 reads `fill`)

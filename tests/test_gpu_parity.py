@@ -251,6 +251,8 @@ _VARIANTS = [
     ("fp32", "logits", 12001, 0),    # ... masked (ld = V is odd: rows start on every 4-byte phase)
     ("fp32", "logits", 30000, 1),    # fp32, 16 chunks per lane, masked (base one element off)
     ("fp32", "logits", 40000, 0),    # fp32, streamed
+    ("bf16", "logits", 66048, 0),    # ... bf16: one slab more than a whole number of rounds of eight waves
+    ("bf16", "logits", 81913, 5),    # ... masked, one slab short of a multiple of four rounds
     ("bf16", "logits", 20001, 0),    # bf16, 8 chunks per lane, masked
     ("bf16", "logits", 50304, 0),    # bf16, 16 chunks per lane, no masking
     ("bf16", "logits", 50257, 0),    # ... masked
