@@ -44,7 +44,7 @@ __global__ __launch_bounds__(kWG) void draft_kernel(const Params P)
         float Z, mq_lane;
         int mq_chunk = 0;
         cq.s = P.scale_d;
-        swept = sweep_streamed_row<DT, true, 2, METHOD != kRRS>(sq, cq.s, sh, phase, mm[0], Z, &mq_lane,
+        swept = sweep_streamed_row<DT, true, 2, METHOD == kSpecHub>(sq, cq.s, sh, phase, mm[0], Z, &mq_lane,
                                                 METHOD == kSpecHub ? &mq_chunk : nullptr);
         if (swept) {
             cq.ms = mm[0] * cq.s;

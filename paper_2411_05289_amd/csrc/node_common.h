@@ -659,9 +659,9 @@ __device__ __forceinline__ void walk_and_verify(const Params& P, VerifyNode veri
 // nothing finite, which refers to 0: its weights may then have lost their low bits).
 // On success: M = maximum of the stored row, Z = sum of 2^((l - M) s); with SLABS the slab
 // sums in LDS are in the same units and visible to every wave.
-// BY4: the slab sums reduced four slabs at a time (the draft kernels that are bound by issue: SpecHub, 960
-// rows of 128256 bf16 elements 31.4 -> 27.9 us, RRSw, 896 rows of 100 thousand 52.8 -> 48.8; the RRS draft
-// 47.9 -> 49.2 and the verify kernels, config 4's 456 -> 475, lose by it).
+// BY4: the slab sums reduced four slabs at a time (the SpecHub draft, 448 rows of 128256 bf16 elements 31.4
+// -> 27.6 us, 3840 rows 186 -> 179; the RRS drafts of 640 rows of 152064 elements 47.9 -> 49.2 and 68 -> 70 us
+// and the verify kernels, config 4's 456 -> 475, lose by it).
 template <int DT, bool SLABS, int AHEAD = 1, bool BY4 = false, class Src>
 __device__ __forceinline__ bool sweep_streamed_row(const Src& src, float s, Shared& sh, int& phase, float& M,
                                                    float& Z, float* lane_max_out = nullptr,
