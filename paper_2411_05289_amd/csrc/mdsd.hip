@@ -201,6 +201,11 @@ constexpr int64_t kWideMaxNodes = 256;
 // with children here and leaves streamed, in two launches, was slower than either (k = 4, 2688 nodes
 // of 152064: 216 + 133 us against 268).
 constexpr int64_t kWideLongRowNodes = 1024, kWideLongRowNodesManyDrafts = 1536;
+// RRS methods on rows of more than eight chunks per lane of a 512-thread workgroup, of which a CU holds two
+// such nodes: some way into the second round of one node per CU (bf16 rows of 50304, k = 2: 403 nodes 21.8 ->
+// 20.1 us, 496 nodes 22.6 -> 24.2; of 50257, RRSw, 432 nodes, 45 % with children: step 54.4 -> 49.2; k = 4:
+// 504 nodes 34.0 -> 30.6).
+constexpr int64_t kWideTwoPerCuNodes = 448, kWideTwoPerCuNodesManyDrafts = 512;
 // Verify.  SpecHub, which reads its rows once or twice: rows of more than eight chunks per lane of a
 // 512-thread workgroup, few nodes (60 nodes of 100 thousand: 28 -> 22 us; rows of 32 thousand 10.3 -> 10.9).
 static int wide_verify_chunks(int method, const mdsd_problem* pb, const Params& P, bool path)
@@ -209,9 +214,10 @@ static int wide_verify_chunks(int method, const mdsd_problem* pb, const Params& 
     const int nit = wide_chunks(P);
     const int64_t nodes = (int64_t)P.B * (path ? 1 : P.N);
     if (method != kSpecHub) {
-        const int64_t most = P.row_chunks <= 16 * kWG ? kWideMaxNodes
-                             : P.k > 2                ? kWideLongRowNodesManyDrafts
-                                                      : kWideLongRowNodes;
+        const bool many = P.k > 2;
+        const int64_t most = P.row_chunks > 16 * kWG  ? (many ? kWideLongRowNodesManyDrafts : kWideLongRowNodes)
+                             : P.row_chunks > 8 * kWG ? (many ? kWideTwoPerCuNodesManyDrafts : kWideTwoPerCuNodes)
+                                                      : kWideMaxNodes;
         return P.row_chunks > 4 * kWG && nodes <= most ? nit : 0;
     }
     const int most_nit = P.stats_in ? 16 : mdsd_wide::kMaxNitTwoRows;
