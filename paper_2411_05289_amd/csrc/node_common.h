@@ -499,8 +499,14 @@ __device__ __forceinline__ RowNorm wave_shifted_norm(const Src& sp, float s, flo
     static_assert((kWaves & (kWaves - 1)) == 0 && kWaves <= 64, "waves per workgroup: a power of two");
     constexpr int E = Src::E;
     const int lane = threadIdx.x & 63, wave = wave_id();
+    // A reference whose product with the scale is large in magnitude would lose the weights: the exponent
+    // l s - (r s, rounded) is off by up to half an ulp of r s, from 2^31 on 128 and more, so that a wave
+    // that holds nothing but tokens masked with a huge negative number (-1e10, the type's lowest value,
+    // whose product overflows) would sum to infinity, times its factor 0.  Such a wave has no reference
+    // either; its weights, formed without a shift, are 0.
+    auto refers = [s](float v) { return fabsf(v * s) < 0x1p31f; };  // false for infinities and NaN
     float r = wave_max(lane_m);
-    bool has_ref = r > -__builtin_inff() && r < __builtin_inff();
+    bool has_ref = refers(r);
     // The cheap estimates can miss every finite element of a wave: a 32-bit word whose upper
     // half is -inf reads as -inf or as a NaN (which the maximum drops) whatever its lower half
     // holds, so a wave whose finite logits all sit at even indices (rows with most tokens masked)
@@ -508,9 +514,9 @@ __device__ __forceinline__ RowNorm wave_shifted_norm(const Src& sp, float s, flo
     // maximum of its elements instead (a branch the whole wave takes together, rarely).
     if (!has_ref) {
         r = wave_max(lane_max(sp));
-        has_ref = r > -__builtin_inff() && r < __builtin_inff();
+        has_ref = refers(r);
     }
-    // a wave that really has nothing finite (its chunks lie past the row or hold -inf only)
+    // a wave that really has nothing to refer to (its chunks lie past the row or hold masked tokens only)
     // shifts by 0, sums to 0 and stays out of the maximum
     if (!has_ref) r = 0.f;
     r = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, r)));

@@ -224,6 +224,29 @@ def test_rows_masked_down_to_a_few_tokens(method, V, K, request):
     note(request, check_case(method, wl, seed=K))
 
 
+# (dtype, V, trees): rows in registers on 512 threads, on any 16-byte phase, on 1024 threads (few nodes), and
+# on 512 with too many nodes for that; a group of lanes per node; four wavefronts per node; streamed rows
+_MASKED_ROWS = [("bf16", 32000, 3), ("bf16", 32001, 3), ("bf16", 32001, 40), ("bf16", 50257, 2), ("fp32", 12000, 3),
+                ("fp32", 20001, 2), ("bf16", 128256, 2), ("bf16", 600, 6), ("bf16", 7000, 4)]
+
+
+@pytest.mark.parametrize("method", ALL)
+@pytest.mark.parametrize("value,T", [("lowest", 1.0), ("lowest", 2.0), (-1e30, 0.7), (-1e10, 1.0), (-1e4, 1.0)])
+@pytest.mark.parametrize("dtype,V,Bn", _MASKED_ROWS, ids=["%s_V%d_B%d" % v for v in _MASKED_ROWS])
+def test_rows_masked_with_a_finite_number(method, dtype, V, Bn, value, T, request):
+    """Rows masked with the type's lowest value or another large negative number instead of -inf: the masked
+    tokens weigh nothing, also where a wavefront's share of the row holds nothing else (its own shift then
+    overflows, or is off by more than the range of an exponent)."""
+    k, depth = 2, 3
+    N = W.tree_nodes(k, depth)
+    td = torch.float32 if dtype == "fp32" else torch.bfloat16
+    low = torch.finfo(td).min if value == "lowest" else value
+    t, d = W.topk_masked_logits(Bn, N, V, 12, dtype=td, seed=V + Bn, device=DEV)
+    t, d = t.masked_fill(t == float("-inf"), low), d.masked_fill(d == float("-inf"), low)
+    wl = W.Workload("masked_%s_V%d" % (dtype, V), Bn, N, V, k, depth, dtype, "logits", T, T, t, d)
+    note(request, check_case(method, wl, seed=V % 1000))
+
+
 # ----------------------------------------------------------------- every dispatched kernel variant
 # (dtype, kind, V, row offset in elements): between them these reach every instantiation the
 # launchers can choose: rows in registers with 4, 8 or 16 chunks per lane, with and without masked
