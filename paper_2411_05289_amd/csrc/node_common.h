@@ -556,7 +556,8 @@ __device__ __forceinline__ RowNorm wave_shifted_norm(const Src& sp, float s, flo
 // EVERY_WAVE = false: only the first wave's copy of `o` is complete (the caller's first thread
 // writes the node's outputs): the search for the drawn slab and inside it is then left to that
 // wave, which reads the slab's chunk from memory, instead of being repeated by all eight.
-template <int DT, int NIT, bool MASKED, bool EVERY_WAVE = true>
+// ESTIMATE: shift by the cheap estimate of the maximum where there is one.
+template <int DT, int NIT, bool MASKED, bool ESTIMATE, bool EVERY_WAVE = true>
 __device__ __forceinline__ void leaf_resident(const Params& P, const RowView& rp,
                                               const RowSrc<DT, NIT, MASKED>& sp, float u, float* rprob,
                                               Shared& sh, int& phase, NodeOut& o)
@@ -576,7 +577,7 @@ __device__ __forceinline__ void leaf_resident(const Params& P, const RowView& rp
         f_lane = n.f_lane;
         return slab_total(rp.nslab, sv);
     };
-    if constexpr (Src::kHasShiftEstimate) {
+    if constexpr (ESTIMATE && Src::kHasShiftEstimate) {
         W = slab_sums(sp.lane_shift_estimate());
         if (__builtin_expect(!(W > 0.f && W < __builtin_inff()), 0)) {
             node_barrier();  // every wave has read the slab sums that are about to be rewritten

@@ -295,7 +295,7 @@ __device__ __forceinline__ NodeOut rrs_node_resident(const Params& P, const Node
     sp.issue(rp, ExpW::fill());
     NodeOut o{MDSD_NONE, -1, 0, 0.f};
     if (id.c0 < 0) {
-            leaf_resident<DT, NIT, MASKED, false>(P, rp, sp, P.u[id.row * (P.k + 1) + P.k], rprob, sh, phase, o);
+        leaf_resident<DT, NIT, MASKED, true, false>(P, rp, sp, P.u[id.row * (P.k + 1) + P.k], rprob, sh, phase, o);
     } else {
         const RowView rq = make_row<DT>(P.draft, P.ld_d, id.row, P.V);
         rrs_resident<DT, NIT, MASKED, WO, STATS>(P, id, rp, rq, sp, need_full, rprob, sh, q_kept, phase, o);

@@ -173,11 +173,13 @@ struct RowSrc {
         }
     }
 
-    // A softmax shift for a quarter of the work of an exact maximum.  bf16 rows only: the largest 32-bit word of this lane's chunks read as a float, which is the
+    // A softmax shift for a quarter of the work of an exact maximum.  bf16 rows only: the largest
+    // 32-bit word of this lane's chunks read as a float, which is the
     // odd-indexed element with its neighbour's bits as extra mantissa (less than one bf16 ulp
     // away from it).  The even-indexed elements may lie above it: whoever shifts by this
     // value checks that the sum of the weights stayed finite and positive, and takes the
-    // exact maximum if not.
+    // exact maximum if not.  A largest element far above the estimate costs precision all the same: half an
+    // ulp of an exponent of 30 is 1e-6 of the weight.
     static constexpr bool kHasShiftEstimate = DT == 1;
     __device__ __forceinline__ float lane_shift_estimate() const
     {

@@ -247,6 +247,36 @@ def test_rows_masked_with_a_finite_number(method, dtype, V, Bn, value, T, reques
     note(request, check_case(method, wl, seed=V % 1000))
 
 
+# (method, dtype, V, trees, draft records handed to verify)
+_PRECISE = [("spechub", "bf16", 32001, 40, True), ("spechub", "bf16", 20001, 40, True),
+            ("spechub", "bf16", 50257, 20, True)]
+
+
+@pytest.mark.parametrize("method,dtype,V,Bn,records", _PRECISE, ids=["%s_%s_V%d_B%d_records_%s" % v for v in _PRECISE])
+def test_residual_mass_keeps_32_bits(method, dtype, V, Bn, records, request):
+    """Peaked rows (T = 0.3), whose few large weights carry the masses.  Formed against the row's largest
+    element such a weight has an exponent near 0 and an error of a few ulps; against a reference 20 or
+    30 below it (an estimate that missed it) half an ulp of that exponent is 1e-6 of the weight.  Bar: each
+    mass is a sum of differences of probabilities (p and c q, each within 1.2e-7 of itself by v_exp_f32
+    and as much by its normaliser) of 1 in all, so 4.8e-7, no part relative to the mass."""
+    k, depth, T = 2, 3, 0.3
+    N = W.tree_nodes(k, depth)
+    td = torch.float32 if dtype == "fp32" else torch.bfloat16
+    t, d = W.llm_like_logits(Bn, N, V, logit_std=3.0, draft_noise_std=1.5, dtype=td, seed=11, device=DEV)
+    wl = W.Workload("precise_%s_V%d" % (dtype, V), Bn, N, V, k, depth, dtype, "logits", T, T, t, d)
+    pb = B.Problem.from_workload(wl)
+    u_d, u_v = uniforms(wl, 12)
+    pb = pb.with_draft_stats() if records else pb
+    tokens = DRAFT[method](pb, u_d)["tokens"]
+    got = VERIFY[method](pb, tokens, u_v, resid_mass=True)
+    o = oracle.batch_verify(METHODS[method], W.rows_as_numpy(t), W.rows_as_numpy(d), _np(tokens), _np(u_v),
+                            temp_target=T, temp_draft=T, nthreads=8, **oracle_kwargs(wl))
+    same = (_np(got["outcome"]) == o["outcome"]) & (o["margin"] >= 1e-6)
+    err = np.abs(_np(got["resid_mass"]).astype(np.float64) - o["resid_mass"])[same]
+    note(request, dict(max=float(err.max()), rms=float(np.sqrt((err ** 2).mean()))))
+    assert err.max() <= 4.8e-7
+
+
 # ----------------------------------------------------------------- every dispatched kernel variant
 # (dtype, kind, V, row offset in elements): between them these reach every instantiation the
 # launchers can choose: rows in registers with 4, 8 or 16 chunks per lane, with and without masked
