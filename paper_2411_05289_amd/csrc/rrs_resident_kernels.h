@@ -15,7 +15,7 @@ namespace MDSD_NS {
 // WO (without replacement): q_{i+1} is q without the tokens rejected so far, rescaled by
 // rho_{i+1} = (mass of q) / (mass left); the mass outside all k drafted tokens is summed (positive
 // terms only) in the first pass over the draft row, the masses left are that plus the later drafts'.
-// STATS = false: no record; the draft row's largest element and mass come from one more pass over it,
+// STATS = false: no record; the draft row's largest element and its mass come from one more pass over it,
 // while the target row is on its way.
 // The first pass over the draft row leaves its first kDraftChunksKept chunks per lane in LDS, so
 // that the passes of later rounds read only the rest of it from memory.
@@ -23,7 +23,7 @@ namespace MDSD_NS {
 // Marked tokens as bits and row ends filled in the packed chunks: bf16 rows of 32001 elements, 31-node
 // trees, B = 64: rrs_verify 49.7 -> 39.8 us, rrsw_verify 52.0 -> 47.9, B = 128 rrsw_verify 94 -> 71; of 50257
 // elements, B = 16: 29.1 -> 25.0 and 32.5 -> 27.5 (those rows were streamed before).  Without records, B = 64
-// trees of 15: 45.7 -> 33.4 us.
+// trees of 15: 45.7 -> 33.8 us.
 // (40 KB per node at 512 threads, three nodes per CU; 28 KB at 256 threads, four nodes per CU; 144 KB at
 // 1024 threads, one node per CU)
 template <int NIT>
@@ -77,38 +77,60 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
     ExpW cp, cq;
     cp.s = P.scale_t;
     cq.s = P.scale_d;
+    float z1[1];
     if constexpr (!STATS) {
+        // Both rows' masses against their largest elements: with references that may lie 20 below them (a sweep
+        // against the first elements, the cheap estimate of the target's maximum) the residual masses of
+        // peaked rows (T = 0.3) were off by 2.0e-7 instead of 0.8e-7.  The draft row is read once, while the
+        // target row is on its way: every lane sums against the largest element it has met and rescales its
+        // sum when that grows (two passes took 2 us more of 30, V = 32000, 960 nodes).  A huge negative
+        // number is no reference (see wave_shifted_norm()).
         RowSrc<DT, 0> row;
         row.init(rq, ExpW::fill());
-        if (!sweep_streamed_row<DT, false, 2>(row, cq.s, sh, phase, st.max_stored, st.rest_mass)) {
-            float m1[1] = {lane_max(row)};
-            block_max<kWaves, 1>(m1, sh.red, phase);
-            st.max_stored = m1[0];
-            cq.ms = m1[0] * cq.s;
-            float z1[1] = {0.f};
-            row.for_each([&](int, int, const float(&a)[E]) {
-                float w[E];
+        const float ninf = -__builtin_inff();
+        float mm[2] = {ninf, ninf}, z[2] = {0.f, 0.f}, lane_ms = ninf;
+        row.template for_each<2>([&](int, int, const float(&a)[E]) {
 #pragma unroll
-                for (int e = 0; e < E; ++e) w[e] = cq(a[e]);
-                z1[0] += chunk_sum<E>(w);
-            });
-            block_sum<kWaves, 1>(z1, sh.red, phase);
-            st.rest_mass = z1[0];
-        }
-    }
-    // ---- target row: shift (cheap estimate first, where there is one) and Zp
-    cq.ms = uniform(st.max_stored * cq.s);
-    float z1[1];
-    auto normaliser = [&](float lane_m) {
-        const RowNorm n = wave_shifted_norm<false>(sp, cp.s, lane_m, sh, phase);
-        cp.ms = uniform(n.ms);
-        z1[0] = n.Z;
-    };
-    if constexpr (Src::kHasShiftEstimate) {
-        normaliser(sp.lane_shift_estimate());
-        if (__builtin_expect(!(z1[0] > 0.f && z1[0] < __builtin_inff()), 0)) normaliser(lane_max(sp));
+            for (int e = 0; e < E; ++e) mm[1] = fmaxf(mm[1], a[e]);
+            const float ms = mm[1] * cq.s;
+            const bool refers = fabsf(ms) < 0x1p31f;
+            ExpW cw;
+            cw.s = cq.s;
+            cw.ms = refers ? ms : 0.f;
+            float w[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) w[e] = cw(a[e]);
+            z[1] = fmaf(z[1], __builtin_amdgcn_exp2f(lane_ms - cw.ms), chunk_sum<E>(w));
+            lane_ms = refers ? ms : ninf;
+        });
+        mm[0] = lane_max(sp);
+        block_max<kWaves, 2>(mm, sh.red, phase);
+        cp.ms = uniform(mm[0] * cp.s);
+        cq.ms = uniform(mm[1] * cq.s);
+        z[1] *= __builtin_amdgcn_exp2f(lane_ms - cq.ms);
+        sp.for_each([&](int, int, const float(&a)[E]) {
+            float w[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) w[e] = cp(a[e]);
+            z[0] += chunk_sum<E>(w);
+        });
+        block_sum<kWaves, 2>(z, sh.red, phase);
+        z1[0] = z[0];
+        st.rest_mass = z[1];
     } else {
-        normaliser(lane_max(sp));
+        // ---- target row: shift (cheap estimate first, where there is one) and Zp
+        cq.ms = uniform(st.max_stored * cq.s);
+        auto normaliser = [&](float lane_m) {
+            const RowNorm n = wave_shifted_norm<false>(sp, cp.s, lane_m, sh, phase);
+            cp.ms = uniform(n.ms);
+            z1[0] = n.Z;
+        };
+        if constexpr (Src::kHasShiftEstimate) {
+            normaliser(sp.lane_shift_estimate());
+            if (__builtin_expect(!(z1[0] > 0.f && z1[0] < __builtin_inff()), 0)) normaliser(lane_max(sp));
+        } else {
+            normaliser(lane_max(sp));
+        }
     }
     const float iZp = uniform(1.f / z1[0]);
     const float iZq = uniform(1.f / st.rest_mass);
@@ -295,7 +317,7 @@ __device__ __forceinline__ NodeOut rrs_node_resident(const Params& P, const Node
     sp.issue(rp, ExpW::fill());
     NodeOut o{MDSD_NONE, -1, 0, 0.f};
     if (id.c0 < 0) {
-        leaf_resident<DT, NIT, MASKED, true, false>(P, rp, sp, P.u[id.row * (P.k + 1) + P.k], rprob, sh, phase, o);
+        leaf_resident<DT, NIT, MASKED, STATS, false>(P, rp, sp, P.u[id.row * (P.k + 1) + P.k], rprob, sh, phase, o);
     } else {
         const RowView rq = make_row<DT>(P.draft, P.ld_d, id.row, P.V);
         rrs_resident<DT, NIT, MASKED, WO, STATS>(P, id, rp, rq, sp, need_full, rprob, sh, q_kept, phase, o);

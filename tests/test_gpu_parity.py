@@ -249,7 +249,10 @@ def test_rows_masked_with_a_finite_number(method, dtype, V, Bn, value, T, reques
 
 # (method, dtype, V, trees, draft records handed to verify)
 _PRECISE = [("spechub", "bf16", 32001, 40, True), ("spechub", "bf16", 20001, 40, True),
-            ("spechub", "bf16", 50257, 20, True)]
+            ("spechub", "bf16", 50257, 20, True),
+            ("rrs", "bf16", 32000, 40, False), ("rrsw", "bf16", 32000, 40, False), ("rrs", "bf16", 32001, 40, False),
+            ("rrsw", "bf16", 32001, 40, False), ("rrs", "fp32", 12000, 40, False), ("rrs", "bf16", 100000, 12, False),
+            ("rrsw", "bf16", 100000, 12, False), ("rrsw", "bf16", 9000, 60, False)]
 
 
 @pytest.mark.parametrize("method,dtype,V,Bn,records", _PRECISE, ids=["%s_%s_V%d_B%d_records_%s" % v for v in _PRECISE])
