@@ -11,6 +11,8 @@
 #include <ATen/ATen.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <utility>
+
 #include "mdsd.h"
 
 namespace {
@@ -107,17 +109,33 @@ bool stream_of(PyObject* o, void*& stream)
     return false;
 }
 
-// a new output, under `name` in the dict; its data pointer
-void* output(PyObject* dict, const char* name, at::IntArrayRef shape, const at::TensorOptions& options)
-{
-    at::Tensor t = at::empty(shape, options);
-    void* data = t.data_ptr();
-    PyObject* o = THPVariable_Wrap(std::move(t));
-    const bool ok = o && PyDict_SetItemString(dict, name, o) == 0;
-    Py_XDECREF(o);
-    if (!ok) throw std::bad_alloc();
-    return data;
-}
+// the outputs of a call; given up with everything in it wherever the call does not come to its end
+struct Outputs {
+    PyObject* dict = PyDict_New();
+    Outputs()
+    {
+        if (!dict) throw std::bad_alloc();
+    }
+    Outputs(const Outputs&) = delete;
+    ~Outputs() { Py_XDECREF(dict); }
+
+    // a new output under `name`; its data pointer
+    void* add(const char* name, at::IntArrayRef shape, const at::TensorOptions& options)
+    {
+        at::Tensor t = at::empty(shape, options);
+        void* data = t.data_ptr();
+        PyObject* o = THPVariable_Wrap(std::move(t));
+        const bool ok = o && PyDict_SetItemString(dict, name, o) == 0;
+        Py_XDECREF(o);
+        if (!ok) throw std::bad_alloc();
+        return data;
+    }
+    // what a call that the library answered with `rc` returns
+    PyObject* answer(int rc)
+    {
+        return rc == MDSD_OK ? std::exchange(dict, nullptr) : PyLong_FromLong(rc);
+    }
+};
 
 template <class F>
 PyObject* guarded(F f)
@@ -128,14 +146,6 @@ PyObject* guarded(F f)
         if (PyErr_Occurred()) return nullptr;
         Py_RETURN_NONE;
     }
-}
-
-// a call that the library answered with `rc`
-PyObject* answer(int rc, PyObject* dict)
-{
-    if (rc == MDSD_OK) return dict;
-    Py_DECREF(dict);
-    return PyLong_FromLong(rc);
 }
 
 // draft(method, stream, <rows>, u)
@@ -149,18 +159,11 @@ PyObject* draft(PyObject*, PyObject* const* a, Py_ssize_t n)
             Py_RETURN_NONE;
         const at::Tensor* u = plain(a[2 + kRowArgs], at::kFloat, {r.B, r.N, r.pb.k});
         if (!u) Py_RETURN_NONE;
-        PyObject* out = PyDict_New();
-        if (!out) return nullptr;
-        int32_t *tokens, *flags, *hub = nullptr;
-        try {
-            const at::TensorOptions ints = r.draft.options().dtype(at::kInt);
-            tokens = (int32_t*)output(out, "tokens", {r.B, r.N}, ints);
-            flags = (int32_t*)output(out, "flags", {r.B, r.N}, ints);
-            if (method == 0) hub = (int32_t*)output(out, "hub", {r.B, r.N}, ints);
-        } catch (...) {
-            Py_DECREF(out);
-            throw;
-        }
+        Outputs out;
+        const at::TensorOptions ints = r.draft.options().dtype(at::kInt);
+        int32_t* tokens = (int32_t*)out.add("tokens", {r.B, r.N}, ints);
+        int32_t* flags = (int32_t*)out.add("flags", {r.B, r.N}, ints);
+        int32_t* hub = method == 0 ? (int32_t*)out.add("hub", {r.B, r.N}, ints) : nullptr;
         const float* up = (const float*)u->data_ptr();
         int rc;
         Py_BEGIN_ALLOW_THREADS;
@@ -168,7 +171,7 @@ PyObject* draft(PyObject*, PyObject* const* a, Py_ssize_t n)
              : method == 1 ? rrs_draft(&r.pb, up, tokens, flags, nullptr, 0, stream)
                            : rrsw_draft(&r.pb, up, tokens, flags, nullptr, 0, stream);
         Py_END_ALLOW_THREADS;
-        return answer(rc, out);
+        return out.answer(rc);
     });
 }
 
@@ -188,37 +191,28 @@ PyObject* verify(PyObject*, PyObject* const* a, Py_ssize_t n)
         if (!tokens || !u || r.pb.depth < 0) Py_RETURN_NONE;
         for (int i = 2; i < 6; ++i)
             if (!PyBool_Check(a[i])) Py_RETURN_NONE;
-        PyObject* out = PyDict_New();
-        if (!out) return nullptr;
+        Outputs out;
         mdsd_result res = {};
-        try {
-            const at::TensorOptions ints = r.draft.options().dtype(at::kInt), floats = ints.dtype(at::kFloat);
-            res.outcome = (int32_t*)output(out, "outcome", {r.B, r.N}, ints);
-            res.token = (int32_t*)output(out, "token", {r.B, r.N}, ints);
-            if (a[2] == Py_True) res.resid_mass = (float*)output(out, "resid_mass", {r.B, r.N}, floats);
-            if (a[3] == Py_True) res.flags = (int32_t*)output(out, "flags", {r.B, r.N}, ints);
-            if (a[4] == Py_True) res.resid_prob = (float*)output(out, "resid_prob", {r.B, r.N, r.V}, floats);
-            if (a[5] == Py_True) {
-                res.accept_depth = (int32_t*)output(out, "accept_depth", {r.B}, ints);
-                res.emitted = (int32_t*)output(out, "emitted", {r.B, r.pb.depth}, ints);
-            }
-        } catch (...) {
-            Py_DECREF(out);
-            throw;
+        const at::TensorOptions ints = r.draft.options().dtype(at::kInt), floats = ints.dtype(at::kFloat);
+        res.outcome = (int32_t*)out.add("outcome", {r.B, r.N}, ints);
+        res.token = (int32_t*)out.add("token", {r.B, r.N}, ints);
+        if (a[2] == Py_True) res.resid_mass = (float*)out.add("resid_mass", {r.B, r.N}, floats);
+        if (a[3] == Py_True) res.flags = (int32_t*)out.add("flags", {r.B, r.N}, ints);
+        if (a[4] == Py_True) res.resid_prob = (float*)out.add("resid_prob", {r.B, r.N, r.V}, floats);
+        if (a[5] == Py_True) {
+            res.accept_depth = (int32_t*)out.add("accept_depth", {r.B}, ints);
+            res.emitted = (int32_t*)out.add("emitted", {r.B, r.pb.depth}, ints);
         }
         const int32_t* tp = (const int32_t*)tokens->data_ptr();
         const float* up = (const float*)u->data_ptr();
         decltype(&spechub_verify) call[] = {spechub_verify,      rrs_verify,      rrsw_verify,
                                             spechub_verify_path, rrs_verify_path, rrsw_verify_path};
-        if (method < 0 || method > 5) {
-            Py_DECREF(out);
-            Py_RETURN_NONE;
-        }
+        if (method < 0 || method > 5) Py_RETURN_NONE;
         int rc;
         Py_BEGIN_ALLOW_THREADS;
         rc = call[method](&r.pb, tp, up, &res, nullptr, 0, stream);
         Py_END_ALLOW_THREADS;
-        return answer(rc, out);
+        return out.answer(rc);
     });
 }
 

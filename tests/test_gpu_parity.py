@@ -2,6 +2,8 @@
 the same seeded rows, tokens and Philox uniforms (see tests/parity.py for the
 bar).  Sizes span several slabs and ragged tails; the large configurations run
 at full size on the GPU and are compared on sampled sequences."""
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -549,6 +551,34 @@ def test_calls_outside_the_native_marshalling():
     with pytest.raises(B.MdsdError) as err:
         B.rrs_verify(dataclasses.replace(pb, depth=2), tok, u_v)
     assert err.value.code == -2
+
+
+def test_calls_given_up_half_way_keep_nothing():
+    """A tensor without storage (what vmap hands to the function it maps) is refused, as by the functions in
+    Python; the outputs that had been allocated by then are freed."""
+    wl = W.config(3, device=DEV, B=4, V=300, depth=3, seed=82)
+    pb = B.Problem.from_workload(wl)
+    u_d, u_v = uniforms(wl, 82)
+    tok = B.spechub_draft(pb, u_d)["tokens"]
+    many_d, many_v = u_d.expand(3, -1, -1, -1).contiguous(), u_v.expand(3, -1, -1, -1).contiguous()
+
+    def refused(call, over):
+        try:
+            torch.vmap(call)(over)
+        except RuntimeError as e:
+            return "storage" in str(e)
+        return False
+
+    calls = ((lambda u: B.spechub_draft(pb, u), many_d), (lambda u: B.rrsw_draft(pb, u), many_d),
+             (lambda u: B.spechub_verify(pb, tok, u, resid_prob=True), many_v),
+             (lambda u: B.rrs_verify_path(pb, tok, u), many_v))
+    assert all(refused(*c) for c in calls)
+    gc.collect()
+    before = torch.cuda.memory_allocated()
+    for _ in range(5):
+        assert all(refused(*c) for c in calls)
+    gc.collect()
+    assert torch.cuda.memory_allocated() == before
 
 
 # ----------------------------------------------------------------- degenerate and invalid inputs
