@@ -4,7 +4,7 @@ Argument marshalling only: torch supplies device memory and the HIP stream;
 every step of the method runs inside ``libmdsd.so``.  There is no fallback: if
 the library has not been built, or a tensor is not on the GPU, the call raises.
 Calls that allocate their outputs are marshalled in native code (``_host.so``,
-csrc/host.cpp); it hands anything out of the ordinary back to the functions here.
+csrc/host.cpp) where that is built; it hands anything out of the ordinary back to the functions here.
 """
 from __future__ import annotations
 
@@ -18,6 +18,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmdsd.so")
+HOST_PATH = os.path.join(_HERE, "_host.so")
 
 FP32, BF16 = 0, 1
 PROBS, LOGITS = 0, 1
@@ -99,10 +100,13 @@ _host = None
 
 
 def _native():
-    """The native marshalling of the calls that allocate their outputs."""
+    """The native marshalling of the calls that allocate their outputs; None where only the library
+    itself has been built: the functions here then do all of it."""
     global _host
     if _host is None:
         lib()
+        if not os.path.exists(HOST_PATH):
+            return None
         try:
             from . import _host as module
         except ImportError as e:
@@ -214,9 +218,10 @@ def workspace_bytes(pb: Problem) -> int:
 
 
 def _draft(fn_name, pb: Problem, u: torch.Tensor, out, with_hub: bool):
-    if out is None and pb.draft.is_cuda:
-        got = _native().draft(_DRAFT_CALLS[fn_name], _stream(), pb.target, pb.draft, pb.kind, pb.k, pb.depth,
-                              pb.temp_target, pb.temp_draft, pb.first_child, pb.draft_stats, u)
+    native = _native() if out is None and pb.draft.is_cuda else None
+    if native is not None:
+        got = native.draft(_DRAFT_CALLS[fn_name], _stream(), pb.target, pb.draft, pb.kind, pb.k, pb.depth,
+                           pb.temp_target, pb.temp_draft, pb.first_child, pb.draft_stats, u)
         if type(got) is dict:
             return got
         if got is not None:
@@ -283,15 +288,17 @@ def alloc_workspace(pb: Problem) -> torch.Tensor:
 
 
 def _verify(fn_name, pb: Problem, tokens: torch.Tensor, u: torch.Tensor, out, workspace=None, **want):
-    if out is None and workspace is None and pb.draft.is_cuda:
-        return _verify_new(fn_name, pb, tokens, u, **want)
+    native = _native() if out is None and workspace is None and pb.draft.is_cuda else None
+    if native is not None:
+        return _verify_new(native, fn_name, pb, tokens, u, **want)
     return _verify_into(fn_name, pb, tokens, u, out, workspace, **want)
 
 
-def _verify_new(fn_name, pb: Problem, tokens, u, *, resid_mass=False, flags=True, resid_prob=False, walk=True):
-    got = _native().verify(_VERIFY_CALLS[fn_name], _stream(), pb.target, pb.draft, pb.kind, pb.k, pb.depth,
-                           pb.temp_target, pb.temp_draft, pb.first_child, pb.draft_stats, tokens, u,
-                           resid_mass, flags, resid_prob, walk)
+def _verify_new(native, fn_name, pb: Problem, tokens, u, *, resid_mass=False, flags=True, resid_prob=False,
+                walk=True):
+    got = native.verify(_VERIFY_CALLS[fn_name], _stream(), pb.target, pb.draft, pb.kind, pb.k, pb.depth,
+                        pb.temp_target, pb.temp_draft, pb.first_child, pb.draft_stats, tokens, u,
+                        resid_mass, flags, resid_prob, walk)
     if type(got) is dict:
         return got
     if got is not None:

@@ -134,3 +134,10 @@ def test_binding_refuses_cpu_tensors():
     pb = B.Problem(t, t, B.LOGITS, 2, 2)
     with pytest.raises(ValueError):
         B.spechub_verify(pb, torch.zeros((1, 3), dtype=torch.int32), torch.zeros((1, 3, 3)))
+
+
+def test_library_alone_is_enough(monkeypatch):
+    """A tree with the library but without _host.so marshals its calls in Python."""
+    monkeypatch.setattr(B, "_host", None)
+    monkeypatch.setattr(B, "HOST_PATH", os.path.join(ROOT, "no_such_file.so"))
+    assert B._native() is None

@@ -553,6 +553,20 @@ def test_calls_outside_the_native_marshalling():
     assert err.value.code == -2
 
 
+def test_calls_without_the_native_marshalling(monkeypatch):
+    wl = W.config(3, device=DEV, B=3, V=300, depth=3, seed=83)
+    pb = B.Problem.from_workload(wl)
+    u_d, u_v = uniforms(wl, 83)
+    got = []
+    for native in (B._native, lambda: None):
+        monkeypatch.setattr(B, "_native", native)
+        for method in ALL:
+            d = DRAFT[method](pb, u_d)
+            got.append(dict(d, **VERIFY[method](pb, d["tokens"], u_v, resid_mass=True)))
+    for a, b in zip(got[:3], got[3:]):
+        assert list(a) == list(b) and all(torch.equal(a[k], b[k]) for k in a)
+
+
 def test_calls_given_up_half_way_keep_nothing():
     """A tensor without storage (what vmap hands to the function it maps) is refused, as by the functions in
     Python; the outputs that had been allocated by then are freed."""
