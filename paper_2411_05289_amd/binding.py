@@ -110,7 +110,7 @@ def _native():
         try:
             from . import _host as module
         except ImportError as e:
-            raise RuntimeError("_host.so is not built (run `python -m paper_2411_05289_amd.build`)") from e
+            raise RuntimeError("_host.so does not load (%s); run `python -m paper_2411_05289_amd.build`" % e) from e
         _host = module
     return _host
 

@@ -141,3 +141,27 @@ def test_library_alone_is_enough(monkeypatch):
     monkeypatch.setattr(B, "_host", None)
     monkeypatch.setattr(B, "HOST_PATH", os.path.join(ROOT, "no_such_file.so"))
     assert B._native() is None
+
+
+def test_marshalling_that_does_not_load_says_why(monkeypatch):
+    """Not every ImportError means that nothing was built: one of another torch fails on a symbol."""
+    import importlib.abc
+    import sys
+
+    class Broken(importlib.abc.MetaPathFinder):
+        def find_spec(self, name, path=None, target=None):
+            if name.endswith("._host"):
+                raise ImportError("undefined symbol: _ZN2at5emptyEv")
+
+    monkeypatch.setattr(B, "_host", None)
+    monkeypatch.setattr(B, "HOST_PATH", __file__)
+    monkeypatch.delitem(sys.modules, B.__package__ + "._host", raising=False)
+    package = sys.modules[B.__package__]
+    kept = package.__dict__.pop("_host", None)
+    monkeypatch.setattr(sys, "meta_path", [Broken()] + sys.meta_path)
+    try:
+        with pytest.raises(RuntimeError, match="does not load .*undefined symbol: _ZN2at5emptyEv"):
+            B._native()
+    finally:
+        if kept is not None:
+            package._host = kept
