@@ -39,17 +39,40 @@ def jobs() -> int:
     return max(1, min(n or (os.cpu_count() or 1), 16))
 
 
-def build_host(verbose: bool = True) -> str:
-    """The native marshalling of the Python binding (host code only), linked to libmdsd.so."""
+def host_compiler() -> str:
+    """$CXX, the system's C++ compiler, or the one that comes with hipcc."""
+    names = [os.environ.get("CXX"), "g++", "c++",
+             os.path.join(os.path.dirname(HIPCC), "..", "llvm", "bin", "clang++")]
+    for name in names:
+        found = shutil.which(name) if name else None
+        if found:
+            return found
+    raise RuntimeError("no C++ compiler found; set CXX")
+
+
+def build_host(verbose: bool = True):
+    """The native marshalling of the Python binding (host code only), linked to libmdsd.so.  Left out, with a
+    message, where there is no torch or no Python headers to compile it against: the library itself
+    needs neither, and the binding then marshals in Python."""
     import sysconfig
-    import torch
+    if os.path.exists(HOST):
+        os.remove(HOST)
+    python_include = sysconfig.get_paths()["include"]
+    try:
+        import torch
+        missing = None if os.path.exists(os.path.join(python_include, "Python.h")) else "Python.h"
+    except ImportError:
+        missing = "torch"
+    if missing:
+        print("_host.so: left out, %s is not there" % missing, flush=True)
+        return None
     where = os.path.dirname(torch.__file__)
     tmp = HOST + ".tmp%d" % os.getpid()
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+    cmd = [host_compiler(), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
            "-I", os.path.join(ROOT, "include"), "-I", os.path.join(where, "include"),
            "-I", os.path.join(where, "include", "torch", "csrc", "api", "include"),
-           "-I", sysconfig.get_paths()["include"], "-o", tmp, os.path.join(CSRC, "host.cpp"),
+           "-I", python_include, "-o", tmp, os.path.join(CSRC, "host.cpp"),
            "-L", HERE, "-l:libmdsd.so", "-L", os.path.join(where, "lib"),
            "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"]
     if verbose:
