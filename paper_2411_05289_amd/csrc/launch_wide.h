@@ -5,7 +5,8 @@
 // every rejected round.  The caller chooses by size (mdsd.hip, where the two sides are measured).
 // nit = 4, 8, 16 or, RRS methods, 20 chunks per lane (20: some of the row spilled, and still ahead: bf16 rows
 // of 152064, k = 4, 672 nodes 145 -> 93 us); SpecHub verify without the draft call's records, which keeps
-// both rows, up to 8; draft 4, fp32 8.
+// both rows, up to 8.  Draft: SpecHub on bf16 rows of up to four chunks per lane, RRS on aligned fp32 rows of up
+// to eight.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -19,6 +20,6 @@ constexpr int kMaxNitTwoRows = 8;
 void launch_spechub(int dtype, int nit, bool path, dim3 grid, hipStream_t st, const mdsd::Params& P);
 void launch_rrs(int dtype, int nit, dim3 grid, hipStream_t st, const mdsd::Params& P);
 void launch_rrsw(int dtype, int nit, dim3 grid, hipStream_t st, const mdsd::Params& P);
-void launch_draft(int method, int dtype, int nit, dim3 grid, hipStream_t st, const mdsd::Params& P);
+void launch_draft(int method, dim3 grid, hipStream_t st, const mdsd::Params& P);
 
 }  // namespace mdsd_wide

@@ -223,14 +223,21 @@ static int wide_verify_chunks(int method, const mdsd_problem* pb, const Params& 
     const int most_nit = P.stats_in ? 16 : mdsd_wide::kMaxNitTwoRows;
     return P.row_chunks > 8 * kWG && nodes <= kWideMaxNodes && nit <= most_nit ? nit : 0;
 }
-// Draft: few nodes, rows whose passes outweigh the draws behind them, which cost more threads' time (7 nodes,
-// fp32 rows of 32000 9.4 -> 8.4 us, bf16 8.3 -> 7.5; bf16 rows of 50257 9.5 -> 10.1).
-static int wide_draft_chunks(const mdsd_problem* pb, const Params& P)
+// Draft, up to 128 nodes with children.  A draw is a chain of barriers, each of which 16 wavefronts pass later
+// than eight, so that only rows whose passes outweigh their draws gain (12 and 120 nodes, 512 against 1024
+// threads): SpecHub on bf16 rows that are resident either way, from 2400 chunks on (rows of 20000 7.64 -> 7.47 and
+// 7.86 -> 7.77 us, 20001 8.31 -> 7.98, 32000 8.51 -> 8.15 and 9.02 -> 8.75; 16640 7.57 -> 7.69; fp32 rows of 12000
+// no difference, of 16500 7.4 -> 7.6), and RRS on aligned fp32 rows that 512 threads would stream (16500,
+// k = 2 6.53 -> 6.21 and 7.74 -> 6.96, 32000 8.11 -> 7.19; k = 4, whose draws weigh double, from 4608 chunks on:
+// 17200 7.87 -> 8.04, 20000 8.23 -> 7.90; 32001 9.69 -> 10.30).  Other RRS rows lose 2 to 8 %, without
+// replacement, every draw of which waits for the one before, 4 to 22 %.
+static bool wide_draft(int method, const mdsd_problem* pb, const Params& P)
 {
     const int64_t nodes = (int64_t)P.B * (P.first_child ? P.N : P.n_internal);
-    if (pb->kind != MDSD_LOGITS || nodes > kWideMaxNodes / 2 || P.row_chunks <= 4 * kWG) return 0;
-    const int nit = wide_chunks(P);
-    return nit <= (pb->dtype == MDSD_FP32 ? 8 : 4) ? nit : 0;
+    if (pb->kind != MDSD_LOGITS || nodes > kWideMaxNodes / 2) return false;
+    if (method == kSpecHub) return pb->dtype == MDSD_BF16 && P.row_chunks > 2400 && P.row_chunks <= 8 * kWG;
+    return method == kRRS && pb->dtype == MDSD_FP32 && !P.masked &&
+           P.row_chunks > (P.k > 2 ? 9 : 8) * kWG && P.row_chunks <= 16 * kWG;
 }
 
 // SpecHub nodes of more than 64 chunks per row, from this many on: one wavefront per node with the rows
@@ -325,8 +332,8 @@ static void launch_draft(int method, const mdsd_problem* pb, const Params& P, hi
     case 4: mdsd_quad::launch_draft(method, pb->dtype, lg, st, P); return;
     default: break;
     }
-    if (const int wide = wide_draft_chunks(pb, P)) {
-        mdsd_wide::launch_draft(method, pb->dtype, wide, node_grid(P, wide), st, P);
+    if (wide_draft(method, pb, P)) {
+        mdsd_wide::launch_draft(method, node_grid(P, 4), st, P);
         return;
     }
     const int es = pb->dtype == MDSD_FP32 ? 4 : 2;

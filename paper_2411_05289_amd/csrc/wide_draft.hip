@@ -8,32 +8,15 @@
 
 namespace mdsd_wide {
 
-template <int DT, int METHOD, int NIT>
-static void launch_nit(dim3 grid, hipStream_t st, const Params& P)
+void launch_draft(int method, dim3 grid, hipStream_t st, const Params& P)
 {
-    if (P.masked)
-        hipLaunchKernelGGL((draft_kernel<DT, true, METHOD, NIT, true>), grid, dim3(kWG), 0, st, P);
+    const dim3 block(kWG);
+    if (method == kRRS)
+        hipLaunchKernelGGL((draft_kernel<0, true, kRRS, 8, false>), grid, block, 0, st, P);
+    else if (P.masked)
+        hipLaunchKernelGGL((draft_kernel<1, true, kSpecHub, 4, true>), grid, block, 0, st, P);
     else
-        hipLaunchKernelGGL((draft_kernel<DT, true, METHOD, NIT, false>), grid, dim3(kWG), 0, st, P);
-}
-
-template <int METHOD>
-static void launch_method(int dtype, int nit, dim3 grid, hipStream_t st, const Params& P)
-{
-    if (dtype == MDSD_FP32)
-        nit == 4 ? launch_nit<0, METHOD, 4>(grid, st, P) : launch_nit<0, METHOD, 8>(grid, st, P);
-    else
-        launch_nit<1, METHOD, 4>(grid, st, P);
-}
-
-void launch_draft(int method, int dtype, int nit, dim3 grid, hipStream_t st, const Params& P)
-{
-    if (method == kSpecHub)
-        launch_method<kSpecHub>(dtype, nit, grid, st, P);
-    else if (method == kRRS)
-        launch_method<kRRS>(dtype, nit, grid, st, P);
-    else
-        launch_method<kRRSw>(dtype, nit, grid, st, P);
+        hipLaunchKernelGGL((draft_kernel<1, true, kSpecHub, 4, false>), grid, block, 0, st, P);
 }
 
 }  // namespace mdsd_wide
