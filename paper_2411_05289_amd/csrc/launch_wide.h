@@ -3,10 +3,10 @@
 // ask for the row at once and share every pass; and long rows of the RRS methods, of which a CU's registers
 // and LDS (nine chunks per lane of the draft row) hold what 512-thread workgroups would stream again in
 // every rejected round.  The caller chooses by size (mdsd.hip, where the two sides are measured).
-// nit = 4, 8, 16 or, RRS methods, 20 chunks per lane (20: some of the row spilled, and still ahead: bf16 rows
-// of 152064, k = 4, 672 nodes 145 -> 93 us); SpecHub verify without the draft call's records, which keeps
-// both rows, up to 8.  Draft: SpecHub on bf16 rows of up to four chunks per lane, RRS on aligned fp32 rows of up
-// to eight.
+// nit, chunks per lane: RRS methods 4, 8, 16 or 20 (20: some of the row spilled, and still ahead: bf16 rows of
+// 152064, k = 4, 672 nodes 145 -> 93 us).  SpecHub verify 8 (without the draft call's records, both rows) or,
+// with records, 8 or 16; path-only 8 for masked rows without records, 16 with records.  Draft: SpecHub on bf16 rows
+// of up to four chunks per lane, RRS on aligned fp32 rows of up to eight.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -15,7 +15,6 @@
 namespace mdsd_wide {
 
 constexpr int kThreads = 1024;
-constexpr int kMaxNitTwoRows = 8;
 
 void launch_spechub(int dtype, int nit, bool path, dim3 grid, hipStream_t st, const mdsd::Params& P);
 void launch_rrs(int dtype, int nit, dim3 grid, hipStream_t st, const mdsd::Params& P);

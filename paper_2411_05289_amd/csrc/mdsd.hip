@@ -206,22 +206,39 @@ constexpr int64_t kWideLongRowNodes = 1024, kWideLongRowNodesManyDrafts = 1536;
 // 20.1 us, 496 nodes 22.6 -> 24.2; of 50257, RRSw, 432 nodes, 45 % with children: step 54.4 -> 49.2; k = 4:
 // 504 nodes 34.0 -> 30.6).
 constexpr int64_t kWideTwoPerCuNodes = 448, kWideTwoPerCuNodesManyDrafts = 512;
-// Verify.  SpecHub, which reads its rows once or twice: rows of more than eight chunks per lane of a
-// 512-thread workgroup, few nodes (60 nodes of 100 thousand: 28 -> 22 us; rows of 32 thousand 10.3 -> 10.9).
-static int wide_verify_chunks(int method, const mdsd_problem* pb, const Params& P, bool path)
+// Verify.  SpecHub, which reads its rows once or twice, up to 256 nodes (512 against 1024 threads, 60 nodes).
+// Rows that 512 threads stream (more than 16 chunks per lane): 66048 bf16 19.3 -> 18.0 us, 100000 28.0 -> 23.0.
+// Rows that they hold too: with the draft call's records aligned ones lose (fp32 17000 8.8 -> 9.2, 32000 11.0 ->
+// 11.0; bf16 33000 11.7 -> 12.0, 50304 14.2 -> 14.4), unaligned ones gain (fp32 32001 12.9 -> 12.3; bf16 33001 12.7
+// -> 12.8, 65001 18.3 -> 17.6), and so do calls without records, which hold both rows (fp32 16400 11.3 -> 11.3,
+// 32000 15.5 -> 14.5, 32001 19.7 -> 17.3; bf16 50304 19.8 -> 18.8).
+// Path-only, where a tree's nodes pass their barriers one after another: resident rows lose with records (8 trees,
+// fp32 17000 18.6 -> 21.3, bf16 50304 28.7 -> 31.2) and without if aligned (fp32 17000 28.8 -> 30.9); without records
+// and unaligned they gain (fp32 32001 51.9 -> 46.8).  Streamed ones gain from 32 trees on (66048 54.5 -> 48.9, 70001
+// 58.7 -> 54.7; up to 16 trees between -9 and +9 % by the paths drawn), rows of more than 20 chunks per lane
+// always (100000, 4 trees 35.8 -> 35.1, 8 trees 45.4 -> 44.0).
+static int wide_spechub_chunks(const mdsd_problem* pb, const Params& P, bool path)
 {
-    if (pb->kind != MDSD_LOGITS || (path && method != kSpecHub)) return 0;
     const int nit = wide_chunks(P);
     const int64_t nodes = (int64_t)P.B * (path ? 1 : P.N);
-    if (method != kSpecHub) {
-        const bool many = P.k > 2;
-        const int64_t most = P.row_chunks > 16 * kWG  ? (many ? kWideLongRowNodesManyDrafts : kWideLongRowNodes)
-                             : P.row_chunks > 8 * kWG ? (many ? kWideTwoPerCuNodesManyDrafts : kWideTwoPerCuNodes)
-                                                      : kWideMaxNodes;
-        return P.row_chunks > 4 * kWG && nodes <= most ? nit : 0;
+    if (nodes > kWideMaxNodes || P.row_chunks <= 8 * kWG) return 0;
+    if (resident_chunks(pb) == 0) {
+        if (!P.stats_in || nit > 16) return 0;
+        return !path || (nit == 16 && (P.B >= 32 || P.row_chunks > 20 * kWG)) ? nit : 0;
     }
-    const int most_nit = P.stats_in ? 16 : mdsd_wide::kMaxNitTwoRows;
-    return P.row_chunks > 8 * kWG && nodes <= kWideMaxNodes && nit <= most_nit ? nit : 0;
+    return P.masked ? (path && P.stats_in ? 0 : nit) : path || P.stats_in ? 0 : nit;
+}
+static int wide_verify_chunks(int method, const mdsd_problem* pb, const Params& P, bool path)
+{
+    if (pb->kind != MDSD_LOGITS) return 0;
+    if (method == kSpecHub) return wide_spechub_chunks(pb, P, path);
+    if (path) return 0;
+    const int64_t nodes = (int64_t)P.B * P.N;
+    const bool many = P.k > 2;
+    const int64_t most = P.row_chunks > 16 * kWG  ? (many ? kWideLongRowNodesManyDrafts : kWideLongRowNodes)
+                         : P.row_chunks > 8 * kWG ? (many ? kWideTwoPerCuNodesManyDrafts : kWideTwoPerCuNodes)
+                                                  : kWideMaxNodes;
+    return P.row_chunks > 4 * kWG && nodes <= most ? wide_chunks(P) : 0;
 }
 // Draft, up to 128 nodes with children.  A draw is a chain of barriers, each of which 16 wavefronts pass later
 // than eight, so that only rows whose passes outweigh their draws gain (12 and 120 nodes, 512 against 1024

@@ -9,34 +9,37 @@
 namespace mdsd_wide {
 
 template <int DT, int NIT, bool MASKED, bool STATS>
-static void launch_one(bool path, dim3 grid, hipStream_t st, const Params& P)
+static void launch_one(dim3 grid, hipStream_t st, const Params& P)
 {
-    if (path)
-        hipLaunchKernelGGL((spechub_path_resident<DT, NIT, MASKED, STATS>), grid, dim3(kWG), 0, st, P);
-    else
-        hipLaunchKernelGGL((spechub_verify_resident<DT, NIT, MASKED, STATS>), grid, dim3(kWG), 0, st, P);
+    hipLaunchKernelGGL((spechub_verify_resident<DT, NIT, MASKED, STATS>), grid, dim3(kWG), 0, st, P);
+}
+template <int DT, int NIT, bool MASKED, bool STATS>
+static void launch_path_one(dim3 grid, hipStream_t st, const Params& P)
+{
+    hipLaunchKernelGGL((spechub_path_resident<DT, NIT, MASKED, STATS>), grid, dim3(kWG), 0, st, P);
 }
 
-template <int DT, int NIT>
-static void launch_nit(bool path, dim3 grid, hipStream_t st, const Params& P)
+template <int DT>
+static void launch_t(int nit, bool path, dim3 grid, hipStream_t st, const Params& P)
 {
-    if (P.stats_in)
-        P.masked ? launch_one<DT, NIT, true, true>(path, grid, st, P) : launch_one<DT, NIT, false, true>(path, grid, st, P);
-    else if constexpr (NIT <= kMaxNitTwoRows)
-        P.masked ? launch_one<DT, NIT, true, false>(path, grid, st, P) : launch_one<DT, NIT, false, false>(path, grid, st, P);
+    static_assert(kMaxSlabs * 64 >= 16 * kWG, "sixteen chunks per lane");
+    if (path) {
+        if (nit == 8)
+            launch_path_one<DT, 8, true, false>(grid, st, P);
+        else
+            P.masked ? launch_path_one<DT, 16, true, true>(grid, st, P) : launch_path_one<DT, 16, false, true>(grid, st, P);
+    } else if (nit == 16) {
+        P.masked ? launch_one<DT, 16, true, true>(grid, st, P) : launch_one<DT, 16, false, true>(grid, st, P);
+    } else if (P.stats_in) {
+        P.masked ? launch_one<DT, 8, true, true>(grid, st, P) : launch_one<DT, 8, false, true>(grid, st, P);
+    } else {
+        P.masked ? launch_one<DT, 8, true, false>(grid, st, P) : launch_one<DT, 8, false, false>(grid, st, P);
+    }
 }
 
 void launch_spechub(int dtype, int nit, bool path, dim3 grid, hipStream_t st, const Params& P)
 {
-    static_assert(kMaxSlabs * 64 >= 16 * kWG, "sixteen chunks per lane");
-    if (dtype == MDSD_FP32)
-        nit == 4   ? launch_nit<0, 4>(path, grid, st, P)
-        : nit == 8 ? launch_nit<0, 8>(path, grid, st, P)
-                   : launch_nit<0, 16>(path, grid, st, P);
-    else
-        nit == 4   ? launch_nit<1, 4>(path, grid, st, P)
-        : nit == 8 ? launch_nit<1, 8>(path, grid, st, P)
-                   : launch_nit<1, 16>(path, grid, st, P);
+    (dtype == MDSD_FP32 ? launch_t<0> : launch_t<1>)(nit, path, grid, st, P);
 }
 
 }  // namespace mdsd_wide
