@@ -194,18 +194,6 @@ static int wide_chunks(const Params& P)
 }
 // a batch that leaves CUs without a node
 constexpr int64_t kWideMaxNodes = 256;
-// RRS methods on rows that the 512-thread kernels would stream again in every rejected round: up to this many
-// nodes.  One node per CU gains on the nodes that reject and loses on leaves, which are loaded and worked
-// on in turns (bf16 rows of 100 thousand, k = 4: 672 nodes 99 -> 57 us, 1344 142 -> 105, 2688 181 -> 176;
-// k = 2, where leaves are the larger part: 480 nodes 60 -> 41 us, 960 88 -> 82, 1920 124 -> 140).  Nodes
-// with children here and leaves streamed, in two launches, was slower than either (k = 4, 2688 nodes
-// of 152064: 216 + 133 us against 268).
-constexpr int64_t kWideLongRowNodes = 1024, kWideLongRowNodesManyDrafts = 1536;
-// RRS methods on rows of more than eight chunks per lane of a 512-thread workgroup, of which a CU holds two
-// such nodes: some way into the second round of one node per CU (bf16 rows of 50304, k = 2: 403 nodes 21.8 ->
-// 20.1 us, 496 nodes 22.6 -> 24.2; of 50257, RRSw, 432 nodes, 45 % with children: step 54.4 -> 49.2; k = 4:
-// 504 nodes 34.0 -> 30.6).
-constexpr int64_t kWideTwoPerCuNodes = 448, kWideTwoPerCuNodesManyDrafts = 512;
 // Verify.  SpecHub, which reads its rows once or twice, up to 256 nodes (512 against 1024 threads, 60 nodes).
 // Rows that 512 threads stream (more than 16 chunks per lane): 66048 bf16 19.3 -> 18.0 us, 100000 28.0 -> 23.0.
 // Rows that they hold too: with the draft call's records aligned ones lose (fp32 17000 8.8 -> 9.2, 32000 11.0 ->
@@ -228,17 +216,46 @@ static int wide_spechub_chunks(const mdsd_problem* pb, const Params& P, bool pat
     }
     return P.masked ? (path && P.stats_in ? 0 : nit) : path || P.stats_in ? 0 : nit;
 }
+// Verify, RRS methods: up to how many nodes (512 against 1024 threads, us).  One node per CU gains on the nodes
+// that reject and loses on leaves, which are loaded and worked on in turns.
+// Rows that the 512-thread kernels would stream again in every rejected round: k = 4 up to 1536 nodes (bf16 rows of
+// 100 thousand, 672 nodes 100 -> 60, 1533 145 -> 109), k = 3, where leaves are a larger part, to 1440 (1391 113 -> 101,
+// 1495 of 100001 115 -> 116), k = 2 to 1024 (620 75 -> 51, 1023 84 -> 76, 1920 124 -> 140).  Rows that use little more
+// than half of their registers (66048: nine of sixteen chunks per lane) or spill them (152064: twenty) sooner
+// meet their end: k = 3 1280 (152064, 1235 167 -> 155, 1495 171 -> 182), k = 2 896 (66048, 868 56.7 -> 51.8, 961 58.6 ->
+// 59.1) and, unaligned or spilling, 832 (70001, 775 57.8 -> 57.5, 868 59.8 -> 60.8; 152064, 775 119 -> 114, 961 121 ->
+// 131; 140001 RRSw, 868 120 -> 123).  Without the draft call's records, whose 512-thread form reads more, always up to
+// 1024 and 1536 (152064, 1023 195 -> 168).
+// Rows of which a CU holds two 512-thread nodes (more than eight chunks per lane): some way into the second round
+// of one node per CU.  k > 2 up to 512 nodes (504 of 50257 39.7 -> 34.6), k = 2 to 384 (372 of 34000 18.0 -> 17.1, 434
+// 18.7 -> 20.6; fp32 17000, 372 14.1 -> 14.1, 420 14.6 -> 15.1), unaligned to 448 (434 of 50257 26.1 -> 25.5).  Aligned
+// rows without records from 257 nodes on only (248 of 34000 21.0 -> 21.2, 372 21.8 -> 21.6, 504 31.7 -> 30.2).
+// Shorter rows: unaligned bf16 ones up to 256 nodes (248 of 32001 18.2 -> 17.2; aligned 24000 13.7 -> 13.8, RRSw 15.0 ->
+// 15.5; fp32 12001 RRSw 13.3 -> 13.6; without records aligned ones 7 to 18 % slower).
+// Nodes with children here and leaves streamed, in two launches, was slower than either (k = 4, 2688 nodes
+// of 152064: 216 + 133 against 268).
+static int64_t wide_rrs_nodes(const mdsd_problem* pb, const Params& P)
+{
+    const bool records = P.stats_in != nullptr;
+    switch (resident_chunks(pb)) {
+    case 4: return 0;
+    case 8: return pb->dtype == MDSD_BF16 && P.masked ? kWideMaxNodes : 0;
+    case 16: return P.k > 2 ? 512 : P.masked ? 448 : 384;
+    default: break;
+    }
+    if (P.k > 3) return 1536;
+    const bool spills = wide_chunks(P) == 20;
+    if (!records || !(spills || P.row_chunks <= 9 * mdsd_wide::kThreads)) return P.k < 3 ? 1024 : records ? 1440 : 1536;
+    return P.k == 3 ? 1280 : P.masked || spills ? 832 : 896;
+}
 static int wide_verify_chunks(int method, const mdsd_problem* pb, const Params& P, bool path)
 {
     if (pb->kind != MDSD_LOGITS) return 0;
     if (method == kSpecHub) return wide_spechub_chunks(pb, P, path);
-    if (path) return 0;
     const int64_t nodes = (int64_t)P.B * P.N;
-    const bool many = P.k > 2;
-    const int64_t most = P.row_chunks > 16 * kWG  ? (many ? kWideLongRowNodesManyDrafts : kWideLongRowNodes)
-                         : P.row_chunks > 8 * kWG ? (many ? kWideTwoPerCuNodesManyDrafts : kWideTwoPerCuNodes)
-                                                  : kWideMaxNodes;
-    return P.row_chunks > 4 * kWG && nodes <= most ? wide_chunks(P) : 0;
+    if (path || nodes > wide_rrs_nodes(pb, P)) return 0;
+    if (resident_chunks(pb) == 16 && !P.stats_in && !P.masked && nodes <= kWideMaxNodes) return 0;
+    return wide_chunks(P);
 }
 // Draft, up to 128 nodes with children.  A draw is a chain of barriers, each of which 16 wavefronts pass later
 // than eight, so that only rows whose passes outweigh their draws gain (12 and 120 nodes, 512 against 1024
