@@ -26,17 +26,22 @@ __device__ __forceinline__ uint4 select_chunk(const uint4 (&d)[NIT], int it)
 }
 
 // this lane's register chunk `it` (run-time value) as floats
-template <int DT, int NIT, bool MASKED>
-__device__ __forceinline__ void get_dyn(const RowSrc<DT, NIT, MASKED>& src, int it, float (&a)[Elem<DT>::kPerChunk])
+template <int DT, int NIT, int ENDS>
+__device__ __forceinline__ void get_dyn(const RowSrc<DT, NIT, ENDS>& src, int it, float (&a)[Elem<DT>::kPerChunk])
 {
+    const int lane = threadIdx.x & 63, wave = wave_id();
     uint4 c = select_chunk<NIT>(src.d, it);
-    if constexpr (MASKED) fill_ends<DT>(c, src.r, it * kWaves + wave_id(), (int)(threadIdx.x & 63), src.fill_words());
-    unpack<DT>(c, a);
+    if constexpr (ENDS == kEndsByElement) {
+        finish_chunk<DT>(src.r, (it * kWaves + wave) * 64 + lane, c, src.fill, a);
+    } else {
+        if constexpr (ENDS == kEndsPacked) fill_ends<DT>(c, src.r, it * kWaves + wave, lane, src.fill_words());
+        unpack<DT>(c, a);
+    }
 }
 
 // the element of this lane's registers at virtual index v (the lane must own v)
-template <int DT, int NIT, bool MASKED>
-__device__ __forceinline__ float own_element(const RowSrc<DT, NIT, MASKED>& src, int v)
+template <int DT, int NIT, int ENDS>
+__device__ __forceinline__ float own_element(const RowSrc<DT, NIT, ENDS>& src, int v)
 {
     constexpr int E = Elem<DT>::kPerChunk;
     const int it = (v / (64 * E)) / kWaves;

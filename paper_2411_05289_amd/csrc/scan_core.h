@@ -93,12 +93,13 @@ __device__ __forceinline__ void fill_ends(uint4& d, const RowView& r, int s, int
 // (any V).  NIT > 0: the row is loaded once, NIT chunks per lane, and stays in
 // registers for all passes (V up to NIT * kWaves * 64 chunks); chunk `it` of a
 // lane belongs to slab it * kWaves + wave, so each load instruction of a wave
-// still covers 1 KiB of consecutive memory.  Masked elements read as `fill`: with MASKED
-// every pass fills the ends of its packed chunks in branches that the wave with such a chunk takes, one
-// scalar test for all others.
-// MASKED = false: the caller has checked that every row starts on a 16-byte boundary and
-// that V is a whole number of chunks, so no element ever needs masking.
-template <int DT, int NIT, bool MASKED = true>
+// still covers 1 KiB of consecutive memory.  Masked elements read as `fill`.
+// ENDS: how they come about.  kEndsPacked: every pass fills the ends of its packed chunks in branches that the
+// wave with such a chunk takes, one scalar test for all others.  kEndsByElement: per element behind a test of
+// every chunk by its lane (NIT > 0 only).  kNoEnds: the caller has checked that every row starts on a 16-byte
+// boundary and that V is a whole number of chunks, so no element ever needs masking.
+enum : int { kNoEnds = 0, kEndsPacked = 1, kEndsByElement = 2 };
+template <int DT, int NIT, int ENDS = kEndsPacked>
 struct RowSrc {
     static constexpr int E = Elem<DT>::kPerChunk;
     static constexpr int kNit = NIT;
@@ -125,8 +126,9 @@ struct RowSrc {
     // registers themselves are left alone: changed in place they cost the RRS kernels a hundred spills.)
     __device__ __forceinline__ uint4 chunk_of(int it, int lane, int wave) const
     {
+        static_assert(ENDS != kEndsByElement, "packed chunks with their ends filled");
         uint4 c = d[it];
-        if constexpr (MASKED) fill_ends<DT>(c, r, it * kWaves + wave, lane, fill_words());
+        if constexpr (ENDS == kEndsPacked) fill_ends<DT>(c, r, it * kWaves + wave, lane, fill_words());
         return c;
     }
     __device__ __forceinline__ uint32_t fill_words() const
@@ -138,7 +140,11 @@ struct RowSrc {
     // this lane's register chunk `it` as floats (it: compile-time constant after unrolling)
     __device__ __forceinline__ void get(int it, float (&a)[E]) const
     {
-        unpack<DT>(chunk_of(it, (int)(threadIdx.x & 63), wave_id()), a);
+        const int lane = threadIdx.x & 63, wave = wave_id();
+        if constexpr (ENDS == kEndsByElement)
+            finish_chunk<DT>(r, (it * kWaves + wave) * 64 + lane, d[it], fill, a);
+        else
+            unpack<DT>(chunk_of(it, lane, wave), a);
     }
 
     // body(slab, chunk, a[E])
@@ -197,8 +203,8 @@ struct RowSrc {
     }
 };
 
-template <int DT, bool MASKED>
-struct RowSrc<DT, 0, MASKED> {
+template <int DT, int ENDS>
+struct RowSrc<DT, 0, ENDS> {
     static constexpr int E = Elem<DT>::kPerChunk;
     static constexpr int kNit = 0;
     RowView r;
@@ -288,8 +294,8 @@ __device__ __forceinline__ void store_slab_sum(float* slab_w, int s, float lane_
 // body(slab, chunk, a[E], b[E]) over two rows with the same head and length.  Streamed rows are
 // asked for AHEAD (1 or 2) steps before their use; the steps past the end read the rows' last
 // chunks again and drop them.
-template <int AHEAD = 1, int DT, int NIT, bool MASKED, class Body>
-__device__ __forceinline__ void for_each2(const RowSrc<DT, NIT, MASKED>& sa, const RowSrc<DT, NIT, MASKED>& sb,
+template <int AHEAD = 1, int DT, int NIT, int ENDS, class Body>
+__device__ __forceinline__ void for_each2(const RowSrc<DT, NIT, ENDS>& sa, const RowSrc<DT, NIT, ENDS>& sb,
                                           Body body)
 {
     static_assert(AHEAD == 1 || AHEAD == 2, "one or two steps ahead");
@@ -351,12 +357,12 @@ __device__ __forceinline__ void unpack_half(const uint4& d, float (&v)[Elem<DT>:
 // body(it, slab, chunk, a, b) with the packed chunks of row a (register chunk it) and of row b, which is
 // read from memory as the loop goes, QW chunks ahead of their use: b is read exactly once and
 // never held whole.  Chunks of b past the end of the row read as `fill_b`.
-template <int QW, int DT, int NIT, bool MASKED, class Body>
-__device__ __forceinline__ void for_each_streamed_at(int lane, int wave, const RowSrc<DT, NIT, MASKED>& sa,
+template <int QW, int DT, int NIT, int ENDS, class Body>
+__device__ __forceinline__ void for_each_streamed_at(int lane, int wave, const RowSrc<DT, NIT, ENDS>& sa,
                                                      const RowView& rb, float fill_b, Body body);
 
-template <int QW, int DT, int NIT, bool MASKED, class Body>
-__device__ __forceinline__ void for_each_streamed(const RowSrc<DT, NIT, MASKED>& sa, const RowView& rb,
+template <int QW, int DT, int NIT, int ENDS, class Body>
+__device__ __forceinline__ void for_each_streamed(const RowSrc<DT, NIT, ENDS>& sa, const RowView& rb,
                                                   float fill_b, Body body)
 {
     for_each_streamed_at<QW>((int)(threadIdx.x & 63), wave_id(), sa, rb, fill_b, body);
@@ -365,8 +371,8 @@ __device__ __forceinline__ void for_each_streamed(const RowSrc<DT, NIT, MASKED>&
 // the same with the lane and wave numbers handed in (a caller that runs the pass inside a loop
 // hands in copies the compiler cannot see through, so that it does not hoist the address and
 // mask arithmetic of every chunk out of that loop and hold it in registers)
-template <int QW, int DT, int NIT, bool MASKED, class Body>
-__device__ __forceinline__ void for_each_streamed_at(int lane, int wave, const RowSrc<DT, NIT, MASKED>& sa,
+template <int QW, int DT, int NIT, int ENDS, class Body>
+__device__ __forceinline__ void for_each_streamed_at(int lane, int wave, const RowSrc<DT, NIT, ENDS>& sa,
                                                      const RowView& rb, float fill_b, Body body)
 {
     static_assert(NIT > 0 && QW > 0, "row a must be resident");
@@ -391,7 +397,7 @@ __device__ __forceinline__ void for_each_streamed_at(int lane, int wave, const R
             if ((s + 1) * 64 > rb.nchunk) {  // the row's last slab, not full
                 if (s * 64 + lane >= rb.nchunk) cur = make_uint4(fw, fw, fw, fw);
             }
-            if constexpr (MASKED) fill_ends<DT>(cur, rb, s, lane, fw);
+            if constexpr (ENDS == kEndsPacked) fill_ends<DT>(cur, rb, s, lane, fw);
             body(it, s, s * 64 + lane, sa.chunk_of(it, lane, wave), cur);
         }
         __builtin_amdgcn_sched_barrier(0);  // one chunk pair at a time
@@ -412,8 +418,8 @@ __device__ __forceinline__ void static_for(F&& f)
 // CACHED = false reads all of b from memory and leaves those chunks in `cache` (one 16-byte
 // entry per thread and chunk, read and written by that thread only: no barrier), a pass with
 // CACHED = true takes them from there and reads only the rest of b from memory.
-template <int QW, int QC, bool CACHED, int DT, int NIT, bool MASKED, class Body>
-__device__ __forceinline__ void for_each_streamed_cached(int lane, int wave, const RowSrc<DT, NIT, MASKED>& sa,
+template <int QW, int QC, bool CACHED, int DT, int NIT, int ENDS, class Body>
+__device__ __forceinline__ void for_each_streamed_cached(int lane, int wave, const RowSrc<DT, NIT, ENDS>& sa,
                                                          const RowView& rb, float fill_b, uint4 (*cache)[kWG],
                                                          Body body)
 {
@@ -440,7 +446,7 @@ __device__ __forceinline__ void for_each_streamed_cached(int lane, int wave, con
             if ((s + 1) * 64 > rb.nchunk) {  // the row's last slab, not full
                 if (s * 64 + lane >= rb.nchunk) cur = make_uint4(fw, fw, fw, fw);
             }
-            if constexpr (MASKED && !(CACHED && it < QC)) fill_ends<DT>(cur, rb, s, lane, fw);
+            if constexpr (ENDS == kEndsPacked && !(CACHED && it < QC)) fill_ends<DT>(cur, rb, s, lane, fw);
             if constexpr (!CACHED && it < QC) cache[it][tid] = cur;
             body(it, s, s * 64 + lane, sa.chunk_of(it, lane, wave), cur);
         }

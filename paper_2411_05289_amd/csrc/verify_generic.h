@@ -19,12 +19,25 @@ __device__ __forceinline__ float in_vgpr(float x)
 // ---------------------------------------------------------------- verify kernel
 // Two workgroups per CU need 4 waves per SIMD, i.e. at most 128 VGPRs; the 16-chunk variant
 // holds 128 VGPRs of row data alone and runs one workgroup per CU.
-template <int DT, bool LOGITS, int METHOD, int NIT>
+//
+// Ends of rows in registers by element where that measured faster than packed (packed -> by element, 4030 nodes):
+// SpecHub on fp32 probabilities of more than 512 chunks (9001 elements 37.1 -> 35.3 us, 3501 14.7 -> 13.8; path-only the
+// other way), the RRS methods on fp32 rows (2501 probabilities, RRS 17.6 -> 16.3; 2501 logits, RRSw 26.9 -> 25.2;
+// path-only 24.3 -> 23.5) and RRS on bf16 probabilities (9001 40.6 -> 39.6), RRSw path-only on bf16 rows (124 nodes, 5001
+// probabilities 19.0 -> 17.2).  Packed ends keep the others: RRSw bf16 9001 73.6 -> 49.0.
+template <int DT, bool LOGITS, int METHOD, int NIT, bool PATH>
+constexpr bool kEndsPerElement =
+    kWG > 64 && (PATH                 ? METHOD != kSpecHub && (DT == 0 || METHOD == kRRSw)
+                 : METHOD == kSpecHub ? kWG >= 256 && NIT < 16 && DT == 0 && !LOGITS
+                 : DT == 0            ? METHOD == kRRSw || !LOGITS
+                                      : METHOD == kRRS && !LOGITS && kWG == 512);
+
+template <int DT, bool LOGITS, int METHOD, int NIT, bool PATH>
 __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id, Shared& sh, int& phase)
 {
     constexpr int E = Elem<DT>::kPerChunk;
     using CV = ToWeight<LOGITS>;
-    using Src = RowSrc<DT, NIT>;
+    using Src = RowSrc<DT, NIT, kEndsPerElement<DT, LOGITS, METHOD, NIT, PATH> ? kEndsByElement : kEndsPacked>;
     const int k = P.k;
     const float* ur = P.u + id.row * (k + 1);
     const bool need_full = (P.resid_mass != nullptr) || (P.resid_prob != nullptr);
@@ -512,7 +525,7 @@ __global__ __launch_bounds__(kWG) void verify_kernel(const Params P)
     __shared__ Shared sh;
     int phase = 0;
     const NodeId id = node_of_block(P);
-    verify_node<DT, LOGITS, METHOD, NIT>(P, id, sh, phase);
+    verify_node<DT, LOGITS, METHOD, NIT, false>(P, id, sh, phase);
 }
 
 template <int DT, bool LOGITS, int METHOD, int NIT>
@@ -520,7 +533,7 @@ __global__ __launch_bounds__(kWG) void verify_path_kernel(const Params P)
 {
     __shared__ Shared sh;
     int phase = 0;
-    walk_and_verify(P, [&](const NodeId& id) { return verify_node<DT, LOGITS, METHOD, NIT>(P, id, sh, phase); });
+    walk_and_verify(P, [&](const NodeId& id) { return verify_node<DT, LOGITS, METHOD, NIT, true>(P, id, sh, phase); });
 }
 
 template <int DT, bool LG, int METHOD>
