@@ -12,29 +12,41 @@ constexpr int kGroupMaxThreads = 512;  // where a tree's groups need more
 // Lanes per node for rows of `chunks` 16-byte chunks, at most four per lane; 0: the rows are too long.
 // Few lanes make the most of every instruction, many make a node's chain of instructions short.  Up to
 // kGroupFewWaves wavefronts, which the chip holds at once, the short chain wins (bf16 rows of 60 elements,
-// 2000 nodes: step 16.5 us with 4 lanes per node, 11.9 with 32; 60000 nodes: 20.9 and 53.3).  nodes: those
-// that get a group.  walk_nodes: nodes per tree where the launch is to walk the trees, else 1: the lanes
-// are then not more than lets a workgroup hold a tree, if there is such a choice (the same rows, 2000
-// nodes in trees of 15: 32 lanes 11.9 us, 64 lanes with the walk by arrival count 14.9).
+// 2000 nodes: step 16.5 us with 4 lanes per node, 11.9 with 32; 60000 nodes: 20.9 and 53.3); rows of more than 64
+// chunks, whose wavefronts wait for memory longer, up to twice as many (1000 elements, 2100 nodes: SpecHub verify
+// 7.4 us with 32 lanes, 6.2 with 64).  path: trees follow their nodes one by one, so that the chain is all there is,
+// also for rows that leave most lanes without a part (60 elements, 64 lanes against 16: 16 trees 13.0 -> 10.5,
+// 1000 14.4 -> 11.7, 4000, where 32 lanes are left, 14.9 -> 15.5).
 constexpr int64_t kGroupFewWaves = 2048;
 // Whether the workgroups of a launch hold whole trees, which they then walk: a tree's groups must fit a
 // workgroup.  Up to kGroupTreesMaxNodes nodes: a wavefront then holds nodes of both kinds and waits for
 // its workgroup, which costs more than a launch once the chip is full (15-node trees of 250 bf16 elements,
-// 8000 nodes: 10.1 us against 7.7 and the walk's 2.5; 60000 nodes: 39 against 24 and 3).
-constexpr int64_t kGroupTreesMaxNodes = 16384;
+// 8000 nodes: 10.1 us against 7.7 and the walk's 2.5; 60000 nodes: 39 against 24 and 3); with one tree of 32 lanes
+// per node in 512 threads sooner (rows of 500 fp32 elements, 15-node trees: 4500 nodes 9.1 inside, 9.8 outside;
+// 9000 nodes 14.3 and 12.0).
+constexpr int64_t kGroupTreesMaxNodes = 16384, kGroupTreesMaxNodes32Lanes = 6144;
 inline bool group_walks_inside(int lanes, int N, int64_t nodes)
 {
-    return nodes <= kGroupTreesMaxNodes && (int64_t)lanes * N <= kGroupMaxThreads;
+    const int64_t threads = (int64_t)lanes * N;
+    if (threads > kGroupMaxThreads) return false;
+    return nodes <= (lanes >= 32 && threads > kGroupThreads ? kGroupTreesMaxNodes32Lanes : kGroupTreesMaxNodes);
 }
+// walk_nodes: nodes per tree where the launch is to walk the trees, else 1: half the lanes are taken where that
+// lets a workgroup hold a tree (rows of 60 bf16 elements, 2000 nodes in trees of 15: 32 lanes 11.9 us, 64 lanes with
+// the walk by arrival count 14.9), but not for rows of more than 96 chunks (1000 elements, 1050 nodes: 9.5 us with
+// 32 lanes, 8.4 with 64 and the walk's launch; fp32 300, 75 chunks: 7.2 and 7.5) and never a quarter (250 elements,
+// 31-node trees: 10.0 with 16 lanes, 8.9 with 64 and the launch).
 inline int group_lanes(int64_t chunks, int64_t nodes, int walk_nodes, bool path)
 {
     if (chunks > 4 * 64) return 0;
     int least = 4;
     while (4 * least < chunks) least *= 2;
     int g = least;
-    while (g < 64 && (path || g < chunks) && 2 * g * nodes <= 64 * kGroupFewWaves) g *= 2;
-    if (!group_walks_inside(g, walk_nodes, nodes) && group_walks_inside(least, walk_nodes, nodes))
-        while (!group_walks_inside(g, walk_nodes, nodes)) g /= 2;
+    const int64_t waves = chunks > 64 ? 2 * kGroupFewWaves : kGroupFewWaves;
+    while (g < 64 && (path || g < chunks) && 2 * g * nodes <= 64 * waves) g *= 2;
+    if (chunks <= 96 && g > least && !group_walks_inside(g, walk_nodes, nodes) &&
+        group_walks_inside(g / 2, walk_nodes, nodes))
+        g /= 2;
     return g;
 }
 

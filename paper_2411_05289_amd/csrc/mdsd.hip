@@ -276,16 +276,20 @@ static bool wide_draft(int method, const mdsd_problem* pb, const Params& P)
 
 // SpecHub nodes of more than 64 chunks per row, from this many on: one wavefront per node with the rows
 // in registers and more wavefronts on a SIMD (60000 nodes of 1000 bf16 elements 68 -> 55 us, of 2000 90 ->
-// 77; 8000 nodes 11.3 against 11.8 us).  The RRS methods gain from their groups at every size (119 -> 80,
-// 146 -> 100 us).
+// 77; 8000 nodes 11.3 against 11.8 us); bf16 rows of more than 128 chunks sooner (1500 elements, 9000 nodes 16.2 ->
+// 16.2, 15000 23.2 -> 20.6; fp32 rows of 250 chunks 17.4 and 20.1).  The RRS methods gain from their groups
+// at every size (119 -> 80, 146 -> 100 us).
 // Path-only from 2048 trees on (4000 trees, 1000 elements 25.4 -> 22.6 us, 2000 elements 33.5 -> 29.7).
-constexpr int64_t kWaveSpecHubMinNodes = 16384, kWaveSpecHubMinPathTrees = 2048;
+constexpr int64_t kWaveSpecHubMinNodes = 16384, kWaveSpecHubMinNodesLong = 10240, kWaveSpecHubMinPathTrees = 2048;
 
 // lanes per node of the verify kernels for short rows; 0: another build takes the call
-static int verify_lanes(int method, const Params& P, bool path)
+static int verify_lanes(int method, int dtype, const Params& P, bool path)
 {
     const int64_t nodes = (int64_t)P.B * (path ? 1 : P.N);
-    if (method == kSpecHub && P.row_chunks > 64 && nodes >= (path ? kWaveSpecHubMinPathTrees : kWaveSpecHubMinNodes)) return 0;
+    const int64_t wave_from = path ? kWaveSpecHubMinPathTrees
+                              : dtype == MDSD_BF16 && P.row_chunks > 128 ? kWaveSpecHubMinNodesLong
+                                                                         : kWaveSpecHubMinNodes;
+    if (method == kSpecHub && P.row_chunks > 64 && nodes >= wave_from) return 0;
     return group_lanes(P.row_chunks, nodes, !path && P.accept_depth ? P.N : 1, path);
 }
 
@@ -293,7 +297,7 @@ static int verify_lanes(int method, const Params& P, bool path)
 static void launch_verify(int method, const mdsd_problem* pb, const Params& P, bool path, hipStream_t st)
 {
     const bool lg = pb->kind == MDSD_LOGITS;
-    if (const int lanes = verify_lanes(method, P, path)) {
+    if (const int lanes = verify_lanes(method, pb->dtype, P, path)) {
         (method == kSpecHub ? launch_group_spechub : method == kRRS ? launch_group_rrs : launch_group_rrsw)(
             lanes, pb->dtype, lg, path, st, P);
         return;
@@ -415,7 +419,7 @@ static int verify_entry(int method, const mdsd_problem* pb, const int32_t* token
     P.accept_depth = out->accept_depth;
     P.emitted = out->emitted;
     // short rows: where a workgroup holds whole trees it walks them without counting arrivals
-    const int lanes = path ? 0 : verify_lanes(method, P, false);
+    const int lanes = path ? 0 : verify_lanes(method, pb->dtype, P, false);
     const bool trees_whole = lanes && out->accept_depth && group_walks_inside(lanes, P.N, (int64_t)P.B * P.N);
     const bool walk_inside = !path && out->accept_depth && (tree_count || trees_whole);
     P.tree_count = walk_inside && !trees_whole ? tree_count : nullptr;
