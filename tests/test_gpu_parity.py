@@ -171,12 +171,13 @@ def test_temperatures(method, T, request):
     note(request, check_case(method, wl, seed=int(T * 10)))
 
 
-@pytest.mark.parametrize("V,Bn", [(4096, 6), (70016, 2)], ids=["in_registers", "streamed"])
+@pytest.mark.parametrize("V,Bn", [(4096, 6), (70016, 2), (1000, 12), (32001, 3), (32001, 40), (128256, 1), (152064, 1)],
+                         ids=["in_registers", "few_nodes", "lanes", "few_nodes_masked", "masked", "few_long", "streamed"])
 def test_rows_with_isolated_peaks(V, Bn, request):
     """bf16 rows whose largest logits sit far above the rest at even and at odd token indices
     (a shift taken from part of the row would overflow or underflow the weights), and
     rows holding -inf (masked tokens): the softmax must still be the exact one.  Once with rows
-    that stay in registers, once with rows long enough to be streamed."""
+    in registers of 512 and of 1024 threads, in a group of lanes, on any 16-byte phase, and streamed."""
     wl = W.config(3, device=DEV, B=Bn, V=V, seed=31)
     g = torch.Generator(device="cpu").manual_seed(31)
     # the target's peaks leave every other weight at zero in fp32; the draft's stay moderate, so
@@ -233,10 +234,11 @@ _MASKED_ROWS = [("bf16", 32000, 3), ("bf16", 32001, 3), ("bf16", 32001, 40), ("b
 
 
 @pytest.mark.parametrize("method", ALL)
-@pytest.mark.parametrize("value,T", [("lowest", 1.0), ("lowest", 2.0), (-1e30, 0.7), (-1e10, 1.0), (-1e4, 1.0)])
+@pytest.mark.parametrize("value,T", [("lowest", 1.0), ("lowest", 2.0), (-1e30, 0.7), (-1e10, 1.0), (-1e4, 1.0),
+                                     (float("-inf"), 1.0)])
 @pytest.mark.parametrize("dtype,V,Bn", _MASKED_ROWS, ids=["%s_V%d_B%d" % v for v in _MASKED_ROWS])
 def test_rows_masked_with_a_finite_number(method, dtype, V, Bn, value, T, request):
-    """Rows masked with the type's lowest value or another large negative number instead of -inf: the masked
+    """Rows masked with the type's lowest value, another large negative number or -inf: the masked
     tokens weigh nothing, also where a wavefront's share of the row holds nothing else (its own shift then
     overflows, or is off by more than the range of an exponent)."""
     k, depth = 2, 3
@@ -283,18 +285,17 @@ def test_residual_mass_keeps_32_bits(method, dtype, V, Bn, records, request):
 
 
 # ----------------------------------------------------------------- every dispatched kernel variant
-# (dtype, kind, V, row offset in elements): between them these reach every instantiation the
-# launchers can choose: rows in registers with 4, 8 or 16 chunks per lane, with and without masked
-# first / last chunks, fp32 and bf16, logits and probabilities, the streamed forms, and the
-# builds for short rows with one, two or four wavefronts per node (rows of up to 256, 512 and
-# 1024 16-byte chunks).
+# (dtype, kind, V, row offset in elements) in batches of a few trees: rows in a group of lanes, in registers of 128,
+# 256, 512 and 1024 threads with 4, 8 or 16 chunks per lane, with and without masked first / last chunks, fp32 and
+# bf16, logits and probabilities, and the streamed forms.  The kernels that only larger batches reach are
+# in the lists below.
 _VARIANTS = [
-    ("fp32", "logits", 1000, 0),     # one wavefront per node: fp32 logits, four chunks per lane
+    ("fp32", "logits", 1000, 0),     # 64 lanes per node: fp32 logits, four chunks per lane
     ("fp32", "logits", 301, 1),      # ... masked
-    ("bf16", "logits", 2040, 0),     # ... bf16 logits, the longest aligned row of that build
+    ("bf16", "logits", 2040, 0),     # ... bf16 logits, one chunk short of the longest row
     ("bf16", "logits", 777, 3),      # ... masked
     ("fp32", "probs", 513, 0),       # ... fp32 probabilities
-    ("bf16", "probs", 2042, 0),      # two wavefronts per node: the shortest row, bf16 probabilities
+    ("bf16", "probs", 2042, 0),      # two wavefronts per node: the shortest unaligned row, bf16 probabilities
     ("fp32", "logits", 1023, 0),     # ... fp32 logits, masked
     ("bf16", "logits", 3000, 0),     # ... bf16 logits
     ("fp32", "probs", 2044, 0),      # ... the longest aligned fp32 row
@@ -312,13 +313,13 @@ _VARIANTS = [
     ("bf16", "logits", 66048, 0),    # ... bf16: one slab more than a whole number of rounds of eight waves
     ("bf16", "logits", 81913, 5),    # ... masked, one slab short of a multiple of four rounds
     ("bf16", "logits", 20001, 0),    # bf16, 8 chunks per lane, masked
-    ("bf16", "logits", 50304, 0),    # bf16, 16 chunks per lane, no masking
+    ("bf16", "logits", 50304, 0),    # bf16, 16 chunks per lane at 512 threads (RRS, few nodes: 1024 threads), no masking
     ("bf16", "logits", 50257, 0),    # ... masked
-    ("bf16", "logits", 65520, 0),    # the longest row that stays in registers
+    ("bf16", "logits", 65520, 0),    # the longest row that 512 threads hold
     ("bf16", "logits", 16385, 5),    # ... masked, one element into a slab
     ("bf16", "logits", 32767, 7),    # ... one element short of one, rows starting at a chunk's last element
     ("fp32", "logits", 8193, 3),     # ... fp32
-    ("bf16", "probs", 1000, 0),      # bf16 probabilities: one wavefront per node
+    ("bf16", "probs", 1000, 0),      # bf16 probabilities: 64 lanes per node
     ("bf16", "probs", 4099, 3),      # ... masked
     ("bf16", "probs", 40000, 0),     # ... 16 chunks per lane / streamed
     ("bf16", "probs", 70016, 0),     # ... streamed
@@ -355,7 +356,7 @@ def test_dispatched_variants(method, dtype, kind, V, off, request):
 # ----------------------------------------------------------------- large batches
 _LARGE = [
     ("bf16", 32000, 0),     # the headline row: 256 threads per node, sixteen chunks per lane
-    ("bf16", 20001, 0),     # ... masked (RRS / RRSw: the generic kernel)
+    ("bf16", 20001, 0),     # ... masked
     ("fp32", 12000, 0),     # fp32
     ("fp32", 12001, 1),     # ... masked
 ]
@@ -409,6 +410,43 @@ def test_few_nodes_with_long_rows(method, dtype, V, off, Bn, request):
     note(request, check_case(method, wl, seed=V % 1000, seqs=range(min(Bn, 8))))
 
 
+# ----------------------------------------------------------------- rows in registers by nodes per batch
+# (methods, dtype, V, row offset, k, depth, trees): more nodes than 1024 threads per node are taken for, on both
+# sides of that bound, and what only those batches reach on 512 threads
+_BY_NODES = [
+    ("rrs", "bf16", 50257, 0, 2, 5, 15), ("rrs", "bf16", 50304, 0, 2, 5, 13),   # 465 and 403: 16 chunks per lane
+    ("rrs", "bf16", 50304, 0, 2, 5, 12),                                        # 372: 1024 threads
+    ("rrs", "bf16", 50304, 0, 4, 3, 25), ("rrs", "fp32", 20001, 0, 4, 3, 25),   # 525
+    ("rrs", "fp32", 20000, 0, 2, 5, 13), ("rrs", "fp32", 20001, 1, 2, 5, 15),
+    ("rrs", "bf16", 20001, 0, 2, 4, 20), ("rrs", "bf16", 20001, 3, 2, 4, 17),   # 300 and 255: 8 chunks, masked
+    ("rrs", "bf16", 20000, 0, 2, 4, 2),
+    ("rrs", "fp32", 12000, 0, 2, 4, 24), ("rrs", "fp32", 12001, 0, 2, 4, 24),
+    ("spechub", "fp32", 20001, 0, 2, 4, 18), ("spechub", "bf16", 50257, 0, 2, 4, 18),
+    ("spechub", "fp32", 20001, 0, 2, 4, 2), ("spechub", "bf16", 65536, 0, 2, 4, 2),
+    ("spechub", "bf16", 66049, 0, 2, 2, 33), ("spechub", "bf16", 90001, 1, 2, 3, 2),   # path-only, 1024 threads
+    ("rrs", "fp32", 70000, 0, 2, 3, 2), ("rrs", "fp32", 70001, 0, 2, 3, 2),     # 20 chunks per lane of 1024 threads
+    ("rrs", "bf16", 70001, 0, 2, 4, 56), ("rrs", "bf16", 66048, 0, 3, 3, 99),   # 840 and 1287: streamed
+    ("rrs", "fp32", 18000, 0, 2, 3, 3), ("rrs", "fp32", 20000, 0, 4, 2, 3),     # drafts on 1024 threads
+]
+
+
+@pytest.mark.parametrize("methods,dtype,V,off,k,depth,Bn", _BY_NODES, ids=["%s_%s_V%d_off%d_k%d_d%d_B%d" % v for v in _BY_NODES])
+def test_rows_in_registers_by_nodes(methods, dtype, V, off, k, depth, Bn, request):
+    N = W.tree_nodes(k, depth)
+    td = torch.float32 if dtype == "fp32" else torch.bfloat16
+    t, d = W.llm_like_logits(Bn, N, V, logit_std=3.0, draft_noise_std=1.5, dtype=td, seed=V + Bn, device=DEV)
+    if off:
+        big_t = torch.zeros((Bn * N * V + off,), dtype=td, device=DEV)
+        big_d = torch.zeros((Bn * N * V + off,), dtype=td, device=DEV)
+        tv, dv = big_t[off:].view(Bn, N, V), big_d[off:].view(Bn, N, V)
+        tv.copy_(t)
+        dv.copy_(d)
+        t, d = tv, dv
+    wl = W.Workload("nodes_%s_V%d_%d" % (dtype, V, Bn * N), Bn, N, V, k, depth, dtype, "logits", 0.9, 1.1, t, d)
+    for method in ("rrs", "rrsw") if methods == "rrs" else ("spechub",):
+        note(request, check_case(method, wl, seed=V % 1000, seqs=sorted({0, 1, Bn // 2, Bn - 1})))
+
+
 # ----------------------------------------------------------------- short rows: lanes per node
 # (dtype, kind, V, row offset, nodes per tree's depth, trees): 4, 8, 16, 32 and 64 lanes per node at the
 # last row they hold and the first they do not (16-byte chunks 4 G and 4 G + 1), in batches small enough
@@ -420,6 +458,13 @@ _SHORT = [
     ("fp32", "logits", 129, 0, 4, 1200),    # 33 chunks, rows on every phase: 16 lanes
     ("bf16", "logits", 505, 0, 2, 6000),    # 64 chunks with the head: 16 lanes
     ("fp32", "logits", 260, 0, 2, 6000),    # 65: 32 lanes (SpecHub: one wavefront per node)
+    ("bf16", "logits", 1000, 0, 2, 5600),   # SpecHub, one wavefront per node: bf16
+    ("bf16", "probs", 1000, 0, 2, 5600),    # ... bf16 probabilities
+    ("fp32", "probs", 300, 0, 2, 5600),     # ... fp32 probabilities
+    ("bf16", "logits", 1500, 0, 3, 1500),   # ... rows of more than 128 chunks from 10240 nodes on
+    ("bf16", "logits", 1000, 0, 3, 300),    # 64 lanes in 2100 nodes, trees of 7: too many for a workgroup
+    ("fp32", "logits", 300, 0, 4, 400),     # 32 lanes, trees of 15 in 512 threads: 6000 nodes
+    ("fp32", "logits", 300, 0, 4, 420),     # ... and 6300: a launch of its own for the walk
     ("bf16", "logits", 1024, 0, 3, 300),    # 128 chunks: 64 lanes in a small batch
     ("fp32", "probs", 1017, 0, 2, 900),     # 255 chunks with the head: 64 lanes
     ("bf16", "logits", 2, 0, 2, 40000),     # one chunk
@@ -450,24 +495,26 @@ def test_short_rows_lanes_per_node(method, dtype, kind, V, off, depth, Bn, reque
 
 
 # ----------------------------------------------------------------- general topology
-@pytest.mark.parametrize("V", [2500, 12000])
+@pytest.mark.parametrize("V,Bn", [(2500, 12), (12000, 12), (50, 12), (600, 12), (50, 2000), (600, 2000)])
 @pytest.mark.parametrize("method", ALL)
-def test_unbalanced_tree(method, V, request):
-    """first_child given: an unbalanced binary tree (left spine deeper than the right)."""
+def test_unbalanced_tree(method, V, Bn, request):
+    """first_child given: an unbalanced binary tree (left spine deeper than the right).  Short rows in batches
+    whose workgroups hold whole trees, or too many lanes for that, and beyond 16384 nodes."""
     fc = [1, 3, -1, 5, -1, 7, -1, -1, -1]      # 0->(1,2) 1->(3,4) 3->(5,6) 5->(7,8)
-    N, k, depth, Bn = len(fc), 2, 5, 12
+    N, k, depth = len(fc), 2, 5
     t, d = W.llm_like_logits(Bn, N, V, logit_std=3.0, draft_noise_std=1.0, dtype=torch.bfloat16, seed=21, device=DEV)
     wl = W.Workload("unbalanced", Bn, N, V, k, depth, "bf16", "logits", 1.0, 1.0, t, d,
                     first_child=torch.tensor(fc, dtype=torch.int32, device=DEV))
-    note(request, check_case(method, wl, seed=21))
+    note(request, check_case(method, wl, seed=21, seqs=None if Bn < 100 else [0, 1, 2, 3, 999, 1998, 1999]))
 
 
+@pytest.mark.parametrize("V", [3000, 60])
 @pytest.mark.parametrize("method", ["rrs", "rrsw"])
-def test_unbalanced_ternary_tree(method, request):
+def test_unbalanced_ternary_tree(method, V, request):
     """first_child given, three children per internal node: 0->(1,2,3) 1->(4,5,6) 3->(7,8,9)
     6->(10,11,12); nodes 2, 4, 5 and the last level are leaves."""
     fc = [1, 4, -1, 7, -1, -1, 10, -1, -1, -1, -1, -1, -1]
-    N, k, depth, V, Bn = len(fc), 3, 4, 3000, 10
+    N, k, depth, Bn = len(fc), 3, 4, 10
     t, d = W.llm_like_logits(Bn, N, V, logit_std=3.0, draft_noise_std=1.0, dtype=torch.bfloat16, seed=22, device=DEV)
     wl = W.Workload("unbalanced3", Bn, N, V, k, depth, "bf16", "logits", 1.0, 1.0, t, d,
                     first_child=torch.tensor(fc, dtype=torch.int32, device=DEV))
@@ -494,7 +541,7 @@ def test_first_child_entries_that_cannot_be_children_count_as_leaves():
             assert torch.equal(res[0][key], res[1][key]), (bad, key)
 
 
-@pytest.mark.parametrize("V", [600, 4000, 9000], ids=["one_wave_per_node", "two_waves_per_node", "eight_waves_per_node"])
+@pytest.mark.parametrize("V", [600, 4000, 9000], ids=["lanes_per_node", "two_waves_per_node", "eight_waves_per_node"])
 @pytest.mark.parametrize("method", ALL)
 def test_trees_of_more_than_64_nodes(method, V, request):
     """127-node trees: the walk (as a launch of its own and inside the verify kernel) goes node
@@ -638,7 +685,8 @@ def test_invalid_tokens_and_pairs_are_flagged():
         assert _np(v["outcome"])[0, 0] == B.BAD_TOKEN
 
 
-@pytest.mark.parametrize("V,dtype,kind", [(4096, torch.bfloat16, "resident"), (70016, torch.bfloat16, "streamed")])
+@pytest.mark.parametrize("V,dtype,kind", [(4096, torch.bfloat16, "resident"), (70016, torch.bfloat16, "few_nodes"),
+                                          (300, torch.bfloat16, "lanes"), (140016, torch.bfloat16, "streamed")])
 def test_unusable_draft_record_is_flagged(V, dtype, kind):
     """A draft record whose hub lies outside the vocabulary makes that node MDSD_BAD_PAIR (never a
     wild read); every other node is verified as with the good records.  Invalid draft tokens
@@ -795,24 +843,33 @@ def test_step_plan_gives_what_the_separate_calls_give(method):
     assert B.StepPlan(method, big, u_d, u_v).walk_in_verify is False   # 160 * 31 nodes: beyond the rule's 3000
 
 
-@pytest.mark.parametrize("shape", ["headline", "small_trees", "long_rows"])
+@pytest.mark.parametrize("shape", ["headline", "small_trees", "many_small_trees", "large_trees", "long_rows"])
 def test_walk_inside_the_verify_kernel_over_many_launches(shape):
     """The arrival counters hand outcomes from workgroup to workgroup inside one launch; a mistake
     in that hand-over would show now and then, not every time.  2000 launches back to back on
-    rotating inputs, each compared on the device with what the walk as a launch of its own gave."""
+    rotating inputs, each compared on the device with what the walk as a launch of its own gave.
+    Short rows: small_trees are walked from LDS by the workgroup that holds them whole; arrivals are counted
+    beyond 16384 nodes and for trees of more nodes than a workgroup has groups of lanes."""
     if shape == "headline":
         wls = [W.config(3, device=DEV, seed=s, B=32) for s in range(3)]
     elif shape == "small_trees":
         wls = [W.toy_pairs(0.25, 0.7, 200, repeats=4, seed=s, device=DEV) for s in range(3)]
+    elif shape == "many_small_trees":
+        wls = [W.toy_pairs(0.25, 0.7, 200, repeats=30, seed=s, device=DEV) for s in range(3)]
+    elif shape == "large_trees":
+        wls = [W.config(3, device=DEV, seed=s, B=6, V=600, depth=7) for s in range(3)]
     else:
         wls = [W.config(5, device=DEV, seed=s, B=8, k=2, depth=4) for s in range(2)]
     plans, want = [], []
     for i, wl in enumerate(wls):
         pb = B.Problem.from_workload(wl)
         u_d, u_v = uniforms(wl, i)
-        ref = B.StepPlan("spechub", pb, u_d, u_v, walk_in_verify=False).run()
+        ref = B.StepPlan("spechub", pb, u_d, u_v)
+        ref.draft()
+        ref.verify()
+        ref.walk()
         torch.cuda.synchronize()
-        want.append({key: ref[key].clone() for key in ("accept_depth", "emitted", "outcome", "token")})
+        want.append({key: ref.out[key].clone() for key in ("accept_depth", "emitted", "outcome", "token")})
         plans.append(B.StepPlan("spechub", pb, u_d, u_v, walk_in_verify=True))
     bad = torch.zeros((), dtype=torch.int64, device=DEV)
     for i in range(2000):
