@@ -305,10 +305,15 @@ static void launch_draft_n(int nit, bool masked, dim3 grid, dim3 block, hipStrea
         hipLaunchKernelGGL((draft_kernel<DT, LG, METHOD, 8, false>), grid, block, 0, st, P);
         return;
     }
+    if constexpr (!LG) {  // logit rows of this size are streamed
+        if (nit == 16) {
+            hipLaunchKernelGGL((draft_kernel<DT, LG, METHOD, 16>), grid, block, 0, st, P);
+            return;
+        }
+    }
     switch (nit) {
     case 4: hipLaunchKernelGGL((draft_kernel<DT, LG, METHOD, 4>), grid, block, 0, st, P); break;
     case 8: hipLaunchKernelGGL((draft_kernel<DT, LG, METHOD, 8>), grid, block, 0, st, P); break;
-    case 16: hipLaunchKernelGGL((draft_kernel<DT, LG, METHOD, 16>), grid, block, 0, st, P); break;
     default: hipLaunchKernelGGL((draft_kernel<DT, LG, METHOD, 0>), grid, block, 0, st, P); break;
     }
 }

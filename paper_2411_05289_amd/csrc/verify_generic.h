@@ -541,11 +541,14 @@ static void launch_verify_n(int nit, bool path, dim3 grid, dim3 block, hipStream
 {
     if (path) {
         // a tree's nodes follow one another: the row is streamed whatever its size would allow,
-        // except for the common 8-chunk case
-        if (nit == 8)
-            hipLaunchKernelGGL((verify_path_kernel<DT, LG, METHOD, 8>), grid, block, 0, st, P);
-        else
-            hipLaunchKernelGGL((verify_path_kernel<DT, LG, METHOD, 0>), grid, block, 0, st, P);
+        // except for the common 8-chunk case of SpecHub on probabilities
+        if constexpr (METHOD == kSpecHub && !LG) {
+            if (nit == 8) {
+                hipLaunchKernelGGL((verify_path_kernel<DT, LG, METHOD, 8>), grid, block, 0, st, P);
+                return;
+            }
+        }
+        hipLaunchKernelGGL((verify_path_kernel<DT, LG, METHOD, 0>), grid, block, 0, st, P);
         return;
     }
     // logit rows that fit in registers have kernels of their own; rows of probabilities in registers: any

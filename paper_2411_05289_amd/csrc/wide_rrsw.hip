@@ -12,14 +12,14 @@ template <int DT, int NIT>
 static void launch_nit(dim3 grid, hipStream_t st, const Params& P)
 {
     const dim3 block(kWG);
-    if (P.stats_in) {
-        if (P.masked)
-            hipLaunchKernelGGL((rrs_verify_resident<DT, NIT, true, true, true>), grid, block, 0, st, P);
-        else
-            hipLaunchKernelGGL((rrs_verify_resident<DT, NIT, false, true, true>), grid, block, 0, st, P);
-    } else {
+    // rows of up to 4096 chunks come here as unaligned bf16 or, by the head that they do not have, as aligned fp32
+    constexpr bool kComesMasked = DT == 1 || NIT > 4;
+    if (!P.stats_in)
         hipLaunchKernelGGL((rrs_verify_resident<DT, NIT, true, true, false>), grid, block, 0, st, P);
-    }
+    else if (kComesMasked && P.masked)
+        hipLaunchKernelGGL((rrs_verify_resident<DT, NIT, kComesMasked, true, true>), grid, block, 0, st, P);
+    else
+        hipLaunchKernelGGL((rrs_verify_resident<DT, NIT, false, true, true>), grid, block, 0, st, P);
 }
 
 void launch_rrsw(int dtype, int nit, dim3 grid, hipStream_t st, const Params& P)
