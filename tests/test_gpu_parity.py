@@ -325,6 +325,18 @@ _VARIANTS = [
     ("bf16", "probs", 70016, 0),     # ... streamed
     ("fp32", "probs", 20000, 0),     # fp32 probabilities, 16 chunks per lane
     ("fp32", "probs", 40000, 0),     # ... streamed
+    ("fp32", "probs", 5000, 0),      # 512 threads, 4 chunks per lane: fp32 probabilities
+    ("fp32", "probs", 5001, 0),      # ... masked
+    ("fp32", "logits", 5001, 0),     # ... fp32 logits, masked
+    ("bf16", "probs", 9001, 0),      # ... bf16 probabilities, masked
+    ("bf16", "logits", 9001, 0),     # ... bf16 logits, masked
+    ("fp32", "probs", 12000, 0),     # 8 chunks per lane
+    ("fp32", "probs", 12001, 0),     # ... masked
+    ("bf16", "probs", 20000, 0),     # ... bf16
+    ("bf16", "probs", 20001, 0),     # ... masked
+    ("fp32", "logits", 32768, 0),    # fp32: the longest aligned row that 1024 threads hold in 8 chunks per lane
+    ("fp32", "logits", 16384, 0),    # ... 4
+    ("fp32", "logits", 90000, 0),    # ... streamed by every method
 ]
 
 
@@ -421,9 +433,12 @@ _BY_NODES = [
     ("rrs", "bf16", 20001, 0, 2, 4, 20), ("rrs", "bf16", 20001, 3, 2, 4, 17),   # 300 and 255: 8 chunks, masked
     ("rrs", "bf16", 20000, 0, 2, 4, 2),
     ("rrs", "fp32", 12000, 0, 2, 4, 24), ("rrs", "fp32", 12001, 0, 2, 4, 24),
+    ("rrs", "fp32", 16384, 0, 2, 4, 24), ("rrs", "fp32", 5001, 0, 2, 4, 24),
+    ("spechub", "fp32", 20001, 0, 2, 2, 257), ("spechub", "bf16", 50257, 0, 2, 2, 257),   # path-only, 512 threads
     ("spechub", "fp32", 20001, 0, 2, 4, 18), ("spechub", "bf16", 50257, 0, 2, 4, 18),
     ("spechub", "fp32", 20001, 0, 2, 4, 2), ("spechub", "bf16", 65536, 0, 2, 4, 2),
     ("spechub", "bf16", 66049, 0, 2, 2, 33), ("spechub", "bf16", 90001, 1, 2, 3, 2),   # path-only, 1024 threads
+    ("spechub", "fp32", 40000, 0, 2, 2, 33),   # ... fp32
     ("rrs", "fp32", 70000, 0, 2, 3, 2), ("rrs", "fp32", 70001, 0, 2, 3, 2),     # 20 chunks per lane of 1024 threads
     ("rrs", "bf16", 70001, 0, 2, 4, 56), ("rrs", "bf16", 66048, 0, 3, 3, 99),   # 840 and 1287: streamed
     ("rrs", "fp32", 18000, 0, 2, 3, 3), ("rrs", "fp32", 20000, 0, 4, 2, 3),     # drafts on 1024 threads
@@ -469,6 +484,32 @@ _SHORT = [
     ("fp32", "probs", 1017, 0, 2, 900),     # 255 chunks with the head: 64 lanes
     ("bf16", "logits", 2, 0, 2, 40000),     # one chunk
     ("bf16", "logits", 24, 0, 6, 40),       # 63-node trees
+    ("fp32", "logits", 16, 0, 2, 40000),    # 4 lanes, also path-only
+    ("bf16", "logits", 60, 0, 2, 40000),
+    ("bf16", "probs", 16, 0, 2, 2000),      # ... whole trees per workgroup
+    ("bf16", "probs", 800, 0, 4, 500),      # 32 lanes, trees of 15
+    ("fp32", "probs", 16, 0, 2, 40000),     # 4 lanes, also path-only; walk by arrival count
+    ("bf16", "probs", 60, 0, 2, 40000),     # ... bf16
+    ("fp32", "logits", 120, 0, 2, 20000),   # 8 lanes
+    ("fp32", "logits", 120, 0, 2, 4000),    # ... whole trees per workgroup
+    ("fp32", "probs", 100, 0, 2, 20000),    # ... fp32 probabilities
+    ("fp32", "probs", 100, 0, 2, 4000),
+    ("bf16", "probs", 200, 0, 2, 20000),    # ... bf16 probabilities
+    ("bf16", "probs", 200, 0, 2, 4000),
+    ("bf16", "logits", 200, 0, 2, 20000),   # ... bf16 logits
+    ("fp32", "probs", 250, 0, 2, 10000),    # 16 lanes
+    ("fp32", "logits", 250, 0, 2, 10000),
+    ("bf16", "probs", 500, 0, 2, 10000),
+    ("bf16", "probs", 500, 0, 2, 2500),
+    ("bf16", "logits", 500, 0, 2, 2500),
+    ("bf16", "probs", 800, 0, 2, 5000),     # 32 lanes
+    ("bf16", "probs", 800, 0, 2, 1500),
+    ("bf16", "logits", 800, 0, 4, 500),     # ... trees of 15 and 7500 nodes: a launch of its own for the walk
+    ("fp32", "probs", 450, 0, 4, 500),
+    ("fp32", "probs", 450, 0, 2, 1500),
+    ("fp32", "logits", 1000, 0, 4, 60),     # 64 lanes, trees of 15
+    ("fp32", "probs", 900, 0, 4, 60),
+    ("bf16", "probs", 1900, 0, 4, 60),
 ]
 
 
