@@ -84,6 +84,16 @@ def read_traffic(kernel_key: str):
     return None
 
 
+def plausible_traffic(traffic, kernel_ms):
+    """(traffic, what it is): counters of a build whose kernels moved more than today's may say more
+    bytes than the memory can carry in the time measured now; such a figure is not reported."""
+    if traffic is None:
+        return None, None
+    if kernel_ms <= 0 or traffic / (kernel_ms * 1e-3) / 1e9 > HBM_PEAK_GBS:
+        return None, "stale: profiles/hbm_traffic.txt implies more than the HBM peak"
+    return traffic, "offline: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of this command, profiles/hbm_traffic.txt"
+
+
 def cpu_baseline(wl_cpu_rows, k, depth, temps, method_id, repeats, threads):
     """The fp64 oracle, as it stands, on a bounded sample of the same workload."""
     import numpy as np
@@ -321,8 +331,8 @@ def main():
     del dst
     tps = float(ad.float().mean().item()) + 1.0
     kernel_key = "%s_verify:%s" % (args.method, wl0.name)
-    traffic = read_traffic(kernel_key)
-    draft_traffic = read_traffic("%s_draft:%s" % (args.method, wl0.name))
+    traffic, traffic_source = plausible_traffic(read_traffic(kernel_key), kernel_ms)
+    draft_traffic, _ = plausible_traffic(read_traffic("%s_draft:%s" % (args.method, wl0.name)), draft_ms)
 
     if toy:
         headline = {"metric": "toy-experiment (p, q) pairs drafted and verified per second at V=50 (App. D)",
@@ -356,8 +366,7 @@ def main():
                      "kernel_reps": reps,
                      "event_bracket_ms": bracket_ms, "event_overhead_ms": event_overhead_ms,
                      "traffic": traffic,
-                     "traffic_source": None if traffic is None else
-                                       "offline: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of this command, profiles/hbm_traffic.txt",
+                     "traffic_source": traffic_source,
                      "hbm_measured_gbs": None if traffic is None else traffic / (kernel_ms * 1e-3) / 1e9,
                      "frac_of_bytes_moved": None if traffic is None else traffic / (kernel_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
                      "plain_copy_reference": {"gbs": plain_copy_gbs, "bytes": copy_bytes,

@@ -1,7 +1,10 @@
 """bench.py's command line and the JSON line it prints: the keys and types the driver reads.
 The GPU case runs a short bench (few steps) on the metric's workload."""
+import glob
 import json
 import os
+import re
+import shutil
 import subprocess
 import sys
 
@@ -15,6 +18,45 @@ def test_more_than_one_gpu_is_refused_with_a_message():
     r = subprocess.run([sys.executable, BENCH, "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode != 0
     assert "one gpu" in r.stderr.lower() and r.stdout.strip() == ""
+
+
+def test_counter_readings_that_the_memory_could_not_carry_are_not_reported():
+    sys.path.insert(0, ROOT)
+    import bench
+    assert bench.plausible_traffic(None, 0.03) == (None, None)
+    got, source = bench.plausible_traffic(150e6, 0.03)          # 5 TB/s
+    assert got == 150e6 and source.startswith("offline")
+    got, source = bench.plausible_traffic(239e6, 0.024)         # 10 TB/s
+    assert got is None and source.startswith("stale")
+    assert bench.plausible_traffic(239e6, 0.0)[0] is None
+
+
+def test_profiles_name_kernels_of_the_library():
+    """Every kernel that a summary under profiles/ names is one the built library holds: figures of a kernel
+    that another has replaced are figures of an older build."""
+    lib = os.path.join(ROOT, "paper_2411_05289_amd", "libmdsd.so")
+    if not os.path.exists(lib) or shutil.which("nm") is None:
+        pytest.skip("needs the built library and nm")
+    names = subprocess.run(["nm", "-C", lib], capture_output=True, text=True, check=True).stdout
+    have = {re.sub(r"^void ", "", l.split(" ", 2)[2]).split("(")[0]
+            for l in names.splitlines() if "mdsd" in l and re.match(r"[0-9a-f]+ \w ", l)}
+    seen = 0
+    for path in sorted(glob.glob(os.path.join(ROOT, "profiles", "*.txt"))):
+        for name in re.findall(r"mdsd\w*::\w+(?:<[^>]*>)?", open(path).read()):
+            if name != "mdsd::Params":
+                assert name in have, (os.path.basename(path), name)
+                seen += 1
+    assert seen > 50
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("config", ["2", "toy"])
+def test_bytes_moved_stay_below_the_memory_peak(config):
+    r = subprocess.run([sys.executable, BENCH, "--config", config, "--steps", "20", "--warmup", "5", "--no-cpu-baseline",
+                        "--no-path-only"], capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stderr[-2000:]
+    roof = json.loads(r.stdout)["roofline"]
+    assert roof["traffic_source"].startswith("offline") and 0 < roof["frac_of_bytes_moved"] < 1
 
 
 @pytest.mark.gpu
