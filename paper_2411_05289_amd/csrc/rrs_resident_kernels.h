@@ -172,7 +172,8 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
         int lane_o = threadIdx.x & 63, wave_o = wave_id();
         ExpW cpo = cp;
         asm volatile("" : "+v"(lane_o), "+s"(wave_o), "+s"(cpo.ms));
-        for_each_streamed_cached<1, kDraftChunksKept<NIT>, decltype(KEPT)::value>(lane_o, wave_o, sp, rq, ExpW::fill(), q_kept, [&](int it, int, int chunk, const uint4& dp, const uint4& dq) {
+        for_each_streamed_cached<1, kDraftChunksKept<NIT>, decltype(KEPT)::value>(
+            lane_o, wave_o, sp, rq, ExpW::fill(), q_kept, [&](int it, int, int chunk, const uint4& dp, const uint4& dq) {
             const uint32_t bits = marks[it * E / 32] >> (it * E % 32);
             const bool some = __ballot((bits & ((1u << E) - 1u)) != 0) != 0;
             float part[2];

@@ -36,8 +36,11 @@ struct ToWeight {
     }
 };
 
-// fixed-shape sum of one lane's chunk; every slab sum is built from it, so a
-// recomputed slab reproduces the stored sum bit for bit
+// fixed-shape sum of one lane's chunk; every slab sum is built from it.  A slab recomputed with
+// store_slab_sum()'s scan reproduces a sum stored by it bit for bit; sums stored several at a time
+// (for_each_sums, SlabSums) add the lanes in another order and may differ from it in their last bits, so
+// that a search inside such a slab ends, like any whose crossing is rounded away, at its last token
+// with a positive weight
 template <int E>
 __device__ __forceinline__ float chunk_sum(const float (&w)[E])
 {

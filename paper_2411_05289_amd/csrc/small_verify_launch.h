@@ -1,6 +1,6 @@
 // The generic verify kernel built for short rows: included once by a translation unit that has set
-// MDSD_WG (threads per node), MDSD_NS (the build's namespace) and MDSD_MAX_SLABS.  Every method, logits or probabilities, fp32 or bf16, full and path-only;
-// rows of up to four chunks per lane, held in registers.
+// MDSD_WG (threads per node), MDSD_NS (the build's namespace) and MDSD_MAX_SLABS.  Every method, logits
+// or probabilities, fp32 or bf16, full and path-only; rows of up to four chunks per lane, held in registers.
 #include "verify_generic.h"
 
 #include "launch_small.h"
