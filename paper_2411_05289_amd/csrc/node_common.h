@@ -248,6 +248,16 @@ __device__ __forceinline__ float lane_max(const Src& src)
     return m;
 }
 
+// the same, on packed elements where the row has them (the draft kernels' rows; see lane_max_packed())
+template <class Src>
+__device__ __forceinline__ float lane_max_of_row(const Src& src)
+{
+    if constexpr (Src::kHasPackedMax)
+        return src.lane_max_packed();
+    else
+        return lane_max(src);
+}
+
 // lowest virtual index at which this lane holds the value m (INT_MAX: nowhere)
 template <class Src>
 __device__ __forceinline__ int lane_first_index_of(const Src& src, float m)

@@ -1,0 +1,72 @@
+"""Draft calls at the edges of their kernels: how many wavefronts share a node and its draws, how a row's largest
+element is found, and where rows begin and end."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2411_05289_amd import binding as B
+from paper_2411_05289_amd import workloads as W
+from parity import DRAFT, METHODS, _np, check_case, oracle_kwargs, uniforms
+import oracle
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.mark.parametrize("method,k", [("spechub", 2), ("rrs", 2), ("rrs", 8), ("rrsw", 3), ("rrsw", 8)])
+@pytest.mark.parametrize("dtype,V", [("bf16", 2100), ("bf16", 4089), ("bf16", 4097), ("bf16", 8186), ("bf16", 16369),
+                                     ("bf16", 32737), ("bf16", 32768), ("bf16", 66000), ("fp32", 4091), ("fp32", 16380),
+                                     ("fp32", 33000)])
+def test_draws_of_every_wave(method, k, dtype, V):
+    """Two, four, eight and sixteen wavefronts per node, up to eight draws: more draws than wavefronts, as many, fewer;
+    rows in registers and streamed, the last slab full and nearly empty.  Tokens, hub and flags are the oracle's
+    except where a uniform lies within 1e-6 of a boundary; the records to fp32 rounding."""
+    wl = W.config(3 if dtype == "bf16" else 2, device=DEV, B=3, V=V, k=k, depth=2, seed=V + k)
+    pb = B.Problem.from_workload(wl).with_draft_stats()
+    u_d, _ = uniforms(wl, V)
+    g = DRAFT[method](pb, u_d)
+    rows = W.rows_as_numpy(wl.draft)
+    o = oracle.batch_draft(METHODS[method], rows, _np(u_d), temp_draft=wl.temp_draft, nthreads=8, **oracle_kwargs(wl))
+    sure = o["margin"][:, 0] > 1e-6
+    assert sure.any()
+    assert (_np(g["tokens"])[sure] == o["tokens"][sure]).all()
+    assert (_np(g["flags"]) == o["flags"]).all()
+    x = wl.draft[:, 0].double()
+    w = torch.exp((x - x.amax(-1, keepdim=True)) / wl.temp_draft)
+    mass = w.sum(-1)
+    if method == "spechub":
+        assert (_np(g["hub"]) == o["hub"]).all()
+        mass = mass - 1.0        # the hub's weight is 1
+    rec = pb.draft_stats[:, 0]
+    assert torch.equal(rec[:, 0].double(), x.amax(-1))
+    # a sum of V positive terms, each within 1e-6 (exponent and exp), added in trees and short chains
+    assert ((rec[:, 1].double() - mass).abs() <= 2e-6 * mass).all()
+
+
+@pytest.mark.parametrize("V,off", [(4104, 0), (4101, 3), (9001, 5), (32760, 0), (32741, 1)])
+def test_largest_element_of_bf16_rows(V, off):
+    """Rows whose largest element is positive, rows of negative numbers only (log-probabilities), rows with -0 or with
+    most tokens at -inf, and rows with NaNs of either sign among their numbers: the record's largest element and
+    the hub (its lowest index) are those of the numbers."""
+    gen = torch.Generator(device=DEV).manual_seed(V)
+    N = 3
+    buf = torch.zeros(6 * N * V + 16, dtype=torch.bfloat16, device=DEV)
+    rows = buf[off:off + 6 * N * V].view(6, N, V)
+    x = torch.randn((6, N, V), generator=gen, device=DEV) * 3
+    x[1] -= 100.0
+    x[2] = torch.where(x[2] > -3, -0.0, x[2] - 5)          # all negative or -0
+    x[3] = torch.where(torch.rand((N, V), generator=gen, device=DEV) < 0.999, -torch.inf, x[3] - 50)
+    x[3, :, V - 1] = -60.0
+    nan = torch.rand((2, N, V), generator=gen, device=DEV) < 0.01
+    x[4][nan[0]] = torch.nan
+    x[5] -= 100.0
+    rows.copy_(x)
+    bits = rows[5].view(torch.int16)
+    bits[nan[1]] = -2                                       # 0xfffe: a negative NaN
+    pb = B.Problem(None, rows, B.LOGITS, 2, 2).with_draft_stats()
+    g = B.spechub_draft(pb, torch.rand((6, N, 2), generator=gen, device=DEV))
+    numbers = torch.nan_to_num(rows.float(), nan=-torch.inf)
+    want = numbers.amax(-1)
+    assert torch.equal(pb.draft_stats[:, 0, 0], want[:, 0])
+    first = torch.where(numbers == want[..., None], torch.arange(V, device=DEV), V).amin(-1)
+    assert torch.equal(g["hub"][:, 0].long(), first[:, 0])
