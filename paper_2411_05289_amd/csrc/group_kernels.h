@@ -950,6 +950,37 @@ __global__ __launch_bounds__(kGroupMaxThreads, kGroupWavesPerSimd) void group_ve
     }
 }
 
+// Wavefront n of a workgroup takes node n of 64 / G trees; the one that comes last walks them (see wave_per_node()).
+// Bound by instruction issue (toy workload: 77 % of the kernel's time, 490 instructions per wavefront of 16 nodes).
+template <int DT, bool LOGITS, int METHOD, int G>
+__global__ __launch_bounds__(kGroupMaxThreads, kGroupWavesPerSimd) void group_tree_kernel(const Params P)
+{
+    constexpr int T = 64 / G;
+    __shared__ int oc[kGroupMaxThreads / 64][T], tk[kGroupMaxThreads / 64][T], arrived;
+    if (threadIdx.x == 0) arrived = 0;
+    __syncthreads();
+    const int lane = threadIdx.x & 63, l = lane & (G - 1), tree = lane / G;
+    NodeId id;
+    id.n = uniform((int)(threadIdx.x / 64));
+    id.b = (int)blockIdx.x * T + tree;
+    id.c0 = group_first_child(P, id.n);
+    id.row = (int64_t)id.b * P.N + id.n;
+    if (id.b < P.B) {
+        const NodeOut o = group_verify_node<DT, LOGITS, METHOD, G>(P, id, l);
+        if (l == 0) {
+            write_group_outputs(P, id, o);
+            oc[id.n][tree] = o.outcome;
+            tk[id.n][tree] = o.token;
+        }
+    }
+    int before = 0;
+    if (lane == 0) before = __hip_atomic_fetch_add(&arrived, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (uniform(before) != P.N - 1) return;
+    const int b = (int)blockIdx.x * T + lane;
+    if (lane >= T || b >= P.B) return;
+    lane_walk(P, b, true, [&](int n) { return oc[n][lane]; }, [&](int n) { return tk[n][lane]; });
+}
+
 // path-only: a group per tree, node after accepted node
 template <int DT, bool LOGITS, int METHOD, int G>
 __global__ __launch_bounds__(kGroupThreads) void group_path_kernel(const Params P)

@@ -31,6 +31,23 @@ inline bool group_walks_inside(int lanes, int N, int64_t nodes)
     if (threads > kGroupMaxThreads) return false;
     return nodes <= (lanes >= 32 && threads > kGroupThreads ? kGroupTreesMaxNodes32Lanes : kGroupTreesMaxNodes);
 }
+// Where the call walks its trees: wavefront n of a workgroup takes node n of 64 / lanes trees, and the one that comes last
+// walks them.  A wavefront's nodes are of one kind, nothing is divided to find them, none waits for the others, and a tree's
+// rows, which share cache lines where they are short, are read by the same CU (toy workload: 151 -> 108 MB, 29 us with the
+// walk's launch -> 26).  Its price is that a workgroup starts only where all its wavefronts find a place.  Against
+// workgroups that hold whole trees of mixed wavefronts (group_walks_inside()) it wins with k = 2 at every size (7-node
+// trees, 14000 nodes: 400 bf16 elements 12.3 -> 9.6 us, 900 24.2 -> 20.3; 3-node trees, 6000 nodes of 16 fp32 6.2 -> 4.8); k = 4,
+// whose nodes with children outlast their leaves, up to 3072 wavefronts (rows of 60 bf16 6000 nodes 13.9 -> 12.2; of 400,
+// 3500 wavefronts, 18.6 -> 20.5).  Against nodes in any order and the walk's launch up to 3072 wavefronts too (7-node trees of
+// 50 fp32, 40000 nodes 10.0 -> 7.6; 100000 13.8 -> 14.9; of 400 bf16, 20000 nodes 14.7 -> 16.2), and 3-node trees of rows in
+// four lanes always (50 fp32, 100000 nodes 14.5 -> 12.3; eight lanes, 200 bf16 25.2 -> 26.4).
+constexpr int64_t kWavePerNodeMaxWaves = 3072;
+inline bool wave_per_node(int lanes, int N, int k, int64_t nodes)
+{
+    if (lanes == 64 || N < 2 || N > kGroupMaxThreads / 64) return false;
+    if (lanes * nodes <= 64 * kWavePerNodeMaxWaves || (lanes == 4 && N <= 3)) return true;
+    return k == 2 && group_walks_inside(lanes, N, nodes);
+}
 // walk_nodes: nodes per tree where the launch is to walk the trees, else 1: half the lanes are taken where that
 // lets a workgroup hold a tree (rows of 60 bf16 elements, 2000 nodes in trees of 15: 32 lanes 11.9 us, 64 lanes with
 // the walk by arrival count 14.9), but not for rows of more than 96 chunks (1000 elements, 1050 nodes: 9.5 us with

@@ -1,0 +1,41 @@
+"""Verify calls at the edges of their routes: rows of probabilities that are streamed with several chunks asked for
+ahead, small trees with a wavefront per node, trees given by a table, and softmax shifts so large that they do not take
+every whole number."""
+import pytest
+import torch
+
+from paper_2411_05289_amd import binding as B
+from paper_2411_05289_amd import workloads as W
+from parity import DRAFT, VERIFY, check_case
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+ALL = ["spechub", "rrs", "rrsw"]
+
+
+def _workload(Bn, N, V, k, depth, dtype, kind, off=0, temps=(0.9, 1.2), first_child=None, seed=5):
+    td = torch.float32 if dtype == "fp32" else torch.bfloat16
+    t, d = W.llm_like_logits(Bn, N, V, logit_std=2.0, draft_noise_std=1.0, dtype=torch.float32, seed=seed, device=DEV)
+    if kind == "probs":
+        t, d = torch.softmax(t.double(), -1), torch.softmax(d.double(), -1)
+        temps = (1.0, 1.0)
+    rows = []
+    for x in (t, d):
+        buf = torch.zeros((Bn * N * V + off,), dtype=td, device=DEV)
+        view = buf[off:].view(Bn, N, V)
+        view.copy_(x)
+        rows.append(view)
+    if first_child is not None:
+        first_child = torch.tensor(first_child, dtype=torch.int32, device=DEV)
+    return W.Workload("routes", Bn, N, V, k, depth, dtype, kind, temps[0], temps[1], rows[0], rows[1],
+                      first_child=first_child)
+
+
+@pytest.mark.parametrize("method,k", [("spechub", 2), ("rrs", 2), ("rrsw", 3), ("rrsw", 4), ("rrs", 7)])
+@pytest.mark.parametrize("V,dtype,Bn", [(16, "fp32", 1), (50, "fp32", 17), (60, "bf16", 700), (200, "bf16", 401),
+                                        (500, "bf16", 203), (450, "fp32", 101), (50, "fp32", 30001)])
+def test_a_wavefront_per_node(method, k, V, dtype, Bn):
+    """Trees of 3, 4, 5, 7 and 8 nodes; the last workgroup short of trees; large batches of small rows."""
+    for depth in (2, 3) if k == 2 and Bn < 9999 else (2,):
+        wl = _workload(Bn, W.tree_nodes(k, depth), V, k, depth, dtype, "logits")
+        check_case(method, wl, seed=V, seqs=sorted({0, Bn // 2, Bn - 1}), full_outputs=Bn < 9999)
