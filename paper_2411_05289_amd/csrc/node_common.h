@@ -74,8 +74,10 @@ __device__ __forceinline__ NodeId node_of_item(const Params& P, int w)
             id.c0 = -1;
         }
     } else {
-        id.b = w / P.N;
-        id.n = w - id.b * P.N;
+        // node by node over the trees: children have higher numbers than their parents, so nodes with
+        // children come early here too
+        id.n = w / P.B;
+        id.b = w - id.n * P.B;
         id.c0 = P.first_child[id.n];
         // an entry that does not point past its own node, or leaves no room for k children, is
         // treated as a leaf (the tree walk applies the same rule, so it always ends)

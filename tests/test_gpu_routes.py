@@ -39,3 +39,13 @@ def test_a_wavefront_per_node(method, k, V, dtype, Bn):
     for depth in (2, 3) if k == 2 and Bn < 9999 else (2,):
         wl = _workload(Bn, W.tree_nodes(k, depth), V, k, depth, dtype, "logits")
         check_case(method, wl, seed=V, seqs=sorted({0, Bn // 2, Bn - 1}), full_outputs=Bn < 9999)
+
+
+@pytest.mark.parametrize("method", ALL)
+@pytest.mark.parametrize("V,dtype,Bn", [(50, "fp32", 33), (600, "bf16", 9), (3000, "bf16", 5), (9001, "bf16", 5),
+                                        (70001, "bf16", 3)])
+def test_tables_node_by_node(method, V, dtype, Bn):
+    """Trees of seven nodes (a wavefront each where the rows are short) and nine."""
+    for fc in ([1, 3, 5, -1, -1, -1, -1], [1, 3, -1, 5, -1, 7, -1, -1, -1]):
+        wl = _workload(Bn, len(fc), V, 2, 5, dtype, "logits", first_child=fc)
+        check_case(method, wl, seed=V, full_outputs=V < 9999)
