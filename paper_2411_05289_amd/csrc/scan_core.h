@@ -269,11 +269,26 @@ struct RowSrc<DT, 0, ENDS> {
     {
         // each chunk is asked for AHEAD steps before its use (the steps past the end read the
         // row's last chunk again and drop it)
-        static_assert(AHEAD == 1 || AHEAD == 2, "one or two steps ahead");
         const int lane = threadIdx.x & 63, wave = wave_id();
         uint4 c[AHEAD];
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) c[i] = fetch_chunk(r, (wave + i * kWaves) * 64 + lane);
+        if constexpr (AHEAD > 2) {
+            // so many steps at once that each keeps its register
+            for (int s0 = wave; s0 < r.nslab; s0 += AHEAD * kWaves) {
+#pragma unroll
+                for (int j = 0; j < AHEAD; ++j) {
+                    const int s = s0 + j * kWaves;
+                    if (j > 0 && s >= r.nslab) break;
+                    const uint4 cur = c[j];
+                    c[j] = fetch_chunk(r, (s + AHEAD * kWaves) * 64 + lane);
+                    float a[E];
+                    finish_chunk<DT>(r, s * 64 + lane, cur, fill, a);
+                    body(s, s * 64 + lane, a);
+                }
+            }
+            return;
+        }
         for (int s = wave; s < r.nslab; s += kWaves) {
             const uint4 nxt = fetch_chunk(r, (s + AHEAD * kWaves) * 64 + lane);
             float a[E];
@@ -303,30 +318,33 @@ struct RowSrc<DT, 0, ENDS> {
     template <int AHEAD = 1, class Body>
     __device__ __forceinline__ void for_each_sums(float* slab_w, Body body) const
     {
-        static_assert(AHEAD == 1 || AHEAD == 2, "one or two steps ahead");
+        static_assert(AHEAD == 1 || AHEAD == 2 || AHEAD == 4 || AHEAD == 8, "a step's register stays the same");
+        constexpr int kGroups = AHEAD <= 4 ? 1 : 2;
         const int lane = threadIdx.x & 63, wave = wave_id();
         uint4 c[AHEAD];
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) c[i] = fetch_chunk(r, (wave + i * kWaves) * 64 + lane);
-        for (int s0 = wave; s0 < r.nslab; s0 += 4 * kWaves) {
-            float sums[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int s0 = wave; s0 < r.nslab; s0 += kGroups * 4 * kWaves) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int s = s0 + j * kWaves;
-                if (j > 0 && s >= r.nslab) break;
-                const uint4 nxt = fetch_chunk(r, (s + AHEAD * kWaves) * 64 + lane);
-                uint4 cur = c[0];
-                end_of_row(cur, s, lane);
-                float a[E];
-                unpack<DT>(cur, a);
-                sums[j] = body(s, s * 64 + lane, a);
+            for (int g = 0; g < kGroups; ++g) {
+                const int s1 = s0 + g * 4 * kWaves;
+                if (g > 0 && s1 >= r.nslab) break;
+                float sums[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int i = 0; i + 1 < AHEAD; ++i) c[i] = c[i + 1];
-                c[AHEAD - 1] = nxt;
+                for (int j = 0; j < 4; ++j) {
+                    const int s = s1 + j * kWaves;
+                    if (j > 0 && s >= r.nslab) break;
+                    uint4 cur = c[(4 * g + j) % AHEAD];
+                    c[(4 * g + j) % AHEAD] = fetch_chunk(r, (s + AHEAD * kWaves) * 64 + lane);
+                    end_of_row(cur, s, lane);
+                    float a[E];
+                    unpack<DT>(cur, a);
+                    sums[j] = body(s, s * 64 + lane, a);
+                }
+                const float t = wave_sums4(sums);
+                const int s = s1 + lane * kWaves;
+                if (lane < 4 && s < r.nslab) slab_w[s] = t;
             }
-            const float t = wave_sums4(sums);
-            const int s = s0 + lane * kWaves;
-            if (lane < 4 && s < r.nslab) slab_w[s] = t;
         }
     }
 };
@@ -345,7 +363,6 @@ template <int AHEAD = 1, int DT, int NIT, int ENDS, class Body>
 __device__ __forceinline__ void for_each2(const RowSrc<DT, NIT, ENDS>& sa, const RowSrc<DT, NIT, ENDS>& sb,
                                           Body body)
 {
-    static_assert(AHEAD == 1 || AHEAD == 2, "one or two steps ahead");
     constexpr int E = Elem<DT>::kPerChunk;
     const int lane = threadIdx.x & 63, wave = wave_id();
     if constexpr (NIT == 0) {
@@ -354,6 +371,23 @@ __device__ __forceinline__ void for_each2(const RowSrc<DT, NIT, ENDS>& sa, const
         for (int i = 0; i < AHEAD; ++i) {
             ca[i] = fetch_chunk(sa.r, (wave + i * kWaves) * 64 + lane);
             cb[i] = fetch_chunk(sb.r, (wave + i * kWaves) * 64 + lane);
+        }
+        if constexpr (AHEAD > 2) {
+            for (int s0 = wave; s0 < sa.r.nslab; s0 += AHEAD * kWaves) {
+#pragma unroll
+                for (int j = 0; j < AHEAD; ++j) {
+                    const int s = s0 + j * kWaves;
+                    if (j > 0 && s >= sa.r.nslab) break;
+                    const uint4 na = ca[j], nb = cb[j];
+                    ca[j] = fetch_chunk(sa.r, (s + AHEAD * kWaves) * 64 + lane);
+                    cb[j] = fetch_chunk(sb.r, (s + AHEAD * kWaves) * 64 + lane);
+                    float a[E], b[E];
+                    finish_chunk<DT>(sa.r, s * 64 + lane, na, sa.fill, a);
+                    finish_chunk<DT>(sb.r, s * 64 + lane, nb, sb.fill, b);
+                    body(s, s * 64 + lane, a, b);
+                }
+            }
+            return;
         }
         for (int s = wave; s < sa.r.nslab; s += kWaves) {
             const uint4 na = fetch_chunk(sa.r, (s + AHEAD * kWaves) * 64 + lane);

@@ -28,9 +28,16 @@ __device__ __forceinline__ float in_vgpr(float x)
 template <int DT, bool LOGITS, int METHOD, int NIT, bool PATH>
 constexpr bool kEndsPerElement =
     kWG > 64 && (PATH                 ? METHOD != kSpecHub && (DT == 0 || METHOD == kRRSw)
-                 : METHOD == kSpecHub ? kWG >= 256 && NIT < 16 && DT == 0 && !LOGITS
+                 : METHOD == kSpecHub ? kWG == 256 && DT == 0 && !LOGITS
                  : DT == 0            ? METHOD == kRRSw || !LOGITS
                                       : METHOD == kRRS && !LOGITS && kWG == 512);
+
+// Streamed rows of probabilities are bound by the loads in flight: a chunk is a dozen instructions of work, and SpecHub's
+// passes ask for as many chunks ahead as the registers of three nodes per CU take, of one row and of a pair of rows
+// (logits, whose chunks are a hundred instructions, gain nothing from more than one or two).  The RRS methods' rounds
+// lose by it (two rows four ahead, 480 nodes with records of 32000 fp32 elements 23.4 -> 24.2 us, RRSw 27.3 -> 29.3;
+// bf16 20001, 4000 nodes 47.6 -> 54.1; so do their leaves), and so they ask ahead in the sweep for the draft mass only.
+constexpr int kProbsAhead = 8, kProbsPairAhead = 4;
 
 template <int DT, bool LOGITS, int METHOD, int NIT, bool PATH>
 __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id, Shared& sh, int& phase)
@@ -43,6 +50,7 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
     const bool need_full = (P.resid_mass != nullptr) || (P.resid_prob != nullptr);
     float* rprob = P.resid_prob ? P.resid_prob + id.row * (int64_t)P.V : nullptr;
 
+    constexpr bool kProbsStreamed = !LOGITS && NIT == 0;
     const RowView rp = make_row<DT>(P.target, P.ld_t, id.row, P.V);
     Src sp;
     int outcome = MDSD_NONE, token = -1, flags = 0;
@@ -67,11 +75,15 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
                 cp.s = (METHOD == kSpecHub ? in_vgpr(P.scale_t) : P.scale_t);
                 cp.ms = mm[0] * cp.s;
             }
-            pass_weights_to_slabs<CV>(sp, cp, nullptr, 0, sh.slab_w);
+            if constexpr (kProbsStreamed && METHOD == kSpecHub)
+                sp.template for_each_sums<kProbsAhead>(sh.slab_w, [](int, int, const float(&a)[E]) { return chunk_sum<E>(a); });
+            else
+                pass_weights_to_slabs<CV>(sp, cp, nullptr, 0, sh.slab_w);
             node_barrier();
         }
-        float W;
-        const int v = draw_from_row<DT, CV>(rp, cp, nullptr, 0, sh.slab_w, ur[k], W);
+        float W = 0.f;
+        int v = -1;
+        if (PATH || rprob || wave_id() == 0) v = draw_from_row<DT, CV>(rp, cp, nullptr, 0, sh.slab_w, ur[k], W);
         token = v < 0 ? -1 : v - rp.head;
         if (v < 0) flags |= MDSD_FLAG_ZERO_RESIDUAL;
         rmass = LOGITS ? 1.f : W;
@@ -96,6 +108,17 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
         CV cp{0.f, 0.f}, cq{0.f, 0.f};
 
         if constexpr (METHOD == kSpecHub) {
+            const int x1 = xt[0], x2 = xt[1];
+            const bool tokens_ok = x1 >= 0 && x1 < P.V && x2 >= 0 && x2 < P.V;
+            // probabilities at the pair: asked for ahead of the rows, at indices brought into them
+            float p_x1 = 0.f, q_x1 = 0.f, p_x2 = 0.f, q_x2 = 0.f;
+            if constexpr (kProbsStreamed) {
+                const int c1 = min(max(x1, 0), P.V - 1), c2 = min(max(x2, 0), P.V - 1);
+                p_x1 = load_elem<DT>(rp, c1);
+                q_x1 = load_elem<DT>(rq, c1);
+                p_x2 = load_elem<DT>(rp, c2);
+                q_x2 = load_elem<DT>(rq, c2);
+            }
             // ---- hub (argmax of the stored draft row), softmax maxima, normalisers: Zp (logits
             // only) and the draft mass outside the hub, Zq' = sum_{y != a} eq.  With the draft
             // call's record of the row at hand, the draft row is not read for any of them.
@@ -121,6 +144,24 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
                 }
                 mm[1] = st.max_stored;
                 a_virt = rq.head + (st.hub < 0 ? 0 : st.hub);
+            } else if constexpr (kProbsStreamed) {
+                // one sweep over the draft row; the target row is not needed for the first tests
+                need_q();
+                float mq_lane = -__builtin_inff();
+                int mq_chunk = 0;
+                sq.template for_each_sums<kProbsAhead>(sh.slab_w, [&](int, int chunk, const float(&a)[E]) {
+                    float cm = a[0];
+#pragma unroll
+                    for (int e = 1; e < E; ++e) cm = fmaxf(cm, a[e]);
+                    mq_chunk = cm > mq_lane ? chunk : mq_chunk;
+                    mq_lane = fmaxf(mq_lane, cm);
+                    return chunk_sum<E>(a);
+                });
+                float m1[1] = {mq_lane};
+                block_max<kWaves, 1>(m1, sh.red, phase);  // barrier: slab sums visible
+                mm[0] = 0.f;
+                mm[1] = m1[0];
+                a_virt = block_argmax_at<DT>(rq, mq_lane, mm[1], mq_chunk, sh, phase);
             } else {
                 need_q();
                 const float mq_lane = lane_max(sq);
@@ -150,6 +191,13 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
                     z[0] = z1[0];
                 }
                 z[1] = st.rest_mass;
+            } else if constexpr (kProbsStreamed) {
+                // the mass outside the hub: its slab's sum formed again without it
+                float w[E];
+                chunk_weights<DT, CV>(rq, cq, &a_virt, 1, a_slab, w);
+                const float without = wave_sum(chunk_sum<E>(w));
+                z[1] = slab_total(rq.nslab, [&](int i) { return i == a_slab ? without : sh.slab_w[i]; });
+                node_barrier();  // every wave has read the slab sums
             } else {
                 for_each2<2>(sp, sq, [&](int s, int chunk, const float(&pa_)[E], const float(&qa_)[E]) {
                     float wp[E], wq[E];
@@ -174,14 +222,13 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
             const float pa = ea_p * h.iZp;
             const float qa = ea_q * h.iZq;
 
-            const int x1 = xt[0], x2 = xt[1];
             bool decided = false, degenerate = false;
             int hub_slot = -1;  // slot of the hub token in the pair
             if (have_stats && st.hub < 0) {  // no usable record for this node
                 flags |= MDSD_FLAG_BAD_PAIR;
                 outcome = MDSD_BAD_PAIR;
                 decided = true;
-            } else if (x1 < 0 || x1 >= P.V || x2 < 0 || x2 >= P.V) {
+            } else if (!tokens_ok) {
                 flags |= MDSD_FLAG_BAD_TOKEN;
                 outcome = MDSD_BAD_TOKEN;
                 decided = true;
@@ -199,8 +246,8 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
                 }
             } else if (x2 == a && x1 != a) {
                 hub_slot = 1;
-                const float px = cp(load_elem<DT>(rp, x1)) * h.iZp;
-                const float qx = cq(load_elem<DT>(rq, x1)) * h.iZq;
+                const float px = cp(kProbsStreamed ? p_x1 : load_elem<DT>(rp, x1)) * h.iZp;
+                const float qx = cq(kProbsStreamed ? q_x1 : load_elem<DT>(rq, x1)) * h.iZq;
                 if (ur[0] * qx < px) {  // pair (x, a): min(p(x)/Q(x,a), 1)
                     outcome = 0;
                     token = x1;
@@ -208,8 +255,8 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
                 }
             } else if (x1 == a && x2 != a) {
                 hub_slot = 0;
-                const float px = cp(load_elem<DT>(rp, x2)) * h.iZp;
-                const float qx = cq(load_elem<DT>(rq, x2)) * h.iZq;
+                const float px = cp(kProbsStreamed ? p_x2 : load_elem<DT>(rp, x2)) * h.iZp;
+                const float qx = cq(kProbsStreamed ? q_x2 : load_elem<DT>(rq, x2)) * h.iZq;
                 if (ur[0] * (h.c * qx) < fmaxf(px - qx, 0.f)) {  // pair (a, x): min(p'(x)/Q(a,x), 1)
                     outcome = 1;
                     token = x2;
@@ -246,7 +293,7 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
                     // ---- residual sums: S_xa = sum Q'(.,a), S_ax = sum Q'(a,.), slab sums of p''
                     float sacc[2] = {0.f, 0.f};
                     need_q();
-                    for_each2<2>(sp, sq, [&](int s, int chunk, const float(&pa_)[E], const float(&qa_)[E]) {
+                    for_each2<(LOGITS ? 2 : kProbsPairAhead)>(sp, sq, [&](int s, int chunk, const float(&pa_)[E], const float(&qa_)[E]) {
                         float ep[E], eq[E], t_xa[E], t_ax[E], w[E];
 #pragma unroll
                         for (int e = 0; e < E; ++e) {
@@ -289,8 +336,9 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
                     rmass = W;
                     bool wrote_prob = false;
                     if (!decided) {
-                        int v = icdf_slabs<E>(rp.nslab, ur[2], W, sv, cw);
-                        if (v < 0) {
+                        int v = -1;
+                        if (W > 0.f && (PATH || wave_id() == 0)) v = icdf_slabs<E>(rp.nslab, ur[2], W, sv, cw);
+                        if (!(W > 0.f)) {
                             // no residual mass: fall back to p itself
                             flags |= MDSD_FLAG_ZERO_RESIDUAL;
                             node_barrier();
@@ -378,6 +426,21 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
                         z[0] = z1[0];
                     }
                     z[1] = st.rest_mass;
+                } else if constexpr (kProbsStreamed) {
+                    // the draft row alone (4000 nodes of 32000 fp32 elements: rrs_verify 180 -> 141 us; 480 nodes 33 -> 29)
+                    need_q();
+                    float z1[1] = {0.f};
+                    sq.template for_each<kProbsAhead>([&](int s, int chunk, const float(&qa_)[E]) {
+                        float wq[E];
+#pragma unroll
+                        for (int e = 0; e < E; ++e) wq[e] = qa_[e];
+                        if constexpr (WO) {
+                            if (slab_has_excluded<E>(s, xv, k)) zero_excluded<E>(wq, chunk, xv, k);
+                        }
+                        z1[0] += chunk_sum<E>(wq);
+                    });
+                    block_sum<kWaves, 1>(z1, sh.red, phase);
+                    z[1] = z1[0];
                 } else {
                     need_q();
                     for_each2(sp, sq, [&](int s, int chunk, const float(&pa_)[E], const float(&qa_)[E]) {
@@ -505,7 +568,8 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
                     // (rows of probabilities are used as given and need not sum to 1)
                     rmass = n_rej == 0 ? 1.f : W;
                     if (!decided) {
-                        const int v = icdf_slabs<E>(rp.nslab, ur[k], W, sv, cw);
+                        int v = -1;
+                        if (PATH || wave_id() == 0) v = icdf_slabs<E>(rp.nslab, ur[k], W, sv, cw);
                         token = v < 0 ? -1 : v - rp.head;
                         if (v < 0) flags |= MDSD_FLAG_ZERO_RESIDUAL;
                     }
@@ -554,17 +618,16 @@ static void launch_verify_n(int nit, bool path, dim3 grid, dim3 block, hipStream
     // logit rows that fit in registers have kernels of their own; rows of probabilities in registers: any
     // size for SpecHub, the smallest for the RRS methods (whose rounds need the registers)
     if constexpr (!LG) {
-        if (nit == 4) {
-            hipLaunchKernelGGL((verify_kernel<DT, LG, METHOD, 4>), grid, block, 0, st, P);
-            return;
-        }
-        if constexpr (METHOD == kSpecHub) {
-            if (nit == 8) {
-                hipLaunchKernelGGL((verify_kernel<DT, LG, METHOD, 8>), grid, block, 0, st, P);
-                return;
-            }
-            if (nit == 16) {
-                hipLaunchKernelGGL((verify_kernel<DT, LG, METHOD, 16>), grid, block, 0, st, P);
+        // SpecHub, 512 threads per node: streamed.  An internal node reads its draft row once, in one sweep, and both
+        // rows again only where the first tests leave it undecided, and three nodes share a CU instead of the one or two
+        // whose rows its registers hold (registers -> streamed, 15-node trees, without records and with: fp32 rows of
+        // 32000, 480 nodes 25.7 -> 21.4 us, 20.2 -> 14.9; 4000 nodes 168 -> 118, 126 -> 92; bf16 20000, 480 nodes 14.5 -> 13.1,
+        // 4000 60 -> 57; fp32 8300 44 -> 43, 33 -> 28).  bf16 rows of four chunks per lane only in small batches (9000
+        // elements, 480 nodes 10.9 -> 10.1, 1500 15.0 -> 17.2).
+        constexpr bool kStreams = METHOD == kSpecHub && kWG == 512;
+        if constexpr (!kStreams || DT == 1) {
+            if (nit == 4 && !(kStreams && (int64_t)P.B * P.N <= 768)) {
+                hipLaunchKernelGGL((verify_kernel<DT, LG, METHOD, 4>), grid, block, 0, st, P);
                 return;
             }
         }

@@ -31,6 +31,23 @@ def _workload(Bn, N, V, k, depth, dtype, kind, off=0, temps=(0.9, 1.2), first_ch
                       first_child=first_child)
 
 
+@pytest.mark.parametrize("method", ALL)
+@pytest.mark.parametrize("dtype,V,off,Bn", [
+    ("fp32", 4097, 0, 3),       # the shortest rows of eight wavefronts, most of which have one slab or two
+    ("fp32", 16384, 0, 3),      # eight slabs per wavefront, the last one full
+    ("fp32", 16385, 0, 3),      # ... and one slab of one chunk more
+    ("fp32", 18433, 3, 3),      # ... and one each, rows that begin inside a chunk
+    ("fp32", 50001, 1, 3),
+    ("bf16", 9001, 5, 3),
+    ("bf16", 9001, 5, 260),     # in registers: more than 768 nodes
+    ("bf16", 32768, 0, 3),
+    ("bf16", 33281, 7, 3),
+])
+def test_streamed_probabilities(method, dtype, V, off, Bn):
+    wl = _workload(Bn, 3, V, 2, 2, dtype, "probs", off)
+    check_case(method, wl, seed=V, seqs=None if Bn < 9 else [0, 1, Bn - 1], full_outputs=Bn < 9)
+
+
 @pytest.mark.parametrize("method,k", [("spechub", 2), ("rrs", 2), ("rrsw", 3), ("rrsw", 4), ("rrs", 7)])
 @pytest.mark.parametrize("V,dtype,Bn", [(16, "fp32", 1), (50, "fp32", 17), (60, "bf16", 700), (200, "bf16", 401),
                                         (500, "bf16", 203), (450, "fp32", 101), (50, "fp32", 30001)])
