@@ -404,9 +404,24 @@ __device__ __forceinline__ void spechub_terms(float ep, float eq, const HubScal&
     w = clamp01(fmaf(-h.c, Qn, pr));            // p''(y)  = max(p' - c Q, 0)
 }
 
-template <int DT, class CV>
+// The same with target weights that are probabilities but for a factor g in (1, 2] (normalise_shift()): everything in
+// units of g, Q = kappa eq, two multiplications less per element.
+struct HubUnits {
+    float kappa, c_kappa;
+};
+
+__device__ __forceinline__ void spechub_terms(float ep, float eq, const HubUnits& h, float& q_xa_res, float& q_ax_res,
+                                              float& w)
+{
+    q_xa_res = clamp01(fmaf(h.kappa, eq, -ep));
+    const float pr = clamp01(fmaf(-h.kappa, eq, ep));
+    q_ax_res = clamp01(fmaf(h.c_kappa, eq, -pr));
+    w = clamp01(fmaf(-h.c_kappa, eq, pr));
+}
+
+template <int DT, class CV, class Hub>
 __device__ __forceinline__ void spechub_chunk_w(const RowView& rp, const RowView& rq, CV cp, CV cq,
-                                                const HubScal& h, int a_virt, int s,
+                                                const Hub& h, int a_virt, int s,
                                                 float (&w)[Elem<DT>::kPerChunk])
 {
     constexpr int E = Elem<DT>::kPerChunk;
@@ -427,6 +442,12 @@ __device__ __forceinline__ void spechub_chunk_w(const RowView& rp, const RowView
 __device__ __forceinline__ float rrs_term(float ep, float eq, float iZp, float c_iZq)
 {
     return fmaxf(fmaf(-c_iZq, eq, ep * iZp), 0.f);
+}
+
+// the same in units of target weights that are at most 1 (normalise_shift()): two instructions less per element
+__device__ __forceinline__ float rrs_term(float ep, float eq, float c_kappa)
+{
+    return clamp01(fmaf(-c_kappa, eq, ep));
 }
 
 template <int DT, class CV>
@@ -496,14 +517,27 @@ __device__ __forceinline__ int draw_resident(int nslab, float u, float W, SlabVa
 // are combined: M = max r_w, Z = sum Z_w f_w with f_w = 2^((r_w - M) s) <= 1.  The factors are
 // formed from the rounded products r_w s themselves (the largest of them is the shift `ms` that
 // later passes use), so that a wave's weights times its factor are the weights those passes
-// compute, not merely close to them.  A wave far below the maximum contributes its true,
+// compute, not merely close to them: the references are rounded down to whole numbers, which makes every
+// factor a power of two.  A wave far below the maximum contributes its true,
 // negligible share.  With SLABS the slab sums left in
 // LDS are in their wave's own units: slab i counts f_(i mod kWaves) times its stored value, and
 // f_lane is that factor for the slabs this lane reads in slab_total() and icdf_find_slab()
 // (slab = a multiple of 64 + lane).
 struct RowNorm {
-    float ms, Z, f_lane;  // ms = M s, the shift of 2^(l s - ms)
+    float ms, Z, f_lane;  // ms = M s rounded down, the shift of 2^(l s - ms)
 };
+
+// Moves the shift `ms` (a whole number) of weights whose sum is Z so that they sum to less than 1, and returns that
+// sum: weights that need no factor to be compared with another row's and clamped to [0, 1].  Everything moves by a power
+// of two, without rounding.  Shifts from 2^24 on, which do not take every whole number, move by as much more as
+// their next steps are apart.
+__device__ __forceinline__ float normalise_shift(float& ms, float Z)
+{
+    const float a = fabsf(ms), n = (float)__builtin_amdgcn_frexp_expf(Z) + (a >= 0x1p24f ? a * 0x1p-23f : 0.f);
+    const float moved = ms + n, by = moved - ms;
+    ms = moved;
+    return __builtin_amdgcn_ldexpf(Z, -(int)by);
+}
 
 template <bool SLABS, class Src>
 __device__ __forceinline__ RowNorm wave_shifted_norm(const Src& sp, float s, float lane_m, Shared& sh, int& phase)
@@ -534,7 +568,7 @@ __device__ __forceinline__ RowNorm wave_shifted_norm(const Src& sp, float s, flo
     r = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, r)));
     ToWeight<true> cw;
     cw.s = s;
-    cw.ms = r * s;
+    cw.ms = floorf(r * s);
     float z = 0.f;
     SlabSums<Src::kNit> sums;
     sp.for_each_it([&](int it, int, int, const float(&a)[E]) {

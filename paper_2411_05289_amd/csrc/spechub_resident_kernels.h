@@ -136,7 +136,7 @@ __device__ __forceinline__ void spechub_resident(const Params& P, const NodeIn& 
         } else {
             normaliser(lane_max(sp));
         }
-        z[0] = z1[0];
+        z[0] = normalise_shift(cp.ms, z1[0]);
         z[1] = in.q_rest;
         lp_hub = in.lpa;
     } else {
@@ -186,6 +186,11 @@ __device__ __forceinline__ void spechub_resident(const Params& P, const NodeIn& 
     h.c = ea_q / Zq_rest;  // q(a) / (1 - q(a)); unused when Zq_rest == 0
     const float pa = ea_p * h.iZp;
     const float qa = ea_q * h.iZq;
+    // STATS: the residual's terms and sums are in units of 1 / z[0]
+    HubUnits hu;
+    hu.kappa = h.iZq * z[0];
+    hu.c_kappa = h.c * hu.kappa;
+    const float unit = STATS ? h.iZp : 1.f;
 
     bool decided = false, degenerate = false;
     int hub_slot = -1;
@@ -302,7 +307,7 @@ __device__ __forceinline__ void spechub_resident(const Params& P, const NodeIn& 
                 }
                 float t_xa[HE], t_ax[HE], w[HE];
 #pragma unroll
-                for (int e = 0; e < HE; ++e) spechub_terms(ep[e], eq[e], h, t_xa[e], t_ax[e], w[e]);
+                for (int e = 0; e < HE; ++e) spechub_terms(ep[e], eq[e], hu, t_xa[e], t_ax[e], w[e]);
                 // the two halves of chunk_sum's tree
                 if constexpr (HE == 4) {
                     part[0][hv] = (t_xa[0] + t_xa[1]) + (t_xa[2] + t_xa[3]);
@@ -326,7 +331,7 @@ __device__ __forceinline__ void spechub_resident(const Params& P, const NodeIn& 
         for_each2(sp, sq, residual_terms);
     }
     block_sum<kWaves, 2>(sacc, sh.red, phase);  // barrier: slab sums visible
-    const float S_xa = sacc[0], S_ax = sacc[1];
+    const float S_xa = sacc[0] * unit, S_ax = sacc[1] * unit;
     if (!decided) {
         if (hub_slot == 1) {  // pair (x, a): the hub draws on what the pairs (a,.) left of p(a)
             if (u1 * S_xa < fmaxf(pa - S_ax, 0.f)) {
@@ -342,7 +347,7 @@ __device__ __forceinline__ void spechub_resident(const Params& P, const NodeIn& 
     }
     auto sv = [&](int i) { return sh.slab_w[i]; };
     const float W = slab_total(rp.nslab, sv);
-    o.rmass = W;
+    o.rmass = W * unit;
     bool wrote_prob = false;
     if (!decided) {
         int v;
@@ -352,7 +357,7 @@ __device__ __forceinline__ void spechub_resident(const Params& P, const NodeIn& 
             v = -1;
             if (W > 0.f && (EVERY_WAVE || wave == 0))
                 v = icdf_slabs<E>(rp.nslab, u2, W, sv, [&](int s, float(&w)[E]) {
-                    spechub_chunk_w<DT, ExpW>(rp, rq, cp, cq, h, a_virt, s, w);
+                    spechub_chunk_w<DT, ExpW>(rp, rq, cp, cq, hu, a_virt, s, w);
                 });
         } else
             v = draw_resident<E>(rp.nslab, u2, W, sv, [&](int it, float(&w)[E]) {
@@ -388,7 +393,10 @@ __device__ __forceinline__ void spechub_resident(const Params& P, const NodeIn& 
     }
     if (rprob && !wrote_prob)
         write_resid_prob<DT>(rprob, rp, W, [&](int s, float(&w)[E]) {
-            spechub_chunk_w<DT, ExpW>(rp, rq, cp, cq, h, a_virt, s, w);
+            if constexpr (STATS)
+                spechub_chunk_w<DT, ExpW>(rp, rq, cp, cq, hu, a_virt, s, w);
+            else
+                spechub_chunk_w<DT, ExpW>(rp, rq, cp, cq, h, a_virt, s, w);
         });
 }
 

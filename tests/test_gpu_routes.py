@@ -66,3 +66,25 @@ def test_tables_node_by_node(method, V, dtype, Bn):
     for fc in ([1, 3, 5, -1, -1, -1, -1], [1, 3, -1, 5, -1, 7, -1, -1, -1]):
         wl = _workload(Bn, len(fc), V, 2, 5, dtype, "logits", first_child=fc)
         check_case(method, wl, seed=V, full_outputs=V < 9999)
+
+
+@pytest.mark.parametrize("method", ALL)
+@pytest.mark.parametrize("shift", [2.0 ** 20, -2.0 ** 23, 2.0 ** 26])
+def test_large_softmax_shifts(method, shift):
+    """Logits that are whole multiples of 8, at T = 8, and the same logits (exactly, in fp32) far from 0, where the
+    shift of the target's weights cannot move by single steps: the same outcomes, tokens and residual masses."""
+    wl = _workload(4, 3, 9000, 2, 2, "fp32", "logits")
+    u = torch.rand((4, 3, 3), generator=torch.Generator(device=DEV).manual_seed(1), device=DEV)
+    results = []
+    for by in (0.0, shift):
+        t, d = (torch.round(x) * 8 + by for x in (wl.target, wl.draft))
+        assert torch.equal(t - by, torch.round(wl.target) * 8)
+        pb = B.Problem(t, d, B.LOGITS, 2, 2, 8.0, 8.0).with_draft_stats()
+        drafted = DRAFT[method](pb, u[..., :2].contiguous())
+        results.append((drafted["tokens"][:, 1:], VERIFY[method](pb, drafted["tokens"], u, resid_mass=True)))
+    (tokens, want), (tokens_far, got) = results
+    assert torch.equal(tokens, tokens_far)
+    for name in ("outcome", "token", "flags"):
+        assert torch.equal(want[name], got[name]), name
+    # the parity bar's bound for residual masses
+    assert ((want["resid_mass"] - got["resid_mass"]).abs() <= 1e-5 * want["resid_mass"] + 5e-7).all()
