@@ -50,6 +50,29 @@ __global__ __launch_bounds__(kWG) void draft_kernel(const Params P)
             if constexpr (METHOD == kSpecHub) a_virt = block_argmax_at<DT>(rq, mq_lane, mm[0], mq_chunk, sh, phase);
         }
     }
+    if constexpr (!LOGITS && NIT == 0) {
+        // a streamed row of probabilities: largest element and slab sums in one sweep; a chunk is a dozen instructions of
+        // work, so the loads in flight bound it and eight chunks are asked for ahead
+        constexpr int E = Elem<DT>::kPerChunk;
+        float lane_m = -__builtin_inff();
+        int lane_m_chunk = 0;
+        sq.template for_each_sums<8>(sh.slab_w, [&](int, int chunk, const float(&a)[E]) {
+            if constexpr (METHOD == kSpecHub) {
+                float cm = a[0];
+#pragma unroll
+                for (int e = 1; e < E; ++e) cm = fmaxf(cm, a[e]);
+                lane_m_chunk = cm > lane_m ? chunk : lane_m_chunk;
+                lane_m = fmaxf(lane_m, cm);
+            }
+            return chunk_sum<E>(a);
+        });
+        if constexpr (METHOD == kSpecHub) {
+            mm[0] = lane_m;
+            block_max<kWaves, 1>(mm, sh.red, phase);
+            a_virt = block_argmax_at<DT>(rq, lane_m, mm[0], lane_m_chunk, sh, phase);
+        }
+        swept = true;
+    }
     if (!swept) {
         if (LOGITS || METHOD == kSpecHub) {
             const float mq_lane = lane_max_of_row(sq);
@@ -90,7 +113,7 @@ static void launch_draft_n(int nit, bool masked, dim3 grid, dim3 block, hipStrea
         hipLaunchKernelGGL((draft_kernel<DT, LG, METHOD, 8, false>), grid, block, 0, st, P);
         return;
     }
-    if constexpr (!LG) {  // logit rows of this size are streamed
+    if constexpr (!LG && METHOD != kSpecHub) {  // the others of this size are streamed
         if (nit == 16) {
             hipLaunchKernelGGL((draft_kernel<DT, LG, METHOD, 16>), grid, block, 0, st, P);
             return;

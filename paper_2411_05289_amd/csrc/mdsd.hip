@@ -363,7 +363,11 @@ static void launch_draft(int method, const mdsd_problem* pb, const Params& P, hi
     // fits two workgroups on a CU, the streaming one four, and its one-sweep statistics are the
     // cheaper (V = 50304, B = 64: spechub_draft 33.7 -> 24.7 us, rrsw_draft 47.2 -> 26.8 us).  At
     // eight chunks per lane the row in registers wins (V = 32000: 18.8 against 19.4 us).
-    if (nit == 16 && lg) nit = 0;  // (rows of probabilities have no one-sweep form and stay in registers)
+    // SpecHub on probabilities the same, in one sweep without exponentials (fp32 32000, 480 nodes with and without
+    // children 11.2 -> 8.9 us, 15 8.1 -> 6.1, 4000 47.3 -> 45.4; bf16 60000 12.2 -> 9.3, 9.1 -> 7.1, 55.3 -> 53.0; eight chunks
+    // per lane lose in large batches: bf16 32000, 4000 nodes 23.0 -> 30.5); the RRS methods, which need no maximum, gain
+    // nothing (8.3 and 8.3) and stay in registers.
+    if (nit == 16 && (lg || method == kSpecHub)) nit = 0;
     const dim3 grid = node_grid(P, nit), block(kWG);
     switch (small_build(pb)) {
     case 2: mdsd_pair::launch_draft(method, pb->dtype, lg, st, P); return;
