@@ -404,19 +404,19 @@ __device__ __forceinline__ void spechub_terms(float ep, float eq, const HubScal&
     w = clamp01(fmaf(-h.c, Qn, pr));            // p''(y)  = max(p' - c Q, 0)
 }
 
-// The same with target weights that are probabilities but for a factor g in (1, 2] (normalise_shift()): everything in
-// units of g, Q = kappa eq, two multiplications less per element.
-struct HubUnits {
-    float kappa, c_kappa;
+// The same with the draft row's normaliser inside the fused multiply-adds: five instructions per element instead of six.
+struct HubFused {
+    float iZp, iZq, c_iZq;
 };
 
-__device__ __forceinline__ void spechub_terms(float ep, float eq, const HubUnits& h, float& q_xa_res, float& q_ax_res,
+__device__ __forceinline__ void spechub_terms(float ep, float eq, const HubFused& h, float& q_xa_res, float& q_ax_res,
                                               float& w)
 {
-    q_xa_res = clamp01(fmaf(h.kappa, eq, -ep));
-    const float pr = clamp01(fmaf(-h.kappa, eq, ep));
-    q_ax_res = clamp01(fmaf(h.c_kappa, eq, -pr));
-    w = clamp01(fmaf(-h.c_kappa, eq, pr));
+    const float Pn = ep * h.iZp;
+    q_xa_res = clamp01(fmaf(h.iZq, eq, -Pn));
+    const float pr = clamp01(fmaf(-h.iZq, eq, Pn));
+    q_ax_res = clamp01(fmaf(h.c_iZq, eq, -pr));
+    w = clamp01(fmaf(-h.c_iZq, eq, pr));
 }
 
 template <int DT, class CV, class Hub>
@@ -444,13 +444,13 @@ __device__ __forceinline__ float rrs_term(float ep, float eq, float iZp, float c
     return fmaxf(fmaf(-c_iZq, eq, ep * iZp), 0.f);
 }
 
-// the same in units of target weights that are at most 1 (normalise_shift()): two instructions less per element
-__device__ __forceinline__ float rrs_term(float ep, float eq, float c_kappa)
+// the same where ep / Zp is a softmax probability, at most 1, so that the clamp comes with the subtraction
+__device__ __forceinline__ float rrs_term01(float ep, float eq, float iZp, float c_iZq)
 {
-    return clamp01(fmaf(-c_kappa, eq, ep));
+    return clamp01(fmaf(-c_iZq, eq, ep * iZp));
 }
 
-template <int DT, class CV>
+template <int DT, class CV, bool CLAMP01 = false>
 __device__ __forceinline__ void rrs_chunk_w(const RowView& rp, const RowView& rq, CV cp, CV cq, float iZp,
                                             float c_iZq, const int* excl, int n_excl, int s,
                                             float (&w)[Elem<DT>::kPerChunk])
@@ -461,7 +461,8 @@ __device__ __forceinline__ void rrs_chunk_w(const RowView& rp, const RowView& rq
     load_chunk<DT>(rp, chunk, CV::fill(), a);
     load_chunk<DT>(rq, chunk, CV::fill(), b);
 #pragma unroll
-    for (int e = 0; e < E; ++e) w[e] = rrs_term(cp(a[e]), cq(b[e]), iZp, c_iZq);
+    for (int e = 0; e < E; ++e)
+        w[e] = CLAMP01 ? rrs_term01(cp(a[e]), cq(b[e]), iZp, c_iZq) : rrs_term(cp(a[e]), cq(b[e]), iZp, c_iZq);
     zero_excluded<E>(w, chunk, excl, n_excl);
 }
 
@@ -516,28 +517,15 @@ __device__ __forceinline__ int draw_resident(int nslab, float u, float W, SlabVa
 // cheap estimates of them) and sums its weights; after one barrier the waves' pairs (r_w, Z_w)
 // are combined: M = max r_w, Z = sum Z_w f_w with f_w = 2^((r_w - M) s) <= 1.  The factors are
 // formed from the rounded products r_w s themselves (the largest of them is the shift `ms` that
-// later passes use), so that a wave's weights times its factor are the weights those passes
-// compute, not merely close to them: the references are rounded down to whole numbers, which makes every
-// factor a power of two.  A wave far below the maximum contributes its true,
+// later passes use), so that a wave's weights times its factor are those passes' weights but for the
+// last bit of an exponent, however large r_w s is.  A wave far below the maximum contributes its true,
 // negligible share.  With SLABS the slab sums left in
 // LDS are in their wave's own units: slab i counts f_(i mod kWaves) times its stored value, and
 // f_lane is that factor for the slabs this lane reads in slab_total() and icdf_find_slab()
 // (slab = a multiple of 64 + lane).
 struct RowNorm {
-    float ms, Z, f_lane;  // ms = M s rounded down, the shift of 2^(l s - ms)
+    float ms, Z, f_lane;  // ms = M s, the shift of 2^(l s - ms)
 };
-
-// Moves the shift `ms` (a whole number) of weights whose sum is Z so that they sum to less than 1, and returns that
-// sum: weights that need no factor to be compared with another row's and clamped to [0, 1].  Everything moves by a power
-// of two, without rounding.  Shifts from 2^24 on, which do not take every whole number, move by as much more as
-// their next steps are apart.
-__device__ __forceinline__ float normalise_shift(float& ms, float Z)
-{
-    const float a = fabsf(ms), n = (float)__builtin_amdgcn_frexp_expf(Z) + (a >= 0x1p24f ? a * 0x1p-23f : 0.f);
-    const float moved = ms + n, by = moved - ms;
-    ms = moved;
-    return __builtin_amdgcn_ldexpf(Z, -(int)by);
-}
 
 template <bool SLABS, class Src>
 __device__ __forceinline__ RowNorm wave_shifted_norm(const Src& sp, float s, float lane_m, Shared& sh, int& phase)
@@ -568,7 +556,7 @@ __device__ __forceinline__ RowNorm wave_shifted_norm(const Src& sp, float s, flo
     r = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, r)));
     ToWeight<true> cw;
     cw.s = s;
-    cw.ms = floorf(r * s);
+    cw.ms = r * s;
     float z = 0.f;
     SlabSums<Src::kNit> sums;
     sp.for_each_it([&](int it, int, int, const float(&a)[E]) {

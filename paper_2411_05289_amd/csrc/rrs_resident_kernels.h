@@ -134,10 +134,7 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
             normaliser(lane_max(sp));
         }
     }
-    // target weights of at most 1: the residual's terms and sums are in units of 1 / Zp
-    const float Zp = uniform(STATS ? normalise_shift(cp.ms, z1[0]) : z1[0]);
-    cp.ms = uniform(cp.ms);
-    const float iZp = uniform(1.f / Zp);
+    const float iZp = uniform(1.f / z1[0]);
     const float iZq = uniform(1.f / st.rest_mass);
     bool bad = false;
     for (int i = 0; i < k; ++i) bad = bad || sh.node_x[i] < 0;
@@ -168,7 +165,7 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
     // tokens, of which the first is the rejected one.  Otherwise they are those of the rejected tokens.
     auto residual_pass = [&](float c_new, auto KEPT, auto REM_) {
         constexpr bool REM = decltype(REM_)::value;
-        const float c_kappa = c_new * iZq * Zp;
+        const float c_iZq = c_new * iZq;
         float lane_rem = 0.f;
         SlabSums<NIT> sums;
         // Opaque copies: the weights of the target row do not change from round to round, and
@@ -190,7 +187,7 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
 #pragma unroll
                 for (int e = 0; e < HE; ++e) {
                     eq[e] = cq(eq[e]);
-                    w[e] = rrs_term(cpo(ep[e]), eq[e], c_kappa);
+                    w[e] = rrs_term01(cpo(ep[e]), eq[e], iZp, c_iZq);
                 }
                 if (__builtin_expect(some, 0)) {
                     asm volatile("" ::: "memory");
@@ -217,7 +214,7 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
             rem_k = rr[0];
         }
         __syncthreads();
-        return slab_total(rp.nslab, [&](int j) { return sh.slab_w[j]; }) * iZp;
+        return slab_total(rp.nslab, [&](int j) { return sh.slab_w[j]; });
     };
     // WO: unnormalised draft mass left before round i (i >= 1): what no draft took, plus the
     // drafts still to come (a repeated token counts once)
@@ -289,9 +286,9 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
         __syncthreads();
         residual_pass(c, std::false_type{}, std::false_type{});  // rare: all of the draft row from memory again
     }
-    const float c_kappa = c * iZq * Zp;
+    const float c_iZq = c * iZq;
     auto cw = [&](int s, float(&w)[E]) {
-        rrs_chunk_w<DT, ExpW>(rp, rq, cp, cq, 1.f, c_kappa, nullptr, 0, s, w);
+        rrs_chunk_w<DT, ExpW, true>(rp, rq, cp, cq, iZp, c_iZq, nullptr, 0, s, w);
         const int chunk = s * 64 + (threadIdx.x & 63);
         for (int j = 0; j < n_rej; ++j) {
             const int off = sh.node_x[j] + rp.head - chunk * E;
@@ -301,7 +298,7 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
     };
     auto sv = [&](int j) { return sh.slab_w[j]; };
     const float W = slab_total(rp.nslab, sv);
-    o.rmass = n_rej == 0 ? 1.f : W * iZp;
+    o.rmass = n_rej == 0 ? 1.f : W;
     if (!decided) {
         // (the kernel's first thread writes the outputs: the first wave's draw is the one that counts)
         int v = -1;

@@ -136,7 +136,7 @@ __device__ __forceinline__ void spechub_resident(const Params& P, const NodeIn& 
         } else {
             normaliser(lane_max(sp));
         }
-        z[0] = normalise_shift(cp.ms, z1[0]);
+        z[0] = z1[0];
         z[1] = in.q_rest;
         lp_hub = in.lpa;
     } else {
@@ -186,11 +186,9 @@ __device__ __forceinline__ void spechub_resident(const Params& P, const NodeIn& 
     h.c = ea_q / Zq_rest;  // q(a) / (1 - q(a)); unused when Zq_rest == 0
     const float pa = ea_p * h.iZp;
     const float qa = ea_q * h.iZq;
-    // STATS: the residual's terms and sums are in units of 1 / z[0]
-    HubUnits hu;
-    hu.kappa = h.iZq * z[0];
-    hu.c_kappa = h.c * hu.kappa;
-    const float unit = STATS ? h.iZp : 1.f;
+    // STATS: the form of the residual's terms (the shift of the target's weights taking in their sum as well, four
+    // instructions per element, costs the exponents of flat rows two bits and does not exist where it is 2^24 and more)
+    const HubFused hf{h.iZp, h.iZq, h.c * h.iZq};
 
     bool decided = false, degenerate = false;
     int hub_slot = -1;
@@ -307,7 +305,7 @@ __device__ __forceinline__ void spechub_resident(const Params& P, const NodeIn& 
                 }
                 float t_xa[HE], t_ax[HE], w[HE];
 #pragma unroll
-                for (int e = 0; e < HE; ++e) spechub_terms(ep[e], eq[e], hu, t_xa[e], t_ax[e], w[e]);
+                for (int e = 0; e < HE; ++e) spechub_terms(ep[e], eq[e], hf, t_xa[e], t_ax[e], w[e]);
                 // the two halves of chunk_sum's tree
                 if constexpr (HE == 4) {
                     part[0][hv] = (t_xa[0] + t_xa[1]) + (t_xa[2] + t_xa[3]);
@@ -331,7 +329,7 @@ __device__ __forceinline__ void spechub_resident(const Params& P, const NodeIn& 
         for_each2(sp, sq, residual_terms);
     }
     block_sum<kWaves, 2>(sacc, sh.red, phase);  // barrier: slab sums visible
-    const float S_xa = sacc[0] * unit, S_ax = sacc[1] * unit;
+    const float S_xa = sacc[0], S_ax = sacc[1];
     if (!decided) {
         if (hub_slot == 1) {  // pair (x, a): the hub draws on what the pairs (a,.) left of p(a)
             if (u1 * S_xa < fmaxf(pa - S_ax, 0.f)) {
@@ -347,7 +345,7 @@ __device__ __forceinline__ void spechub_resident(const Params& P, const NodeIn& 
     }
     auto sv = [&](int i) { return sh.slab_w[i]; };
     const float W = slab_total(rp.nslab, sv);
-    o.rmass = W * unit;
+    o.rmass = W;
     bool wrote_prob = false;
     if (!decided) {
         int v;
@@ -357,7 +355,7 @@ __device__ __forceinline__ void spechub_resident(const Params& P, const NodeIn& 
             v = -1;
             if (W > 0.f && (EVERY_WAVE || wave == 0))
                 v = icdf_slabs<E>(rp.nslab, u2, W, sv, [&](int s, float(&w)[E]) {
-                    spechub_chunk_w<DT, ExpW>(rp, rq, cp, cq, hu, a_virt, s, w);
+                    spechub_chunk_w<DT, ExpW>(rp, rq, cp, cq, hf, a_virt, s, w);
                 });
         } else
             v = draw_resident<E>(rp.nslab, u2, W, sv, [&](int it, float(&w)[E]) {
@@ -394,7 +392,7 @@ __device__ __forceinline__ void spechub_resident(const Params& P, const NodeIn& 
     if (rprob && !wrote_prob)
         write_resid_prob<DT>(rprob, rp, W, [&](int s, float(&w)[E]) {
             if constexpr (STATS)
-                spechub_chunk_w<DT, ExpW>(rp, rq, cp, cq, hu, a_virt, s, w);
+                spechub_chunk_w<DT, ExpW>(rp, rq, cp, cq, hf, a_virt, s, w);
             else
                 spechub_chunk_w<DT, ExpW>(rp, rq, cp, cq, h, a_virt, s, w);
         });

@@ -88,3 +88,58 @@ def test_large_softmax_shifts(method, shift):
         assert torch.equal(want[name], got[name]), name
     # the parity bar's bound for residual masses
     assert ((want["resid_mass"] - got["resid_mass"]).abs() <= 1e-5 * want["resid_mass"] + 5e-7).all()
+
+
+@pytest.mark.parametrize("method", ["spechub"])
+@pytest.mark.parametrize("dtype,V,off,Bn", [
+    ("bf16", 9000, 0, 3), ("bf16", 9001, 3, 3),                 # 512 threads per node, four chunks per lane
+    ("bf16", 32000, 0, 3), ("bf16", 32001, 5, 3),               # ... eight; 1024 threads where unaligned
+    ("fp32", 32000, 0, 3), ("fp32", 32001, 1, 3),               # ... sixteen; 1024 threads
+    ("bf16", 50304, 0, 3), ("bf16", 70001, 1, 3),               # 1024 threads, resident and streamed
+    ("bf16", 32000, 0, 768), ("bf16", 32001, 0, 768),           # 256 threads
+])
+def test_target_rows_far_from_zero(method, dtype, V, off, Bn):
+    """Softmax shifts of 2^24 and more, which do not take every whole number, up to the bound of a usable reference, 2^31:
+    target rows of one mask value throughout are uniform, and a temperature near 0 leaves the largest element."""
+    for fill, T in ((-3e8, 1.0), (-1e9, 1.0), (-1e9, 0.7), (2e7, 1.0)):
+        wl = _workload(Bn, 3, V, 2, 2, dtype, "logits", off, temps=(T, 1.0))
+        wl.target[::2] = fill
+        check_case(method, wl, seed=V, seqs=[0, 1, Bn - 1], full_outputs=Bn < 9)
+    if dtype == "fp32":  # largest logits of 5 to 9: shifts of 2^29.4 and more
+        check_case(method, _workload(Bn, 3, V, 2, 2, dtype, "logits", off, temps=(1e-8, 1.0)), seed=V)
+
+
+@pytest.mark.parametrize("method", ALL)
+@pytest.mark.parametrize("dtype,V", [("bf16", 9000), ("bf16", 32000), ("bf16", 32001), ("fp32", 32000), ("bf16", 50304)])
+def test_acceptance_of_flat_rows(method, dtype, V):
+    """The probability that the first acceptance test holds a token's p(x) to be, on flat target rows (the exponents
+    of their weights relative to the largest are small, relative to their sum they are not): the root's first test is u q(x) <
+    p(x) with q(x) = 1/2 exactly, so the uniforms between which it changes give p(x), here for 64 of the likelier tokens."""
+    X, steps = 64, 48
+    gen = torch.Generator(device=DEV).manual_seed(V)
+    td = torch.float32 if dtype == "fp32" else torch.bfloat16
+    target = (0.5 * torch.randn((X, 3, V), generator=gen, device=DEV)).to(td)
+    p = torch.softmax(target[:, 0].double(), -1)
+    likely = p[:, 1:].topk(200, -1).indices + 1
+    x = likely[torch.arange(X, device=DEV), torch.randint(200, (X,), generator=gen, device=DEV)]
+    # the draft's mass lies on token 0, the hub, and on x in equal parts
+    draft = torch.full((X, 3, V), -torch.inf, dtype=td, device=DEV)
+    draft[..., 0] = 0.0
+    draft.scatter_(2, x[:, None, None].expand(X, 3, 1), 0.0)
+    tokens = torch.full((X, 3), -1, dtype=torch.int32, device=DEV)
+    tokens[:, 1], tokens[:, 2] = x, 0
+    pb = B.Problem(target, draft, B.LOGITS, 2, 2, 1.0, 1.0).with_draft_stats()
+    DRAFT[method](pb, torch.rand((X, 3, 2), generator=gen, device=DEV))
+    exact = 2 * p[torch.arange(X, device=DEV), x]
+    accepted = torch.zeros(X, dtype=torch.int64, device=DEV)
+    offsets = (torch.arange(steps, device=DEV) - steps // 2 + 0.5) * 4e-8
+    for off in offsets:
+        u = torch.full((X, 3, 3), 0.5, device=DEV)
+        u[:, 0, 0] = (exact * (1 + off)).float()
+        accepted += VERIFY[method](pb, tokens, u)["outcome"][:, 0] == 0
+    assert ((accepted > 0) & (accepted < steps)).all()
+    error = (accepted - steps // 2).double() * 4e-8
+    # In units of 2^-24 = 6e-8, root mean squares: the exponent, of up to 4 in magnitude, is rounded by 1.4 at most, 0.8, the
+    # exponential by 0.6, the reciprocal of the sum and the product by 0.6 each, u and its product by 0.6, the grid of
+    # offsets by 0.2: 1.5, or 0.9e-7; and as much again for the sum itself.  (Measured: 0.8e-7 to 1.2e-7.)
+    assert error.square().mean().sqrt() < 1.3e-7, error.square().mean().sqrt()
