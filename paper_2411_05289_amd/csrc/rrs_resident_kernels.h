@@ -105,9 +105,7 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
         });
         mm[0] = lane_max(sp);
         block_max<kWaves, 2>(mm, sh.red, phase);
-        // (an ulp up, so that no weight is above 1)
-        cp.ms = mm[0] * cp.s;
-        cp.ms = uniform(fmaf(fabsf(cp.ms), 0x1p-23f, cp.ms));
+        cp.ms = uniform(mm[0] * cp.s);
         cq.ms = uniform(mm[1] * cq.s);
         z[1] *= __builtin_amdgcn_exp2f(lane_ms - cq.ms);
         sp.for_each([&](int, int, const float(&a)[E]) {

@@ -90,7 +90,7 @@ def test_large_softmax_shifts(method, shift):
     assert ((want["resid_mass"] - got["resid_mass"]).abs() <= 1e-5 * want["resid_mass"] + 5e-7).all()
 
 
-@pytest.mark.parametrize("method", ["spechub"])
+@pytest.mark.parametrize("method", ALL)
 @pytest.mark.parametrize("dtype,V,off,Bn", [
     ("bf16", 9000, 0, 3), ("bf16", 9001, 3, 3),                 # 512 threads per node, four chunks per lane
     ("bf16", 32000, 0, 3), ("bf16", 32001, 5, 3),               # ... eight; 1024 threads where unaligned
