@@ -518,13 +518,14 @@ __device__ __forceinline__ int draw_resident(int nslab, float u, float W, SlabVa
 // are combined: M = max r_w, Z = sum Z_w f_w with f_w = 2^((r_w - M) s) <= 1.  The factors are
 // formed from the rounded products r_w s themselves (the largest of them is the shift `ms` that
 // later passes use), so that a wave's weights times its factor are those passes' weights but for the
-// last bit of an exponent, however large r_w s is.  A wave far below the maximum contributes its true,
+// last bit of an exponent, however large r_w s is; the shifts are rounded down to whole numbers, which makes
+// every factor a power of two.  A wave far below the maximum contributes its true,
 // negligible share.  With SLABS the slab sums left in
 // LDS are in their wave's own units: slab i counts f_(i mod kWaves) times its stored value, and
 // f_lane is that factor for the slabs this lane reads in slab_total() and icdf_find_slab()
 // (slab = a multiple of 64 + lane).
 struct RowNorm {
-    float ms, Z, f_lane;  // ms = M s, the shift of 2^(l s - ms)
+    float ms, Z, f_lane;  // ms = M s rounded down, the shift of 2^(l s - ms)
 };
 
 template <bool SLABS, class Src>
@@ -556,7 +557,7 @@ __device__ __forceinline__ RowNorm wave_shifted_norm(const Src& sp, float s, flo
     r = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, r)));
     ToWeight<true> cw;
     cw.s = s;
-    cw.ms = r * s;
+    cw.ms = floorf(r * s);
     float z = 0.f;
     SlabSums<Src::kNit> sums;
     sp.for_each_it([&](int it, int, int, const float(&a)[E]) {
