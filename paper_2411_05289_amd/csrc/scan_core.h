@@ -576,8 +576,9 @@ __device__ __forceinline__ float slab_total(int nslab, SlabVal slab_val)
 }
 
 // Inverse CDF in two stages.  Stage 1 (every wave, redundantly): scan the slab
-// sums for the first slab whose running sum exceeds t = u * W.  Returns false
-// when there is nothing to draw (W == 0).  If rounding leaves no crossing the
+// sums for the first slab with a positive sum whose running sum exceeds t = u * W.  (The running
+// sums add their terms in different orders and may rise by a rounding where a slab holds nothing.)
+// Returns false when there is nothing to draw (W == 0).  If rounding leaves no crossing the
 // last slab with positive sum is taken and t becomes +inf, so that stage 2
 // falls through to its last positive element.
 struct SlabHit {
@@ -600,8 +601,8 @@ __device__ __forceinline__ bool icdf_find_slab(int nslab, float u, float W, Slab
         const float v = (base + lane < nslab) ? slab_val(base + lane) : 0.f;
         const float incl = wave_scan_add(v);
         const float excl = carry + wave_shift_up(incl, 0.f);
-        const unsigned long long hit = __ballot(carry + incl > h.t);
         const unsigned long long pos = __ballot(v > 0.f);
+        const unsigned long long hit = __ballot(carry + incl > h.t) & pos;
         if (hit) {
             const int l = __ffsll(hit) - 1;
             h.slab = base + l;
@@ -618,7 +619,7 @@ __device__ __forceinline__ bool icdf_find_slab(int nslab, float u, float W, Slab
 }
 
 // Stage 2 (one wave): w = this lane's chunk of the slab found in stage 1.
-// Returns the virtual index of the first element whose running sum exceeds t,
+// Returns the virtual index of the first element with positive weight whose running sum exceeds t,
 // else the last element with positive weight, else -1 (same value in every lane).
 template <int E>
 __device__ __forceinline__ int icdf_in_slab(const float (&w)[E], const SlabHit& h)
@@ -628,8 +629,8 @@ __device__ __forceinline__ int icdf_in_slab(const float (&w)[E], const SlabHit& 
     const float ls = chunk_sum<E>(w);
     const float incl = wave_scan_add(ls);
     const float lane_excl = wave_shift_up(incl, 0.f);
-    const unsigned long long hit = __ballot(h.excl + incl > t);
     const unsigned long long pos = __ballot(ls > 0.f);
+    const unsigned long long hit = __ballot(h.excl + incl > t) & pos;
     int l;
     if (hit) {
         l = __ffsll(hit) - 1;
@@ -639,6 +640,7 @@ __device__ __forceinline__ int icdf_in_slab(const float (&w)[E], const SlabHit& 
         t = __builtin_inff();
     }
     float run = h.excl + lane_excl;
+    t = fmaxf(t, run);  // above t already, where the crossing was at a lane or slab without weight: the first element with weight
     int e_sel = -1, e_last = -1;
 #pragma unroll
     for (int e = 0; e < E; ++e) {

@@ -353,6 +353,7 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
                                 wrote_prob = true;
                             }
                         }
+                        if (v < 0) flags |= MDSD_FLAG_ZERO_RESIDUAL;
                         token = v < 0 ? -1 : v - rp.head;
                     }
                     if (rprob && !wrote_prob) write_resid_prob<DT>(rprob, rp, W, cw);

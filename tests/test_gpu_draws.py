@@ -1,5 +1,5 @@
 """Draft calls at the edges of their kernels: how many wavefronts share a node and its draws, how a row's largest
-element is found, and where rows begin and end."""
+element is found, and where rows begin and end; draws, in draft and verify calls, at the edges of tokens without weight."""
 import numpy as np
 import pytest
 import torch
@@ -70,3 +70,81 @@ def test_largest_element_of_bf16_rows(V, off):
     assert torch.equal(pb.draft_stats[:, 0, 0], want[:, 0])
     first = torch.where(numbers == want[..., None], torch.arange(V, device=DEV), V).amin(-1)
     assert torch.equal(g["hub"][:, 0].long(), first[:, 0])
+
+
+def _rounded_boundaries(count, seed):
+    """Vectors of 64 weights, half of them 0, with a uniform u for which u * total lies between the running sums in
+    front of and behind a weight of 0: the sums are formed as a wavefront forms them, lanes 1, 2, 4 and 8 below in rows of
+    16, then row by row, and may differ by a rounding there."""
+    f = np.float32
+
+    def running(v):
+        v = v.copy()
+        for k in (1, 2, 4, 8):
+            below = np.zeros((4, 16), f)
+            below[:, k:] = v.reshape(4, 16)[:, :16 - k]
+            v = v + below.reshape(64)
+        v[16:32] += v[15]
+        v[48:] += v[47]
+        v[32:] += v[31]
+        return v
+
+    rng = np.random.default_rng(seed)
+    weights, us = [], []
+    while len(us) < count:
+        v = np.where(rng.random(64) < 0.5, rng.random(64) / 32, 0.0).astype(f)
+        v[[0, 63]] = f(0.03125)
+        r = running(v)
+        for n in np.nonzero((v[1:] == 0) & (r[1:] > r[:-1]))[0]:
+            near = f(r[n] / r[63])
+            for u in (near, np.nextafter(near, f(1)), np.nextafter(near, f(0))):
+                if r[n] <= u * r[63] < r[n + 1] and len(us) < count:
+                    weights.append(v)
+                    us.append(u)
+                    break
+    return np.stack(weights), np.array(us, f)
+
+
+@pytest.mark.parametrize("method", ["spechub", "rrs", "rrsw"])
+@pytest.mark.parametrize("V,stride", [(16384, 256), (16384, 4), (4864, 4), (40000, 256)])
+def test_draws_at_rounded_boundaries(method, V, stride):
+    """Rows with one token in every second slab or lane, and uniforms at which the running sums exceed the threshold at a
+    slab or lane without weight: draft draws, leaves and residuals (draft mass on tokens that the target lacks, so that the
+    residual is the target's row) give a token with weight next to the threshold, and no flag."""
+    Bn = 64
+    weights, us = _rounded_boundaries(Bn, V + stride)
+    row = np.zeros((Bn, V), np.float32)
+    row[:, :64 * stride:stride] = weights
+    rows = torch.from_numpy(row).to(DEV)[:, None].expand(Bn, 3, V).contiguous()
+    u = torch.from_numpy(us).to(DEV)
+    other = torch.zeros_like(rows)
+    other[..., 1:3] = 0.5           # the hub and one token more, without weight in `rows`
+
+    def check(token):
+        token = _np(token)
+        assert (token >= 0).all() and (row[np.arange(Bn), token] > 0).all()
+        c = row.astype(np.float64).cumsum(-1)
+        t = us.astype(np.float64) * c[:, -1]
+        at, w = c[np.arange(Bn), token], row[np.arange(Bn), token]
+        assert (np.maximum(at - w - t, t - at) <= 1e-6).all()
+
+    # verify: the root's tokens are rejected, its token and those of the leaves drawn from `rows`
+    tokens = torch.full((Bn, 3), -1, dtype=torch.int32, device=DEV)
+    tokens[:, 1], tokens[:, 2] = 2, 1
+    pb = B.Problem(rows, other, B.PROBS, 2, 2)
+    u_v = torch.full((Bn, 3, 3), 0.5, device=DEV)
+    u_v[..., 2] = u[:, None]
+    g = getattr(B, method + "_verify")(pb, tokens, u_v)
+    assert (g["outcome"] == -1).all()
+    for n in (1, 2):
+        check(g["token"][:, n])
+    check(g["token"][:, 0])
+    assert (g["flags"][:, 1:] == 0).all()
+    if method != "rrsw":            # (RRSw: both drafts rejected, the draft's mass is exhausted)
+        assert (g["flags"][:, 0] == 0).all()
+    # draft: the first draw
+    u_d = torch.full((Bn, 3, 2), 0.25, device=DEV)
+    u_d[:, 0, 0] = u
+    d = DRAFT[method](B.Problem(None, rows, B.PROBS, 2, 2), u_d)
+    check(d["tokens"][:, 1])
+    assert (d["flags"] == 0).all()
