@@ -899,9 +899,19 @@ __global__ __launch_bounds__(kGroupMaxThreads, kGroupWavesPerSimd) void group_ve
 {
     const int l = threadIdx.x & (G - 1), slot = threadIdx.x / G, groups = blockDim.x / G;
     if constexpr (!TREES) {
-        const int64_t item = (int64_t)blockIdx.x * groups + slot;
-        if (item >= (int64_t)P.B * P.N) return;
-        const NodeId id = node_of_item(P, (int)item);
+        NodeId id;
+        if (P.first_child && table_by_waves(G, DT == 1, (int64_t)P.B * P.N)) {
+            const int wave = uniform((int)(blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64)), tile = wave / P.N;
+            id.n = wave - tile * P.N;
+            id.b = tile * (64 / G) + (int)(threadIdx.x & 63) / G;
+            if (id.b >= P.B) return;
+            id.c0 = group_first_child(P, id.n);
+            id.row = (int64_t)id.b * P.N + id.n;
+        } else {
+            const int64_t item = (int64_t)blockIdx.x * groups + slot;
+            if (item >= (int64_t)P.B * P.N) return;
+            id = node_of_item(P, (int)item);
+        }
         const NodeOut o = group_verify_node<DT, LOGITS, METHOD, G>(P, id, l);
         if (P.tree_count == nullptr) {
             if (l == 0) write_group_outputs(P, id, o);

@@ -29,7 +29,11 @@ static void launch_group_verify_g(bool path, hipStream_t st, const Params& P)
         return;
     }
     const int groups = kGroupThreads / G;
-    const int64_t nodes = (int64_t)P.B * P.N;
+    int64_t nodes = (int64_t)P.B * P.N;
+    if (P.first_child && table_by_waves(G, DT == 1, nodes)) {  // whole wavefronts: the last ones may be short of trees
+        constexpr int trees = 64 / G;
+        nodes = ((int64_t)P.B + trees - 1) / trees * trees * P.N;
+    }
     hipLaunchKernelGGL((group_verify_kernel<DT, LG, METHOD, G, false>), dim3((unsigned)((nodes + groups - 1) / groups)),
                        dim3(kGroupThreads), 0, st, P);
 }

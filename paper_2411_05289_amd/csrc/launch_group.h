@@ -48,6 +48,19 @@ inline bool wave_per_node(int lanes, int N, int k, int64_t nodes)
     if (lanes * nodes <= 64 * kWavePerNodeMaxWaves || (lanes == 4 && N <= 3)) return true;
     return k == 2 && group_walks_inside(lanes, N, nodes);
 }
+// Trees given by a table whose walk is not in the workgroup.  Rows in four lanes are shorter than two cache lines: node by
+// node over the batch, the neighbours that share a line are read far apart (rows of 50 fp32 elements, SpecHub step, 31-node
+// trees, 20000 nodes 16.7 us, 150000 40.3; tree by tree 15.6 and 34.9), and tree by tree a wavefront mixes kinds of
+// nodes.  So a wavefront takes one node number of its 16 trees and the next one the next number: 15.4 and 34.0 (9-node
+// trees, 20000 and 150000 nodes: node by node 15.2 and 35.7, tree by tree 15.3 and 34.9, now 14.6 and 31.8).  bf16 rows, whose chunks
+// are twice the work, up to 64 K nodes (60 elements, 9-node trees, 20000 nodes 17.1 -> 16.7, 50000 24.7 -> 23.1, 150000 39.0
+// -> 40.2; 100 elements 43.1 -> 45.1).  More lanes: node by node (240 bf16 elements, 50000 nodes 31.8 against 33.2; tree by
+// tree 39.1).
+constexpr int64_t kTableByWavesMaxNodesBf16 = 65536;
+__host__ __device__ constexpr bool table_by_waves(int lanes, bool bf16, int64_t nodes)
+{
+    return lanes == 4 && (!bf16 || nodes <= kTableByWavesMaxNodesBf16);
+}
 // walk_nodes: nodes per tree where the launch is to walk the trees, else 1: half the lanes are taken where that
 // lets a workgroup hold a tree (rows of 60 bf16 elements, 2000 nodes in trees of 15: 32 lanes 11.9 us, 64 lanes with
 // the walk by arrival count 14.9), but not for rows of more than 96 chunks (1000 elements, 1050 nodes: 9.5 us with

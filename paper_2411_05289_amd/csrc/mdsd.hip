@@ -182,6 +182,23 @@ static dim3 node_grid(const Params& P, int nit)
     return dim3((unsigned)(P.B * P.N));
 }
 
+// Trees given by a table, a workgroup per node: node by node over the batch (SpecHub and RRSw steps of 9- and 31-node trees,
+// tree by tree -> node by node: bf16 rows of 32000, 1800 nodes 54.9 -> 50.4 and 63.8 -> 57.2 us, 56.7 -> 55.4 and 66.0 ->
+// 64.3; of 128256, 900 nodes 117 -> 115, 133 -> 115, 126 -> 117, 143 -> 131, 3600 312 -> 292, 383 -> 342, 322 -> 318, 401 ->
+// 393), but tree by tree where the rows are held in registers and so many that the launch's end weighs less than the
+// place of neighbouring rows in memory: SpecHub from 400 MB of rows per call on (fp32 rows of 8000, 432 MB 137 against 141
+// and 141 against 148; bf16 of 32000, 864 MB 256 against 264, 265 against 272; of 50304, 270 MB 112 against 105, 720 MB 243
+// against 239, 250 against 256), the RRS methods from 800 MB on (432 MB RRSw 165 against 164, 170 against 174, bf16 of
+// 8000, 576 MB 343 against 330, 357 against 353; of 32000, 864 MB 276 against 281, 285 against 287).  Handing a node's trees
+// round among the XCDs, as node_of_block() does for complete trees, makes no difference here (1800 nodes of 32000 50.6,
+// 57.6).
+static int table_by_tree(int method, const mdsd_problem* pb)
+{
+    if (pb->kind != MDSD_LOGITS || resident_chunks(pb) == 0) return 0;
+    const int64_t bytes = (int64_t)pb->B * pb->N * pb->V * (pb->dtype == MDSD_FP32 ? 4 : 2);
+    return bytes >= (method == kSpecHub ? 400000000 : 800000000);
+}
+
 // tree nodes per batch from which the 256-thread verify kernels take over from the 512-thread ones
 constexpr int64_t kHalfWidthMinNodes = 2300;
 
@@ -429,6 +446,7 @@ static int verify_entry(int method, const mdsd_problem* pb, const int32_t* token
                              (wave_per_node(lanes, P.N, P.k, nodes) || group_walks_inside(lanes, P.N, nodes));
     const bool walk_inside = !path && out->accept_depth && (tree_count || trees_whole);
     P.tree_count = walk_inside && !trees_whole ? tree_count : nullptr;
+    if (pb->first_child && !lanes) P.n_internal = table_by_tree(method, pb);
     P.tokens = tokens;
     P.u = u;
     P.outcome = out->outcome;
@@ -491,6 +509,7 @@ static int draft_entry(int method, const mdsd_problem* pb, const float* u, int32
     if (rc == kEmptyBatch) return MDSD_OK;
     if (rc != MDSD_OK) return rc;
     if (!u || !tokens) return MDSD_E_NULL;
+    if (pb->first_child) P.n_internal = table_by_tree(method, pb);
     P.u = u;
     P.tokens_out = tokens;
     P.hub_out = hub;

@@ -75,9 +75,11 @@ __device__ __forceinline__ NodeId node_of_item(const Params& P, int w)
         }
     } else {
         // node by node over the trees: children have higher numbers than their parents, so nodes with
-        // children come early here too
-        id.n = w / P.B;
-        id.b = w - id.n * P.B;
+        // children come early here too; or tree by tree
+        const bool by_tree = P.n_internal != 0;
+        const int per = by_tree ? P.N : P.B, q = w / per, r = w - q * per;
+        id.n = by_tree ? r : q;
+        id.b = by_tree ? q : r;
         id.c0 = P.first_child[id.n];
         // an entry that does not point past its own node, or leaves no room for k children, is
         // treated as a leaf (the tree walk applies the same rule, so it always ends)

@@ -15,7 +15,8 @@ struct Params {
     // log2(e) / temperature, formed once on the host: the correctly rounded quotient, which the
     // kernels would otherwise each compute again with a dozen instructions per wave
     float scale_t, scale_d;
-    int B, N, V, k, depth, n_internal;
+    int B, N, V, k, depth;
+    int n_internal;  // complete trees: nodes with children; trees given by a table: 1 = launched tree by tree, 0 = node by node
     int masked;      // some row may start or end inside a 16-byte chunk
     int row_chunks;  // 16-byte chunks that a row touches at most
     const int32_t* first_child;

@@ -69,6 +69,16 @@ def test_tables_node_by_node(method, V, dtype, Bn):
 
 
 @pytest.mark.parametrize("method", ALL)
+@pytest.mark.parametrize("V,dtype,Bn", [(50, "fp32", 2003), (17, "fp32", 2001), (60, "bf16", 2015), (60, "bf16", 7300),
+                                        (110, "fp32", 2003), (8000, "fp32", 1400), (30000, "bf16", 1500)])
+def test_tables_of_large_batches(method, V, dtype, Bn):
+    """Nine-node trees beyond the workgroups that walk them: a wavefront per node number of sixteen trees, the last ones short
+    of trees; node by node; tree by tree where the rows are 400 and 800 MB."""
+    wl = _workload(Bn, 9, V, 2, 5, dtype, "logits", first_child=[1, 3, -1, 5, -1, 7, -1, -1, -1])
+    check_case(method, wl, seed=V, seqs=[0, 1, 15, 16, Bn // 2, Bn - 2, Bn - 1], full_outputs=V < 999)
+
+
+@pytest.mark.parametrize("method", ALL)
 @pytest.mark.parametrize("shift", [2.0 ** 20, -2.0 ** 23, 2.0 ** 26])
 def test_large_softmax_shifts(method, shift):
     """Logits that are whole multiples of 8, at T = 8, and the same logits (exactly, in fp32) far from 0, where the
