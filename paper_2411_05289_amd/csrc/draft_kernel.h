@@ -87,7 +87,7 @@ __global__ __launch_bounds__(kWG) void draft_kernel(const Params P)
         pass_weights_to_slabs<CV>(sq, cq, nullptr, 0, sh.slab_w);
     }
 
-    const Drawn d = draw_tokens<METHOD, DT>(rq, cq, sh, ur, k, a_virt, [] {});
+    const Drawn d = draw_tokens<METHOD, DT>(rq, cq, sh, ur, k, a_virt);
     if (d.here) sh.node_x[threadIdx.x & 63] = d.token;
     node_barrier();
     const int hub = METHOD == kSpecHub ? a_virt - rq.head : -1;

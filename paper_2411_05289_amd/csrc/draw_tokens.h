@@ -14,18 +14,15 @@
 
 namespace MDSD_NS {
 
-// One inverse-CDF draw by one wavefront: W the slab sums' total.  behind(): called once, behind the request for
-// the chunk that is searched, so that what the caller asks for there does not delay it (loads arrive in the
-// order in which they were asked for).  weights_of(raw, s, w): this lane's weights of slab s, of which it
-// holds the chunk `raw`.  Returns a virtual index, -1 without mass.
-template <int DT, class SlabVal, class WeightsOf, class Behind>
-__device__ __forceinline__ int draw_one(const RowView& rq, SlabVal sv, float W, float u, WeightsOf weights_of, Behind behind)
+// One inverse-CDF draw by one wavefront: W the slab sums' total.  weights_of(raw, s, w): this lane's weights
+// of slab s, of which it holds the chunk `raw`.  Returns a virtual index, -1 without mass.
+template <int DT, class SlabVal, class WeightsOf>
+__device__ __forceinline__ int draw_one(const RowView& rq, SlabVal sv, float W, float u, WeightsOf weights_of)
 {
     constexpr int E = Elem<DT>::kPerChunk;
     SlabHit h{0, 0.f, 0.f};
     const bool found = icdf_find_slab(rq.nslab, u, W, sv, h);
     const uint4 raw = fetch_chunk(rq, (found ? h.slab : 0) * 64 + (int)(threadIdx.x & 63));
-    behind();
     if (!found) return -1;
     float w[E];
     weights_of(raw, h.slab, w);
@@ -40,13 +37,12 @@ struct Drawn {
 
 // The draws of a node, called by all of its wavefronts.  SpecHub makes two side by side: from the row, and from the row
 // without the hub (the second token where the first draw gave the hub).  sh.slab_w: the slab sums of the row's
-// weights cq, visible behind the barrier that this function begins with (RRSw takes drawn tokens out of them).  u: the node's k uniforms.  a_virt: SpecHub,
-// the hub's virtual index.  behind(): called once by every wave, see draw_one().  Behind the caller's next barrier
-// sh.bcast_f is the record's rest_mass (SpecHub: the mass outside the hub, otherwise the whole row's).
+// weights cq, visible behind the barrier that this function begins with (RRSw takes drawn tokens out of them).  u: the
+// node's k uniforms.  a_virt: SpecHub, the hub's virtual index.  Behind the caller's next barrier sh.bcast_f is the
+// record's rest_mass (SpecHub: the mass outside the hub, otherwise the whole row's).
 // A token that is removed changes its slab's sum only, which is formed again without it (never by subtraction).
-template <int METHOD, int DT, class CV, class Behind>
-__device__ __forceinline__ Drawn draw_tokens(const RowView& rq, CV cq, Shared& sh, const float* u, int k, int a_virt,
-                                             Behind behind)
+template <int METHOD, int DT, class CV>
+__device__ __forceinline__ Drawn draw_tokens(const RowView& rq, CV cq, Shared& sh, const float* u, int k, int a_virt)
 {
     constexpr int E = Elem<DT>::kPerChunk;
     static_assert(kWaves >= 2, "SpecHub's two draws take a wave each");
@@ -68,7 +64,7 @@ __device__ __forceinline__ Drawn draw_tokens(const RowView& rq, CV cq, Shared& s
     };
     if constexpr (METHOD == kSpecHub) {
         if (wave == 0) {
-            put(0, draw_one<DT>(rq, sv, slab_total(rq.nslab, sv), u[0], weights, behind));
+            put(0, draw_one<DT>(rq, sv, slab_total(rq.nslab, sv), u[0], weights));
         } else if (wave == 1) {
             // the mass outside the hub: its slab's sum without it
             float w[E];
@@ -81,24 +77,16 @@ __device__ __forceinline__ Drawn draw_tokens(const RowView& rq, CV cq, Shared& s
             put(1, draw_one<DT>(rq, sv_rest, rest, u[1], [&](const uint4& raw, int s, float(&ww)[E]) {
                 weights(raw, s, ww);
                 zero_excluded<E>(ww, s * 64 + lane, &a_virt, 1);
-            }, behind));
-        } else {
-            behind();
+            }));
         }
     } else if constexpr (METHOD == kRRS) {
-        if (wave >= k) {
-            behind();
-        } else {
+        if (wave < k) {
             const float W = slab_total(rq.nslab, sv);
             if (wave == 0 && lane == 0) sh.bcast_f = W;
-            put(wave, draw_one<DT>(rq, sv, W, u[wave], weights, behind));
-            for (int i = wave + kWaves; i < k; i += kWaves) put(i, draw_one<DT>(rq, sv, W, u[i], weights, [] {}));
+            for (int i = wave; i < k; i += kWaves) put(i, draw_one<DT>(rq, sv, W, u[i], weights));
         }
     } else {
-        if (wave != 0) {
-            behind();
-            return out;
-        }
+        if (wave != 0) return out;
         for (int i = 0; i < k; ++i) {
             const float W = slab_total(rq.nslab, sv);
             if (i == 0 && lane == 0) sh.bcast_f = W;
@@ -115,8 +103,6 @@ __device__ __forceinline__ Drawn draw_tokens(const RowView& rq, CV cq, Shared& s
                 for (int j = 0; j < i; ++j) without(__builtin_amdgcn_readlane(out.token, j) + rq.head);
 #pragma unroll
                 for (int e = 0; e < E; ++e) ww[e] = w[e];
-            }, [&] {
-                if (i == 0) behind();
             });
             if (v >= 0 && i + 1 < k) {  // the last draw removes nothing
                 without(v);

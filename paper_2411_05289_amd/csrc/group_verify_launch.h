@@ -13,15 +13,15 @@ static void launch_group_verify_g(bool path, hipStream_t st, const Params& P)
                            dim3(kGroupThreads), 0, st, P);
         return;
     }
-    if constexpr (G < 64) {
-        if (P.accept_depth && wave_per_node(G, P.N, P.k, (int64_t)P.B * P.N)) {
-            const int trees = 64 / G;
-            hipLaunchKernelGGL((group_tree_kernel<DT, LG, METHOD, G>), dim3((unsigned)((P.B + trees - 1) / trees)),
-                               dim3(64 * P.N), 0, st, P);
-            return;
+    if (P.accept_depth && walks_in_workgroups(G, P.N, P.k, (int64_t)P.B * P.N)) {
+        if constexpr (G < 64) {
+            if (wave_per_node(G, P.N, P.k, (int64_t)P.B * P.N)) {
+                const int trees = 64 / G;
+                hipLaunchKernelGGL((group_tree_kernel<DT, LG, METHOD, G>), dim3((unsigned)((P.B + trees - 1) / trees)),
+                                   dim3(64 * P.N), 0, st, P);
+                return;
+            }
         }
-    }
-    if (P.accept_depth && group_walks_inside(G, P.N, (int64_t)P.B * P.N)) {
         const int threads = G * P.N <= kGroupThreads ? kGroupThreads : kGroupMaxThreads;
         const int trees = threads / G / P.N;
         hipLaunchKernelGGL((group_verify_kernel<DT, LG, METHOD, G, true>), dim3((unsigned)((P.B + trees - 1) / trees)),

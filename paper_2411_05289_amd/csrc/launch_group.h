@@ -61,6 +61,11 @@ __host__ __device__ constexpr bool table_by_waves(int lanes, bool bf16, int64_t 
 {
     return lanes == 4 && (!bf16 || nodes <= kTableByWavesMaxNodesBf16);
 }
+// Whether the call's workgroups hold whole trees and walk them, by either of the two.
+inline bool walks_in_workgroups(int lanes, int N, int k, int64_t nodes)
+{
+    return wave_per_node(lanes, N, k, nodes) || group_walks_inside(lanes, N, nodes);
+}
 // walk_nodes: nodes per tree where the launch is to walk the trees, else 1: half the lanes are taken where that
 // lets a workgroup hold a tree (rows of 60 bf16 elements, 2000 nodes in trees of 15: 32 lanes 11.9 us, 64 lanes with
 // the walk by arrival count 14.9), but not for rows of more than 96 chunks (1000 elements, 1050 nodes: 9.5 us with
@@ -80,7 +85,7 @@ inline int group_lanes(int64_t chunks, int64_t nodes, int walk_nodes, bool path)
     return g;
 }
 
-// Verify.  The walk is part of the launch (P.accept_depth set) where group_walks_inside() says so, or
+// Verify.  The walk is part of the launch (P.accept_depth set) where walks_in_workgroups() says so, or
 // with P.tree_count; otherwise it is the caller's.  path: one group per tree, the walk always inside.
 void launch_group_spechub(int lanes, int dtype, bool logits, bool path, hipStream_t st, const Params& P);
 void launch_group_rrs(int lanes, int dtype, bool logits, bool path, hipStream_t st, const Params& P);

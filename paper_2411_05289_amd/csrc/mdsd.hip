@@ -442,8 +442,7 @@ static int verify_entry(int method, const mdsd_problem* pb, const int32_t* token
     // short rows: where a workgroup holds whole trees it walks them without counting arrivals
     const int lanes = path ? 0 : verify_lanes(method, pb->dtype, P, false);
     const int64_t nodes = (int64_t)P.B * P.N;
-    const bool trees_whole = lanes && out->accept_depth &&
-                             (wave_per_node(lanes, P.N, P.k, nodes) || group_walks_inside(lanes, P.N, nodes));
+    const bool trees_whole = lanes && out->accept_depth && walks_in_workgroups(lanes, P.N, P.k, nodes);
     const bool walk_inside = !path && out->accept_depth && (tree_count || trees_whole);
     P.tree_count = walk_inside && !trees_whole ? tree_count : nullptr;
     if (pb->first_child && !lanes) P.n_internal = table_by_tree(method, pb);
