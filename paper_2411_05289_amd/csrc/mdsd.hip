@@ -274,14 +274,14 @@ static int wide_verify_chunks(int method, const mdsd_problem* pb, const Params& 
     if (resident_chunks(pb) == 16 && !P.stats_in && !P.masked && nodes <= kWideMaxNodes) return 0;
     return wide_chunks(P);
 }
-// Draft, up to 128 nodes with children.  A draw is a chain of barriers, each of which 16 wavefronts pass later
-// than eight, so that only rows whose passes outweigh their draws gain (12 and 120 nodes, 512 against 1024
-// threads): SpecHub on bf16 rows that are resident either way, from 2400 chunks on (rows of 20000 7.64 -> 7.47 and
-// 7.86 -> 7.77 us, 20001 8.31 -> 7.98, 32000 8.51 -> 8.15 and 9.02 -> 8.75; 16640 7.57 -> 7.69; fp32 rows of 12000
-// no difference, of 16500 7.4 -> 7.6), and RRS on aligned fp32 rows that 512 threads would stream (16500,
-// k = 2 6.53 -> 6.21 and 7.74 -> 6.96, 32000 8.11 -> 7.19; k = 4, whose draws weigh double, from 4608 chunks on:
-// 17200 7.87 -> 8.04, 20000 8.23 -> 7.90; 32001 9.69 -> 10.30).  Other RRS rows lose 2 to 8 %, without
-// replacement, every draw of which waits for the one before, 4 to 22 %.
+// Draft, up to 128 nodes with children (12 and 120 nodes, 512 against 1024 threads): SpecHub on bf16 rows that are
+// resident either way, from 2400 chunks on (rows of 20000 5.62 -> 5.52 and 5.81 -> 5.70 us, 24001 6.62 -> 6.24 and 6.81 ->
+// 6.57, 32000 6.37 -> 6.14 and 6.73 -> 6.63; 16640 5.45 -> 5.40 and 5.59 -> 5.72; fp32 rows of 12000 4.84 -> 4.86 and 4.96 ->
+// 5.05), and RRS on aligned fp32 rows that 512 threads would stream (k = 2, 16500 5.29 -> 4.59 and 6.22 -> 5.04, 32000 6.86 ->
+// 5.49 and 8.84 -> 7.11; k = 4, 20000 5.85 -> 4.99 and 6.67 -> 5.58).  Other resident rows of the RRS methods lose up to 6 %
+// (fp32 9000, bf16 16640 to 32000: -0.3 to +6).  Since every draw crosses one barrier, more of the rows that 512 threads stream
+// would gain, for which there is no kernel of 1024: k = 4 below 4608 chunks (16500 5.42 -> 4.77), fp32 32001 6.84 -> 5.95, RRSw
+// 32000 7.94 -> 6.58, SpecHub 32000 7.08 -> 6.51, bf16 50304 RRS 7.12 -> 6.28, RRSw 8.33 -> 7.42, SpecHub 7.94 -> 7.48.
 static bool wide_draft(int method, const mdsd_problem* pb, const Params& P)
 {
     const int64_t nodes = (int64_t)P.B * (P.first_child ? P.N : P.n_internal);

@@ -357,7 +357,7 @@ __device__ __forceinline__ void store_slab_sum(float* slab_w, int s, float lane_
 }
 
 // body(slab, chunk, a[E], b[E]) over two rows with the same head and length.  Streamed rows are
-// asked for AHEAD (1 or 2) steps before their use; the steps past the end read the rows' last
+// asked for AHEAD steps before their use; the steps past the end read the rows' last
 // chunks again and drop them.
 template <int AHEAD = 1, int DT, int NIT, int ENDS, class Body>
 __device__ __forceinline__ void for_each2(const RowSrc<DT, NIT, ENDS>& sa, const RowSrc<DT, NIT, ENDS>& sb,

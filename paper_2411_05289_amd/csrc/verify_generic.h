@@ -17,12 +17,10 @@ __device__ __forceinline__ float in_vgpr(float x)
 }
 
 // ---------------------------------------------------------------- verify kernel
-// Two workgroups per CU need 4 waves per SIMD, i.e. at most 128 VGPRs; the 16-chunk variant
-// holds 128 VGPRs of row data alone and runs one workgroup per CU.
-//
 // Ends of rows in registers by element where that measured faster than packed (packed -> by element, 4030 nodes):
-// SpecHub on fp32 probabilities of more than 512 chunks (9001 elements 37.1 -> 35.3 us, 3501 14.7 -> 13.8; path-only the
-// other way), the RRS methods on fp32 rows (2501 probabilities, RRS 17.6 -> 16.3; 2501 logits, RRSw 26.9 -> 25.2;
+// SpecHub on fp32 probabilities, 256 threads per node (3501 elements 14.7 -> 13.8 us; path-only the other way; 512 threads,
+// 15-node trees without records: 8000 elements, 240 nodes 7.6 -> 8.0, 4200 elements 480 nodes 7.0 -> 7.3, 2250 14.3 ->
+// 13.2), the RRS methods on fp32 rows (2501 probabilities, RRS 17.6 -> 16.3; 2501 logits, RRSw 26.9 -> 25.2;
 // path-only 24.3 -> 23.5) and RRS on bf16 probabilities (9001 40.6 -> 39.6), RRSw path-only on bf16 rows (124 nodes, 5001
 // probabilities 19.0 -> 17.2).  Packed ends keep the others: RRSw bf16 9001 73.6 -> 49.0.
 template <int DT, bool LOGITS, int METHOD, int NIT, bool PATH>
@@ -616,18 +614,30 @@ static void launch_verify_n(int nit, bool path, dim3 grid, dim3 block, hipStream
         hipLaunchKernelGGL((verify_path_kernel<DT, LG, METHOD, 0>), grid, block, 0, st, P);
         return;
     }
-    // logit rows that fit in registers have kernels of their own; rows of probabilities in registers: any
-    // size for SpecHub, the smallest for the RRS methods (whose rounds need the registers)
+    // logit rows that fit in registers have kernels of their own; rows of probabilities in registers: four chunks
+    // per lane at most, and only where they are not the better streamed
     if constexpr (!LG) {
         // SpecHub, 512 threads per node: streamed.  An internal node reads its draft row once, in one sweep, and both
         // rows again only where the first tests leave it undecided, and three nodes share a CU instead of the one or two
-        // whose rows its registers hold (registers -> streamed, 15-node trees, without records and with: fp32 rows of
-        // 32000, 480 nodes 25.7 -> 21.4 us, 20.2 -> 14.9; 4000 nodes 168 -> 118, 126 -> 92; bf16 20000, 480 nodes 14.5 -> 13.1,
-        // 4000 60 -> 57; fp32 8300 44 -> 43, 33 -> 28).  bf16 rows of four chunks per lane only in small batches (9000
-        // elements, 480 nodes 10.9 -> 10.1, 1500 15.0 -> 17.2).
-        constexpr bool kStreams = METHOD == kSpecHub && kWG == 512;
-        if constexpr (!kStreams || DT == 1) {
-            if (nit == 4 && !(kStreams && (int64_t)P.B * P.N <= 768)) {
+        // whose rows its registers hold (registers -> streamed, 15-node trees, verify alone without records and with: fp32
+        // rows of 32000, 15 nodes 13.3 -> 11.3 us, 8.2 -> 7.9, 480 24.1 -> 19.9, 16.9 -> 13.1, 2250 95 -> 67, 67 -> 52; of 9000, 15
+        // 7.1 -> 7.0, 5.0 -> 5.1, 480 10.1 -> 9.7, 7.6 -> 7.2; bf16 rows of 18000, 15 8.3 -> 7.9, 5.7 -> 5.7, 480 11.4 -> 10.5, 8.4 -> 7.9).
+        // Rows of four chunks per lane, of which a CU holds two nodes in registers, only in part:
+        // fp32, the longer ones where nodes share a CU (8001 elements, 240 nodes 7.6 -> 7.6, 5.3 -> 5.4, 480 9.7 -> 9.3, 7.3 ->
+        // 6.9, 2250 21.6 -> 21.2, 16.0 -> 14.8; 6001, 240 6.8 -> 7.1, 5.0 -> 5.2, 480 8.7 -> 8.3, 6.3 -> 6.0, 2250 16.9 -> 17.3,
+        // 13.1 -> 12.9; 4200, 480 7.0 -> 7.4, 5.2 -> 5.6, 2250 14.3 -> 15.8, 11.0 -> 12.2);
+        // bf16, twice the work per chunk, where a third node per CU saves a round, from 513 to 768 nodes (9000 elements, 480
+        // nodes 8.2 -> 8.3, 5.8 -> 6.1, 600 9.7 -> 9.3, 6.7 -> 6.8, 750 10.2 -> 9.5, 7.4 -> 7.1, 900 10.4 -> 10.0, 7.7 -> 8.2, 1200
+        // 11.8 -> 13.1, 8.4 -> 9.7), and the longer ones from 257 (14001 elements, 240 nodes 8.2 -> 8.0, 5.7 -> 5.8, 480 10.3 ->
+        // 9.6, 7.6 -> 7.0; 12000 7.6 -> 7.8, 5.4 -> 5.7, 9.5 -> 9.2, 6.8 -> 6.7).
+        if (nit == 4) {
+            bool streams = false;
+            if constexpr (METHOD == kSpecHub && kWG == 512) {
+                const int64_t nodes = (int64_t)P.B * P.N;
+                const bool longer = P.row_chunks > 1400;
+                streams = DT == 0 ? longer && nodes > 256 : nodes > (longer ? 256 : 512) && nodes <= 768;
+            }
+            if (!streams) {
                 hipLaunchKernelGGL((verify_kernel<DT, LG, METHOD, 4>), grid, block, 0, st, P);
                 return;
             }

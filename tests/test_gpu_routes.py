@@ -33,12 +33,17 @@ def _workload(Bn, N, V, k, depth, dtype, kind, off=0, temps=(0.9, 1.2), first_ch
 
 @pytest.mark.parametrize("method", ALL)
 @pytest.mark.parametrize("dtype,V,off,Bn", [
-    ("fp32", 4097, 0, 3),       # the shortest rows of eight wavefronts, most of which have one slab or two
+    ("fp32", 4097, 0, 3),       # the shortest rows of eight wavefronts, in registers
+    ("fp32", 8101, 3, 3),
+    ("fp32", 5601, 1, 87),      # streamed: 261 nodes of more than 1400 chunks
+    ("fp32", 9001, 0, 3),       # ... the shortest that always are
     ("fp32", 16384, 0, 3),      # eight slabs per wavefront, the last one full
     ("fp32", 16385, 0, 3),      # ... and one slab of one chunk more
     ("fp32", 18433, 3, 3),      # ... and one each, rows that begin inside a chunk
     ("fp32", 50001, 1, 3),
-    ("bf16", 9001, 5, 3),
+    ("bf16", 9001, 5, 3),       # in registers
+    ("bf16", 9001, 5, 171),     # streamed: 513 nodes
+    ("bf16", 14001, 3, 86),     # ... 258 nodes of longer rows
     ("bf16", 9001, 5, 260),     # in registers: more than 768 nodes
     ("bf16", 32768, 0, 3),
     ("bf16", 33281, 7, 3),
