@@ -84,17 +84,22 @@ def test_tables_of_large_batches(method, V, dtype, Bn):
 
 
 @pytest.mark.parametrize("method", ALL)
-@pytest.mark.parametrize("shift", [2.0 ** 20, -2.0 ** 23, 2.0 ** 26])
-def test_large_softmax_shifts(method, shift):
-    """Logits that are whole multiples of 8, at T = 8, and the same logits (exactly, in fp32) far from 0, where the
-    shift of the target's weights cannot move by single steps: the same outcomes, tokens and residual masses."""
+@pytest.mark.parametrize("records", [True, False])
+@pytest.mark.parametrize("step,shift", [(8.0, 2.0 ** 20), (8.0, -2.0 ** 23), (8.0, 2.0 ** 26), (8.0, 15e6 * 8), (8.0, -16e6 * 8),
+                                        (16.0, -15e6 * 16), (64.0, 15e6 * 64), (64.0, -16e6 * 64)])
+def test_large_softmax_shifts(method, step, shift, records):
+    """Logits that are whole multiples of a step, at T = 8, and the same logits (exactly, in fp32) far from 0, where the
+    softmax shift takes large values, 1.9e5 to 1.2e7 and, from 15e6 steps on, 2^24.4 to 2^27.5, where it does not take every
+    whole number: the same outcomes, tokens and residual masses."""
     wl = _workload(4, 3, 9000, 2, 2, "fp32", "logits")
     u = torch.rand((4, 3, 3), generator=torch.Generator(device=DEV).manual_seed(1), device=DEV)
     results = []
     for by in (0.0, shift):
-        t, d = (torch.round(x) * 8 + by for x in (wl.target, wl.draft))
-        assert torch.equal(t - by, torch.round(wl.target) * 8)
-        pb = B.Problem(t, d, B.LOGITS, 2, 2, 8.0, 8.0).with_draft_stats()
+        t, d = (torch.round(x) * step + by for x in (wl.target, wl.draft))
+        assert torch.equal(t - by, torch.round(wl.target) * step)
+        pb = B.Problem(t, d, B.LOGITS, 2, 2, 8.0, 8.0)
+        if records:
+            pb = pb.with_draft_stats()
         drafted = DRAFT[method](pb, u[..., :2].contiguous())
         results.append((drafted["tokens"][:, 1:], VERIFY[method](pb, drafted["tokens"], u, resid_mass=True)))
     (tokens, want), (tokens_far, got) = results
