@@ -58,7 +58,8 @@ def parse():
     ap.add_argument("--walk-in-verify", action="store_true",
                     help="two launches per step whatever the batch size: the verify kernel walks each tree "
                          "itself when the tree's last node is done (the default up to "
-                         "binding.WALK_IN_VERIFY_MAX_NODES tree nodes per batch, three launches beyond)")
+                         "binding.WALK_IN_VERIFY_MAX_NODES tree nodes per batch and for the toy experiment, three launches "
+                         "beyond)")
     ap.add_argument("--graph", action="store_true",
                     help="replay one HIP graph per step instead of launching its kernels one by one "
                          "(measured slower on this workload: 58.8 against 53.8 us per step)")
@@ -163,8 +164,9 @@ def main():
     stream = B._stream()
 
     # where the tree walk runs: inside the verify kernel (two launches per step) or as a launch
-    # of its own (three); by default the binding's rule by batch size decides
-    fused = plans[0].walk_in_verify
+    # of its own (three); by default as StepPlan.run() places it: by the binding's rule by batch size, and the toy
+    # experiment's trees, whose rows are short, in the verify kernel's workgroups at any size
+    fused = plans[0].walk_in_verify or toy
     if args.separate_walk:
         fused = False
     if args.walk_in_verify:
