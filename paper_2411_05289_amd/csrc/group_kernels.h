@@ -961,7 +961,7 @@ __global__ __launch_bounds__(kGroupMaxThreads, kGroupWavesPerSimd) void group_ve
 }
 
 // Wavefront n of a workgroup takes node n of 64 / G trees; the one that comes last walks them (see wave_per_node()).
-// Bound by instruction issue (toy workload: 77 % of the kernel's time, 490 instructions per wavefront of 16 nodes).
+// Bound by instruction issue (toy workload: 77 % of the kernel's time, 492 instructions per wavefront of 16 nodes).
 template <int DT, bool LOGITS, int METHOD, int G>
 __global__ __launch_bounds__(kGroupMaxThreads, kGroupWavesPerSimd) void group_tree_kernel(const Params P)
 {

@@ -33,7 +33,7 @@ inline bool group_walks_inside(int lanes, int N, int64_t nodes)
 }
 // Where the call walks its trees: wavefront n of a workgroup takes node n of 64 / lanes trees, and the one that comes last
 // walks them.  A wavefront's nodes are of one kind, nothing is divided to find them, none waits for the others, and a tree's
-// rows, which share cache lines where they are short, are read by the same CU (toy workload: 149 -> 108 MB, 29 us with the
+// rows, which share cache lines where they are short, are read by the same CU (toy workload: 148 -> 111 MB, 29 us with the
 // walk's launch -> 26).  Its price is that a workgroup starts only where all its wavefronts find a place.  Against
 // workgroups that hold whole trees of mixed wavefronts (group_walks_inside()) it wins with k = 2 at every size (7-node
 // trees, 14000 nodes: 400 bf16 elements 12.3 -> 9.6 us, 900 24.2 -> 20.3; 3-node trees, 6000 nodes of 16 fp32 6.2 -> 4.8); k = 4,
