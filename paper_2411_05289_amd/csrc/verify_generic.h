@@ -81,7 +81,7 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
         }
         float W = 0.f;
         int v = -1;
-        if (PATH || rprob || wave_id() == 0) v = draw_from_row<DT, CV>(rp, cp, nullptr, 0, sh.slab_w, ur[k], W);
+        if (PATH || kWaves == 1 || rprob || wave_id() == 0) v = draw_from_row<DT, CV>(rp, cp, nullptr, 0, sh.slab_w, ur[k], W);
         token = v < 0 ? -1 : v - rp.head;
         if (v < 0) flags |= MDSD_FLAG_ZERO_RESIDUAL;
         rmass = LOGITS ? 1.f : W;
@@ -106,9 +106,16 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
         CV cp{0.f, 0.f}, cq{0.f, 0.f};
 
         if constexpr (METHOD == kSpecHub) {
-            const int x1 = xt[0], x2 = xt[1];
-            const bool tokens_ok = x1 >= 0 && x1 < P.V && x2 >= 0 && x2 < P.V;
-            // probabilities at the pair: asked for ahead of the rows, at indices brought into them
+            // The pair is read ahead of the rows (960 nodes of 9000 bf16 probabilities, read where it is tested: step 16.3 -> 16.5
+            // us; 6200 of 6000 bf16 logits 40.9 -> 41.2), but not by single wavefronts (60000 nodes of 736 fp32 logits 84.6 us, read
+            // here 85.9; of 832 bf16, 43000 nodes, 57.2 and 57.9).
+            constexpr bool kPairLate = kWaves == 1 && !kProbsStreamed;
+            int x1 = -1, x2 = -1;
+            if constexpr (!kPairLate) {
+                x1 = xt[0];
+                x2 = xt[1];
+            }
+            // streamed probabilities: those at the pair are asked for too, at indices brought into the rows
             float p_x1 = 0.f, q_x1 = 0.f, p_x2 = 0.f, q_x2 = 0.f;
             if constexpr (kProbsStreamed) {
                 const int c1 = min(max(x1, 0), P.V - 1), c2 = min(max(x2, 0), P.V - 1);
@@ -220,6 +227,11 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
             const float pa = ea_p * h.iZp;
             const float qa = ea_q * h.iZq;
 
+            if constexpr (kPairLate) {
+                x1 = xt[0];
+                x2 = xt[1];
+            }
+            const bool tokens_ok = x1 >= 0 && x1 < P.V && x2 >= 0 && x2 < P.V;
             bool decided = false, degenerate = false;
             int hub_slot = -1;  // slot of the hub token in the pair
             if (have_stats && st.hub < 0) {  // no usable record for this node
@@ -335,7 +347,7 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
                     bool wrote_prob = false;
                     if (!decided) {
                         int v = -1;
-                        if (W > 0.f && (PATH || wave_id() == 0)) v = icdf_slabs<E>(rp.nslab, ur[2], W, sv, cw);
+                        if (W > 0.f && (PATH || kWaves == 1 || wave_id() == 0)) v = icdf_slabs<E>(rp.nslab, ur[2], W, sv, cw);
                         if (!(W > 0.f)) {
                             // no residual mass: fall back to p itself
                             flags |= MDSD_FLAG_ZERO_RESIDUAL;
