@@ -249,6 +249,22 @@ int rrsw_verify(const mdsd_problem* pb, const int32_t* tokens, const float* u,
                 const mdsd_result* out, void* ws, size_t ws_bytes, void* stream);
 
 /*
+ * spechub_step / rrs_step / rrsw_step -- the draft call and the verify call of a method in one, for callers
+ * that hold both rows of every node already (measured logits, acceptance studies, simulations): the same
+ * arguments, outputs and errors as the two calls one after the other, everything checked before
+ * anything is launched.  With pb->draft_stats set, and neither out->resid_mass nor
+ * out->resid_prob, most rows are drafted and verified by one kernel that reads each row once as
+ * far as the method allows; other calls launch the two.  ws as for the verify calls.
+ */
+int spechub_step(const mdsd_problem* pb, const float* u_draft, const float* u_verify, int32_t* tokens,
+                 int32_t* hub, int32_t* draft_flags, const mdsd_result* out, void* ws, size_t ws_bytes,
+                 void* stream);
+int rrs_step(const mdsd_problem* pb, const float* u_draft, const float* u_verify, int32_t* tokens,
+             int32_t* draft_flags, const mdsd_result* out, void* ws, size_t ws_bytes, void* stream);
+int rrsw_step(const mdsd_problem* pb, const float* u_draft, const float* u_verify, int32_t* tokens,
+              int32_t* draft_flags, const mdsd_result* out, void* ws, size_t ws_bytes, void* stream);
+
+/*
  * spechub_verify_path / rrs_verify_path / rrsw_verify_path -- the same verification
  * restricted to the nodes that decide what the step emits (Sec. 2: verification follows the
  * accepted tokens down the tree and stops at the first node that accepts none; the nodes

@@ -22,11 +22,12 @@ HOST_PATH = os.path.join(_HERE, "_host.so")
 
 FP32, BF16 = 0, 1
 PROBS, LOGITS = 0, 1
+E_LAUNCH = -8
 NONE, BAD_PAIR, BAD_TOKEN, UNVISITED = -1, -2, -3, -4
 FLAG_DEGENERATE_HUB, FLAG_ZERO_RESIDUAL, FLAG_Q_EXHAUSTED, FLAG_BAD_PAIR, FLAG_BAD_TOKEN = 1, 2, 4, 8, 16
 
 EXPORTS = ("mdsd_workspace_bytes", "spechub_draft", "spechub_verify", "spechub_verify_static", "rrs_draft", "rrsw_draft",
-           "rrs_verify", "rrsw_verify", "spechub_verify_path", "rrs_verify_path", "rrsw_verify_path",
+           "rrs_verify", "rrsw_verify", "spechub_step", "rrs_step", "rrsw_step", "spechub_verify_path", "rrs_verify_path", "rrsw_verify_path",
            "mdsd_tree_walk", "mdsd_philox_uniform", "mdsd_strerror", "mdsd_version")
 
 
@@ -84,6 +85,11 @@ def lib():
             f.argtypes = vv
             f.restype = C.c_int
         for f in (L.spechub_draft, L.rrs_draft, L.rrsw_draft):
+            f.restype = C.c_int
+        L.rrs_step.argtypes = [C.c_void_p] * 7 + [C.c_size_t, C.c_void_p]
+        L.rrsw_step.argtypes = L.rrs_step.argtypes
+        L.spechub_step.argtypes = [C.c_void_p] * 8 + [C.c_size_t, C.c_void_p]
+        for f in (L.spechub_step, L.rrs_step, L.rrsw_step):
             f.restype = C.c_int
         L.spechub_verify_static.argtypes = [C.c_void_p] * 5
         L.spechub_verify_static.restype = C.c_int
@@ -458,6 +464,13 @@ class StepPlan:
         fresp = C.byref(fres)
         self._verify_walk = lambda st: vfn(pbp, tk, uv, fresp, wsp, wsn, st)
         self._verify_then_walk = lambda st: vfn(pbp, tk, uv, fresp, None, 0, st)
+        # draft and verify in one call, the walk placed as above
+        wsa = (wsp, wsn) if self.walk_in_verify else (None, 0)
+        if method == "spechub":
+            self._step = lambda st: L.spechub_step(pbp, ud, uv, tk, hb, df, fresp, *wsa, st)
+        else:
+            sfn = L.rrs_step if method == "rrs" else L.rrsw_step
+            self._step = lambda st: sfn(pbp, ud, uv, tk, df, fresp, *wsa, st)
         # path-only: its result structure carries the walk outputs, the walk is in the kernel
         pres = _Result()
         for name in ("outcome", "token", "flags", "accept_depth", "emitted"):
@@ -497,11 +510,17 @@ class StepPlan:
             raise MdsdError(rc, "mdsd_tree_walk")
 
     def run(self, stream=None):
+        """The whole step, draft() and the verification with its walk, in one call."""
         st = _stream() if stream is None else stream
-        self.draft(st)
-        rc = self._verify_walk(st) if self.walk_in_verify else self._verify_then_walk(st)
+        rc = self._step(st)
+        if rc == E_LAUNCH:
+            raise MdsdError(rc, self.method + "_step")
         if rc != 0:
-            raise MdsdError(rc, self.method + "_verify")
+            # refused before anything was launched: the call that refuses it says so
+            self.draft(st)
+            rc = self._verify_walk(st) if self.walk_in_verify else self._verify_then_walk(st)
+            if rc != 0:
+                raise MdsdError(rc, self.method + "_verify")
         return self.out
 
 

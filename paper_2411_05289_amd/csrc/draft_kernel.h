@@ -7,32 +7,36 @@
 
 namespace MDSD_NS {
 
-// ---------------------------------------------------------------- draft kernel
-template <int DT, bool LOGITS, int METHOD, int NIT, bool MASKED = true>
-__global__ __launch_bounds__(kWG) void draft_kernel(const Params P)
+// ---------------------------------------------------------------- one node's draft
+// Entries of a leaf, which drafts nothing, by the node's first thread.
+__device__ __forceinline__ void write_leaf_draft(const Params& P, const NodeId& id, int32_t* flags)
+{
+    if ((int)threadIdx.x != 0) return;
+    if (P.hub_out) P.hub_out[id.row] = -1;
+    if (flags) flags[id.row] = 0;
+    if (P.stats_out) P.stats_out[id.row] = mdsd_row_stats{0.f, 0.f, -1, 0};
+}
+
+// What a node's draft leaves with its threads: the record of the draft row in all of them, draft token i in
+// thread i < k.  (SpecHub: sh.node_x still holds the draws that token_of_draws() reads.)
+struct NodeDraft {
+    mdsd_row_stats record;
+    int token;
+};
+
+// The k draft tokens of a node with children, with their record, written to memory and returned.  u: the node's k
+// uniforms; flags: where draft flags go, or nullptr.  row_done(row) is called once the row's slab sums are on their way
+// to LDS; the registers that hold the row are free behind it.  LEFT: see draw_tokens().
+template <int DT, bool LOGITS, int METHOD, int NIT, bool MASKED, bool LEFT = false, class RowDone>
+__device__ __forceinline__ NodeDraft draft_node(const Params& P, const NodeId& id, const RowView& rq, const float* u,
+                                                int32_t* flags_out, Shared& sh, int& phase, RowDone row_done)
 {
     using CV = ToWeight<LOGITS>;
-    __shared__ Shared sh;
-    int phase = 0;
-    // one group of kWG threads per node; a leaf only records that it has no hub
-    const NodeId id = node_of_block(P);
-    const int b = id.b, n = id.n, c0 = id.c0;
     const int64_t row = id.row;
-    if (n == 0 && (int)threadIdx.x == 0) P.tokens_out[(int64_t)b * P.N] = -1;
-    if (c0 < 0) {
-        if ((int)threadIdx.x == 0) {
-            if (P.hub_out) P.hub_out[row] = -1;
-            if (P.flags) P.flags[row] = 0;
-            if (P.stats_out) P.stats_out[row] = mdsd_row_stats{0.f, 0.f, -1, 0};
-        }
-        return;
-    }
     const int k = P.k;
-    const float* ur = P.u + row * k;
-    const RowView rq = make_row<DT>(P.draft, P.ld_d, row, P.V);
     RowSrc<DT, NIT, MASKED ? kEndsPacked : kNoEnds> sq;
     sq.init(rq, CV::fill());
-    int32_t* xt = P.tokens_out + (int64_t)b * P.N + c0;
+    int32_t* xt = P.tokens_out + (int64_t)id.b * P.N + id.c0;
 
     CV cq{0.f, 0.f};
     int a_virt = rq.head;
@@ -87,17 +91,41 @@ __global__ __launch_bounds__(kWG) void draft_kernel(const Params P)
         pass_weights_to_slabs<CV>(sq, cq, nullptr, 0, sh.slab_w);
     }
 
-    const Drawn d = draw_tokens<METHOD, DT>(rq, cq, sh, ur, k, a_virt);
+    row_done(sq);
+
+    const Drawn d = draw_tokens<METHOD, DT, LEFT>(rq, cq, sh, u, k, a_virt);
     if (d.here) sh.node_x[threadIdx.x & 63] = d.token;
     node_barrier();
     const int hub = METHOD == kSpecHub ? a_virt - rq.head : -1;
     int flags = 0;
-    if ((int)threadIdx.x < k) xt[threadIdx.x] = token_of_draws<METHOD>(sh, k, hub, (int)threadIdx.x, flags);
-    if ((int)threadIdx.x == 0) {
-        if (P.stats_out) P.stats_out[row] = mdsd_row_stats{mm[0], sh.bcast_f, hub, 0};
-        if (P.hub_out) P.hub_out[row] = hub;
-        if (P.flags) P.flags[row] = flags;
+    NodeDraft out{mdsd_row_stats{mm[0], sh.bcast_f, hub, 0}, -1};
+    if ((int)threadIdx.x < k) {
+        out.token = token_of_draws<METHOD>(sh, k, hub, (int)threadIdx.x, flags);
+        xt[threadIdx.x] = out.token;
     }
+    if ((int)threadIdx.x == 0) {
+        if (P.stats_out) P.stats_out[row] = out.record;
+        if (P.hub_out) P.hub_out[row] = hub;
+        if (flags_out) flags_out[row] = flags;
+    }
+    return out;
+}
+
+// ---------------------------------------------------------------- draft kernel
+template <int DT, bool LOGITS, int METHOD, int NIT, bool MASKED = true>
+__global__ __launch_bounds__(kWG) void draft_kernel(const Params P)
+{
+    __shared__ Shared sh;
+    int phase = 0;
+    // one group of kWG threads per node; a leaf only records that it has no hub
+    const NodeId id = node_of_block(P);
+    if (id.n == 0 && (int)threadIdx.x == 0) P.tokens_out[(int64_t)id.b * P.N] = -1;
+    if (id.c0 < 0) {
+        write_leaf_draft(P, id, P.flags);
+        return;
+    }
+    const RowView rq = make_row<DT>(P.draft, P.ld_d, id.row, P.V);
+    draft_node<DT, LOGITS, METHOD, NIT, MASKED>(P, id, rq, P.u + id.row * P.k, P.flags, sh, phase, [](const auto&) {});
 }
 
 template <int DT, bool LG, int METHOD>

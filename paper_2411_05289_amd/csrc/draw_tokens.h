@@ -41,7 +41,8 @@ struct Drawn {
 // node's k uniforms.  a_virt: SpecHub, the hub's virtual index.  Behind the caller's next barrier sh.bcast_f is the
 // record's rest_mass (SpecHub: the mass outside the hub, otherwise the whole row's).
 // A token that is removed changes its slab's sum only, which is formed again without it (never by subtraction).
-template <int METHOD, int DT, class CV>
+// LEFT (RRSw): sh.bcast_left is then the mass outside all k drafted tokens.
+template <int METHOD, int DT, bool LEFT = false, class CV>
 __device__ __forceinline__ Drawn draw_tokens(const RowView& rq, CV cq, Shared& sh, const float* u, int k, int a_virt)
 {
     constexpr int E = Elem<DT>::kPerChunk;
@@ -104,7 +105,7 @@ __device__ __forceinline__ Drawn draw_tokens(const RowView& rq, CV cq, Shared& s
 #pragma unroll
                 for (int e = 0; e < E; ++e) ww[e] = w[e];
             });
-            if (v >= 0 && i + 1 < k) {  // the last draw removes nothing
+            if (v >= 0 && (LEFT || i + 1 < k)) {  // nothing is drawn behind the last draw
                 without(v);
                 const float sum = wave_sum(chunk_sum<E>(w));
                 // this wave's LDS instructions run in order; the compiler has to keep them so
@@ -114,6 +115,21 @@ __device__ __forceinline__ Drawn draw_tokens(const RowView& rq, CV cq, Shared& s
                 __builtin_amdgcn_wave_barrier();
             }
             put(i, v);
+        }
+        if constexpr (LEFT) {
+            if (__builtin_amdgcn_readlane(out.token, 0) < 0) {  // no mass (or a NaN): token 0 is the draft, see token_of_draws()
+                float w[E];
+                weights(fetch_chunk(rq, lane), 0, w);
+                const int token0 = rq.head;
+                zero_excluded<E>(w, lane, &token0, 1);
+                const float sum = wave_sum(chunk_sum<E>(w));
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                if (lane == 0) sh.slab_w[0] = sum;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
+            const float left = slab_total(rq.nslab, sv);
+            if (lane == 0) sh.bcast_left = left;
         }
     }
     return out;

@@ -15,6 +15,11 @@ void launch_rrs_resident(int dtype, int nit, bool masked, dim3 grid, dim3 block,
 void launch_rrsw_resident(int dtype, int nit, bool masked, dim3 grid, dim3 block, hipStream_t st, const Params& P);
 
 // verify_generic_*.hip: every other case (nit = 0: rows streamed in every pass)
+// drafting and verifying a node in one launch (step_resident_kernels.h)
+void launch_step_spechub(int dtype, int nit, bool masked, dim3 grid, hipStream_t st, const Params& P);
+void launch_step_rrs(int dtype, int nit, bool masked, dim3 grid, hipStream_t st, const Params& P);
+void launch_step_rrsw(int dtype, int nit, bool masked, dim3 grid, hipStream_t st, const Params& P);
+
 void launch_verify_generic_spechub(int dtype, bool logits, int nit, bool path, dim3 grid, dim3 block,
                                    hipStream_t st, const Params& P);
 void launch_verify_generic_rrs(int dtype, bool logits, int nit, bool path, dim3 grid, dim3 block, hipStream_t st,

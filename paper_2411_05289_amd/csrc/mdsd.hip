@@ -520,6 +520,85 @@ static int draft_entry(int method, const mdsd_problem* pb, const float* u, int32
     return hipGetLastError() == hipSuccess ? MDSD_OK : MDSD_E_LAUNCH;
 }
 
+// Steps, 256 threads per node instead of 512 (half the reductions and barriers per element, all nodes with children of the
+// serving batch on the chip at once, but twice the chain per node): from how many nodes on (512 -> 256 threads, us a
+// step, 31-node trees unless noted).  Rows of four chunks per lane at 512 threads, k = 2: bf16 12000, 1488 nodes
+// SpecHub 21.3 -> 21.0, RRS 22.3 -> 22.5, 1736 24.2 -> 23.2, 26.9 -> 25.4, 3968 47.1 -> 39.0, 49.6 -> 43.7; fp32 7001,
+// 1240 18.0 -> 20.3, 1736 23.7 -> 22.4, RRSw 29.0 -> 26.5.  Eight chunks, SpecHub on aligned rows: bf16 32000, 1736 44.4
+// -> 45.2, 1984 48.7 -> 46.9, 26000 42.4 -> 39.8.  The others of eight chunks: SpecHub 28001, 1984 46.5 -> 47.7, 2480 56.5
+// -> 59.8, 2976 65.7 -> 65.0; RRS 32000, 2480 60.5 -> 62.1, 2976 69.1 -> 67.9, 3968 87.9 -> 83.9, RRSw 64.7 -> 65.6, 73.4 ->
+// 71.5.  k = 4, whose nodes wait longest for one another, as those (12000, 1680 24.0 -> 25.8; 30000, 2310 53.4 -> 56.7).
+static bool half_width_step(int method, const Params& P, int nit)
+{
+    const int64_t nodes = (int64_t)P.B * P.N;
+    if (nit > 8) return false;
+    if (P.k > 2) return nodes >= 2900;
+    return nodes >= (nit == 4 ? 1600 : method == kSpecHub && !P.masked ? 1900 : 2900);
+}
+
+// A step's kernel that drafts and verifies every node in one launch; false: there is none for this call.
+static bool launch_step(int method, const mdsd_problem* pb, const Params& P, hipStream_t st)
+{
+    if (pb->kind != MDSD_LOGITS || P.stats_out == nullptr || P.resid_mass || P.resid_prob) return false;
+    if (verify_lanes(method, pb->dtype, P, false) || small_build(pb)) return false;
+    const int nit = resident_chunks(pb);
+    if (nit == 0 || wide_verify_chunks(method, pb, P, false)) return false;
+    const bool masked = rows_need_mask(pb);
+    const dim3 grid = node_grid(P, nit);
+    if (half_width_step(method, P, nit)) {
+        mdsd_half::launch_step(method, pb->dtype, 2 * nit, masked, grid, st, P);
+        return true;
+    }
+    (method == kSpecHub ? launch_step_spechub : method == kRRS ? launch_step_rrs : launch_step_rrsw)(pb->dtype, nit, masked,
+                                                                                                   grid, st, P);
+    return true;
+}
+
+// draft and verification in one call, in one launch where there is a kernel for it
+static int step_entry(int method, const mdsd_problem* pb, const float* u_draft, const float* u_verify, int32_t* tokens,
+                      int32_t* hub, int32_t* draft_flags, const mdsd_result* out, int32_t* tree_count, void* stream)
+{
+    Params P = {};
+    const int rc = validate(pb, method, true, &P);
+    if (rc == kEmptyBatch) return MDSD_OK;
+    if (rc != MDSD_OK) return rc;
+    if (!u_draft || !u_verify || !tokens || !out || !out->outcome || !out->token) return MDSD_E_NULL;
+    if ((out->accept_depth == nullptr) != (out->emitted == nullptr)) return MDSD_E_NULL;
+    P.accept_depth = out->accept_depth;
+    P.emitted = out->emitted;
+    P.tree_count = out->accept_depth ? tree_count : nullptr;
+    if (pb->first_child) P.n_internal = table_by_tree(method, pb);
+    P.u_draft = u_draft;
+    P.u = u_verify;
+    P.tokens = P.tokens_out = tokens;
+    P.hub_out = hub;
+    P.draft_flags = draft_flags;
+    P.outcome = out->outcome;
+    P.token = out->token;
+    P.resid_mass = out->resid_mass;
+    P.flags = out->flags;
+    P.resid_prob = out->resid_prob;
+    P.stats_in = P.stats_out = pb->draft_stats;
+    hipStream_t st = (hipStream_t)stream;
+    (void)hipGetLastError();
+    if (launch_step(method, pb, P, st)) {
+        if (hipGetLastError() != hipSuccess) return MDSD_E_LAUNCH;
+        if (P.accept_depth && !P.tree_count) return walk(pb, P.outcome, P.token, P.accept_depth, P.emitted, st);
+        return MDSD_OK;
+    }
+    const int drafted = draft_entry(method, pb, u_draft, tokens, hub, draft_flags, stream);
+    return drafted != MDSD_OK ? drafted : verify_entry(method, pb, tokens, u_verify, out, false, tree_count, stream);
+}
+
+static int step_with_workspace(int method, const mdsd_problem* pb, const float* u_draft, const float* u_verify,
+                               int32_t* tokens, int32_t* hub, int32_t* draft_flags, const mdsd_result* out, void* ws,
+                               size_t ws_bytes, void* stream)
+{
+    if (ws && pb && ws_bytes < walk_workspace_bytes(pb->B)) return MDSD_E_WORKSPACE;
+    if (ws && ((uintptr_t)ws & 3)) return MDSD_E_ALIGN;
+    return step_entry(method, pb, u_draft, u_verify, tokens, hub, draft_flags, out, (int32_t*)ws, stream);
+}
+
 }  // namespace mdsd
 
 // ---------------------------------------------------------------- C ABI
@@ -584,6 +663,27 @@ int rrsw_verify(const mdsd_problem* pb, const int32_t* tokens, const float* u, c
                 void* ws, size_t ws_bytes, void* stream)
 {
     return mdsd::verify_with_workspace(mdsd::kRRSw, pb, tokens, u, out, ws, ws_bytes, stream);
+}
+
+int spechub_step(const mdsd_problem* pb, const float* u_draft, const float* u_verify, int32_t* tokens, int32_t* hub,
+                 int32_t* draft_flags, const mdsd_result* out, void* ws, size_t ws_bytes, void* stream)
+{
+    return mdsd::step_with_workspace(mdsd::kSpecHub, pb, u_draft, u_verify, tokens, hub, draft_flags, out, ws, ws_bytes,
+                                     stream);
+}
+
+int rrs_step(const mdsd_problem* pb, const float* u_draft, const float* u_verify, int32_t* tokens, int32_t* draft_flags,
+             const mdsd_result* out, void* ws, size_t ws_bytes, void* stream)
+{
+    return mdsd::step_with_workspace(mdsd::kRRS, pb, u_draft, u_verify, tokens, nullptr, draft_flags, out, ws, ws_bytes,
+                                     stream);
+}
+
+int rrsw_step(const mdsd_problem* pb, const float* u_draft, const float* u_verify, int32_t* tokens, int32_t* draft_flags,
+              const mdsd_result* out, void* ws, size_t ws_bytes, void* stream)
+{
+    return mdsd::step_with_workspace(mdsd::kRRSw, pb, u_draft, u_verify, tokens, nullptr, draft_flags, out, ws, ws_bytes,
+                                     stream);
 }
 
 int spechub_verify_path(const mdsd_problem* pb, const int32_t* tokens, const float* u, const mdsd_result* out,

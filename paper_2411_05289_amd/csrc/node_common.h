@@ -45,6 +45,7 @@ struct Shared {
     float slab_w[kMaxSlabs];
     float bcast_f;  // one value handed from one lane to the workgroup
     int bcast_i;
+    float bcast_left;
     // RRS path for rows in registers: the node's draft tokens, the stored logits at them, the uniforms
     int node_x[MDSD_MAX_K];
     float node_lp[MDSD_MAX_K], node_lq[MDSD_MAX_K], node_u[MDSD_MAX_K + 1];

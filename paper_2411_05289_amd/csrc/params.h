@@ -35,7 +35,10 @@ struct Params {
     // draft kernels
     int32_t* tokens_out;
     int32_t* hub_out;
-    // draft-row statistics: written by the SpecHub draft kernel, read by the SpecHub verify kernel
+    // step kernels, which draft and verify a node in one go: u and flags are the verify call's
+    const float* u_draft;
+    int32_t* draft_flags;
+    // draft-row statistics: written by the draft kernels, read by the verify kernels
     mdsd_row_stats* stats_out;
     const mdsd_row_stats* stats_in;
 };

@@ -2,7 +2,7 @@
 // Device code and kernels; the launchers are in the translation units that include this file
 // (rrs_resident.hip: the main build; half_verify.hip: 256 threads per node).
 #pragma once
-#include "launch.h"
+#include "draft_kernel.h"
 
 namespace MDSD_NS {
 
@@ -31,12 +31,16 @@ constexpr int kDraftChunksKept = kWG == 1024  ? (NIT < 9 ? NIT : 9)
                                  : kWG == 256 ? (NIT < 7 ? NIT : 7)
                                               : (NIT < 5 ? NIT : 5);
 
-template <int DT, int NIT, bool MASKED, bool WO, bool STATS>
+// STEP: the node was drafted here a moment ago: `drafted` has its tokens and its record, and without replacement
+// sh.bcast_left the draft mass outside the drafted tokens.  KEPT_AT_ENTRY: q_kept holds the draft row's first chunks.
+template <int DT, int NIT, bool MASKED, bool WO, bool STATS, bool STEP = false, bool KEPT_AT_ENTRY = false>
 __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, const RowView& rp,
                                              const RowView& rq, const RowSrc<DT, NIT, MASKED>& sp,
                                              bool need_full, float* rprob, Shared& sh,
-                                             uint4 (*q_kept)[kWG], int& phase, NodeOut& o)
+                                             uint4 (*q_kept)[kWG], int& phase, NodeOut& o,
+                                             const NodeDraft* drafted = nullptr)
 {
+    static_assert(STATS || !STEP, "a step has its record");
     constexpr int E = Elem<DT>::kPerChunk;
     constexpr int HE = E / 2;
     using Src = RowSrc<DT, NIT, MASKED>;
@@ -44,19 +48,24 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
     const float* ur = P.u + id.row * (k + 1);
     const int32_t* xt = P.tokens + (int64_t)id.b * P.N + id.c0;
     mdsd_row_stats st;
-    if constexpr (STATS) st = P.stats_in[id.row];
+    if constexpr (STEP)
+        st = drafted->record;
+    else if constexpr (STATS)
+        st = P.stats_in[id.row];
     // tokens, the stored logits at them and the uniforms go through LDS (lane i of the first wave
     // fetches draft i), so that no lane holds arrays of them; visible after the first barrier.
     // The tokens and uniforms come over the scalar path (their addresses are the same in every
     // lane), so that waiting for a token does not wait for the row behind it; the look-ups at the
     // tokens are then queued right behind the row, at indices brought into it, and arrive with it.
     int x = -1;
+    if constexpr (STEP) x = drafted->token;
     float u_mine = 0.f;
     for (int i = 0; i < k; ++i) {
-        const int xi = xt[i];
+        int xi = -1;
+        if constexpr (!STEP) xi = xt[i];
         const float ui = ur[i];
         if ((int)threadIdx.x == i) {
-            x = xi;
+            if constexpr (!STEP) x = xi;
             u_mine = ui;
         }
     }
@@ -145,6 +154,8 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
     bool decided = false, slabs_current = false;
     int n_rej = 0;
     float rem_k = 0.f;  // WO: unnormalised draft mass outside all k drafted tokens (after the first pass)
+    constexpr bool SUMS_LEFT = WO && !STEP;
+    if constexpr (WO && STEP) rem_k = uniform(sh.bcast_left);
     // The marked tokens that this lane's chunks hold, one bit per element: a chunk whose byte is 0 in
     // every lane -- nearly all are -- costs a pass one test.  (The tokens' places compared chunk by chunk
     // instead filled the passes with scalars: 390 to 2800 spills of them.)
@@ -251,11 +262,11 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
         if (i > 0) __syncthreads();  // earlier readers of the slab sums are done
         float W_new;
         if (i == 0) {
-            if constexpr (WO)
+            if constexpr (SUMS_LEFT)
                 for (int j = 1; j < k; ++j) mark(sh.node_x[j]);
             mark(xi);
-            W_new = residual_pass(c_new, std::false_type{}, std::bool_constant<WO>{});
-            if constexpr (WO) {
+            W_new = residual_pass(c_new, std::bool_constant<KEPT_AT_ENTRY>{}, std::bool_constant<SUMS_LEFT>{});
+            if constexpr (SUMS_LEFT) {
 #pragma unroll
                 for (int j = 0; j < kWords; ++j) marks[j] = 0;
                 mark(xi);
@@ -282,7 +293,7 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
     if (decided && !need_full) return;
     if (!slabs_current) {
         __syncthreads();
-        residual_pass(c, std::false_type{}, std::false_type{});  // rare: all of the draft row from memory again
+        residual_pass(c, std::bool_constant<KEPT_AT_ENTRY>{}, std::false_type{});  // rare: all of the draft row from memory again
     }
     const float c_iZq = c * iZq;
     auto cw = [&](int s, float(&w)[E]) {

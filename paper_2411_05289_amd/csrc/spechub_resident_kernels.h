@@ -2,7 +2,7 @@
 // Device code and kernels; the launchers are in the translation units that include this file
 // (spechub_resident.hip: the main build; half_verify.hip: 256 threads per node).
 #pragma once
-#include "launch.h"
+#include "draft_kernel.h"
 
 namespace MDSD_NS {
 
@@ -92,11 +92,13 @@ __device__ __forceinline__ void fetch_node_inputs(const Params& P, const NodeId&
 // the first test has failed.
 // EVERY_WAVE = false: only the first wave's copy of `o` is complete (the caller's first thread
 // writes the node's outputs), and the final draw is left to that wave.
-template <int DT, int NIT, bool MASKED, bool STATS, bool EVERY_WAVE = true>
+// KEPT: that many of the draft row's first chunks per lane are in q_kept.
+template <int DT, int NIT, bool MASKED, bool STATS, bool EVERY_WAVE = true, int KEPT = 0>
 __device__ __forceinline__ void spechub_resident(const Params& P, const NodeIn& in, const RowView& rp,
                                                  const RowView& rq, const RowSrc<DT, NIT, MASKED>& sp,
                                                  RowSrc<DT, NIT, MASKED>& sq, bool need_full,
-                                                 float* rprob, Shared& sh, int& phase, NodeOut& o)
+                                                 float* rprob, Shared& sh, int& phase, NodeOut& o,
+                                                 uint4 (*q_kept)[kWG] = nullptr)
 {
     constexpr int E = Elem<DT>::kPerChunk;
     const int lane = threadIdx.x & 63, wave = wave_id();
@@ -284,7 +286,7 @@ __device__ __forceinline__ void spechub_resident(const Params& P, const NodeIn& 
     if constexpr (STATS) {
         // the draft row's only read.  Half a chunk at a time, so that few values are live at once.
         SlabSums<NIT> wsums;
-        for_each_streamed<kStreamAhead>(sp, rq, ExpW::fill(), [&](int it, int s, int chunk, const uint4& dp, const uint4& dq) {
+        auto chunk_pair = [&](int it, int s, int chunk, const uint4& dp, const uint4& dq) {
             constexpr int HE = E / 2;
             float part[3][2];
             auto half = [&](auto H) {
@@ -323,7 +325,11 @@ __device__ __forceinline__ void spechub_resident(const Params& P, const NodeIn& 
             sacc[0] += part[0][0] + part[0][1];
             sacc[1] += part[1][0] + part[1][1];
             wsums.put(it, part[2][0] + part[2][1]);
-        });
+        };
+        if constexpr (KEPT > 0)
+            for_each_streamed_cached<1, KEPT, true>(lane, wave, sp, rq, ExpW::fill(), q_kept, chunk_pair);
+        else
+            for_each_streamed<kStreamAhead>(sp, rq, ExpW::fill(), chunk_pair);
         wsums.store(sh.slab_w, rp.nslab);
     } else {
         for_each2(sp, sq, residual_terms);

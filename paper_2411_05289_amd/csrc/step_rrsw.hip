@@ -1,0 +1,22 @@
+// Launchers of the step kernels of one method, main build (512 threads per node).
+#include "step_resident_kernels.h"
+
+namespace mdsd {
+
+template <int DT>
+static void launch_of(int nit, bool masked, dim3 grid, hipStream_t st, const Params& P)
+{
+    if (nit == 4)
+        launch_step_nit<kRRSw, DT, 4>(masked, grid, st, P);
+    else if (nit == 8)
+        launch_step_nit<kRRSw, DT, 8>(masked, grid, st, P);
+    else
+        launch_step_nit<kRRSw, DT, 16>(masked, grid, st, P);
+}
+
+void launch_step_rrsw(int dtype, int nit, bool masked, dim3 grid, hipStream_t st, const Params& P)
+{
+    (dtype == MDSD_FP32 ? launch_of<0> : launch_of<1>)(nit, masked, grid, st, P);
+}
+
+}  // namespace mdsd

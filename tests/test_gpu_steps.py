@@ -1,0 +1,141 @@
+"""StepPlan.run(), which drafts and verifies a node in one kernel where there is one for its rows, against the CPU oracle
+at the edges of those kernels, and against the two calls on rows with little or nothing to draw from."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2411_05289_amd import binding as B
+from paper_2411_05289_amd import workloads as W
+from parity import BAND, METHODS, _check_stats, _compare_nodes, _compare_walk, _internal_mask, _np, mismatch_allowance
+from parity import oracle_kwargs, uniforms
+from test_gpu_routes import _workload
+import oracle
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+ALL = ["spechub", "rrs", "rrsw"]
+
+
+def _poison(plan):
+    for t in (*plan.out.values(), plan.tokens, plan.draft_flags, plan.hub, plan.pb.draft_stats):
+        if t is not None:
+            t.fill_(-9)
+
+
+def _check_step(method, wl, seqs):
+    """The drafted tokens are the oracle's except at nodes with a uniform near a boundary; the rest of the step is
+    compared with the oracle on the tokens that the step drafted."""
+    pb = B.Problem.from_workload(wl)
+    u_d, u_v = uniforms(wl, wl.V)
+    ok = oracle_kwargs(wl)
+    idx = torch.as_tensor(seqs, device=DEV)
+    t_np, d_np = W.rows_as_numpy(wl.target[idx]), W.rows_as_numpy(wl.draft[idx])
+    o_d = oracle.batch_draft(METHODS[method], d_np, _np(u_d[idx]), temp_draft=wl.temp_draft, nthreads=8, **ok)
+    internal = _internal_mask(wl)
+    sure = np.zeros((len(seqs), wl.N), dtype=bool)
+    first = _np(wl.first_child) if wl.first_child is not None else wl.k * np.arange(wl.N) + 1
+    for n in np.nonzero(internal)[0]:
+        sure[:, first[n]:first[n] + wl.k] = (o_d["margin"][:, n] >= BAND)[:, None]
+    for placement in (True, False):
+        plan = B.StepPlan(method, pb, u_d, u_v, walk_in_verify=placement)
+        for _ in range(2):
+            _poison(plan)
+            out = plan.run()
+            torch.cuda.synchronize()
+            assert not plan.workspace.any()
+            tokens = _np(plan.tokens[idx])
+            assert (tokens == o_d["tokens"])[sure].all() and (tokens[:, 0] == -1).all()
+            assert (_np(plan.draft_flags[idx]) == o_d["flags"])[:, internal].all()
+            assert not plan.draft_flags[:, torch.as_tensor(~internal, device=DEV)].any()
+            if method == "spechub":
+                assert (_np(plan.hub[idx]) == np.where(internal, o_d["hub"], -1)).all()
+            _check_stats(wl, _np(plan.pb.draft_stats[idx]), d_np, o_d["hub"] if method == "spechub" else None, internal)
+            o_v = oracle.batch_verify(METHODS[method], t_np, d_np, tokens, _np(u_v[idx]), temp_target=wl.temp_target,
+                                      temp_draft=wl.temp_draft, nthreads=8, **ok)
+            near = o_v["margin"] < BAND
+            ctx = dict(method=method, wl=wl, t_np=t_np, d_np=d_np, tokens=tokens, uv=_np(u_v[idx]))
+            assert _compare_nodes(out, o_v, idx, near, "step", ctx) <= mismatch_allowance(near)
+            _compare_walk(wl, out, o_v, idx, near)
+
+
+@pytest.mark.parametrize("method,k", [("spechub", 2), ("rrs", 2), ("rrsw", 2), ("rrs", 5), ("rrsw", 4)])
+@pytest.mark.parametrize("dtype,V,off,Bn", [
+    ("bf16", 8185, 0, 5), ("bf16", 16369, 0, 5), ("fp32", 8188, 0, 5), ("fp32", 4101, 3, 5),  # four chunks per lane
+    ("bf16", 16384, 0, 5), ("bf16", 32737, 7, 5), ("fp32", 16380, 0, 5),                      # eight
+    ("bf16", 32768, 0, 5), ("bf16", 65521, 1, 5), ("fp32", 20001, 2, 5),                      # sixteen, drafted from memory
+    ("bf16", 9001, 3, 1000), ("fp32", 16384, 0, 1000), ("bf16", 16400, 0, 1000),              # 256 threads per node
+])
+def test_rows_in_registers(method, k, dtype, V, off, Bn):
+    wl = _workload(Bn, W.tree_nodes(k, 2), V, k, 2, dtype, "logits", off)
+    _check_step(method, wl, range(Bn) if Bn < 9 else [0, 1, 7, 8, Bn - 1])
+
+
+@pytest.mark.parametrize("method", ALL)
+@pytest.mark.parametrize("V,dtype,Bn", [(9001, "bf16", 5), (33000, "bf16", 3), (9001, "bf16", 200)])
+def test_trees_given_by_a_table(method, V, dtype, Bn):
+    wl = _workload(Bn, 9, V, 2, 5, dtype, "logits", first_child=[1, 3, -1, 5, -1, 7, -1, -1, -1])
+    _check_step(method, wl, range(Bn) if Bn < 9 else [0, 1, Bn - 1])
+
+
+@pytest.mark.parametrize("method,k", [("spechub", 2), ("rrs", 3), ("rrsw", 3)])
+@pytest.mark.parametrize("dtype,V,off", [("bf16", 9001, 3), ("bf16", 20000, 0), ("bf16", 40001, 1), ("fp32", 9000, 0)])
+def test_rows_with_little_to_draw_from(method, k, dtype, V, off):
+    """One token with all the draft mass, as many as there are drafts, none, tokens at the type's lowest value, a NaN, a
+    +inf, target rows with a single token: what the two calls give, flags and records included."""
+    Bn, N = 12, W.tree_nodes(k, 2)
+    wl = _workload(Bn, N, V, k, 2, dtype, "logits", off)
+    low = torch.finfo(wl.draft.dtype).min
+    d, t = wl.draft, wl.target
+    d[0], d[1], d[2], d[3] = -torch.inf, -torch.inf, -torch.inf, low
+    d[0, :, V - 3] = 1.0
+    d[1, :, 5:5 + k] = 2.0
+    d[3, :, ::97] = 3.0
+    d[4, :, 0] = torch.nan
+    d[5, :, V - 1] = torch.nan
+    d[6, :, 7] = torch.inf
+    t[7] = -torch.inf
+    t[7, :, 11] = 0.0
+    t[8] = low
+    t[8, :, V // 2] = 0.0
+    d[9], t[9] = -torch.inf, -torch.inf
+    d[9, :, 3] = t[9, :, 4] = 0.0
+    d[10] = -torch.inf
+    d[10, :, 0] = 0.0
+    pb = B.Problem.from_workload(wl)
+    u_d, u_v = uniforms(wl, 3)
+    plan = B.StepPlan(method, pb, u_d, u_v)
+    names = ("outcome", "token", "flags", "accept_depth", "emitted")
+    _poison(plan)
+    plan.draft()
+    plan._verify_walk(B._stream())
+    torch.cuda.synchronize()
+    want = {n: plan.out[n].clone() for n in names}
+    drafted = (plan.tokens.clone(), plan.draft_flags.clone(), plan.hub.clone())
+    records = plan.pb.draft_stats.clone()
+    _poison(plan)
+    out = plan.run()
+    torch.cuda.synchronize()
+    for got, w in zip((plan.tokens, plan.draft_flags, plan.hub), drafted):
+        assert torch.equal(got, w)
+    for n in names:
+        assert torch.equal(out[n], want[n]), n
+    got = plan.pb.draft_stats
+    assert torch.equal(got.view(torch.int32)[..., 2], records.view(torch.int32)[..., 2])
+    # sums of V positive terms in another order
+    assert torch.allclose(got[..., :2], records[..., :2], rtol=2e-6, atol=0.0, equal_nan=True)
+
+
+def test_what_run_refuses():
+    """run() reports what draft() or the verify call would refuse, by the name of that call."""
+    wl = _workload(2, 3, 9000, 2, 2, "bf16", "logits")
+    u_d, u_v = uniforms(wl, 1)
+    for field, value, name in (("temp_draft", 0.0, "spechub_draft"), ("temp_target", 0.0, "spechub_verify"),
+                               ("depth", 3, "spechub_draft")):
+        plan = B.StepPlan("spechub", B.Problem.from_workload(wl), u_d, u_v)
+        setattr(plan._cp, field, value)
+        with pytest.raises(B.MdsdError, match=name):
+            plan.run()
+    no_records = B.StepPlan("spechub", B.Problem.from_workload(wl), u_d, u_v, hand_stats=False)
+    with_records = B.StepPlan("spechub", B.Problem.from_workload(wl), u_d, u_v)
+    for key, got in no_records.run().items():
+        assert torch.equal(got, with_records.run()[key])
