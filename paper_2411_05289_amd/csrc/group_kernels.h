@@ -417,11 +417,125 @@ constexpr bool kLateDraft = G >= 16 && METHOD == kSpecHub;
 template <int DT, int METHOD>
 constexpr bool kKeepWeights = DT == 0 || METHOD != kSpecHub;
 
+// ---------------------------------------------------------------- one node's draft
+// What a group's draft leaves in its lanes: the record, and SpecHub's pair.
+struct GroupDrafted {
+    mdsd_row_stats record;
+    int x1, x2;
+};
+
+// The entries of a leaf, which drafts nothing, by the lane that calls it.
+__device__ __forceinline__ void group_leaf_draft(const Params& P, int64_t row, int32_t* flags)
+{
+    if (P.hub_out) P.hub_out[row] = -1;
+    if (flags) flags[row] = 0;
+    if (P.stats_out) P.stats_out[row] = mdsd_row_stats{0.f, 0.f, -1, 0};
+}
+
+// The draft of one node with children.  q: its draft row, asked for; behind the call it holds the row's weights.  ur: the
+// node's uniforms, the first of which is u0.  put(i, x): draft token i, the same in every lane of the group.
+template <int DT, bool LOGITS, int METHOD, int G, class Row, class Put>
+__device__ __forceinline__ GroupDrafted group_draft_node(const Params& P, const RowView& rq, Row& q, int l, int parts,
+                                                         const float* ur, float u0, int64_t row, int32_t* flags_out, Put put)
+{
+    constexpr int E = Elem<DT>::kPerChunk;
+    constexpr int C = kGroupChunks;
+    using CV = ToWeight<LOGITS>;
+    const int k = P.k;
+    GroupDrafted out{mdsd_row_stats{0.f, 0.f, -1, 0}, -1, -1};
+    q.take(rq, l, P, parts);
+    CV cq{0.f, 0.f};
+    float m = 0.f;
+    int hub = rq.head;
+    int flags = 0;
+    if (LOGITS || METHOD == kSpecHub) {
+        float lane_m[C];
+        m = q.max_of_row(lane_m, parts);
+        if constexpr (METHOD == kSpecHub) hub = q.first_index_of(m, lane_m, l, rq.head, parts);
+    }
+    if constexpr (LOGITS) {
+        cq.s = P.scale_d;
+        cq.ms = m * cq.s;
+    }
+    q.form_weights(cq, parts);
+    float t[C];
+    q.part_sums(t, parts);
+    // removed places are taken out where a part is looked at; only the sum of their part changes
+    uint32_t removed = 0;
+    auto part_of = [&](int part, float(&x)[E]) {
+        q.pick(part, x, parts);
+        const uint32_t bits = removed >> (part * E);
+#pragma unroll
+        for (int e = 0; e < E; ++e) x[e] = as_f(as_i(x[e]) & __builtin_amdgcn_sbfe(~bits, e, 1));
+    };
+    auto remove = [&](int v) {
+        const int place = Row::place_of(v, l), part = v / (E * G);
+        removed |= place < 0 ? 0u : 1u << place;
+        float x[E];
+        part_of(part, x);
+        const float s = group_sum<G>(chunk_sum<E>(x));
+#pragma unroll
+        for (int i = 0; i < C; ++i) t[i] = part == i ? s : t[i];
+    };
+    if constexpr (METHOD == kSpecHub) {
+        const float u1 = ur[1];
+        const int v = group_draw<E, G>(t, parts_total(t), u0, l,
+                                       [&](int part, float(&x)[E]) { q.pick(part, x, parts); });
+        const int first = v;
+        int second = hub;
+        if (v == hub || P.stats_out) {
+            remove(hub);
+            const float rest = parts_total(t);
+            out.record = mdsd_row_stats{m, rest, hub - rq.head, 0};
+            if (P.stats_out && l == 0) P.stats_out[row] = out.record;
+            if (v == hub) {
+                second = group_draw<E, G>(t, rest, u1, l, part_of);
+                if (second < 0) {
+                    second = hub;
+                    flags |= MDSD_FLAG_DEGENERATE_HUB;
+                }
+            }
+        }
+        out.x1 = first < 0 ? -1 : first - rq.head;
+        out.x2 = second - rq.head;
+        put(0, out.x1);
+        put(1, out.x2);
+    } else {
+        int prev = rq.head;
+        float W = parts_total(t), u = u0;
+        out.record = mdsd_row_stats{m, W, -1, 0};
+        if (P.stats_out && l == 0) P.stats_out[row] = out.record;
+        for (int i = 0; i < k; ++i) {
+            const float next_u = i + 1 < k ? ur[i + 1] : 0.f;
+            int v = group_draw<E, G>(t, W, u, l, part_of);
+            if (v < 0) {
+                v = prev;
+                flags |= MDSD_FLAG_Q_EXHAUSTED;
+            } else if (METHOD == kRRSw && i + 1 < k) {
+                remove(v);
+                W = parts_total(t);
+            }
+            prev = v;
+            u = next_u;
+            put(i, v - rq.head);
+        }
+    }
+    if (l == 0) {
+        if (P.hub_out) P.hub_out[row] = METHOD == kSpecHub ? hub - rq.head : -1;
+        if (flags_out) flags_out[row] = flags;
+    }
+    return out;
+}
+
 // ---------------------------------------------------------------- one node's verification
 // The decisions, bounds and flags are those of verify_node() (verify_generic.h); what differs is where
 // the weights live and how sums travel.  l: this lane's number in its group.
-template <int DT, bool LOGITS, int METHOD, int G>
-__device__ __forceinline__ NodeOut group_verify_node(const Params& P, const NodeId& id, int l)
+// STEP: the node is drafted first, and its draft row's weights, its record and its tokens stay where they are (the RRS
+// methods' tokens in step_tokens, the group's own part of the LDS); the target row is asked for before the draft.  One launch
+// instead of two, and each row read and unpacked once (us a step): toy workload 40.1 -> 34.1; 100 15-node trees of 1000 bf16 elements
+// SpecHub 14.7 -> 10.4, RRSw 19.0 -> 15.5, 4000 RRS 70.2 -> 58.9; 1000 of 60 12.9 -> 10.5.
+template <int DT, bool LOGITS, int METHOD, int G, bool STEP = false>
+__device__ __forceinline__ NodeOut group_verify_node(const Params& P, const NodeId& id, int l, int* step_tokens = nullptr)
 {
     constexpr int E = Elem<DT>::kPerChunk;
     constexpr int C = kGroupChunks;
@@ -438,9 +552,15 @@ __device__ __forceinline__ NodeOut group_verify_node(const Params& P, const Node
     Row p;
     p.ask(rp, l, parts);
 
+    if constexpr (STEP) {
+        if (id.n == 0 && l == 0) P.tokens_out[id.row] = -1;
+    }
     if (id.c0 < 0) {
         // ---- leaf: the k = 0 case of Alg. 1, token ~ p
         const float u = ur[k];
+        if constexpr (STEP) {
+            if (l == 0) group_leaf_draft(P, id.row, P.draft_flags);
+        }
         p.take(rp, l, P, parts);
         CV cp{0.f, 0.f};
         if constexpr (LOGITS) {
@@ -460,12 +580,30 @@ __device__ __forceinline__ NodeOut group_verify_node(const Params& P, const Node
     }
 
     const RowView rq = make_row<DT>(P.draft, P.ld_d, id.row, P.V);
-    const bool have_stats = P.stats_in != nullptr;
+    const bool have_stats = STEP || P.stats_in != nullptr;
     Row q;
-    if (!kLateDraft<G, METHOD> || !have_stats) q.ask(rq, l, parts);
+    if (STEP || !kLateDraft<G, METHOD> || !have_stats) q.ask(rq, l, parts);
     const int32_t* xt = P.tokens + (int64_t)id.b * P.N + id.c0;
     mdsd_row_stats st{0.f, 0.f, 0, 0};
-    if (have_stats) st = P.stats_in[id.row];
+    GroupDrafted drafted;
+    if constexpr (STEP) {
+        const float* ud = P.u_draft + id.row * k;
+        int32_t* out = P.tokens_out + (int64_t)id.b * P.N + id.c0;
+        drafted = group_draft_node<DT, LOGITS, METHOD, G>(P, rq, q, l, parts, ud, ud[0], id.row, P.draft_flags, [&](int i, int x) {
+            if (l != 0) return;
+            out[i] = x;
+            if constexpr (METHOD != kSpecHub) step_tokens[i] = x;
+        });
+        st = drafted.record;
+        if constexpr (METHOD != kSpecHub) {
+            // lanes of this wavefront only, whose LDS instructions run in order; the compiler has to keep them so
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            xt = step_tokens;
+        }
+    } else if (have_stats) {
+        st = P.stats_in[id.row];
+    }
     CV cp{0.f, 0.f}, cq{0.f, 0.f};
     if constexpr (LOGITS) {
         cp.s = P.scale_t;
@@ -474,7 +612,7 @@ __device__ __forceinline__ NodeOut group_verify_node(const Params& P, const Node
     auto look_up = [&](const RowView& r, int x) { return load_elem<DT>(r, min(max(x, 0), P.V - 1)); };
 
     if constexpr (METHOD == kSpecHub) {
-        const int x1 = xt[0], x2 = xt[1];
+        const int x1 = STEP ? drafted.x1 : xt[0], x2 = STEP ? drafted.x2 : xt[1];
         const float u0 = ur[0], u1 = ur[1], u2 = ur[2];
         // the stored values at the pair and the hub: asked for here, used behind the row's statistics
         const float lp1 = look_up(rp, x1), lq1 = look_up(rq, x1), lp2 = look_up(rp, x2), lq2 = look_up(rq, x2);
@@ -492,14 +630,14 @@ __device__ __forceinline__ NodeOut group_verify_node(const Params& P, const Node
         int hub_place = -1;
         // the draft row's weights, the hub's set to 0
         auto take_q = [&]() {
-            q.take(rq, l, P, parts);
+            if constexpr (!STEP) q.take(rq, l, P, parts);
             if (!have_stats) {
                 float m[C];
                 mq = q.max_of_row(m, parts);
                 a_virt = q.first_index_of(mq, m, l, rq.head, parts);  // a row of NaNs has no maximum: stay in bounds
             }
             if constexpr (LOGITS) cq.ms = mq * cq.s;
-            q.form_weights(cq, parts);
+            if constexpr (!STEP) q.form_weights(cq, parts);
             hub_place = Row::place_of(a_virt, l);
             q.drop(hub_place, parts);
         };
@@ -573,7 +711,7 @@ __device__ __forceinline__ NodeOut group_verify_node(const Params& P, const Node
         }
         if (decided && !need_full) return o;
         if (have_stats) {
-            if constexpr (kLateDraft<G, METHOD>) q.ask(rq, l, parts);
+            if constexpr (!STEP && kLateDraft<G, METHOD>) q.ask(rq, l, parts);
             take_q();
         }
 
@@ -696,9 +834,9 @@ __device__ __forceinline__ NodeOut group_verify_node(const Params& P, const Node
         p.form_weights(cp, parts);
         float iZp = 1.f;
         if constexpr (LOGITS) iZp = 1.f / row_total(p, parts);
-        q.take(rq, l, P, parts);
+        if constexpr (!STEP) q.take(rq, l, P, parts);
         if constexpr (LOGITS) cq.ms = (have_stats ? st.max_stored : q.max_of_row(parts)) * cq.s;
-        q.form_weights(cq, parts);
+        if constexpr (!STEP) q.form_weights(cq, parts);
         // the draft mass outside the drafted tokens (a sum of positive terms, never a difference)
         float rem_k = 0.f;
         if constexpr (WO) {
@@ -894,10 +1032,13 @@ __device__ __forceinline__ void count_and_walk(const Params& P, const NodeId& id
 // workgroup; internal nodes in its first groups, so that most wavefronts hold nodes of one kind), and
 // walks them from LDS: no arrival counters, no launch of its own for the walk.  TREES = false: nodes in
 // one dimension, nodes with children first; the walk by arrival count, or left to the caller.
-template <int DT, bool LOGITS, int METHOD, int G, bool TREES>
+// STEP = true: the nodes are drafted first (see group_verify_node()).
+template <int DT, bool LOGITS, int METHOD, int G, bool TREES, bool STEP = false>
 __global__ __launch_bounds__(kGroupMaxThreads, kGroupWavesPerSimd) void group_verify_kernel(const Params P)
 {
+    __shared__ int drafts[STEP && METHOD != kSpecHub ? kGroupMaxThreads / G : 1][MDSD_MAX_K];
     const int l = threadIdx.x & (G - 1), slot = threadIdx.x / G, groups = blockDim.x / G;
+    int* mine = drafts[STEP && METHOD != kSpecHub ? slot : 0];
     if constexpr (!TREES) {
         NodeId id;
         if (P.first_child && table_by_waves(G, DT == 1, (int64_t)P.B * P.N)) {
@@ -912,7 +1053,7 @@ __global__ __launch_bounds__(kGroupMaxThreads, kGroupWavesPerSimd) void group_ve
             if (item >= (int64_t)P.B * P.N) return;
             id = node_of_item(P, (int)item);
         }
-        const NodeOut o = group_verify_node<DT, LOGITS, METHOD, G>(P, id, l);
+        const NodeOut o = group_verify_node<DT, LOGITS, METHOD, G, STEP>(P, id, l, mine);
         if (P.tree_count == nullptr) {
             if (l == 0) write_group_outputs(P, id, o);
             return;
@@ -944,7 +1085,7 @@ __global__ __launch_bounds__(kGroupMaxThreads, kGroupWavesPerSimd) void group_ve
         if (tree < trees && id.b < P.B) {
             id.c0 = group_first_child(P, id.n);
             id.row = (int64_t)id.b * P.N + id.n;
-            const NodeOut o = group_verify_node<DT, LOGITS, METHOD, G>(P, id, l);
+            const NodeOut o = group_verify_node<DT, LOGITS, METHOD, G, STEP>(P, id, l, mine);
             if (l == 0) {
                 write_group_outputs(P, id, o);
                 oc[tree * P.N + id.n] = o.outcome;
@@ -962,10 +1103,12 @@ __global__ __launch_bounds__(kGroupMaxThreads, kGroupWavesPerSimd) void group_ve
 
 // Wavefront n of a workgroup takes node n of 64 / G trees; the one that comes last walks them (see wave_per_node()).
 // Bound by instruction issue (toy workload: 77 % of the kernel's time, 492 instructions per wavefront of 16 nodes).
-template <int DT, bool LOGITS, int METHOD, int G>
+template <int DT, bool LOGITS, int METHOD, int G, bool STEP = false>
 __global__ __launch_bounds__(kGroupMaxThreads, kGroupWavesPerSimd) void group_tree_kernel(const Params P)
 {
     constexpr int T = 64 / G;
+    __shared__ int drafts[STEP && METHOD != kSpecHub ? kGroupMaxThreads / G : 1][MDSD_MAX_K];
+    int* mine = drafts[STEP && METHOD != kSpecHub ? threadIdx.x / G : 0];
     __shared__ int oc[kGroupMaxThreads / 64][T], tk[kGroupMaxThreads / 64][T], arrived;
     if (threadIdx.x == 0) arrived = 0;
     __syncthreads();
@@ -976,7 +1119,7 @@ __global__ __launch_bounds__(kGroupMaxThreads, kGroupWavesPerSimd) void group_tr
     id.c0 = group_first_child(P, id.n);
     id.row = (int64_t)id.b * P.N + id.n;
     if (id.b < P.B) {
-        const NodeOut o = group_verify_node<DT, LOGITS, METHOD, G>(P, id, l);
+        const NodeOut o = group_verify_node<DT, LOGITS, METHOD, G, STEP>(P, id, l, mine);
         if (l == 0) {
             write_group_outputs(P, id, o);
             oc[id.n][tree] = o.outcome;
@@ -1044,10 +1187,7 @@ __global__ __launch_bounds__(kGroupThreads) void group_path_kernel(const Params 
 template <int DT, bool LOGITS, int METHOD, int G>
 __global__ __launch_bounds__(kGroupMaxThreads) void group_draft_kernel(const Params P)
 {
-    constexpr int E = Elem<DT>::kPerChunk;
-    constexpr int C = kGroupChunks;
-    using CV = ToWeight<LOGITS>;
-    using Row = GroupRow<DT, G, CV, true>;
+    using Row = GroupRow<DT, G, ToWeight<LOGITS>, true>;
     const int l = threadIdx.x & (G - 1), groups = blockDim.x / G;
     const int64_t item = (int64_t)blockIdx.x * groups + threadIdx.x / G;
     const int k = P.k;
@@ -1057,11 +1197,7 @@ __global__ __launch_bounds__(kGroupMaxThreads) void group_draft_kernel(const Par
     const int b = (int)(item / per_tree), n = (int)(item - (int64_t)b * per_tree);
     const int c0 = group_first_child(P, n);
     const int64_t row = (int64_t)b * P.N + n;
-    auto leaf_entries = [&](int64_t r) {
-        if (P.hub_out) P.hub_out[r] = -1;
-        if (P.flags) P.flags[r] = 0;
-        if (P.stats_out) P.stats_out[r] = mdsd_row_stats{0.f, 0.f, -1, 0};
-    };
+    auto leaf_entries = [&](int64_t r) { group_leaf_draft(P, r, P.flags); };
     if (n == 0 && l == 0) P.tokens_out[row] = -1;
     if (c0 < 0) {
         if (l == 0) leaf_entries(row);
@@ -1080,85 +1216,9 @@ __global__ __launch_bounds__(kGroupMaxThreads) void group_draft_kernel(const Par
         for (int j = l; j < k; j += G)
             if (c0 + j >= P.n_internal) leaf_entries(row - n + c0 + j);
 
-    q.take(rq, l, P, parts);
-    CV cq{0.f, 0.f};
-    float m = 0.f;
-    int hub = rq.head;
-    int flags = 0;
-    if (LOGITS || METHOD == kSpecHub) {
-        float lane_m[C];
-        m = q.max_of_row(lane_m, parts);
-        if constexpr (METHOD == kSpecHub) hub = q.first_index_of(m, lane_m, l, rq.head, parts);
-    }
-    if constexpr (LOGITS) {
-        cq.s = P.scale_d;
-        cq.ms = m * cq.s;
-    }
-    q.form_weights(cq, parts);
-    float t[C];
-    q.part_sums(t, parts);
-    // removed places are taken out where a part is looked at; only the sum of their part changes
-    uint32_t removed = 0;
-    auto part_of = [&](int part, float(&x)[E]) {
-        q.pick(part, x, parts);
-        const uint32_t bits = removed >> (part * E);
-#pragma unroll
-        for (int e = 0; e < E; ++e) x[e] = as_f(as_i(x[e]) & __builtin_amdgcn_sbfe(~bits, e, 1));
-    };
-    auto remove = [&](int v) {
-        const int place = Row::place_of(v, l), part = v / (E * G);
-        removed |= place < 0 ? 0u : 1u << place;
-        float x[E];
-        part_of(part, x);
-        const float s = group_sum<G>(chunk_sum<E>(x));
-#pragma unroll
-        for (int i = 0; i < C; ++i) t[i] = part == i ? s : t[i];
-    };
-    if constexpr (METHOD == kSpecHub) {
-        const float u1 = ur[1];
-        const int v = group_draw<E, G>(t, parts_total(t), u0, l,
-                                       [&](int part, float(&x)[E]) { q.pick(part, x, parts); });
-        const int first = v;
-        int second = hub;
-        if (v == hub || P.stats_out) {
-            remove(hub);
-            const float rest = parts_total(t);
-            if (P.stats_out && l == 0) P.stats_out[row] = mdsd_row_stats{m, rest, hub - rq.head, 0};
-            if (v == hub) {
-                second = group_draw<E, G>(t, rest, u1, l, part_of);
-                if (second < 0) {
-                    second = hub;
-                    flags |= MDSD_FLAG_DEGENERATE_HUB;
-                }
-            }
-        }
-        if (l == 0) {
-            xt[0] = first < 0 ? -1 : first - rq.head;
-            xt[1] = second - rq.head;
-        }
-    } else {
-        int prev = rq.head;
-        float W = parts_total(t), u = u0;
-        if (P.stats_out && l == 0) P.stats_out[row] = mdsd_row_stats{m, W, -1, 0};
-        for (int i = 0; i < k; ++i) {
-            const float next_u = i + 1 < k ? ur[i + 1] : 0.f;
-            int v = group_draw<E, G>(t, W, u, l, part_of);
-            if (v < 0) {
-                v = prev;
-                flags |= MDSD_FLAG_Q_EXHAUSTED;
-            } else if (METHOD == kRRSw && i + 1 < k) {
-                remove(v);
-                W = parts_total(t);
-            }
-            prev = v;
-            u = next_u;
-            if (l == 0) xt[i] = v - rq.head;
-        }
-    }
-    if (l == 0) {
-        if (P.hub_out) P.hub_out[row] = METHOD == kSpecHub ? hub - rq.head : -1;
-        if (P.flags) P.flags[row] = flags;
-    }
+    group_draft_node<DT, LOGITS, METHOD, G>(P, rq, q, l, parts, ur, u0, row, P.flags, [&](int i, int x) {
+        if (l == 0) xt[i] = x;
+    });
 }
 
 }  // namespace mdsd

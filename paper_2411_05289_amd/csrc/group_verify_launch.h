@@ -5,26 +5,28 @@
 namespace mdsd {
 
 template <int DT, bool LG, int METHOD, int G>
-static void launch_group_verify_g(bool path, hipStream_t st, const Params& P)
+static void launch_group_path_g(hipStream_t st, const Params& P)
 {
-    if (path) {
-        const int groups = kGroupThreads / G;
-        hipLaunchKernelGGL((group_path_kernel<DT, LG, METHOD, G>), dim3((unsigned)((P.B + groups - 1) / groups)),
-                           dim3(kGroupThreads), 0, st, P);
-        return;
-    }
+    const int groups = kGroupThreads / G;
+    hipLaunchKernelGGL((group_path_kernel<DT, LG, METHOD, G>), dim3((unsigned)((P.B + groups - 1) / groups)),
+                       dim3(kGroupThreads), 0, st, P);
+}
+
+template <int DT, bool LG, int METHOD, int G, bool STEP = false>
+static void launch_group_nodes_g(hipStream_t st, const Params& P)
+{
     if (P.accept_depth && walks_in_workgroups(G, P.N, P.k, (int64_t)P.B * P.N)) {
         if constexpr (G < 64) {
             if (wave_per_node(G, P.N, P.k, (int64_t)P.B * P.N)) {
                 const int trees = 64 / G;
-                hipLaunchKernelGGL((group_tree_kernel<DT, LG, METHOD, G>), dim3((unsigned)((P.B + trees - 1) / trees)),
+                hipLaunchKernelGGL((group_tree_kernel<DT, LG, METHOD, G, STEP>), dim3((unsigned)((P.B + trees - 1) / trees)),
                                    dim3(64 * P.N), 0, st, P);
                 return;
             }
         }
         const int threads = G * P.N <= kGroupThreads ? kGroupThreads : kGroupMaxThreads;
         const int trees = threads / G / P.N;
-        hipLaunchKernelGGL((group_verify_kernel<DT, LG, METHOD, G, true>), dim3((unsigned)((P.B + trees - 1) / trees)),
+        hipLaunchKernelGGL((group_verify_kernel<DT, LG, METHOD, G, true, STEP>), dim3((unsigned)((P.B + trees - 1) / trees)),
                            dim3(threads), 0, st, P);
         return;
     }
@@ -34,20 +36,32 @@ static void launch_group_verify_g(bool path, hipStream_t st, const Params& P)
         constexpr int trees = 64 / G;
         nodes = ((int64_t)P.B + trees - 1) / trees * trees * P.N;
     }
-    hipLaunchKernelGGL((group_verify_kernel<DT, LG, METHOD, G, false>), dim3((unsigned)((nodes + groups - 1) / groups)),
+    hipLaunchKernelGGL((group_verify_kernel<DT, LG, METHOD, G, false, STEP>), dim3((unsigned)((nodes + groups - 1) / groups)),
                        dim3(kGroupThreads), 0, st, P);
+}
+
+// f(integral_constant<int, lanes>)
+template <class F>
+static void with_lanes(int lanes, F f)
+{
+    switch (lanes) {
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    case 8: f(std::integral_constant<int, 8>{}); break;
+    case 16: f(std::integral_constant<int, 16>{}); break;
+    case 32: f(std::integral_constant<int, 32>{}); break;
+    default: f(std::integral_constant<int, 64>{}); break;
+    }
 }
 
 template <int DT, bool LG, int METHOD>
 static void launch_group_verify_t(int lanes, bool path, hipStream_t st, const Params& P)
 {
-    switch (lanes) {
-    case 4: launch_group_verify_g<DT, LG, METHOD, 4>(path, st, P); break;
-    case 8: launch_group_verify_g<DT, LG, METHOD, 8>(path, st, P); break;
-    case 16: launch_group_verify_g<DT, LG, METHOD, 16>(path, st, P); break;
-    case 32: launch_group_verify_g<DT, LG, METHOD, 32>(path, st, P); break;
-    default: launch_group_verify_g<DT, LG, METHOD, 64>(path, st, P); break;
-    }
+    with_lanes(lanes, [&](auto G) {
+        if (path)
+            launch_group_path_g<DT, LG, METHOD, decltype(G)::value>(st, P);
+        else
+            launch_group_nodes_g<DT, LG, METHOD, decltype(G)::value>(st, P);
+    });
 }
 
 template <int METHOD>

@@ -11,7 +11,9 @@ namespace mdsd_half {
 template <int METHOD, int DT>
 static void launch_of(int nit, bool masked, dim3 grid, hipStream_t st, const Params& P)
 {
-    nit == 8 ? launch_step_nit<METHOD, DT, 8>(masked, grid, st, P) : launch_step_nit<METHOD, DT, 16>(masked, grid, st, P);
+    nit == 4   ? launch_step_nit<METHOD, DT, 4>(masked, grid, st, P)
+    : nit == 8 ? launch_step_nit<METHOD, DT, 8>(masked, grid, st, P)
+               : launch_step_nit<METHOD, DT, 16>(masked, grid, st, P);
 }
 
 template <int METHOD>

@@ -91,6 +91,11 @@ void launch_group_spechub(int lanes, int dtype, bool logits, bool path, hipStrea
 void launch_group_rrs(int lanes, int dtype, bool logits, bool path, hipStream_t st, const Params& P);
 void launch_group_rrsw(int lanes, int dtype, bool logits, bool path, hipStream_t st, const Params& P);
 
+// Logit rows, drafted and verified in one launch; the walk as for the verify calls.
+void launch_group_step_spechub(int lanes, int dtype, hipStream_t st, const Params& P);
+void launch_group_step_rrs(int lanes, int dtype, hipStream_t st, const Params& P);
+void launch_group_step_rrsw(int lanes, int dtype, hipStream_t st, const Params& P);
+
 void launch_group_draft(int method, int lanes, int dtype, bool logits, hipStream_t st, const Params& P);
 
 }  // namespace mdsd

@@ -22,6 +22,11 @@ MDSD_DECLARE_SMALL_BUILD(mdsd_quad, 256)  // four: up to 8184 / 4092
 
 #undef MDSD_DECLARE_SMALL_BUILD
 
+namespace mdsd_pair {
+// logit rows, drafted and verified in one launch (four wavefronts per node: mdsd_half::launch_step)
+void launch_step(int method, int dtype, bool masked, dim3 grid, hipStream_t st, const mdsd::Params& P);
+}  // namespace mdsd_pair
+
 namespace mdsd_wave {
 constexpr int kMaxChunks = 4 * 64;
 void launch_spechub(int dtype, bool logits, bool path, dim3 grid, hipStream_t st, const mdsd::Params& P);

@@ -19,6 +19,10 @@ constexpr int kThreads = 1024;
 void launch_spechub(int dtype, int nit, bool path, dim3 grid, hipStream_t st, const mdsd::Params& P);
 void launch_rrs(int dtype, int nit, dim3 grid, hipStream_t st, const mdsd::Params& P);
 void launch_rrsw(int dtype, int nit, dim3 grid, hipStream_t st, const mdsd::Params& P);
+// drafted and verified in one launch
+void launch_step_spechub(int dtype, int nit, bool masked, dim3 grid, hipStream_t st, const mdsd::Params& P);
+void launch_step_rrs(int dtype, int nit, bool masked, dim3 grid, hipStream_t st, const mdsd::Params& P);
+void launch_step_rrsw(int dtype, int nit, bool masked, dim3 grid, hipStream_t st, const mdsd::Params& P);
 void launch_draft(int method, dim3 grid, hipStream_t st, const mdsd::Params& P);
 
 }  // namespace mdsd_wide

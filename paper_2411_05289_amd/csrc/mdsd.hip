@@ -531,26 +531,84 @@ static int draft_entry(int method, const mdsd_problem* pb, const float* u, int32
 static bool half_width_step(int method, const Params& P, int nit)
 {
     const int64_t nodes = (int64_t)P.B * P.N;
-    if (nit > 8) return false;
+    if (nit == 0 || nit > 8) return false;
     if (P.k > 2) return nodes >= 2900;
     return nodes >= (nit == 4 ? 1600 : method == kSpecHub && !P.masked ? 1900 : 2900);
+}
+
+// Steps, 1024 threads per node: chunks per lane, 0 = another build takes the call.  Later than in the verify calls, since
+// the draft gains from them too (512 -> 1024 threads, us a step, 31-node trees unless noted).
+// Rows of eight chunks per lane at 512 threads, up to 384 nodes where unaligned or long: bf16 20001, 372 nodes SpecHub 17.4
+// -> 16.6, RRSw 20.9 -> 19.4, 32000 19.5 -> 19.0, 23.0 -> 22.1, 496 23.9 -> 24.3, 25.9 -> 26.1; 20000 15.6 -> 15.6.  Sixteen: SpecHub
+// to 384 (50304, 372 27.4 -> 25.5, 434 29.1 -> 30.6), RRS methods to 640 (50257, 620 48.8 ->
+// 45.0, 744 49.6 -> 53.8), k > 2 to 800 (21-node trees, 40000, 756 42.1 -> 38.0).  Streamed rows: SpecHub to 640 (128256, 372 60.2
+// -> 50.9, 620 85.5 -> 78.6, 744 90.7 -> 91.1; 152064, 558 96.6 -> 85.3); k = 2 to 896, 1300 or 1100 by length (70001, 1240 91 -> 102;
+// 128256, 1240 159 -> 141, 1488 164 -> 165; 152064, 1240 186 -> 187); k = 3 to 1280 or 1950 (70001, 1950 113 -> 137; 100000, 1950
+// 163 -> 159; 152064, 1300 192 -> 166, 2600 280 -> 308); k = 4 to 1536 or 2200 (70001, 2100 124 -> 145; 152064, 1680 242 -> 195, 2100
+// 265 -> 252, 2688 with a quarter of them nearly uniform 312 -> 330).
+static int wide_step_chunks(int method, const mdsd_problem* pb, const Params& P)
+{
+    const int nit = resident_chunks(pb), wide = wide_chunks(P);
+    const bool longer = P.row_chunks > 9 * mdsd_wide::kThreads;
+    const int64_t nodes = (int64_t)P.B * P.N;
+    // Up to 256 nodes SpecHub stays where its verify call would run (aligned rows of sixteen chunks, streamed ones of more than
+    // sixteen at 1024 threads): the same sums in the same order, and the step gives what the two calls give.
+    if (method == kSpecHub && nodes <= kWideMaxNodes && nit != 8 && !(nit == 16 ? P.masked : wide == 16)) return 0;
+    int64_t most = 0;
+    if (nit == 8)
+        most = P.masked || P.row_chunks > 3072 ? 384 : 0;
+    else if (nit == 16)
+        most = method == kSpecHub ? 384 : P.k > 2 ? 800 : 640;
+    else if (nit == 0)
+        most = method == kSpecHub ? 640
+               : P.k == 2         ? (!longer ? 896 : wide == 20 ? 1100 : 1300)
+               : P.k == 3         ? (longer ? 1950 : 1280)
+               : P.k > 3          ? (longer ? 2200 : 1536)
+                                  : 1024;
+    return nodes <= most ? wide : 0;
+}
+
+// Lanes per node of the step kernels for short rows; 0: another build takes the call.  SpecHub in large batches of more
+// than 64 chunks, whose verify calls take a wavefront per node, as well (4000 trees of 15 nodes, two launches -> one: bf16
+// 1000 73.6 -> 64.3 us, fp32 1000 95.2 -> 79.3), but bf16 rows of more than 128 chunks up to 24576 nodes only (1900, 18000 nodes
+// 44.5 -> 41.9; 1300, 27000 50.2 -> 50.9; 1100, 60000 91 -> 102).
+static int step_lanes(int method, int dtype, const Params& P)
+{
+    const int64_t nodes = (int64_t)P.B * P.N;
+    if (method == kSpecHub && dtype == MDSD_BF16 && P.row_chunks > 128 && nodes > 24576) return 0;
+    return group_lanes(P.row_chunks, nodes, P.accept_depth ? P.N : 1, false);
 }
 
 // A step's kernel that drafts and verifies every node in one launch; false: there is none for this call.
 static bool launch_step(int method, const mdsd_problem* pb, const Params& P, hipStream_t st)
 {
     if (pb->kind != MDSD_LOGITS || P.stats_out == nullptr || P.resid_mass || P.resid_prob) return false;
-    if (verify_lanes(method, pb->dtype, P, false) || small_build(pb)) return false;
-    const int nit = resident_chunks(pb);
-    if (nit == 0 || wide_verify_chunks(method, pb, P, false)) return false;
-    const bool masked = rows_need_mask(pb);
-    const dim3 grid = node_grid(P, nit);
-    if (half_width_step(method, P, nit)) {
-        mdsd_half::launch_step(method, pb->dtype, 2 * nit, masked, grid, st, P);
+    if (const int lanes = step_lanes(method, pb->dtype, P)) {
+        (method == kSpecHub ? launch_group_step_spechub
+         : method == kRRS   ? launch_group_step_rrs
+                            : launch_group_step_rrsw)(lanes, pb->dtype, st, P);
         return true;
     }
-    (method == kSpecHub ? launch_step_spechub : method == kRRS ? launch_step_rrs : launch_step_rrsw)(pb->dtype, nit, masked,
-                                                                                                   grid, st, P);
+    const bool masked = rows_need_mask(pb);
+    const int nit = resident_chunks(pb), wide = wide_step_chunks(method, pb, P), small = small_build(pb);
+    const dim3 grid = node_grid(P, wide ? wide : nit);
+    if (small == 1) return false;  // SpecHub in large batches
+    // streamed rows, RRSw, k = 2, many nodes: in two launches the draft, which runs four nodes on a CU, is the faster by as much
+    // as the launch costs (bf16 100000, 1984 nodes 166 us, in one 170; 128256 212 and 214; 1488 173 and 166)
+    if (nit == 0 && !wide && method == kRRSw && P.k == 2 && (int64_t)P.B * P.N > 1700) return false;
+    if (small == 2)
+        mdsd_pair::launch_step(method, pb->dtype, masked, grid, st, P);
+    else if (small == 4)
+        mdsd_half::launch_step(method, pb->dtype, 4, masked, grid, st, P);
+    else if (wide)
+        (method == kSpecHub ? mdsd_wide::launch_step_spechub
+         : method == kRRS   ? mdsd_wide::launch_step_rrs
+                            : mdsd_wide::launch_step_rrsw)(pb->dtype, wide, masked, grid, st, P);
+    else if (half_width_step(method, P, nit))
+        mdsd_half::launch_step(method, pb->dtype, 2 * nit, masked, grid, st, P);
+    else
+        (method == kSpecHub ? launch_step_spechub : method == kRRS ? launch_step_rrs : launch_step_rrsw)(pb->dtype, nit, masked,
+                                                                                                        grid, st, P);
     return true;
 }
 
@@ -566,8 +624,10 @@ static int step_entry(int method, const mdsd_problem* pb, const float* u_draft, 
     if ((out->accept_depth == nullptr) != (out->emitted == nullptr)) return MDSD_E_NULL;
     P.accept_depth = out->accept_depth;
     P.emitted = out->emitted;
-    P.tree_count = out->accept_depth ? tree_count : nullptr;
-    if (pb->first_child) P.n_internal = table_by_tree(method, pb);
+    const int lanes = step_lanes(method, pb->dtype, P);
+    const bool trees_whole = lanes && out->accept_depth && walks_in_workgroups(lanes, P.N, P.k, (int64_t)P.B * P.N);
+    P.tree_count = out->accept_depth && !trees_whole ? tree_count : nullptr;
+    if (pb->first_child && !lanes) P.n_internal = table_by_tree(method, pb);
     P.u_draft = u_draft;
     P.u = u_verify;
     P.tokens = P.tokens_out = tokens;
@@ -583,7 +643,7 @@ static int step_entry(int method, const mdsd_problem* pb, const float* u_draft, 
     (void)hipGetLastError();
     if (launch_step(method, pb, P, st)) {
         if (hipGetLastError() != hipSuccess) return MDSD_E_LAUNCH;
-        if (P.accept_depth && !P.tree_count) return walk(pb, P.outcome, P.token, P.accept_depth, P.emitted, st);
+        if (P.accept_depth && !P.tree_count && !trees_whole) return walk(pb, P.outcome, P.token, P.accept_depth, P.emitted, st);
         return MDSD_OK;
     }
     const int drafted = draft_entry(method, pb, u_draft, tokens, hub, draft_flags, stream);

@@ -716,7 +716,9 @@ __device__ __forceinline__ bool sweep_streamed_row(const Src& src, float s, Shar
     const int lane = threadIdx.x & 63, wave = wave_id();
     const float ninf = -__builtin_inff();
     float a0[E];
-    load_chunk<DT>(src.r, wave * 64 + lane, ninf, a0);  // slabs past the row read as -inf
+    // (sixteen waves: in pairs, each against the first slab of the one of eight whose slabs they share, so that the slab
+    // sums are those of the 512-thread build bit for bit)
+    load_chunk<DT>(src.r, (wave & 7) * 64 + lane, ninf, a0);  // slabs past the row read as -inf
     float r = a0[0];
 #pragma unroll
     for (int e = 1; e < E; ++e) r = fmaxf(r, a0[e]);

@@ -12,6 +12,7 @@
 // in one, 31-node trees, bf16: SpecHub 32000, 16 trees 25.4 -> 21.2, 64 52.1 -> 46.9, 256 159 -> 151; 12000, 16 17.7 -> 13.1, 64
 // 32.2 -> 24.3; RRS 32000, 64 54.5 -> 51.9, RRSw 57.4 -> 55.4, unaligned 32001 74.8 -> 59.0; fp32 32000, one 15-node tree 19.0 ->
 // 16.6.
+// 128 and 1024 threads: 64 trees of bf16 3000 23.2 -> 17.0, RRSw 26.2 -> 19.0; 8 trees of 128256 SpecHub 49.9 -> 46.6, RRS 61.8 -> 52.8.
 // Both rows asked for at the start (two nodes per CU) was slower (64 trees 55.0), and so were leaves among the nodes with
 // children (one to every four of them 51.3, to every one 58.2).
 #pragma once
@@ -20,19 +21,22 @@
 
 namespace MDSD_NS {
 
-// chunks per lane of the draft row while it is drafted from: the draft kernels' choice
-template <int NIT>
-constexpr int kStepDraftNit = kWG == 512 && NIT == 16 ? 0 : NIT;
+// Chunks per lane of the draft row while it is drafted from, 0 = streamed: the draft kernels' choice, with whose slab sums,
+// records and tokens a step's agree bit for bit (a draw among 100 thousand tokens is within rounding of its neighbour once in
+// a thousand).
+template <int METHOD, int DT, int NIT, bool MASKED>
+constexpr int kStepDraftNit =
+    NIT * kWG <= 4096 || (kWG == 1024 && NIT == 8 && METHOD == kRRS && DT == 0 && !MASKED) ? NIT : 0;
 
 // The draft row's first chunks stay in LDS from the draft on (where they were in registers for it).
-template <int METHOD, int NIT>
-constexpr int kStepKept = kStepDraftNit<NIT> ? kDraftChunksKept<NIT> : 0;
+template <int METHOD, int DT, int NIT, bool MASKED>
+constexpr int kStepKept = kStepDraftNit<METHOD, DT, NIT, MASKED> ? kDraftChunksKept<NIT> : 0;
 
 template <int METHOD, int DT, int NIT, bool MASKED>
 __device__ __forceinline__ NodeOut step_node_resident(const Params& P, const NodeId& id, Shared& sh,
                                                       uint4 (*q_kept)[kWG], int& phase)
 {
-    constexpr int kKept = kStepKept<METHOD, NIT>;
+    constexpr int kKept = kStepKept<METHOD, DT, NIT, MASKED>;
     constexpr int NU = METHOD == kSpecHub ? 2 : 0;
     const int k = NU ? NU : P.k;
     const float* ur = P.u + id.row * (k + 1);
@@ -46,7 +50,7 @@ __device__ __forceinline__ NodeOut step_node_resident(const Params& P, const Nod
         leaf_resident<DT, NIT, MASKED, METHOD != kSpecHub || !MASKED, false>(P, rp, sp, ur[k], nullptr, sh, phase, o);
     } else {
         const RowView rq = make_row<DT>(P.draft, P.ld_d, id.row, P.V);
-        NodeDraft d = draft_node<DT, true, METHOD, kStepDraftNit<NIT>, MASKED, METHOD == kRRSw>(
+        NodeDraft d = draft_node<DT, true, METHOD, kStepDraftNit<METHOD, DT, NIT, MASKED>, MASKED, METHOD == kRRSw>(
             P, id, rq, P.u_draft + id.row * k, P.draft_flags, sh, phase, [&](const auto& row) {
                 if constexpr (kKept > 0) {
                     const int lane = threadIdx.x & 63, wave = wave_id();
@@ -87,7 +91,7 @@ __device__ __forceinline__ NodeOut step_node_resident(const Params& P, const Nod
 template <int DT, int NIT, bool MASKED>
 __global__ __launch_bounds__(kWG, (kVerifyWavesPerSimd<NIT, true>)) void spechub_step_resident(const Params P)
 {
-    constexpr int kKept = kStepKept<kSpecHub, NIT>;
+    constexpr int kKept = kStepKept<kSpecHub, DT, NIT, MASKED>;
     __shared__ Shared sh;
     __shared__ uint4 q_kept[kKept ? kKept : 1][kWG];
     int phase = 0;
@@ -95,7 +99,7 @@ __global__ __launch_bounds__(kWG, (kVerifyWavesPerSimd<NIT, true>)) void spechub
 }
 
 template <int DT, int NIT, bool MASKED, bool WO>
-__global__ __launch_bounds__(kWG, (kWG != 512 || NIT > 8 ? 4 : kStatsWavesPerSimd)) void rrs_step_resident(const Params P)
+__global__ __launch_bounds__(kWG, (kWG > 512 || kWG == 256 || NIT > 8 ? 4 : kStatsWavesPerSimd)) void rrs_step_resident(const Params P)
 {
     __shared__ Shared sh;
     __shared__ uint4 q_kept[kDraftChunksKept<NIT>][kWG];

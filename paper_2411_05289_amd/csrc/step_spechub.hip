@@ -1,5 +1,6 @@
 // Launchers of the step kernels of one method, main build (512 threads per node).
 #include "step_resident_kernels.h"
+#include "verify_generic.h"
 
 namespace mdsd {
 
@@ -10,8 +11,10 @@ static void launch_of(int nit, bool masked, dim3 grid, hipStream_t st, const Par
         launch_step_nit<kSpecHub, DT, 4>(masked, grid, st, P);
     else if (nit == 8)
         launch_step_nit<kSpecHub, DT, 8>(masked, grid, st, P);
-    else
+    else if (nit == 16)
         launch_step_nit<kSpecHub, DT, 16>(masked, grid, st, P);
+    else
+        hipLaunchKernelGGL((step_streamed_kernel<DT, kSpecHub>), grid, dim3(kWG), 0, st, P);
 }
 
 void launch_step_spechub(int dtype, int nit, bool masked, dim3 grid, hipStream_t st, const Params& P)

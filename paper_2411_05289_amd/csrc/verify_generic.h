@@ -2,7 +2,7 @@
 // streamed, one workgroup per node or (path-only) per tree.  Instantiated per method in
 // verify_generic_*.hip.
 #pragma once
-#include "launch.h"
+#include "draft_kernel.h"
 
 namespace MDSD_NS {
 
@@ -37,7 +37,8 @@ constexpr bool kEndsPerElement =
 // bf16 20001, 4000 nodes 47.6 -> 54.1; so do their leaves), and so they ask ahead in the sweep for the draft mass only.
 constexpr int kProbsAhead = 8, kProbsPairAhead = 4;
 
-template <int DT, bool LOGITS, int METHOD, int NIT, bool PATH>
+// STEP: the node is drafted first, and its record and its tokens do not come back from memory.
+template <int DT, bool LOGITS, int METHOD, int NIT, bool PATH, bool STEP = false>
 __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id, Shared& sh, int& phase)
 {
     constexpr int E = Elem<DT>::kPerChunk;
@@ -56,8 +57,12 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
 
     sp.init(rp, CV::fill());
 
+    if constexpr (STEP) {
+        if (id.n == 0 && (int)threadIdx.x == 0) P.tokens_out[id.row] = -1;
+    }
     if (id.c0 < 0) {
         // ---- leaf: the k = 0 case of Alg. 1, token ~ p
+        if constexpr (STEP) write_leaf_draft(P, id, P.draft_flags);
         CV cp{0.f, 0.f};
         bool swept = false;
         if constexpr (LOGITS && NIT == 0) {
@@ -102,6 +107,14 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
         // one wavefront per node: the rows are a few hundred bytes and every trip to memory is a
         // quarter of the node's life, so the draft row is asked for together with the target row
         if constexpr (kWaves == 1) need_q();
+        mdsd_row_stats record{0.f, 0.f, -1, 0};
+        if constexpr (STEP) {
+            record = draft_node<DT, LOGITS, METHOD, NIT, true, METHOD == kRRSw>(P, id, rq, P.u_draft + id.row * k, P.draft_flags,
+                                                                               sh, phase, [](const auto&) {}).record;
+            record.max_stored = uniform(record.max_stored);
+            record.rest_mass = uniform(record.rest_mass);
+            record.hub = uniform(record.hub);
+        }
         const int32_t* xt = P.tokens + (int64_t)id.b * P.N + id.c0;
         CV cp{0.f, 0.f}, cq{0.f, 0.f};
 
@@ -111,7 +124,11 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
             // here 85.9; of 832 bf16, 43000 nodes, 57.2 and 57.9).
             constexpr bool kPairLate = kWaves == 1 && !kProbsStreamed;
             int x1 = -1, x2 = -1;
-            if constexpr (!kPairLate) {
+            if constexpr (STEP) {
+                int none = 0;
+                x1 = uniform(token_of_draws<kSpecHub>(sh, 2, record.hub, 0, none));
+                x2 = uniform(token_of_draws<kSpecHub>(sh, 2, record.hub, 1, none));
+            } else if constexpr (!kPairLate) {
                 x1 = xt[0];
                 x2 = xt[1];
             }
@@ -127,10 +144,13 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
             // ---- hub (argmax of the stored draft row), softmax maxima, normalisers: Zp (logits
             // only) and the draft mass outside the hub, Zq' = sum_{y != a} eq.  With the draft
             // call's record of the row at hand, the draft row is not read for any of them.
-            const bool have_stats = P.stats_in != nullptr;
+            const bool have_stats = STEP || P.stats_in != nullptr;
             mdsd_row_stats st{0.f, 0.f, 0, 0};
             if (have_stats) {
-                st = P.stats_in[id.row];
+                if constexpr (STEP)
+                    st = record;
+                else
+                    st = P.stats_in[id.row];
                 if (st.hub < 0 || st.hub >= P.V) st.hub = -1;
             }
             float mm[2], z[2] = {0.f, 0.f};
@@ -227,7 +247,7 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
             const float pa = ea_p * h.iZp;
             const float qa = ea_q * h.iZq;
 
-            if constexpr (kPairLate) {
+            if constexpr (kPairLate && !STEP) {
                 x1 = xt[0];
                 x2 = xt[1];
             }
@@ -375,7 +395,12 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
             int xs[MDSD_MAX_K];
             bool bad = false;
             for (int i = 0; i < k; ++i) {
-                xs[i] = xt[i];
+                if constexpr (STEP) {
+                    const int x = uniform(sh.node_x[i]);  // as token_of_draws() has it
+                    xs[i] = x < 0 ? (i > 0 ? xs[i - 1] : 0) : x;
+                } else {
+                    xs[i] = xt[i];
+                }
                 if (xs[i] < 0 || xs[i] >= P.V) bad = true;
             }
             if (bad) {
@@ -386,9 +411,9 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
                 // statistics of the draft row.  Without replacement the mass outside the drafted
                 // tokens is needed too, from the second round on: the first rejected round's pass
                 // over the draft row sums it.
-                const bool have_stats = P.stats_in != nullptr;
-                mdsd_row_stats st{0.f, 0.f, -1, 0};
-                if (have_stats) st = P.stats_in[id.row];
+                const bool have_stats = STEP || P.stats_in != nullptr;
+                mdsd_row_stats st = record;
+                if (!STEP && have_stats) st = P.stats_in[id.row];
                 float z[2] = {0.f, 0.f};
                 bool swept = false;
                 if constexpr (LOGITS) {
@@ -474,8 +499,9 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
                 // draft mass (unnormalised) left before round i: what no draft took (a sum of
                 // positive terms; with a record, known after the first rejected round) plus the
                 // drafts still to come, a repeated token counting once
-                const bool rem_pending = WO && have_stats;
+                const bool rem_pending = WO && !STEP && have_stats;
                 float rem_k = rem_pending ? 0.f : z[1];
+                if constexpr (WO && STEP) rem_k = uniform(sh.bcast_left);
                 auto mass_left = [&](int i) {
                     float m = rem_k;
                     for (int j = k - 1; j >= i; --j) m += (WO && !dup[j]) ? eqx[j] : 0.f;
@@ -601,6 +627,16 @@ __global__ __launch_bounds__(kWG) void verify_kernel(const Params P)
     int phase = 0;
     const NodeId id = node_of_block(P);
     verify_node<DT, LOGITS, METHOD, NIT, false>(P, id, sh, phase);
+}
+
+// Steps on rows too long for registers, three nodes per CU like the verify kernel (two launches -> one: config 4, SpecHub
+// 627 -> 603 us; 32 15-node trees of 128256 65.6 -> 63.2; 128 21-node trees of 152064, k = 4, RRS 312 -> 308, RRSw 336 -> 319).
+template <int DT, int METHOD>
+__global__ __launch_bounds__(kWG, 6) void step_streamed_kernel(const Params P)
+{
+    __shared__ Shared sh;
+    int phase = 0;
+    verify_node<DT, true, METHOD, 0, false, true>(P, node_of_block(P), sh, phase);
 }
 
 template <int DT, bool LOGITS, int METHOD, int NIT>

@@ -58,27 +58,53 @@ def _check_step(method, wl, seqs):
             _compare_walk(wl, out, o_v, idx, near)
 
 
-@pytest.mark.parametrize("method,k", [("spechub", 2), ("rrs", 2), ("rrsw", 2), ("rrs", 5), ("rrsw", 4)])
+@pytest.mark.parametrize("method,k", [("spechub", 2), ("rrs", 2), ("rrsw", 2), ("rrs", 5), ("rrsw", 4), ("rrsw", 1)])
 @pytest.mark.parametrize("dtype,V,off,Bn", [
     ("bf16", 8185, 0, 5), ("bf16", 16369, 0, 5), ("fp32", 8188, 0, 5), ("fp32", 4101, 3, 5),  # four chunks per lane
     ("bf16", 16384, 0, 5), ("bf16", 32737, 7, 5), ("fp32", 16380, 0, 5),                      # eight
     ("bf16", 32768, 0, 5), ("bf16", 65521, 1, 5), ("fp32", 20001, 2, 5),                      # sixteen, drafted from memory
     ("bf16", 9001, 3, 1000), ("fp32", 16384, 0, 1000), ("bf16", 16400, 0, 1000),              # 256 threads per node
+    ("bf16", 2049, 0, 5), ("bf16", 4081, 3, 5), ("fp32", 1021, 2, 5), ("fp32", 2041, 1, 5),     # 128
+    ("bf16", 4089, 0, 5), ("bf16", 8177, 5, 5), ("fp32", 4085, 3, 5),                         # 256, four chunks
+    ("bf16", 32768, 0, 200), ("bf16", 65521, 1, 200),                                         # 512, sixteen
 ])
 def test_rows_in_registers(method, k, dtype, V, off, Bn):
     wl = _workload(Bn, W.tree_nodes(k, 2), V, k, 2, dtype, "logits", off)
     _check_step(method, wl, range(Bn) if Bn < 9 else [0, 1, 7, 8, Bn - 1])
 
 
+@pytest.mark.parametrize("method,k", [("spechub", 2), ("rrs", 2), ("rrsw", 3)])
+@pytest.mark.parametrize("dtype,V,off,Bn", [
+    ("bf16", 65600, 0, 3), ("bf16", 131073, 3, 3), ("bf16", 163000, 1, 3), ("fp32", 70001, 1, 3),  # 1024 threads, up to 20 chunks
+    ("bf16", 66001, 1, 800), ("fp32", 33001, 0, 800), ("bf16", 200000, 0, 3),                      # from memory
+])
+def test_long_rows(method, k, dtype, V, off, Bn):
+    wl = _workload(Bn, W.tree_nodes(k, 2), V, k, 2, dtype, "logits", off)
+    _check_step(method, wl, range(Bn) if Bn < 9 else [0, 1, Bn - 1])
+
+
+@pytest.mark.parametrize("method,k", [("spechub", 2), ("rrs", 2), ("rrs", 7), ("rrsw", 3), ("rrsw", 8), ("rrs", 1)])
+@pytest.mark.parametrize("V,dtype,Bn", [(16, "fp32", 1), (50, "fp32", 17), (60, "bf16", 700), (200, "bf16", 401),
+                                        (1025, "bf16", 9), (2041, "bf16", 33), (1019, "fp32", 9), (50, "fp32", 30001),
+                                        (600, "bf16", 9000)])
+def test_short_rows(method, k, V, dtype, Bn):
+    """Groups of 4 to 64 lanes: whole trees in a workgroup, a wavefront per node number, nodes in any order."""
+    for depth in (2, 3) if k == 2 and Bn < 9000 else (2,):
+        wl = _workload(Bn, W.tree_nodes(k, depth), V, k, depth, dtype, "logits", off=1)
+        _check_step(method, wl, sorted({0, Bn // 2, Bn - 1}))
+
+
 @pytest.mark.parametrize("method", ALL)
-@pytest.mark.parametrize("V,dtype,Bn", [(9001, "bf16", 5), (33000, "bf16", 3), (9001, "bf16", 200)])
+@pytest.mark.parametrize("V,dtype,Bn", [(9001, "bf16", 5), (33000, "bf16", 3), (9001, "bf16", 200), (50, "fp32", 33),
+                                        (60, "bf16", 2015), (3000, "bf16", 5), (70001, "bf16", 3), (70001, "bf16", 150)])
 def test_trees_given_by_a_table(method, V, dtype, Bn):
     wl = _workload(Bn, 9, V, 2, 5, dtype, "logits", first_child=[1, 3, -1, 5, -1, 7, -1, -1, -1])
     _check_step(method, wl, range(Bn) if Bn < 9 else [0, 1, Bn - 1])
 
 
 @pytest.mark.parametrize("method,k", [("spechub", 2), ("rrs", 3), ("rrsw", 3)])
-@pytest.mark.parametrize("dtype,V,off", [("bf16", 9001, 3), ("bf16", 20000, 0), ("bf16", 40001, 1), ("fp32", 9000, 0)])
+@pytest.mark.parametrize("dtype,V,off", [("bf16", 9001, 3), ("bf16", 20000, 0), ("bf16", 40001, 1), ("fp32", 9000, 0),
+                                        ("bf16", 60, 0), ("fp32", 999, 1), ("bf16", 3001, 5), ("bf16", 170001, 1)])
 def test_rows_with_little_to_draw_from(method, k, dtype, V, off):
     """One token with all the draft mass, as many as there are drafts, none, tokens at the type's lowest value, a NaN, a
     +inf, target rows with a single token: what the two calls give, flags and records included."""
