@@ -263,12 +263,30 @@ __device__ __forceinline__ float lane_max_of_row(const Src& src)
         return lane_max(src);
 }
 
-// lowest virtual index at which this lane holds the value m (INT_MAX: nowhere)
+// Lowest virtual index at which this lane holds the value m, its largest element, INT_MAX: nowhere or, for rows in
+// registers, only behind another lane's.  The wave that holds a row's maximum looks for it while the others wait: a row
+// in registers is searched chunk by chunk, the wave's chunks being in the order of their indices, and only a chunk that
+// some lane's maximum may be in is looked at element by element (39 instructions a chunk of bf16 elements without; 64 trees of
+// 32000 SpecHub draft and verify 52.3 -> 51.8 us, a step of 16 trees 21.7 -> 20.6; 256 threads with sixteen chunks, which have
+// no register to spare, lose what the others gain: step 46.8 -> 47.2).
 template <class Src>
 __device__ __forceinline__ int lane_first_index_of(const Src& src, float m)
 {
     constexpr int E = Src::E;
     int idx = INT_MAX;
+    if constexpr (Src::kNit > 0 && !(kWG == 256 && Src::kNit == 16)) {
+        bool found = false;
+        src.for_each_packed([&](int chunk, auto may_hold, auto elements) {
+            if (found || !__any(may_hold(m))) return;
+            float a[E];
+            elements(a);
+#pragma unroll
+            for (int e = E - 1; e >= 0; --e)
+                if (a[e] == m) idx = chunk * E + e;
+            found = __any(idx != INT_MAX);
+        });
+        return idx;
+    }
     src.for_each([&](int, int chunk, const float(&a)[E]) {
 #pragma unroll
         for (int e = E - 1; e >= 0; --e)

@@ -184,6 +184,38 @@ struct RowSrc {
         }
     }
 
+    // body(chunk, may_hold, elements): may_hold(m) is false only if no element of this lane's chunk is m, where none is
+    // larger (positive numbers of bf16 rows compared on the packed halves); elements(a) gives the chunk's elements.
+    template <class Body>
+    __device__ __forceinline__ void for_each_packed(Body body) const
+    {
+        typedef short v2i16 __attribute__((ext_vector_type(2)));
+        const int lane = threadIdx.x & 63, wave = wave_id();
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+            const int s = it * kWaves + wave;
+            if (s >= r.nslab) continue;
+            auto elements = [&](float(&a)[E]) { get(it, a); };
+            auto may_hold = [&](float m) {
+                if constexpr (DT == 1 && ENDS != kEndsByElement) {
+                    const uint4 c = chunk_of(it, lane, wave);
+                    const v2i16 xy = __builtin_elementwise_max(__builtin_bit_cast(v2i16, c.x), __builtin_bit_cast(v2i16, c.y));
+                    const v2i16 zw = __builtin_elementwise_max(__builtin_bit_cast(v2i16, c.z), __builtin_bit_cast(v2i16, c.w));
+                    const v2i16 top = __builtin_elementwise_max(xy, zw);
+                    return !(m > 0.f) || max((int)top.x, (int)top.y) >= (int)(__builtin_bit_cast(uint32_t, m) >> 16);
+                } else {
+                    float a[E];
+                    get(it, a);
+                    float cm = a[0];
+#pragma unroll
+                    for (int e = 1; e < E; ++e) cm = fmaxf(cm, a[e]);
+                    return cm >= m;
+                }
+            };
+            body(s * 64 + lane, may_hold, elements);
+        }
+    }
+
     // Largest element of this lane's chunks (NaNs dropped), bf16 rows: on the packed halves as 16-bit integers, 4
     // instructions per chunk instead of 12 and no unpacked element that the compiler would like to keep for a
     // later pass.  The largest signed integer is the largest element unless all are negative (then it is the
