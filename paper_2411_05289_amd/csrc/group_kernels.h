@@ -938,7 +938,10 @@ __device__ __forceinline__ NodeOut group_verify_node(const Params& P, const Node
                 }
             }
         }
-        if (decided && !need_full) return o;
+        if (decided && (!need_full || (n_rej == 0 && !rprob))) {
+            o.rmass = 1.f;
+            return o;
+        }
         if (!parts_current) residual_parts(c);
         const float W = parts_total(t);
         // the mass the rejections took p down to: nothing rejected, nothing taken

@@ -17,7 +17,7 @@ namespace MDSD_NS {
 // terms only) in the first pass over the draft row, the masses left are that plus the later drafts'.
 // STATS = false: no record; the draft row's largest element and its mass come from one more pass over it,
 // while the target row is on its way.
-// The first pass over the draft row leaves its first kDraftChunksKept chunks per lane in LDS, so
+// The first pass over the draft row (without records the one for its mass) leaves its first kDraftChunksKept chunks per lane in LDS, so
 // that the passes of later rounds read only the rest of it from memory.
 // Bound by instruction issue and the reads of the draft row in about equal parts (see the residual pass).
 // Marked tokens as bits and row ends filled in the packed chunks: bf16 rows of 32001 elements, 31-node
@@ -98,7 +98,14 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
         row.init(rq, ExpW::fill());
         const float ninf = -__builtin_inff();
         float mm[2] = {ninf, ninf}, z[2] = {0.f, 0.f}, lane_ms = ninf;
-        row.template for_each<2>([&](int, int, const float(&a)[E]) {
+        const int lane = threadIdx.x & 63, wave = wave_id();
+        uint4 c0 = fetch_chunk(rq, wave * 64 + lane), c1 = fetch_chunk(rq, (wave + kWaves) * 64 + lane);
+        for (int it = 0, s = wave; s < rq.nslab; ++it, s += kWaves) {
+            const uint4 next = fetch_chunk(rq, (s + 2 * kWaves) * 64 + lane);
+            row.end_of_row(c0, s, lane);
+            if (it < kDraftChunksKept<NIT>) q_kept[it][threadIdx.x] = c0;
+            float a[E];
+            unpack<DT>(c0, a);
 #pragma unroll
             for (int e = 0; e < E; ++e) mm[1] = fmaxf(mm[1], a[e]);
             const float ms = mm[1] * cq.s;
@@ -111,7 +118,9 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
             for (int e = 0; e < E; ++e) w[e] = cw(a[e]);
             z[1] = fmaf(z[1], __builtin_amdgcn_exp2f(lane_ms - cw.ms), chunk_sum<E>(w));
             lane_ms = refers ? ms : ninf;
-        });
+            c0 = c1;
+            c1 = next;
+        }
         mm[0] = lane_max(sp);
         block_max<kWaves, 2>(mm, sh.red, phase);
         cp.ms = uniform(mm[0] * cp.s);
@@ -150,6 +159,7 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
         o.outcome = MDSD_BAD_TOKEN;
         return;
     }
+    constexpr bool KEPT_BY_NOW = KEPT_AT_ENTRY || !STATS;
     float c = 0.f, Wc = 1.f;
     bool decided = false, slabs_current = false;
     int n_rej = 0;
@@ -265,7 +275,7 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
             if constexpr (SUMS_LEFT)
                 for (int j = 1; j < k; ++j) mark(sh.node_x[j]);
             mark(xi);
-            W_new = residual_pass(c_new, std::bool_constant<KEPT_AT_ENTRY>{}, std::bool_constant<SUMS_LEFT>{});
+            W_new = residual_pass(c_new, std::bool_constant<KEPT_BY_NOW>{}, std::bool_constant<SUMS_LEFT>{});
             if constexpr (SUMS_LEFT) {
 #pragma unroll
                 for (int j = 0; j < kWords; ++j) marks[j] = 0;
@@ -290,10 +300,15 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
             }
         }
     }
-    if (decided && !need_full) return;
+    // A first draft accepted: the mass is 1 as it stands, and only the distribution itself needs the pass over both rows
+    // (31-node trees asked for masses, three nodes in five: 64 trees of 32000 without records MASS_FIGURES).
+    if (decided && (!need_full || (n_rej == 0 && !rprob))) {
+        o.rmass = 1.f;
+        return;
+    }
     if (!slabs_current) {
         __syncthreads();
-        residual_pass(c, std::bool_constant<KEPT_AT_ENTRY>{}, std::false_type{});  // rare: all of the draft row from memory again
+        residual_pass(c, std::bool_constant<KEPT_BY_NOW>{}, std::false_type{});  // rare: all of the draft row from memory again
     }
     const float c_iZq = c * iZq;
     auto cw = [&](int s, float(&w)[E]) {

@@ -580,7 +580,9 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
                         }
                     }
                 }
-                if (!decided || need_full) {
+                if (decided && n_rej == 0 && !rprob) {
+                    rmass = 1.f;  // nothing rejected, nothing taken
+                } else if (!decided || need_full) {
                     const float c_iZq = c * iZq;
                     auto cw = [&](int s, float(&w)[E]) {
                         rrs_chunk_w<DT, CV>(rp, rq, cp, cq, iZp, c_iZq, xv, n_rej, s, w);
