@@ -17,11 +17,16 @@ __device__ __forceinline__ void write_leaf_draft(const Params& P, const NodeId& 
     if (P.stats_out) P.stats_out[id.row] = mdsd_row_stats{0.f, 0.f, -1, 0};
 }
 
-// What a node's draft leaves with its threads: the record of the draft row in all of them, draft token i in
-// thread i < k.  (SpecHub: sh.node_x still holds the draws that token_of_draws() reads.)
+// What a node's draft leaves with its threads: the record of the draft row in all of them (its rest_mass in sh.bcast_f),
+// draft token i in thread i < k.  (sh.node_x still holds the draws that token_of_draws() reads.)
 struct NodeDraft {
-    mdsd_row_stats record;
-    int token;
+    float max_stored;
+    int hub, token;
+
+    __device__ __forceinline__ mdsd_row_stats record(const Shared& sh) const
+    {
+        return mdsd_row_stats{uniform(max_stored), uniform(sh.bcast_f), uniform(hub), 0};
+    }
 };
 
 // The k draft tokens of a node with children, with their record, written to memory and returned.  u: the node's k
@@ -98,13 +103,13 @@ __device__ __forceinline__ NodeDraft draft_node(const Params& P, const NodeId& i
     node_barrier();
     const int hub = METHOD == kSpecHub ? a_virt - rq.head : -1;
     int flags = 0;
-    NodeDraft out{mdsd_row_stats{mm[0], sh.bcast_f, hub, 0}, -1};
+    NodeDraft out{mm[0], hub, -1};
     if ((int)threadIdx.x < k) {
         out.token = token_of_draws<METHOD>(sh, k, hub, (int)threadIdx.x, flags);
         xt[threadIdx.x] = out.token;
     }
     if ((int)threadIdx.x == 0) {
-        if (P.stats_out) P.stats_out[row] = out.record;
+        if (P.stats_out) P.stats_out[row] = mdsd_row_stats{mm[0], sh.bcast_f, hub, 0};
         if (P.hub_out) P.hub_out[row] = hub;
         if (flags_out) flags_out[row] = flags;
     }

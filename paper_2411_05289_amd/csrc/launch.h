@@ -11,8 +11,8 @@ void launch_spechub_resident(int dtype, int nit, bool masked, bool path, dim3 gr
                              const Params& P);
 
 // rrs_resident.hip, rrsw_resident.hip: RRS / RRSw on logit rows in registers
-void launch_rrs_resident(int dtype, int nit, bool masked, dim3 grid, dim3 block, hipStream_t st, const Params& P);
-void launch_rrsw_resident(int dtype, int nit, bool masked, dim3 grid, dim3 block, hipStream_t st, const Params& P);
+void launch_rrs_resident(int dtype, int nit, bool masked, bool path, dim3 grid, dim3 block, hipStream_t st, const Params& P);
+void launch_rrsw_resident(int dtype, int nit, bool masked, bool path, dim3 grid, dim3 block, hipStream_t st, const Params& P);
 
 // verify_generic_*.hip: every other case (nit = 0: rows streamed in every pass)
 // drafting and verifying a node in one launch (step_resident_kernels.h)

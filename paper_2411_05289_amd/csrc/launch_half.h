@@ -16,6 +16,8 @@ constexpr int kMaxChunks = 16 * 256;
 void launch_spechub(int dtype, bool masked, dim3 grid, hipStream_t st, const mdsd::Params& P);
 // RRS / RRSw with P.stats_in set
 void launch_rrs(bool without_replacement, int dtype, bool masked, dim3 grid, hipStream_t st, const mdsd::Params& P);
+// nit: 8, or 16 (RRSw only)
+void launch_draft(int method, int dtype, int nit, bool masked, dim3 grid, hipStream_t st, const mdsd::Params& P);
 // nit: 4, 8 or 16 chunks per lane
 void launch_step(int method, int dtype, int nit, bool masked, dim3 grid, hipStream_t st, const mdsd::Params& P);
 

@@ -352,8 +352,9 @@ static void launch_verify(int method, const mdsd_problem* pb, const Params& P, b
         launch_spechub_resident(pb->dtype, nit, rows_need_mask(pb), path, grid, block, st, P);
         return;
     }
-    if (method != kSpecHub && lg && nit > 0 && !path) {
-        (method == kRRSw ? launch_rrsw_resident : launch_rrs_resident)(pb->dtype, nit, rows_need_mask(pb), grid, block, st, P);
+    if (method != kSpecHub && lg && nit > 0) {
+        (method == kRRSw ? launch_rrsw_resident : launch_rrs_resident)(pb->dtype, nit, rows_need_mask(pb), path, grid, block, st,
+                                                                       P);
         return;
     }
     // The generic RRS rounds hold many registers beside two resident rows (8 chunks per lane and
@@ -366,6 +367,18 @@ static void launch_verify(int method, const mdsd_problem* pb, const Params& P, b
         launch_verify_generic_rrs(pb->dtype, lg, nit, path, grid, block, st, P);
     else
         launch_verify_generic_rrsw(pb->dtype, lg, nit, path, grid, block, st, P);
+}
+
+// Draft, 256 threads per node: chunks per lane, 0 = not.  Half the reductions per element, worth more than the longer chain of
+// a node once the nodes with children do not fit the chip at once (512 -> 256 threads, us a call, 31-node trees; the same
+// bits).  Rows of four chunks per lane at 512 threads: bf16 12000, 960 nodes with children SpecHub 10.0 -> 10.4, 1920 16.1 -> 14.8,
+// RRS 14.0 -> 13.2, RRSw 16.5 -> 14.5; fp32 7000, 1920 14.6 -> 13.0.  Eight chunks, RRSw: 32000, 960 17.1 -> 18.1, 1920 30.3 ->
+// 29.1, 3840 51.7 -> 50.6; the others lose (SpecHub 1920 28.7 -> 31.8, RRS 26.8 -> 27.1).
+static int half_draft_chunks(int method, const mdsd_problem* pb, const Params& P, int nit)
+{
+    const int64_t nodes = (int64_t)P.B * (P.first_child ? P.N : P.n_internal);
+    if (pb->kind != MDSD_LOGITS || nodes < 1536) return 0;
+    return nit == 4 ? 8 : nit == 8 && method == kRRSw && nodes >= 1920 ? 16 : 0;
 }
 
 static void launch_draft(int method, const mdsd_problem* pb, const Params& P, hipStream_t st)
@@ -397,6 +410,10 @@ static void launch_draft(int method, const mdsd_problem* pb, const Params& P, hi
     }
     const int es = pb->dtype == MDSD_FP32 ? 4 : 2;
     const bool masked = ((uintptr_t)pb->draft & 15) || ((pb->ld_d * es) & 15) || (pb->V % (16 / es));
+    if (const int half = half_draft_chunks(method, pb, P, nit)) {
+        mdsd_half::launch_draft(method, pb->dtype, half, masked, grid, st, P);
+        return;
+    }
     if (method == kSpecHub)
         launch_draft_spechub(pb->dtype, lg, nit, masked, grid, block, st, P);
     else if (method == kRRS)

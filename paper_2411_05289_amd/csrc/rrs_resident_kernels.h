@@ -31,14 +31,14 @@ constexpr int kDraftChunksKept = kWG == 1024  ? (NIT < 9 ? NIT : 9)
                                  : kWG == 256 ? (NIT < 7 ? NIT : 7)
                                               : (NIT < 5 ? NIT : 5);
 
-// STEP: the node was drafted here a moment ago: `drafted` has its tokens and its record, and without replacement
+// STEP: the node was drafted here a moment ago: draft token i is thread i's `drafted`, `record` its record, and without replacement
 // sh.bcast_left the draft mass outside the drafted tokens.  KEPT_AT_ENTRY: q_kept holds the draft row's first chunks.
 template <int DT, int NIT, bool MASKED, bool WO, bool STATS, bool STEP = false, bool KEPT_AT_ENTRY = false>
 __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, const RowView& rp,
                                              const RowView& rq, const RowSrc<DT, NIT, MASKED>& sp,
                                              bool need_full, float* rprob, Shared& sh,
                                              uint4 (*q_kept)[kWG], int& phase, NodeOut& o,
-                                             const NodeDraft* drafted = nullptr)
+                                             int drafted = -1, mdsd_row_stats record = {})
 {
     static_assert(STATS || !STEP, "a step has its record");
     constexpr int E = Elem<DT>::kPerChunk;
@@ -49,7 +49,7 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
     const int32_t* xt = P.tokens + (int64_t)id.b * P.N + id.c0;
     mdsd_row_stats st;
     if constexpr (STEP)
-        st = drafted->record;
+        st = record;
     else if constexpr (STATS)
         st = P.stats_in[id.row];
     // tokens, the stored logits at them and the uniforms go through LDS (lane i of the first wave
@@ -58,7 +58,7 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
     // lane), so that waiting for a token does not wait for the row behind it; the look-ups at the
     // tokens are then queued right behind the row, at indices brought into it, and arrive with it.
     int x = -1;
-    if constexpr (STEP) x = drafted->token;
+    if constexpr (STEP) x = drafted;
     float u_mine = 0.f;
     for (int i = 0; i < k; ++i) {
         int xi = -1;
@@ -360,6 +360,21 @@ __global__ __launch_bounds__(kWG, (kWG != 512 || NIT > 8 ? 4 : kStatsWavesPerSim
     __shared__ uint4 q_kept[kDraftChunksKept<NIT>][kWG];
     int phase = 0;
     rrs_node_resident<DT, NIT, MASKED, WO, STATS>(P, node_of_block(P), sh, q_kept, phase);
+}
+
+// Path-only: one workgroup per tree.  A node's decisions are the same in every wave; its token, and the draw that may give
+// it, are the first wave's, which writes them.  Where the row was streamed from memory in every round before, draft and path
+// call, us, 31-node trees: bf16 32000, 16 trees RRS 46.6 -> 34.2, RRSw 57.5 -> 39.1, 64 68.5 -> 49.4, 77.3 -> 53.0, 1000 287 -> 260,
+// 312 -> 267; 50304, 64 83 -> 63, 100 -> 71; 64 21-node trees of 32000, k = 4, 65.5 -> 43.2, 85.6 -> 55.4.
+template <int DT, int NIT, bool MASKED, bool WO, bool STATS>
+__global__ __launch_bounds__(kWG, 4) void rrs_path_resident(const Params P)
+{
+    __shared__ Shared sh;
+    __shared__ uint4 q_kept[kDraftChunksKept<NIT>][kWG];
+    int phase = 0;
+    walk_and_verify(P, [&](const NodeId& id) {
+        return rrs_node_resident<DT, NIT, MASKED, WO, STATS>(P, id, sh, q_kept, phase);
+    });
 }
 
 }  // namespace MDSD_NS

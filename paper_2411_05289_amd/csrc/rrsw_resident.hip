@@ -3,9 +3,9 @@
 
 namespace mdsd {
 
-void launch_rrsw_resident(int dtype, int nit, bool masked, dim3 grid, dim3 block, hipStream_t st, const Params& P)
+void launch_rrsw_resident(int dtype, int nit, bool masked, bool path, dim3 grid, dim3 block, hipStream_t st, const Params& P)
 {
-    launch_rrs_resident_m<true>(dtype, nit, masked, grid, block, st, P);
+    launch_rrs_resident_m<true>(dtype, nit, masked, path, grid, block, st, P);
 }
 
 }  // namespace mdsd

@@ -50,7 +50,7 @@ __device__ __forceinline__ NodeOut step_node_resident(const Params& P, const Nod
         leaf_resident<DT, NIT, MASKED, METHOD != kSpecHub || !MASKED, false>(P, rp, sp, ur[k], nullptr, sh, phase, o);
     } else {
         const RowView rq = make_row<DT>(P.draft, P.ld_d, id.row, P.V);
-        NodeDraft d = draft_node<DT, true, METHOD, kStepDraftNit<METHOD, DT, NIT, MASKED>, MASKED, METHOD == kRRSw>(
+        const NodeDraft d = draft_node<DT, true, METHOD, kStepDraftNit<METHOD, DT, NIT, MASKED>, MASKED, METHOD == kRRSw>(
             P, id, rq, P.u_draft + id.row * k, P.draft_flags, sh, phase, [&](const auto& row) {
                 if constexpr (kKept > 0) {
                     const int lane = threadIdx.x & 63, wave = wave_id();
@@ -60,28 +60,26 @@ __device__ __forceinline__ NodeOut step_node_resident(const Params& P, const Nod
                 asm volatile("" ::: "memory");  // not before the draft row's registers are free
                 sp.issue(rp, ExpW::fill());
             });
-        d.record.max_stored = uniform(d.record.max_stored);
-        d.record.rest_mass = uniform(d.record.rest_mass);
-        d.record.hub = uniform(d.record.hub);
+        const mdsd_row_stats record = d.record(sh);
         if constexpr (METHOD == kSpecHub) {
             NodeIn in;
             int flags = 0;
             in.u0 = ur[0];
             in.u1 = ur[1];
             in.u2 = ur[2];
-            in.x1 = uniform(token_of_draws<kSpecHub>(sh, 2, d.record.hub, 0, flags));
-            in.x2 = uniform(token_of_draws<kSpecHub>(sh, 2, d.record.hub, 1, flags));
+            in.x1 = uniform(token_of_draws<kSpecHub>(sh, 2, record.hub, 0, flags));
+            in.x2 = uniform(token_of_draws<kSpecHub>(sh, 2, record.hub, 1, flags));
             in.tokens_ok = in.x1 >= 0 && in.x1 < P.V && in.x2 >= 0 && in.x2 < P.V;
-            in.hub = d.record.hub >= 0 && d.record.hub < P.V ? d.record.hub : -1;
-            in.q_max = d.record.max_stored;
-            in.q_rest = d.record.rest_mass;
+            in.hub = record.hub >= 0 && record.hub < P.V ? record.hub : -1;
+            in.q_max = record.max_stored;
+            in.q_rest = record.rest_mass;
             fetch_node_lookups<DT, true>(id, P.V, rp, rq, in);
             RowSrc<DT, NIT, MASKED> unused;
             spechub_resident<DT, NIT, MASKED, true, false, kKept>(P, in, rp, rq, sp, unused, false, nullptr, sh, phase, o,
                                                                      q_kept);
         } else {
             rrs_resident<DT, NIT, MASKED, METHOD == kRRSw, true, true, (kKept > 0)>(P, id, rp, rq, sp, false, nullptr, sh,
-                                                                                    q_kept, phase, o, &d);
+                                                                                    q_kept, phase, o, d.token, record);
         }
     }
     write_node_outputs(P, id, o.outcome, o.token, o.rmass, o.flags);

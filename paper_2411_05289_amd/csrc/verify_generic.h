@@ -110,10 +110,7 @@ __device__ __forceinline__ NodeOut verify_node(const Params& P, const NodeId& id
         mdsd_row_stats record{0.f, 0.f, -1, 0};
         if constexpr (STEP) {
             record = draft_node<DT, LOGITS, METHOD, NIT, true, METHOD == kRRSw>(P, id, rq, P.u_draft + id.row * k, P.draft_flags,
-                                                                               sh, phase, [](const auto&) {}).record;
-            record.max_stored = uniform(record.max_stored);
-            record.rest_mass = uniform(record.rest_mass);
-            record.hub = uniform(record.hub);
+                                                                               sh, phase, [](const auto&) {}).record(sh);
         }
         const int32_t* xt = P.tokens + (int64_t)id.b * P.N + id.c0;
         CV cp{0.f, 0.f}, cq{0.f, 0.f};
