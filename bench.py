@@ -1,11 +1,11 @@
 #!/usr/bin/env python3
 """Benchmark of the sampling-verification hot path on one MI355X.
 
-A step = one pass of the whole path over one batch of synthetic token trees:
-spechub_draft (pair sampling for every internal node), spechub_verify (every
-node) and the tree walk, which the verify kernel runs itself at this batch size
-(two launches per step; a third launch for large batches, see --separate-walk).  Inputs are resident in HBM; the step rotates over
-several distinct copies of the batch so that the working set exceeds the
+A step = one pass of the whole path over one batch of synthetic token trees: pair sampling for every
+internal node, verification of every node and the tree walk, as StepPlan.run() does them (one
+launch at this batch size; --separate-walk and --walk-in-verify: the draft and the verify call one after
+the other, the walk a launch of its own or part of the verify kernel).  The draft and verify kernels
+are timed by themselves beside it.  Inputs are resident in HBM; the step rotates over several distinct copies of the batch so that the working set exceeds the
 256 MiB Infinity Cache and "HBM GB/s" is not cache bandwidth.
 
 Prints ONE JSON line (see the keys below).  --gpus above 1 is refused: this
@@ -172,8 +172,14 @@ def main():
     if args.walk_in_verify:
         fused = True
 
+    # the step in one call, unless the draft and the verify call were asked for
+    in_one = not (args.separate_walk or args.walk_in_verify)
+
     def step(i, ev=None):
         pl = plans[i % copies]
+        if in_one and ev is None:
+            pl.run(stream)
+            return pl.out["accept_depth"]
         pl.draft(stream)
         if ev is not None:
             ev[0].record()
@@ -207,7 +213,7 @@ def main():
     for i in range(args.warmup):
         step(i)
     torch.cuda.synchronize()
-    # Optional: one HIP graph per input copy holding the step's three launches, replayed in the
+    # Optional: one HIP graph per input copy holding the step's launches, replayed in the
     # timed region.
     graphs = []
     if args.graph:
@@ -217,12 +223,15 @@ def main():
             g = torch.cuda.CUDAGraph()
             with torch.cuda.graph(g, stream=side):
                 st = B._stream()
-                pl.draft(st)
-                if fused:
-                    pl.verify_and_walk(st)
+                if in_one:
+                    pl.run(st)
                 else:
-                    pl.verify(st)
-                    pl.walk(st)
+                    pl.draft(st)
+                    if fused:
+                        pl.verify_and_walk(st)
+                    else:
+                        pl.verify(st)
+                        pl.walk(st)
             graphs.append(g)
         torch.cuda.synchronize()
         # a replay must give what the eager step gives (checked on every copy, twice, with eager work between)
@@ -350,6 +359,8 @@ def main():
                    "k": k, "storage": wl0.dtype, "temperature": wl0.temp_target,
                    "step": "draft+verify+walk",
                    "launch": "hip graph replay" if graphs else
+                             "StepPlan.run(): drafted and verified in one launch where there is a kernel for the rows, the "
+                             "walk %s" % ("in it" if fused else "a launch of its own") if in_one else
                              ("two launches (walk inside the verify kernel)" if fused else "three launches"),
                    "input_copies_rotated": copies,
                    "settle_s_before_warmup": SETTLE_S,

@@ -410,8 +410,9 @@ WALK_IN_VERIFY_MAX_NODES = 3000
 
 
 class StepPlan:
-    """Marshalled arguments of one draft + verify + walk step, so that a serving loop pays
-    two or three foreign calls per step and nothing else.  The tensors handed in must stay
+    """Marshalled arguments of one draft + verify + walk step, so that a loop pays one
+    to three foreign calls per step and nothing else: run() where both rows of every node are at hand, draft() and one of the
+    verify calls where the target rows come between them.  The tensors handed in must stay
     alive and in place for the life of the plan.  walk_in_verify: True = the verify kernel
     walks the trees (one launch), False = the verify call places the walk (a launch of its own but for
     short rows), None = by batch size (WALK_IN_VERIFY_MAX_NODES)."""
