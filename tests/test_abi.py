@@ -165,3 +165,27 @@ def test_marshalling_that_does_not_load_says_why(monkeypatch):
     finally:
         if kept is not None:
             package._host = kept
+
+
+@pytest.mark.parametrize("missing", range(5))
+def test_steps_reject_before_anything_is_launched(missing):
+    """spechub_step checks the arguments of both calls first: each pointer that it needs, the workspace, the rows."""
+    L = B.lib()
+    res = B._Result()
+    res.outcome, res.token = 0x3000, 0x4000
+    args = [0x5000, 0x6000, 0x7000]          # never dereferenced
+    if missing < 3:
+        args[missing] = None
+    if missing == 3:
+        res.token = None
+
+    def call(p, ws=None, ws_bytes=0, out=C.byref(res)):
+        return L.spechub_step(C.byref(p), *args, None, None, None if missing == 4 else out, ws, ws_bytes, None)
+    assert call(_problem()) == -1
+    args[:] = [0x5000, 0x6000, 0x7000]
+    res.token, missing = 0x4000, -1
+    assert call(_problem(), 0x8000, 3) == -7 and call(_problem(), 0x8002, 8) == -6
+    assert call(_problem(temp_target=0.0)) == -4 and call(_problem(temp_draft=0.0)) == -4
+    res.emitted = 0x9000
+    assert call(_problem()) == -1
+    assert call(_problem(B=0)) == 0

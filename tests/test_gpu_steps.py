@@ -1,5 +1,7 @@
 """StepPlan.run(), which drafts and verifies a node in one kernel where there is one for its rows, against the CPU oracle
 at the edges of those kernels, and against the two calls on rows with little or nothing to draw from."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -165,3 +167,24 @@ def test_what_run_refuses():
     with_records = B.StepPlan("spechub", B.Problem.from_workload(wl), u_d, u_v)
     for key, got in no_records.run().items():
         assert torch.equal(got, with_records.run()[key])
+
+
+@pytest.mark.parametrize("method", ALL)
+@pytest.mark.parametrize("V,dtype", [(60, "bf16"), (3000, "bf16"), (9001, "bf16"), (70001, "bf16"), (33000, "fp32")])
+def test_trees_of_one_node_and_steps_without_a_walk(method, V, dtype):
+    """A tree that is its root drafts nothing; the C calls may leave the walk out."""
+    wl = _workload(5, 1, V, 2, 1, dtype, "logits")
+    _check_step(method, wl, range(5))
+    wl = _workload(5, 7, V, 2, 3, dtype, "logits")
+    u_d, u_v = uniforms(wl, 2)
+    plan = B.StepPlan(method, B.Problem.from_workload(wl), u_d, u_v)
+    want = {n: t.clone() for n, t in plan.run().items()}
+    _poison(plan)
+    hub = [plan.hub.data_ptr()] if method == "spechub" else []
+    args = [u_d.data_ptr(), u_v.data_ptr(), plan.tokens.data_ptr(), *hub, plan.draft_flags.data_ptr()]
+    rc = getattr(B.lib(), method + "_step")(C.byref(plan._cp), *args, C.byref(plan._res), None, 0, B._stream())
+    torch.cuda.synchronize()
+    assert rc == 0
+    for n in ("outcome", "token", "flags"):
+        assert torch.equal(plan.out[n], want[n]), n
+    assert (plan.out["accept_depth"] == -9).all() and (plan.out["emitted"] == -9).all()
