@@ -554,15 +554,25 @@ static bool half_width_step(int method, const Params& P, int nit)
 }
 
 // Steps, 1024 threads per node: chunks per lane, 0 = another build takes the call.  Later than in the verify calls, since
-// the draft gains from them too (512 -> 1024 threads, us a step, 31-node trees unless noted).
+// the draft gains from them too (512 -> 1024 threads, us a step, 31-node trees unless noted).  256 nodes run at once, so
+// that the gain ends a little before a multiple of that.
 // Rows of eight chunks per lane at 512 threads, up to 384 nodes where unaligned or long: bf16 20001, 372 nodes SpecHub 17.4
 // -> 16.6, RRSw 20.9 -> 19.4, 32000 19.5 -> 19.0, 23.0 -> 22.1, 496 23.9 -> 24.3, 25.9 -> 26.1; 20000 15.6 -> 15.6.  Sixteen: SpecHub
-// to 384 (50304, 372 27.4 -> 25.5, 434 29.1 -> 30.6), RRS methods to 640 (50257, 620 48.8 ->
-// 45.0, 744 49.6 -> 53.8), k > 2 to 800 (21-node trees, 40000, 756 42.1 -> 38.0).  Streamed rows: SpecHub to 640 (128256, 372 60.2
-// -> 50.9, 620 85.5 -> 78.6, 744 90.7 -> 91.1; 152064, 558 96.6 -> 85.3); k = 2 to 896, 1300 or 1100 by length (70001, 1240 91 -> 102;
-// 128256, 1240 159 -> 141, 1488 164 -> 165; 152064, 1240 186 -> 187); k = 3 to 1280 or 1950 (70001, 1950 113 -> 137; 100000, 1950
-// 163 -> 159; 152064, 1300 192 -> 166, 2600 280 -> 308); k = 4 to 1536 or 2200 (70001, 2100 124 -> 145; 152064, 1680 242 -> 195, 2100
-// 265 -> 252, 2688 with a quarter of them nearly uniform 312 -> 330).
+// to 384 (50304, 372 27.4 -> 25.5, 434 29.1 -> 30.6); RRS methods, k = 2, to 640 (50304, 558 45.2 -> 43.9), fp32 rows and those of
+// less than 5000 chunks to 448 (34000, 403 26.3 -> 24.3, 496 28.7 -> 30.2; fp32 24000 RRSw, 496 31.2 -> 30.8, 620 36.1 -> 39.8); k = 1
+// to 256 (50304, 250 24.8 -> 23.9, 400 34.9 -> 41.8); k = 3 to 768 (13-node trees, 50304, 650 42.0 -> 40.7, 780 43.9 -> 46.3), k = 4
+// to 870 (21-node trees, 819 48.8 -> 45.9, 861 49.1 -> 47.6, 966 49.8 -> 51.8).
+// Streamed rows: SpecHub to 640 (128256, 372 60.2 -> 50.9, 620 85.5 -> 78.6, 744 90.7 -> 91.1; 152064, 558 96.6 -> 85.3).  RRS
+// methods, by k (and by length: more than 9216 chunks, 16384), unaligned rows, whose wide kernels spill, sooner:
+//   1  256 (70001, 250 39.2 -> 32.9, 400 48.6 -> 56.4; 152064, 400 90.4 -> 94.8)
+//   2  as far as the verify call (70001, 868 75.2 -> 79.5), long rows 1300 (128256, 1240 159 -> 147, 1364 161 -> 160), longest 1100
+//      (152064 RRSw, 1054 160 -> 159, 1240 190 -> 189); unaligned 1024 (100001, 1054 108 -> 115, 1240 126 -> 134; 128257, 1147 150 -> 149),
+//      longest 780 (152065 RRSw, 713 144 -> 140, 806 148 -> 155)
+//   3  1280 (70001, 1300 97.5 -> 99.1), longer 1950 (100000, 1898 162 -> 163; 152064, 1300 192 -> 165, 2054 239 -> 247), unaligned 1400
+//      (100001, 1300 133 -> 127, 1495 136 -> 143; 152065, 1495 200 -> 206)
+//   4  1536 (70001, 1491 120 -> 108, 1701 121 -> 126), longer 2500 (100000, 2394 205 -> 190, 2793 210 -> 217; 128256, 2394 255 -> 228;
+//      152064, 2205 254 -> 253, 2394 305 -> 274, 2793 310 -> 317, 2688 with a quarter of them nearly uniform 312 -> 330), unaligned
+//      1800 or 1950 (100001, 1701 165 -> 153, 1890 168 -> 173; 128257, 1890 211 -> 196, 2058 215 -> 214; 152065, 2058 254 -> 260).
 static int wide_step_chunks(int method, const mdsd_problem* pb, const Params& P)
 {
     const int nit = resident_chunks(pb), wide = wide_chunks(P);
@@ -574,15 +584,69 @@ static int wide_step_chunks(int method, const mdsd_problem* pb, const Params& P)
     int64_t most = 0;
     if (nit == 8)
         most = P.masked || P.row_chunks > 3072 ? 384 : 0;
+    else if (nit == 16 && method == kSpecHub)
+        most = 384;
     else if (nit == 16)
-        most = method == kSpecHub ? 384 : P.k > 2 ? 800 : 640;
+        most = P.k > 3 ? 870 : P.k == 3 ? 768 : P.k == 1 ? 256 : pb->dtype == MDSD_FP32 || P.row_chunks < 5000 ? 448 : 640;
+    else if (nit == 0 && method == kSpecHub)
+        most = 640;
+    else if (nit == 0 && P.k == 1)
+        most = 256;
+    else if (nit == 0 && P.k == 2)
+        most = !longer    ? wide_rrs_nodes(pb, P)
+               : P.masked ? (wide == 20 ? 780 : 1024)
+                          : (wide == 20 ? 1100 : 1300);
+    else if (nit == 0 && P.k == 3)
+        most = !longer ? 1280 : P.masked ? 1400 : 1950;
     else if (nit == 0)
-        most = method == kSpecHub ? 640
-               : P.k == 2         ? (!longer ? 896 : wide == 20 ? 1100 : 1300)
-               : P.k == 3         ? (longer ? 1950 : 1280)
-               : P.k > 3          ? (longer ? 2200 : 1536)
-                                  : 1024;
+        most = !longer ? 1536 : !P.masked ? 2500 : P.row_chunks > 14000 ? 1950 : 1800;
     return nodes <= most ? wide : 0;
+}
+
+// Steps whose two calls one after the other are faster than one launch.  A draft kernel runs four nodes on a CU, 1024 at once,
+// but the step kernels of long rows run three (streamed rows, 768), two (sixteen chunks per lane, 512) or one (1024 threads,
+// 256): where the nodes with children fill a little more than the chip holds, what is left of them drafts by itself.  By
+// `inner`, the number of nodes with children (two launches -> one, us a step, 31-node trees, k = 2, unless noted):
+// Streamed rows, 769 to 1024 of them, RRS 70001, 750 99.1 -> 94.1, 795 109 -> 110, 900 116 -> 118, 945 118 -> 121, 1065 136 -> 127;
+// RRSw 115 -> 117, 121 -> 124, 123 -> 127, 142 -> 133; RRS 152064, 795 216 -> 222, 1065 279 -> 263; k = 1 100000, 800 112 -> 116; RRSw, k =
+// 3, to 840 only (13-node trees, 128256, 800 248 -> 252, 860 259 -> 257); SpecHub never (100000, 820 147 -> 140).  RRS, k = 4, up to
+// 2450 nodes on unaligned rows (152065, 2058 247 -> 254, 2394 303 -> 307, 2604 307 -> 308).
+// Sixteen chunks per lane, RRS 50304, 480 51.3 -> 49.0, 525 54.7 -> 58.1, 720 68.2 -> 71.0, 870 80.3 -> 79.7, 1065 98.4 -> 93.9, 1215
+// 109 -> 106, 1455 122 -> 123, 1785 145 -> 148, 2910 230 -> 235; RRSw 54.1 -> 51.3, 56.8 -> 61.5, 71.4 -> 75.6, 83.1 -> 83.9, 102 -> 98.4, 114
+// -> 111, 128 -> 129, 152 -> 156, 237 -> 245; fp32 24000 RRS 675 53.2 -> 53.9, 840 63.1 -> 62.4; k = 1 50304, 416 39.0 -> 37.2, 560 44.8 ->
+// 49.4, 1200 80.4 -> 82.8; k = 3 (42001, RRSw, 13-node trees, 400 62.0 -> 57.2, 528 69.8 -> 71.4, 584 76.9 -> 75.4, 952 109 -> 111,
+// 1200 138 -> 137, 1848 196 -> 203); SpecHub 33000, 1455 87.2 -> 86.9, 1785 99.1 -> 101, 4350 221 -> 232.
+// Between the sizes that 1024 threads gain at and those that 512 do: bf16, k = 2, from the third node of every CU on while the
+// verify call still takes 1024 threads (100000, 496 nodes 64.1 -> 57.8, 558 68.8 -> 69.8, 744 79.9 -> 81.6, 806 85.5 -> 89.6, 1147
+// 125 -> 116; 138048, 675 110 -> 116; fp32 40000, 713 56.6 -> 56.0, unaligned 45445, 720 68.9 -> 71.6); RRS on longer rows from
+// 1024 nodes on (152064, 961 149 -> 150, 1054 154 -> 163), unaligned from 512 on (152065, 558 109 -> 112, 713 133 -> 135; 868 at 512
+// threads 149 -> 146); k = 1, long rows, from 256 nodes on (128256, 400 69.8 -> 77.8, 700 96.4 -> 103, 850 of 100000 94.8 ->
+// 90.8).  Sixteen chunks, k > 2, fewer than 256 of them but too many nodes for 1024 threads (65500, 819 61.7 -> 65.0, 1050
+// 66.0 -> 67.5; 38000 41.6 -> 41.1, unaligned 38156 39.4 -> 40.2).
+static bool step_in_two(int method, const mdsd_problem* pb, const Params& P, int nit, int wide)
+{
+    const int64_t nodes = (int64_t)P.B * P.N, inner = (int64_t)P.B * ((P.N - 1) / P.k);
+    const bool bf16 = pb->dtype == MDSD_BF16;
+    if (nit == 16) {
+        if (wide) return false;
+        if (method == kSpecHub) return inner > 1550;
+        if (P.k > 2 && inner <= 256) return P.row_chunks > (P.masked ? 4500 : 5000);
+        if (inner > 1350) return true;
+        if (P.k > 2) return inner <= 1024 && (inner > 900 || (method == kRRSw && inner > 512 && inner <= 545));
+        return inner > 512 && (P.k == 1 || inner <= (bf16 || method == kRRSw ? 1024 : 750));
+    }
+    if (nit != 0 || method == kSpecHub) return false;
+    const int chunks = wide_chunks(P);  // 0: too long for 1024 threads
+    const bool longer = P.row_chunks > 9 * mdsd_wide::kThreads;
+    if (P.k == 2 && (bf16 || P.masked) && chunks && nodes > 2 * kWideMaxNodes) {
+        if (P.row_chunks < 18 * mdsd_wide::kThreads && nodes <= wide_rrs_nodes(pb, P)) return true;
+        if (chunks == 20 && method == kRRS && (P.masked ? nodes <= wide_rrs_nodes(pb, P) : wide && nodes > 4 * kWideMaxNodes))
+            return true;
+    }
+    if (wide) return false;
+    if (P.k == 1 && longer && chunks && chunks < 20 && inner <= 600) return true;
+    if (P.k > 3) return method == kRRS && longer && chunks && nodes <= 2450;
+    return inner > 768 && (P.k < 3 ? inner <= 1024 : method == kRRSw && inner <= 840);
 }
 
 // Lanes per node of the step kernels for short rows; 0: another build takes the call.  SpecHub in large batches of more
@@ -610,9 +674,7 @@ static bool launch_step(int method, const mdsd_problem* pb, const Params& P, hip
     const int nit = resident_chunks(pb), wide = wide_step_chunks(method, pb, P), small = small_build(pb);
     const dim3 grid = node_grid(P, wide ? wide : nit);
     if (small == 1) return false;  // SpecHub in large batches
-    // streamed rows, RRSw, k = 2, many nodes: in two launches the draft, which runs four nodes on a CU, is the faster by as much
-    // as the launch costs (bf16 100000, 1984 nodes 166 us, in one 170; 128256 212 and 214; 1488 173 and 166)
-    if (nit == 0 && !wide && method == kRRSw && P.k == 2 && (int64_t)P.B * P.N > 1700) return false;
+    if (small == 0 && step_in_two(method, pb, P, nit, wide)) return false;
     if (small == 2)
         mdsd_pair::launch_step(method, pb->dtype, masked, grid, st, P);
     else if (small == 4)

@@ -188,3 +188,39 @@ def test_trees_of_one_node_and_steps_without_a_walk(method, V, dtype):
     for n in ("outcome", "token", "flags"):
         assert torch.equal(plan.out[n], want[n]), n
     assert (plan.out["accept_depth"] == -9).all() and (plan.out["emitted"] == -9).all()
+
+
+@pytest.mark.parametrize("method,V,k,depth,Bn", [
+    ("rrs", 42001, 1, 5, 170),       # sixteen chunks per lane, 680 nodes with children: one launch would take 1.13 times as long
+    ("rrsw", 65500, 2, 5, 42),       # ... 630, 1.10
+    ("rrs", 70001, 1, 5, 170),       # longer rows on 1024 threads, 850 nodes: 1.30
+    ("rrs", 100000, 1, 5, 140),      # ... 700 nodes: 1.14
+    ("rrs", 100001, 3, 3, 131),      # ... 1703 nodes: 1.15
+])
+def test_one_call_is_not_slower_than_two(method, V, k, depth, Bn):
+    """Where the nodes with children fill a little more than the chip holds of a step kernel."""
+    wl = _workload(Bn, W.tree_nodes(k, depth), V, k, depth, "bf16", "logits")
+    u_d, u_v = uniforms(wl, 4)
+    plan = B.StepPlan(method, B.Problem.from_workload(wl), u_d, u_v)
+    assert plan.walk_in_verify
+    st = B._stream()
+
+    def two():
+        plan.draft(st)
+        plan.verify_and_walk(st)
+
+    def run():
+        plan.run(st)
+
+    best = {two: float("inf"), run: float("inf")}
+    for _ in range(12):
+        for call in best:
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            for _ in range(40):
+                call()
+            end.record()
+            end.synchronize()
+            best[call] = min(best[call], begin.elapsed_time(end))
+    # runs of one side differ by less than 2 %
+    assert best[run] < 1.04 * best[two], (best[run], best[two])
