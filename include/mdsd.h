@@ -251,9 +251,12 @@ int rrsw_verify(const mdsd_problem* pb, const int32_t* tokens, const float* u,
 /*
  * spechub_step / rrs_step / rrsw_step -- the draft call and the verify call of a method in one, for callers
  * that hold both rows of every node already (measured logits, acceptance studies, simulations): the same
- * arguments, outputs and errors as the two calls one after the other, everything checked before
- * anything is launched.  With pb->draft_stats set, and neither out->resid_mass nor
- * out->resid_prob, most rows are drafted and verified by one kernel that reads each row once as
+ * arguments and errors as the two calls one after the other, everything checked before anything is
+ * launched, and their outputs up to the rounding of sums that are formed in another order: a token, slot or
+ * flag can differ where a uniform lies within that of a boundary.  (On rows of more than 256 16-byte chunks the
+ * drafted tokens, flags and records are the draft call's bit for bit, RRS on aligned fp32 rows of 16384 to
+ * 32768 elements excepted.)  With pb->draft_stats set, and neither out->resid_mass nor
+ * out->resid_prob, rows of most sizes are drafted and verified by one kernel that reads each row once as
  * far as the method allows; other calls launch the two.  ws as for the verify calls.
  */
 int spechub_step(const mdsd_problem* pb, const float* u_draft, const float* u_verify, int32_t* tokens,

@@ -579,7 +579,8 @@ static int wide_step_chunks(int method, const mdsd_problem* pb, const Params& P)
     const bool longer = P.row_chunks > 9 * mdsd_wide::kThreads;
     const int64_t nodes = (int64_t)P.B * P.N;
     // Up to 256 nodes SpecHub stays where its verify call would run (aligned rows of sixteen chunks, streamed ones of more than
-    // sixteen at 1024 threads): the same sums in the same order, and the step gives what the two calls give.
+    // sixteen at 1024 threads): the same sums in the same order, and the step gives what the two calls give bit for bit.  Rows of
+    // eight chunks are not kept back: their draft is the same at any width, only the sums over the target row change their order.
     if (method == kSpecHub && nodes <= kWideMaxNodes && nit != 8 && !(nit == 16 ? P.masked : wide == 16)) return 0;
     int64_t most = 0;
     if (nit == 8)
@@ -649,7 +650,8 @@ static bool step_in_two(int method, const mdsd_problem* pb, const Params& P, int
     return inner > 768 && (P.k < 3 ? inner <= 1024 : method == kRRSw && inner <= 840);
 }
 
-// Lanes per node of the step kernels for short rows; 0: another build takes the call.  SpecHub in large batches of more
+// Lanes per node of the step kernels for short rows; 0: another build takes the call.  As in the verify calls, by the number of
+// all nodes; a draft call goes by those with children and may take more lanes, whose sums have another order.  SpecHub in large batches of more
 // than 64 chunks, whose verify calls take a wavefront per node, as well (4000 trees of 15 nodes, two launches -> one: bf16
 // 1000 73.6 -> 64.3 us, fp32 1000 95.2 -> 79.3), but bf16 rows of more than 128 chunks up to 24576 nodes only (1900, 18000 nodes
 // 44.5 -> 41.9; 1300, 27000 50.2 -> 50.9; 1100, 60000 91 -> 102).

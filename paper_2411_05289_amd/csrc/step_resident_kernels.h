@@ -23,7 +23,7 @@ namespace MDSD_NS {
 
 // Chunks per lane of the draft row while it is drafted from, 0 = streamed: the draft kernels' choice, with whose slab sums,
 // records and tokens a step's agree bit for bit (a draw among 100 thousand tokens is within rounding of its neighbour once in
-// a thousand).
+// a thousand).  Not RRS on aligned fp32 rows at 1024 threads, which a draft call holds in registers in small batches only.
 template <int METHOD, int DT, int NIT, bool MASKED>
 constexpr int kStepDraftNit =
     NIT * kWG <= 4096 || (kWG == 1024 && NIT == 8 && METHOD == kRRS && DT == 0 && !MASKED) ? NIT : 0;

@@ -190,6 +190,65 @@ def test_trees_of_one_node_and_steps_without_a_walk(method, V, dtype):
     assert (plan.out["accept_depth"] == -9).all() and (plan.out["emitted"] == -9).all()
 
 
+def _both(method, wl, seed):
+    """What run() leaves and what draft() and the verify call leave, as dicts of tensors."""
+    u_d, u_v = uniforms(wl, seed)
+    plan = B.StepPlan(method, B.Problem.from_workload(wl), u_d, u_v)
+    sides = []
+    for call in (plan.run, lambda: (plan.draft(), plan.verify_and_walk())):
+        _poison(plan)
+        call()
+        torch.cuda.synchronize()
+        records = plan.pb.draft_stats
+        left = dict(plan.out, tokens=plan.tokens, draft_flags=plan.draft_flags, largest=records[..., 0], rest=records[..., 1],
+                    record_hub=records.view(torch.int32)[..., 2])
+        if method == "spechub":
+            left["hub"] = plan.hub
+        sides.append({n: t.clone() for n, t in left.items() if t is not None})
+    return sides
+
+
+@pytest.mark.parametrize("method,k", [("spechub", 2), ("rrs", 2), ("rrsw", 2), ("rrs", 3), ("rrsw", 4)])
+@pytest.mark.parametrize("dtype,V,off,nodes", [
+    ("bf16", 2100, 0, 900), ("bf16", 7001, 3, 900), ("bf16", 9001, 1, 900), ("bf16", 12000, 0, 3300), ("fp32", 7001, 2, 3300),
+    ("bf16", 20001, 1, 300), ("bf16", 32000, 0, 380), ("bf16", 20001, 0, 3300), ("bf16", 50304, 0, 300), ("bf16", 42001, 1, 900),
+    ("fp32", 20001, 1, 300), ("bf16", 70001, 1, 400), ("bf16", 128256, 0, 300), ("bf16", 152064, 0, 300), ("bf16", 131073, 3, 900),
+])
+def test_drafts_of_a_step(method, k, dtype, V, off, nodes):
+    """Rows of more than 256 chunks: the tokens, flags and records of the draft call, bit for bit."""
+    N = W.tree_nodes(k, 3)
+    one, two = _both(method, _workload(max(1, nodes // N), N, V, k, 3, dtype, "logits", off, seed=V), 6)
+    for n in ("tokens", "draft_flags", "largest", "rest", "record_hub", "hub"):
+        if n in one:
+            assert torch.equal(one[n], two[n]), n
+
+
+@pytest.mark.parametrize("method,k,depth,dtype,V,Bn", [
+    ("spechub", 2, 4, "bf16", 60, 1500), ("rrs", 2, 4, "bf16", 60, 1500), ("rrsw", 3, 3, "bf16", 60, 1700),  # 4 lanes, drafted with 8 or 16
+    ("spechub", 2, 4, "fp32", 50, 900), ("rrsw", 2, 4, "fp32", 50, 900),                                     # 8 and 16
+    ("spechub", 2, 4, "bf16", 1000, 400), ("rrs", 4, 3, "bf16", 1000, 400), ("rrsw", 2, 2, "bf16", 250, 1500),
+    ("rrs", 2, 4, "fp32", 20000, 24), ("rrs", 3, 3, "fp32", 32000, 50),                                      # 1024 threads, drafted from memory
+])
+def test_steps_within_rounding(method, k, depth, dtype, V, Bn):
+    """Where the sums of the draft call are formed in another order: what both leave is the same except where a uniform lies
+    within rounding of a boundary."""
+    N = W.tree_nodes(k, depth)
+    one, two = _both(method, _workload(Bn, N, V, k, depth, dtype, "logits", seed=V), 8)
+    # A row's V boundaries move by less than 2^-25 each (half an ulp of sums that are mostly far from the largest), so that of
+    # `nodes` nodes with k + 1 draws and k tests fewer than 2 (2 k + 1) V 2^-25 find a uniform on the other side; each changes its tree
+    # only.  (Counted at V = 32000: one in 2600 nodes, a 25th of that.)  One tree more, for the batches in which that is none.
+    expected = 2.0 ** -24 * (2 * k + 1) * V * Bn * N
+    other = torch.zeros(Bn, dtype=torch.bool, device=DEV)
+    for n in ("outcome", "token", "flags", "tokens", "draft_flags", "accept_depth", "emitted"):
+        other |= (one[n] != two[n]).view(Bn, -1).any(1)
+    assert int(other.sum()) <= 1 + expected
+    for n in ("largest", "record_hub", "hub"):
+        if n in one:
+            assert torch.equal(one[n], two[n]), n
+    # sums of V positive terms in another order
+    assert torch.allclose(one["rest"], two["rest"], rtol=2e-6, atol=0.0)
+
+
 @pytest.mark.parametrize("method,V,k,depth,Bn", [
     ("rrs", 42001, 1, 5, 170),       # sixteen chunks per lane, 680 nodes with children: one launch would take 1.13 times as long
     ("rrsw", 65500, 2, 5, 42),       # ... 630, 1.10
