@@ -148,3 +148,37 @@ def test_draws_at_rounded_boundaries(method, V, stride):
     d = DRAFT[method](B.Problem(None, rows, B.PROBS, 2, 2), u_d)
     check(d["tokens"][:, 1])
     assert (d["flags"] == 0).all()
+
+
+@pytest.mark.parametrize("method,k", [("spechub", 2), ("rrs", 2), ("rrs", 4), ("rrsw", 2), ("rrsw", 4)])
+@pytest.mark.parametrize("dtype,V,off,Bn", [
+    ("bf16", 9001, 3, 1536), ("bf16", 12000, 0, 1601), ("bf16", 16369, 1, 1601), ("fp32", 7001, 2, 1601), ("fp32", 8000, 0, 1601),
+    ("bf16", 20001, 1, 1920), ("bf16", 32000, 0, 1921), ("fp32", 12000, 0, 1921), ("fp32", 16373, 3, 1921),
+])
+def test_drafts_of_large_batches(method, k, dtype, V, off, Bn):
+    """256 threads per node where the nodes with children do not fit the chip at once: the oracle's tokens, hub and flags except
+    where a uniform lies within 1e-6 of a boundary, and bit for bit what the same rows draft in a small batch."""
+    N = W.tree_nodes(k, 2)
+    buf = torch.zeros(Bn * N * V + 16, dtype=torch.float32 if dtype == "fp32" else torch.bfloat16, device=DEV)
+    rows = buf[off:off + Bn * N * V].view(Bn, N, V)
+    rows.normal_(0.0, 2.0, generator=torch.Generator(device=DEV).manual_seed(V))
+    wl = W.Workload("large", Bn, N, V, k, 2, dtype, "logits", 1.0, 0.9, rows, rows)
+    u_d, _ = uniforms(wl, V)
+    pb = B.Problem.from_workload(wl).with_draft_stats()
+    g = DRAFT[method](pb, u_d)
+    for part in (slice(0, 4), slice(Bn - 4, Bn)):
+        small = B.Problem(rows[part], rows[part], B.LOGITS, k, 2, 1.0, 0.9).with_draft_stats()
+        s = DRAFT[method](small, u_d[part].contiguous())
+        for name, t in s.items():
+            if t is not None:
+                assert torch.equal(t, g[name][part]), name
+        assert torch.equal(small.draft_stats.view(torch.int32), pb.draft_stats[part].view(torch.int32))
+    seqs = [0, Bn // 2, Bn - 1]
+    o = oracle.batch_draft(METHODS[method], W.rows_as_numpy(rows[seqs]), _np(u_d[seqs]), temp_draft=0.9, nthreads=8,
+                           **oracle_kwargs(wl))
+    sure = o["margin"][:, 0] > 1e-6
+    assert sure.any()
+    assert (_np(g["tokens"][seqs])[sure] == o["tokens"][sure]).all()
+    assert (_np(g["flags"][seqs]) == o["flags"]).all()
+    if method == "spechub":
+        assert (_np(g["hub"][seqs]) == o["hub"]).all()

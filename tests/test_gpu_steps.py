@@ -85,6 +85,21 @@ def test_long_rows(method, k, dtype, V, off, Bn):
     _check_step(method, wl, range(Bn) if Bn < 9 else [0, 1, Bn - 1])
 
 
+@pytest.mark.parametrize("method,k", [("spechub", 2), ("rrs", 2), ("rrsw", 2), ("rrsw", 4)])
+@pytest.mark.parametrize("dtype,V,off,nodes", [
+    ("bf16", 32000, 0, 300), ("bf16", 50304, 0, 300), ("bf16", 131080, 0, 300), ("bf16", 140001, 1, 300),  # 1024 threads
+    ("bf16", 152064, 0, 30), ("bf16", 152064, 0, 300), ("bf16", 152064, 0, 600), ("fp32", 20000, 0, 300), ("fp32", 70000, 0, 300),
+    ("bf16", 50304, 0, 600), ("bf16", 131080, 0, 600),
+    ("fp32", 7000, 0, 3000), ("fp32", 7001, 1, 3000), ("bf16", 9000, 0, 3000),                             # 256, eight chunks
+    ("bf16", 20001, 3, 3000), ("fp32", 12000, 0, 3000), ("fp32", 12001, 3, 3000),                          # ... sixteen
+])
+def test_builds_by_batch_size(method, k, dtype, V, off, nodes):
+    """Batches that take another number of threads per node than the smallest ones."""
+    N = W.tree_nodes(k, 3)
+    Bn = -(-nodes // N)
+    _check_step(method, _workload(Bn, N, V, k, 3, dtype, "logits", off), [0, Bn // 2, Bn - 1])
+
+
 @pytest.mark.parametrize("method,k", [("spechub", 2), ("rrs", 2), ("rrs", 7), ("rrsw", 3), ("rrsw", 8), ("rrs", 1)])
 @pytest.mark.parametrize("V,dtype,Bn", [(16, "fp32", 1), (50, "fp32", 17), (60, "bf16", 700), (200, "bf16", 401),
                                         (1025, "bf16", 9), (2041, "bf16", 33), (1019, "fp32", 9), (50, "fp32", 30001),
