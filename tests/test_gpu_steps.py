@@ -8,8 +8,8 @@ import torch
 
 from paper_2411_05289_amd import binding as B
 from paper_2411_05289_amd import workloads as W
-from parity import BAND, METHODS, _check_stats, _compare_nodes, _compare_walk, _internal_mask, _np, mismatch_allowance
-from parity import oracle_kwargs, uniforms
+from parity import BAND, METHODS, _check_stats, _compare_nodes, _compare_walk, _internal_mask, _np, check_case
+from parity import mismatch_allowance, oracle_kwargs, uniforms
 from test_gpu_routes import _workload
 import oracle
 
@@ -92,6 +92,10 @@ def test_long_rows(method, k, dtype, V, off, Bn):
     ("bf16", 50304, 0, 600), ("bf16", 131080, 0, 600),
     ("fp32", 7000, 0, 3000), ("fp32", 7001, 1, 3000), ("bf16", 9000, 0, 3000),                             # 256, eight chunks
     ("bf16", 20001, 3, 3000), ("fp32", 12000, 0, 3000), ("fp32", 12001, 3, 3000),                          # ... sixteen
+    ("bf16", 6000, 0, 30), ("fp32", 3000, 0, 30), ("fp32", 1500, 0, 30),                                   # ... four; 128
+    ("bf16", 20001, 1, 900), ("fp32", 12001, 1, 900), ("fp32", 20001, 1, 600), ("fp32", 20000, 0, 600),    # 512
+    ("fp32", 33001, 0, 1400), ("fp32", 66000, 0, 2800),                                                    # ... from memory
+    ("fp32", 12001, 1, 300), ("fp32", 40001, 1, 300), ("fp32", 70001, 1, 300),                             # 1024, unaligned
 ])
 def test_builds_by_batch_size(method, k, dtype, V, off, nodes):
     """Batches that take another number of threads per node than the smallest ones."""
@@ -109,6 +113,30 @@ def test_short_rows(method, k, V, dtype, Bn):
     for depth in (2, 3) if k == 2 and Bn < 9000 else (2,):
         wl = _workload(Bn, W.tree_nodes(k, depth), V, k, depth, dtype, "logits", off=1)
         _check_step(method, wl, sorted({0, Bn // 2, Bn - 1}))
+
+
+@pytest.mark.parametrize("method", ALL)
+@pytest.mark.parametrize("what", ["step", "logits", "probs"])
+@pytest.mark.parametrize("dtype,V,depth,Bn", [
+    ("bf16", 16, 2, 1), ("bf16", 16, 4, 1), ("bf16", 16, 4, 1101),      # 4 lanes per node: a wavefront per node number, whole
+    ("bf16", 30, 2, 1), ("bf16", 30, 4, 1), ("bf16", 240, 4, 1101),     # trees in a workgroup, nodes in any order; 8 lanes
+    ("bf16", 60, 2, 1), ("bf16", 60, 4, 1), ("bf16", 250, 4, 1101),     # 16
+    ("bf16", 250, 2, 700), ("bf16", 250, 4, 1), ("bf16", 900, 5, 201),  # 32
+    ("bf16", 250, 2, 1), ("bf16", 250, 5, 1),                           # 64, no wavefront per node number
+    ("fp32", 16, 2, 1), ("fp32", 16, 4, 1), ("fp32", 16, 4, 1101),
+    ("fp32", 14, 2, 1), ("fp32", 14, 4, 1), ("fp32", 100, 4, 1101),
+    ("fp32", 30, 2, 1), ("fp32", 30, 4, 1), ("fp32", 250, 4, 1101),
+    ("fp32", 100, 2, 1), ("fp32", 100, 4, 1), ("fp32", 400, 5, 201),
+    ("fp32", 250, 2, 1), ("fp32", 400, 4, 1),
+])
+def test_every_group(method, what, dtype, V, depth, Bn):
+    """Short rows: every number of lanes with every way of walking the trees."""
+    wl = _workload(Bn, W.tree_nodes(2, depth), V, 2, depth, dtype, "probs" if what == "probs" else "logits")
+    seqs = sorted({0, Bn // 2, Bn - 1})
+    if what == "step":
+        _check_step(method, wl, seqs)
+    else:
+        check_case(method, wl, seed=V, seqs=seqs, full_outputs=Bn < 999)
 
 
 @pytest.mark.parametrize("method", ALL)
