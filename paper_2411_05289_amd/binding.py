@@ -398,14 +398,16 @@ def tree_walk(pb: Problem, outcome, token, accept_depth=None, emitted=None):
     return ad, em
 
 
-# Up to this many tree nodes per batch, StepPlan.run() hands the verify call its workspace, with which
-# the kernel walks the trees itself (two launches per step); beyond it the call launches the walk
+# Up to this many tree nodes per batch, StepPlan.run() hands the step call its workspace, with which
+# the kernel walks the trees itself; beyond it the call launches the walk
 # behind the kernel (rows short enough for whole trees in a workgroup are walked inside either way).
 # The arrival count keeps a finished workgroup about a microsecond longer on its compute unit, which
 # costs more than the walk's own launch (2-3 us) once a batch is several times what the chip holds at once: measured on one MI355X,
-# 31-node trees at V = 32000, the two placements timed in turns in one process: B = 16 26.4 against
-# 26.6 us per step, B = 32 36.9 / 37.5, B = 64 54.6 / 54.9, B = 96 73.5 / 73.5, B = 128 91.6 / 91.1,
-# B = 256 171.1 / 166.7, B = 1024 632 / 621.
+# SpecHub on 31-node trees, walk inside against walk behind, us a step drafted and verified in one launch (and in two): V = 32000 bf16,
+# 496 nodes 20.0 / 20.9 (25.0 / 25.1), 2015 47.1 / 48.3 (52.3 / 52.7), 3007 62.6 / 63.4 (69.3 / 69.3), 3999 78.9 / 78.8 (87.2 / 86.2),
+# 7998 153 / 151 (166 / 161); V = 9000, 3007 27.6 / 28.5, 3999 33.8 / 33.7, 6014 47.7 / 47.1; V = 128256, 992 101.0 / 101.8, 2015 181 /
+# 179, 3999 328 / 316; RRS, V = 32000, 3999 83.5 / 84.2, 6014 121 / 119.  Rows with two wavefronts per node would walk behind the
+# kernel from the start (V = 3000, 992 nodes 14.3 / 12.9, 2015 17.1 / 13.6, 3999 19.0 / 18.0; RRS 17.1 / 14.7, 19.0 / 19.8).
 WALK_IN_VERIFY_MAX_NODES = 3000
 
 

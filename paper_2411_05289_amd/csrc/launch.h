@@ -14,12 +14,12 @@ void launch_spechub_resident(int dtype, int nit, bool masked, bool path, dim3 gr
 void launch_rrs_resident(int dtype, int nit, bool masked, bool path, dim3 grid, dim3 block, hipStream_t st, const Params& P);
 void launch_rrsw_resident(int dtype, int nit, bool masked, bool path, dim3 grid, dim3 block, hipStream_t st, const Params& P);
 
-// verify_generic_*.hip: every other case (nit = 0: rows streamed in every pass)
-// drafting and verifying a node in one launch (step_resident_kernels.h)
+// step_*.hip: drafting and verifying a node in one launch (nit = 0: rows streamed in every pass)
 void launch_step_spechub(int dtype, int nit, bool masked, dim3 grid, hipStream_t st, const Params& P);
 void launch_step_rrs(int dtype, int nit, bool masked, dim3 grid, hipStream_t st, const Params& P);
 void launch_step_rrsw(int dtype, int nit, bool masked, dim3 grid, hipStream_t st, const Params& P);
 
+// verify_generic_*.hip: every other verification (nit = 0: rows streamed in every pass)
 void launch_verify_generic_spechub(int dtype, bool logits, int nit, bool path, dim3 grid, dim3 block,
                                    hipStream_t st, const Params& P);
 void launch_verify_generic_rrs(int dtype, bool logits, int nit, bool path, dim3 grid, dim3 block, hipStream_t st,

@@ -563,9 +563,9 @@ static bool half_width_step(int method, const Params& P, int nit)
 // to 256 (50304, 250 24.8 -> 23.9, 400 34.9 -> 41.8); k = 3 to 768 (13-node trees, 50304, 650 42.0 -> 40.7, 780 43.9 -> 46.3), k = 4
 // to 870 (21-node trees, 819 48.8 -> 45.9, 861 49.1 -> 47.6, 966 49.8 -> 51.8).
 // Streamed rows: SpecHub to 640 (128256, 372 60.2 -> 50.9, 620 85.5 -> 78.6, 744 90.7 -> 91.1; 152064, 558 96.6 -> 85.3).  RRS
-// methods, by k (and by length: more than 9216 chunks, 16384), unaligned rows, whose wide kernels spill, sooner:
+// methods, by k and by length (more than 9216 chunks; 16384), unaligned rows less far:
 //   1  256 (70001, 250 39.2 -> 32.9, 400 48.6 -> 56.4; 152064, 400 90.4 -> 94.8)
-//   2  as far as the verify call (70001, 868 75.2 -> 79.5), long rows 1300 (128256, 1240 159 -> 147, 1364 161 -> 160), longest 1100
+//   2  as far as the verify call takes 1024 threads (70001, 868 75.2 -> 79.5), long rows 1300 (128256, 1240 159 -> 147, 1364 161 -> 160), longest 1100
 //      (152064 RRSw, 1054 160 -> 159, 1240 190 -> 189); unaligned 1024 (100001, 1054 108 -> 115, 1240 126 -> 134; 128257, 1147 150 -> 149),
 //      longest 780 (152065 RRSw, 713 144 -> 140, 806 148 -> 155)
 //   3  1280 (70001, 1300 97.5 -> 99.1), longer 1950 (100000, 1898 162 -> 163; 152064, 1300 192 -> 165, 2054 239 -> 247), unaligned 1400

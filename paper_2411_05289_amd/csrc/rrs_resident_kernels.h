@@ -308,7 +308,7 @@ __device__ __forceinline__ void rrs_resident(const Params& P, const NodeId& id, 
     }
     if (!slabs_current) {
         __syncthreads();
-        residual_pass(c, std::bool_constant<KEPT_BY_NOW>{}, std::false_type{});  // rare: all of the draft row from memory again
+        residual_pass(c, std::bool_constant<KEPT_BY_NOW>{}, std::false_type{});  // rare: the pass once more, with the c of before
     }
     const float c_iZq = c * iZq;
     auto cw = [&](int s, float(&w)[E]) {
@@ -366,6 +366,9 @@ __global__ __launch_bounds__(kWG, (kWG != 512 || NIT > 8 ? 4 : kStatsWavesPerSim
 // it, are the first wave's, which writes them.  Where the row was streamed from memory in every round before, draft and path
 // call, us, 31-node trees: bf16 32000, 16 trees RRS 46.6 -> 34.2, RRSw 57.5 -> 39.1, 64 68.5 -> 49.4, 77.3 -> 53.0, 1000 287 -> 260,
 // 312 -> 267; 50304, 64 83 -> 63, 100 -> 71; 64 21-node trees of 32000, k = 4, 65.5 -> 43.2, 85.6 -> 55.4.
+// Two workgroups per CU are asked for, at which the bf16 instances of eight chunks per lane on aligned rows and those of sixteen
+// spill 13 to 17 vector registers (up to 68 bytes a lane), fp32 ones of sixteen up to 10, and the walk's scalars go to vector
+// lanes (90 to 190 of them).  What one workgroup per CU would give has not been measured.
 template <int DT, int NIT, bool MASKED, bool WO, bool STATS>
 __global__ __launch_bounds__(kWG, 4) void rrs_path_resident(const Params P)
 {

@@ -13,6 +13,9 @@
 // 32.2 -> 24.3; RRS 32000, 64 54.5 -> 51.9, RRSw 57.4 -> 55.4, unaligned 32001 74.8 -> 59.0; fp32 32000, one 15-node tree 19.0 ->
 // 16.6.
 // 128 and 1024 threads: 64 trees of bf16 3000 23.2 -> 17.0, RRSw 26.2 -> 19.0; 8 trees of 128256 SpecHub 49.9 -> 46.6, RRS 61.8 -> 52.8.
+// Registers: at four waves per SIMD the bf16 kernels of sixteen chunks on aligned rows spill 15 of them (64 bytes a lane; SpecHub
+// with 256 and 1024 threads, RRS with any), those of twenty chunks 13 to 71 (RRS on aligned rows 212 bytes); without them, by an
+// exact maximum, the 256-thread kernel was slower (46.9 -> 48.8).
 // Both rows asked for at the start (two nodes per CU) was slower (64 trees 55.0), and so were leaves among the nodes with
 // children (one to every four of them 51.3, to every one 58.2).
 #pragma once

@@ -629,7 +629,7 @@ __global__ __launch_bounds__(kWG) void verify_kernel(const Params P)
 }
 
 // Steps on rows too long for registers, three nodes per CU like the verify kernel (two launches -> one: config 4, SpecHub
-// 627 -> 603 us; 32 15-node trees of 128256 65.6 -> 63.2; 128 21-node trees of 152064, k = 4, RRS 312 -> 308, RRSw 336 -> 319).
+// 627 -> 603 us; 32 15-node trees of 128256 65.6 -> 63.2; 128 21-node trees of 152064, k = 4, RRS 313 -> 315, RRSw 335 -> 322).
 template <int DT, int METHOD>
 __global__ __launch_bounds__(kWG, 6) void step_streamed_kernel(const Params P)
 {
