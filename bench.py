@@ -2,10 +2,11 @@
 """Benchmark of the sampling-verification hot path on one MI355X.
 
 A step = one pass of the whole path over one batch of synthetic token trees: pair sampling for every
-internal node, verification of every node and the tree walk, as StepPlan.run() does them (one
-launch at this batch size; --separate-walk and --walk-in-verify: the draft and the verify call one after
-the other, the walk a launch of its own or part of the verify kernel).  The draft and verify kernels
-are timed by themselves beside it.  Inputs are resident in HBM; the step rotates over several distinct copies of the batch so that the working set exceeds the
+internal node, verification of every node and the tree walk, as StepPlan.run() does them: both rows of every
+node are at hand, and most sizes take one launch, this one too (--separate-walk and --walk-in-verify: the draft and the verify
+call one after the other, the walk a launch of its own or part of the verify kernel).  `draft_then_verify` is the same
+work as a decoder does it, whose target rows come after its draft: the two calls, timed beside the step with each of their
+kernels.  Inputs are resident in HBM; the step rotates over several distinct copies of the batch so that the working set exceeds the
 256 MiB Infinity Cache and "HBM GB/s" is not cache bandwidth.
 
 Prints ONE JSON line (see the keys below).  --gpus above 1 is refused: this
@@ -62,7 +63,7 @@ def parse():
                          "beyond)")
     ap.add_argument("--graph", action="store_true",
                     help="replay one HIP graph per step instead of launching its kernels one by one "
-                         "(measured slower on this workload: 58.8 against 53.8 us per step)")
+                         "(slower on this workload when a step was two launches: 58.8 against 53.8 us)")
     ap.add_argument("--no-path-only", action="store_true",
                     help="skip the extra measurement of the path-only step (draft + *_verify_path)")
     ap.add_argument("--calibration-copy", action="store_true",
@@ -163,9 +164,9 @@ def main():
     plans = [B.StepPlan(args.method, pbs[i], u_d[i], u_v[i], hand_stats=not args.no_stats) for i in range(copies)]
     stream = B._stream()
 
-    # where the tree walk runs: inside the verify kernel (two launches per step) or as a launch
-    # of its own (three); by default as StepPlan.run() places it: by the binding's rule by batch size, and the toy
-    # experiment's trees, whose rows are short, in the verify kernel's workgroups at any size
+    # where the tree walk runs: inside the step's or verify kernel or as a launch
+    # of its own; by default as StepPlan.run() places it: by the binding's rule by batch size, and the toy
+    # experiment's trees, whose rows are short, in the kernel's workgroups at any size
     fused = plans[0].walk_in_verify or toy
     if args.separate_walk:
         fused = False
@@ -299,22 +300,31 @@ def main():
     verify_launch = (lambda pl: pl.verify_and_walk(stream)) if fused else (lambda pl: pl.verify(stream))
     kernel_ms, one_ms = differential(lambda pl: pl.draft(stream), verify_launch)
     event_overhead_ms = one_ms - kernel_ms
-    achieved = alg_bytes / (kernel_ms * 1e-3) / 1e9
+    # the timed step's launches, bracketed the same way
+    run_ms, run_one_ms = differential(lambda pl: None, lambda pl: pl.run(stream)) if in_one else (None, None)
     draft_ms, _ = differential(lambda pl: None, lambda pl: pl.draft(stream))
     # the other placement of the walk, measured beside the one the step uses: the same verify
     # kernel without (or with) the walk in it, and the step with three (or two) launches
     other_launch = (lambda pl: pl.verify(stream)) if fused else (lambda pl: pl.verify_and_walk(stream))
     other_kernel_ms, _ = differential(lambda pl: pl.draft(stream), other_launch)
-    torch.cuda.synchronize()
-    t1 = time.perf_counter()
-    for i in range(args.steps):
-        pl = plans[i % copies]
-        pl.draft(stream)
-        other_launch(pl)
-        if fused:
-            pl.walk(stream)
-    torch.cuda.synchronize()
-    other_step_ms = 1e3 * (time.perf_counter() - t1) / args.steps
+
+    def two_calls(walk_inside):
+        """ms of a step that is the draft and the verify call one after the other."""
+        torch.cuda.synchronize()
+        t1 = time.perf_counter()
+        for i in range(args.steps):
+            pl = plans[i % copies]
+            pl.draft(stream)
+            if walk_inside:
+                pl.verify_and_walk(stream)
+            else:
+                pl.verify(stream)
+                pl.walk(stream)
+        torch.cuda.synchronize()
+        return 1e3 * (time.perf_counter() - t1) / args.steps
+
+    other_step_ms = two_calls(not fused)
+    two_calls_ms = two_calls(fused) if in_one else ms_per_step
     es = 2 if wl0.dtype == "bf16" else 4
     draft_bytes = Bn * wl0.n_internal * wl0.V * es
     # Reference line: a plain device copy of the same target rows (the library's copy kernel,
@@ -341,8 +351,11 @@ def main():
     plain_copy_gbs = copy_bytes / (copy_ms * 1e-3) / 1e9 if copy_ms > 0 else None
     del dst
     tps = float(ad.float().mean().item()) + 1.0
-    kernel_key = "%s_verify:%s" % (args.method, wl0.name)
-    traffic, traffic_source = plausible_traffic(read_traffic(kernel_key), kernel_ms)
+    timed = "%s_step" % args.method if in_one else "%s_verify" % args.method
+    timed_ms = run_ms if in_one else kernel_ms
+    traffic, traffic_source = plausible_traffic(read_traffic("%s:%s" % (timed, wl0.name)), timed_ms)
+    achieved = alg_bytes / (timed_ms * 1e-3) / 1e9
+    verify_traffic, _ = plausible_traffic(read_traffic("%s_verify:%s" % (args.method, wl0.name)), kernel_ms)
     draft_traffic, _ = plausible_traffic(read_traffic("%s_draft:%s" % (args.method, wl0.name)), draft_ms)
 
     if toy:
@@ -367,38 +380,55 @@ def main():
                    "early_exit": True,
                    "draft_stats_handed_to_verify": not args.no_stats,
                    "tokens_per_step_last_batch": tps},
+        # Of what the timed step launches (--separate-walk, --walk-in-verify: of its verify kernel).
         # achieved = ALGORITHMIC bytes (every needed row once: the target row of every node, the draft
-        # row of every internal node) / kernel time.  With the draft call's records and early exit
-        # the kernel skips the draft rows of nodes decided by their first test, so it moves fewer
-        # bytes than that: `traffic` (rocprofv3 counters, offline) and `frac_of_bytes_moved` say
-        # what the memory system really did.
-        "roofline": {"bound": "hbm", "kernel": "%s_verify" % args.method, "achieved": achieved,
+        # row of every internal node) / kernel time.  `traffic` (rocprofv3 counters, offline) and
+        # `frac_of_bytes_moved` say what the memory system really did: a step's rejected nodes read their draft
+        # row again, a verify kernel that is handed the draft call's records skips those of the others.
+        "roofline": {"bound": "hbm", "kernel": timed, "achieved": achieved,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-                     "achieved_is": "algorithmic bytes (includes rows an early exit skips) / kernel time",
-                     "algorithmic_bytes_per_launch": alg_bytes, "kernel_ms": kernel_ms,
+                     "achieved_is": "algorithmic bytes (every needed row once) / time of the step's launches" if in_one else
+                                    "algorithmic bytes (includes rows an early exit skips) / kernel time",
+                     "algorithmic_bytes_per_launch": alg_bytes, "kernel_ms": timed_ms,
                      "kernel_reps": reps,
-                     "event_bracket_ms": bracket_ms, "event_overhead_ms": event_overhead_ms,
+                     "event_bracket_ms": run_one_ms if in_one else bracket_ms,
+                     "event_overhead_ms": run_one_ms - run_ms if in_one else event_overhead_ms,
                      "traffic": traffic,
                      "traffic_source": traffic_source,
-                     "hbm_measured_gbs": None if traffic is None else traffic / (kernel_ms * 1e-3) / 1e9,
-                     "frac_of_bytes_moved": None if traffic is None else traffic / (kernel_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
+                     "hbm_measured_gbs": None if traffic is None else traffic / (timed_ms * 1e-3) / 1e9,
+                     "frac_of_bytes_moved": None if traffic is None else traffic / (timed_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
                      "plain_copy_reference": {"gbs": plain_copy_gbs, "bytes": copy_bytes,
                                               "what": "device copy of the target rows of one input copy, "
                                                       "bytes read + written"}},
-        "other_walk_placement": {
-            "launch": "three launches (walk as a launch of its own)" if fused else "two launches (walk inside the verify kernel)",
-            "ms_per_step": other_step_ms, "nodes_per_s": Bn * N / (other_step_ms * 1e-3),
-            "verify_kernel_ms": other_kernel_ms,
-            "verify_frac": alg_bytes / (other_kernel_ms * 1e-3) / 1e9 / HBM_PEAK_GBS},
-        "other_kernels": {"%s_draft" % args.method: {
-            "kernel_ms": draft_ms, "algorithmic_bytes_per_launch": draft_bytes,
-            "achieved": draft_bytes / (draft_ms * 1e-3) / 1e9 if draft_ms > 0 else None,
-            "frac": draft_bytes / (draft_ms * 1e-3) / 1e9 / HBM_PEAK_GBS if draft_ms > 0 else None,
-            "traffic": draft_traffic}},
+        # what a decoder does, whose target rows come after its draft
+        "draft_then_verify": {
+            "step": "the draft call, then the verify call",
+            "launch": "two launches (walk inside the verify kernel)" if fused else "three launches (walk as a launch of its own)",
+            "ms_per_step": two_calls_ms, "nodes_per_s": Bn * N / (two_calls_ms * 1e-3),
+            "other_walk_placement": {
+                "launch": "three launches (walk as a launch of its own)" if fused else
+                          "two launches (walk inside the verify kernel)",
+                "ms_per_step": other_step_ms, "nodes_per_s": Bn * N / (other_step_ms * 1e-3),
+                "verify_kernel_ms": other_kernel_ms,
+                "verify_frac": alg_bytes / (other_kernel_ms * 1e-3) / 1e9 / HBM_PEAK_GBS},
+            "kernels": {
+                "%s_draft" % args.method: {
+                    "kernel_ms": draft_ms, "algorithmic_bytes_per_launch": draft_bytes,
+                    "achieved": draft_bytes / (draft_ms * 1e-3) / 1e9 if draft_ms > 0 else None,
+                    "frac": draft_bytes / (draft_ms * 1e-3) / 1e9 / HBM_PEAK_GBS if draft_ms > 0 else None,
+                    "traffic": draft_traffic},
+                # (the draft call reads the draft rows too: not counted twice)
+                "%s_verify" % args.method: {
+                    "kernel_ms": kernel_ms, "algorithmic_bytes_per_launch": alg_bytes,
+                    "achieved_is": "algorithmic bytes (includes rows an early exit skips) / kernel time",
+                    "achieved": alg_bytes / (kernel_ms * 1e-3) / 1e9,
+                    "frac": alg_bytes / (kernel_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
+                    "event_bracket_ms": bracket_ms, "event_overhead_ms": event_overhead_ms,
+                    "traffic": verify_traffic}}},
         "whole_step": {"algorithmic_bytes": alg_bytes, "gbs": alg_bytes / (ms_per_step * 1e-3) / 1e9,
                        "frac": alg_bytes / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                       "what": "the verify call's algorithmic bytes over the whole step's time "
-                               "(the draft call re-reads the draft rows: not counted twice)"},
+                       "what": "every needed row once (target rows of all nodes, draft rows of those with children) over the whole "
+                               "step's time, launch gaps included"},
     }
     if not args.no_path_only:
         # the same step with verification restricted to the nodes the walk visits (the walk is
@@ -420,7 +450,8 @@ def main():
                             "trees_per_s": Bn * psteps / pdt,
                             "visited_nodes_per_s": visited * psteps / pdt,
                             "visited_nodes_last_batch": visited,
-                            "full_step_trees_per_s": Bn * args.steps / dt}
+                            "draft_then_verify_trees_per_s": Bn / (two_calls_ms * 1e-3),
+                           "full_step_trees_per_s": Bn * args.steps / dt}
     if not args.no_cpu_baseline:
         threads = min(16, os.cpu_count() or 1)
         sample_B = min(Bn, max(1, (64 * 32000) // wl0.V))     # about 2000 config-3-sized node rows

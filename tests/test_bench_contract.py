@@ -81,3 +81,20 @@ def test_json_line_of_a_short_run():
     cpu = d["cpu_baseline"]
     assert cpu["kind"] == "oracle" and cpu["unit"] == "nodes/s" and cpu["value"] > 0 and cpu["cores"] >= 1
     assert d["path_only"]["trees_per_s"] > 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("args,kernel", [([], "spechub_step"), (["--walk-in-verify"], "spechub_verify")])
+def test_the_roofline_is_of_what_is_timed(args, kernel):
+    """A step in one call beside the draft and the verify call one after the other, each under its own name."""
+    r = subprocess.run([sys.executable, BENCH, "--steps", "50", "--warmup", "5", "--no-cpu-baseline"] + args,
+                       capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stderr[-2000:]
+    d = json.loads(r.stdout)
+    assert d["roofline"]["kernel"] == kernel and d["roofline"]["kernel_ms"] <= 1.05 * d["ms_per_step"]
+    two = d["draft_then_verify"]
+    assert set(two["kernels"]) == {"spechub_draft", "spechub_verify"}
+    assert abs(two["nodes_per_s"] - 64 * 31 / (two["ms_per_step"] * 1e-3)) < 1e-6 * two["nodes_per_s"]
+    assert sum(k["kernel_ms"] for k in two["kernels"].values()) <= 1.05 * two["ms_per_step"]
+    if args:
+        assert two["ms_per_step"] == d["ms_per_step"]
