@@ -565,9 +565,9 @@ static bool half_width_step(int method, const Params& P, int nit)
 // Streamed rows: SpecHub to 640 (128256, 372 60.2 -> 50.9, 620 85.5 -> 78.6, 744 90.7 -> 91.1; 152064, 558 96.6 -> 85.3).  RRS
 // methods, by k and by length (more than 9216 chunks; 16384), unaligned rows less far:
 //   1  256 (70001, 250 39.2 -> 32.9, 400 48.6 -> 56.4; 152064, 400 90.4 -> 94.8)
-//   2  as far as the verify call takes 1024 threads (70001, 868 75.2 -> 79.5), long rows 1300 (128256, 1240 159 -> 147, 1364 161 -> 160), longest 1100
-//      (152064 RRSw, 1054 160 -> 159, 1240 190 -> 189); unaligned 1024 (100001, 1054 108 -> 115, 1240 126 -> 134; 128257, 1147 150 -> 149),
-//      longest 780 (152065 RRSw, 713 144 -> 140, 806 148 -> 155)
+//   2  as far as the verify call takes 1024 threads (70001, 868 75.2 -> 79.5), long rows 1300 (128256, 1240 159 -> 147, 1364 161 ->
+//      160), longest 1100 (152064 RRSw, 1054 160 -> 159, 1240 190 -> 189); unaligned 1024 (100001, 1054 108 -> 115, 1240 126 -> 134;
+//      128257, 1147 150 -> 149), longest 780 (152065 RRSw, 713 144 -> 140, 806 148 -> 155)
 //   3  1280 (70001, 1300 97.5 -> 99.1), longer 1950 (100000, 1898 162 -> 163; 152064, 1300 192 -> 165, 2054 239 -> 247), unaligned 1400
 //      (100001, 1300 133 -> 127, 1495 136 -> 143; 152065, 1495 200 -> 206)
 //   4  1536 (70001, 1491 120 -> 108, 1701 121 -> 126), longer 2500 (100000, 2394 205 -> 190, 2793 210 -> 217; 128256, 2394 255 -> 228;
@@ -612,18 +612,20 @@ static int wide_step_chunks(int method, const mdsd_problem* pb, const Params& P)
 // RRSw 115 -> 117, 121 -> 124, 123 -> 127, 142 -> 133; RRS 152064, 795 216 -> 222, 1065 279 -> 263; k = 1 100000, 800 112 -> 116; RRSw, k =
 // 3, to 840 only (13-node trees, 128256, 800 248 -> 252, 860 259 -> 257); SpecHub never (100000, 820 147 -> 140).  RRS, k = 4, up to
 // 2450 nodes on unaligned rows (152065, 2058 247 -> 254, 2394 303 -> 307, 2604 307 -> 308).
-// Sixteen chunks per lane, RRS 50304, 480 51.3 -> 49.0, 525 54.7 -> 58.1, 720 68.2 -> 71.0, 870 80.3 -> 79.7, 1065 98.4 -> 93.9, 1215
-// 109 -> 106, 1455 122 -> 123, 1785 145 -> 148, 2910 230 -> 235; RRSw 54.1 -> 51.3, 56.8 -> 61.5, 71.4 -> 75.6, 83.1 -> 83.9, 102 -> 98.4, 114
-// -> 111, 128 -> 129, 152 -> 156, 237 -> 245; fp32 24000 RRS 675 53.2 -> 53.9, 840 63.1 -> 62.4; k = 1 50304, 416 39.0 -> 37.2, 560 44.8 ->
-// 49.4, 1200 80.4 -> 82.8; k = 3 (42001, RRSw, 13-node trees, 400 62.0 -> 57.2, 528 69.8 -> 71.4, 584 76.9 -> 75.4, 952 109 -> 111,
-// 1200 138 -> 137, 1848 196 -> 203); SpecHub 33000, 1455 87.2 -> 86.9, 1785 99.1 -> 101, 4350 221 -> 232.
-// Between the sizes that 1024 threads gain at and those that 512 do: bf16, k = 2, from the third node of every CU on while the
-// verify call still takes 1024 threads (100000, 496 nodes 64.1 -> 57.8, 558 68.8 -> 69.8, 744 79.9 -> 81.6, 806 85.5 -> 89.6, 1147
-// 125 -> 116; 138048, 675 110 -> 116; fp32 40000, 713 56.6 -> 56.0, unaligned 45445, 720 68.9 -> 71.6); RRS on longer rows from
-// 1024 nodes on (152064, 961 149 -> 150, 1054 154 -> 163), unaligned from 512 on (152065, 558 109 -> 112, 713 133 -> 135; 868 at 512
-// threads 149 -> 146); k = 1, long rows, from 256 nodes on (128256, 400 69.8 -> 77.8, 700 96.4 -> 103, 850 of 100000 94.8 ->
-// 90.8).  Sixteen chunks, k > 2, fewer than 256 of them but too many nodes for 1024 threads (65500, 819 61.7 -> 65.0, 1050
-// 66.0 -> 67.5; 38000 41.6 -> 41.1, unaligned 38156 39.4 -> 40.2).
+// Sixteen chunks per lane, RRS 50304, 480 51.3 -> 49.0, 525 54.7 -> 58.1, 720 68.2 -> 71.0, 870 80.3 -> 79.7, 1065 98.4 ->
+// 93.9, 1215 109 -> 106, 1455 122 -> 123, 1785 145 -> 148, 2910 230 -> 235; RRSw 54.1 -> 51.3, 56.8 -> 61.5, 71.4 -> 75.6,
+// 83.1 -> 83.9, 102 -> 98.4, 114 -> 111, 128 -> 129, 152 -> 156, 237 -> 245; fp32 24000 RRS 675 53.2 -> 53.9, 840 63.1 ->
+// 62.4; k = 1 50304, 416 39.0 -> 37.2, 560 44.8 -> 49.4, 1200 80.4 -> 82.8; k = 3 (42001, RRSw, 13-node trees, 400 62.0 ->
+// 57.2, 528 69.8 -> 71.4, 584 76.9 -> 75.4, 952 109 -> 111, 1200 138 -> 137, 1848 196 -> 203); SpecHub 33000, 1455 87.2 ->
+// 86.9, 1785 99.1 -> 101, 4350 221 -> 232.
+// Between the sizes that 1024 threads gain at and those that 512 do: bf16, k = 2, from the third node of every CU on while
+// the verify call still takes 1024 threads (100000, 496 nodes 64.1 -> 57.8, 558 68.8 -> 69.8, 744 79.9 -> 81.6, 806 85.5 ->
+// 89.6, 1147 125 -> 116; 138048, 675 110 -> 116; fp32 40000, 713 56.6 -> 56.0, unaligned 45445, 720 68.9 -> 71.6); RRS on
+// longer rows from 1024 nodes on (152064, 961 149 -> 150, 1054 154 -> 163), unaligned from 512 on (152065, 558 109 -> 112,
+// 713 133 -> 135; 868 at 512 threads 149 -> 146); k = 1, long rows, from 256 nodes on (128256, 400 69.8 -> 77.8, 700 96.4 ->
+// 103, 850 of 100000 94.8 -> 90.8), the longest for a little (138886, 272 64.7 -> 69.0; 152064, 400 97.1 -> 90.4).  Sixteen
+// chunks, k > 2, fewer than 256 of them but too many nodes for 1024 threads (65500, 819 61.7 -> 65.0, 1050 66.0 -> 67.5;
+// 38000 41.6 -> 41.1, unaligned 38156 39.4 -> 40.2).
 static bool step_in_two(int method, const mdsd_problem* pb, const Params& P, int nit, int wide)
 {
     const int64_t nodes = (int64_t)P.B * P.N, inner = (int64_t)P.B * ((P.N - 1) / P.k);
@@ -645,16 +647,16 @@ static bool step_in_two(int method, const mdsd_problem* pb, const Params& P, int
             return true;
     }
     if (wide) return false;
-    if (P.k == 1 && longer && chunks && chunks < 20 && inner <= 600) return true;
+    if (P.k == 1 && longer && chunks && (chunks < 20 ? inner <= 600 : nodes <= 320)) return true;
     if (P.k > 3) return method == kRRS && longer && chunks && nodes <= 2450;
     return inner > 768 && (P.k < 3 ? inner <= 1024 : method == kRRSw && inner <= 840);
 }
 
-// Lanes per node of the step kernels for short rows; 0: another build takes the call.  As in the verify calls, by the number of
-// all nodes; a draft call goes by those with children and may take more lanes, whose sums have another order.  SpecHub in large batches of more
-// than 64 chunks, whose verify calls take a wavefront per node, as well (4000 trees of 15 nodes, two launches -> one: bf16
-// 1000 73.6 -> 64.3 us, fp32 1000 95.2 -> 79.3), but bf16 rows of more than 128 chunks up to 24576 nodes only (1900, 18000 nodes
-// 44.5 -> 41.9; 1300, 27000 50.2 -> 50.9; 1100, 60000 91 -> 102).
+// Lanes per node of the step kernels for short rows; 0: another build takes the call.  As in the verify calls, by the number
+// of all nodes; a draft call goes by those with children and may take more lanes, whose sums have another order.  SpecHub in
+// large batches of more than 64 chunks, whose verify calls take a wavefront per node, as well (4000 trees of 15 nodes, two
+// launches -> one: bf16 1000 73.6 -> 64.3 us, fp32 1000 95.2 -> 79.3), but bf16 rows of more than 128 chunks up to 24576
+// nodes only (1900, 18000 nodes 44.5 -> 41.9; 1300, 27000 50.2 -> 50.9; 1100, 60000 91 -> 102).
 static int step_lanes(int method, int dtype, const Params& P)
 {
     const int64_t nodes = (int64_t)P.B * P.N;
